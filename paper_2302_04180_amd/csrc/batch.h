@@ -50,7 +50,8 @@ __device__ __forceinline__ Tile tile_at(const Batch& B, int t) {
 
 // Run body(desc, rows, rec) on every tile of the table assigned to this
 // workgroup (logical index b out of G).  CHECK: skip systems that have stopped.
-template <int N, int K, bool CHECK, class Body>
+// Rows: the body multiplies by the system's matrix.
+template <int N, int K, bool CHECK, bool Rows, class Body>
 __device__ __forceinline__ void tile_loop(const Batch& B, const Shm<N>& s, int b, int G, Body body) {
   const int nt = B.count[0];
   for (int t = b; t < nt; t += G) {
@@ -58,7 +59,9 @@ __device__ __forceinline__ void tile_loop(const Batch& B, const Shm<N>& s, int b
     if (T.sys < 0) continue;
     const SysDesc& D = B.sys[T.sys];
     if (CHECK && D.V.st->done) continue;
+    if (Rows) pat_load(D.A, s);
     if (K > 0) shm_init(s, K);
+    else if (Rows) __syncthreads();
     body(D, Range{T.lo, T.hi}, T.rec);
     __syncthreads();
   }
@@ -133,7 +136,7 @@ template <int N>
 __global__ void __launch_bounds__(1024) kb_std_init(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
-  tile_loop<N, 1, false>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  tile_loop<N, 1, false, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
     std_init_body<N>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -142,7 +145,7 @@ template <int N, bool Far, bool Unif>
 __global__ void __launch_bounds__(1024) kb_std_A(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 0, false);
-  tile_loop<N, 0, true>(B, s, blockIdx.x, gridDim.x,
+  tile_loop<N, 0, true, false>(B, s, blockIdx.x, gridDim.x,
                         [&](const SysDesc& D, Range R, int) {
                           const State* st = D.V.st;
                           std_A_body<Far, Unif>(D.A, D.V, R, st->beta, st->omega, st->iter > 0);
@@ -153,7 +156,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) kb_std_B(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
-  tile_loop<N, 1, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  tile_loop<N, 1, true, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
     std_B_body<N, Unif, false>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -162,7 +165,7 @@ template <int N, bool Far, bool Unif>
 __global__ void __launch_bounds__(1024) kb_std_C(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 0, false);
-  tile_loop<N, 0, true>(B, s, blockIdx.x, gridDim.x,
+  tile_loop<N, 0, true, false>(B, s, blockIdx.x, gridDim.x,
                         [&](const SysDesc& D, Range R, int) { std_C_body<Far, Unif>(D.A, D.V, R, D.V.st->alpha); });
 }
 
@@ -170,7 +173,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) kb_std_D(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 2, true);
-  tile_loop<N, 2, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  tile_loop<N, 2, true, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
     std_D_body<N, Unif, false>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -179,7 +182,7 @@ template <int N, bool Far, bool Unif>
 __global__ void __launch_bounds__(1024) kb_std_E(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 2, false);
-  tile_loop<N, 2, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  tile_loop<N, 2, true, false>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
     const State* st = D.V.st;
     std_E_body<N, Far, Unif>(D.A, D.V, D.red, R, rec, s, st->alpha, st->omega, st->iter);
   });
@@ -189,7 +192,7 @@ template <int N>
 __global__ void __launch_bounds__(1024) kb_resid(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
-  tile_loop<N, 1, false>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  tile_loop<N, 1, false, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
     resid_body<N>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -201,7 +204,7 @@ template <int N>
 __global__ void __launch_bounds__(1024) kb_pipe_init1(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
-  tile_loop<N, 1, false>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  tile_loop<N, 1, false, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
     pipe_init1_body<N>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -210,7 +213,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) kb_pipe_init2(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
-  tile_loop<N, 1, false>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  tile_loop<N, 1, false, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
     pipe_init2_body<N, Unif>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -252,6 +255,8 @@ __global__ void __launch_bounds__(1024) kb_pipe_spmv_fin(Batch B) {
       block_finalize_last<N, K>(s, D.red, 0);
       if (threadIdx.x == 0) finish_step<N, K, F>(s, D.V);
     }
+    pat_load(D.A, s);
+    __syncthreads();
     if (W == 0) spmv_hat_body<N, Unif>(D.A, D.V.w, D.V.wh, D.V.t, Range{T.lo, T.hi}, s);
     else spmv_hat_body<N, Unif>(D.A, D.V.z, D.V.zh, D.V.v, Range{T.lo, T.hi}, s);
     __syncthreads();
@@ -265,7 +270,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) kb_pcg_init(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 2, true);
-  tile_loop<N, 2, false>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  tile_loop<N, 2, false, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
     pcg_init_body<N, Unif>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -274,7 +279,7 @@ template <int N>
 __global__ void __launch_bounds__(1024) kb_pcg_S1(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
-  tile_loop<N, 1, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  tile_loop<N, 1, true, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
     pcg_S1_body<N, false>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -283,7 +288,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) kb_pcg_S3(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 2, false);
-  tile_loop<N, 2, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  tile_loop<N, 2, true, false>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
     pcg_S3_body<N, Unif, false>(D.A, D.V, D.red, R, rec, s, D.V.st->rho, D.V.st->iter);
   });
 }
@@ -292,7 +297,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) kb_pcg_S10(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 0, false);
-  tile_loop<N, 0, true>(B, s, blockIdx.x, gridDim.x,
+  tile_loop<N, 0, true, false>(B, s, blockIdx.x, gridDim.x,
                         [&](const SysDesc& D, Range R, int) { pcg_S10_body<Unif>(D.A, D.V, R, D.V.st->alpha); });
 }
 
@@ -302,7 +307,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) kb_pipe_spmv(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 0, true);
-  tile_loop<N, 0, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int) {
+  tile_loop<N, 0, true, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int) {
     spmv_hat_body<N, Unif>(D.A, D.V.w, D.V.wh, D.V.t, R, s);
   });
 }

@@ -22,6 +22,12 @@ struct rpk_matrix {
   int* scol = nullptr;
   double* sval = nullptr;
   long long sell_entries = 0;      // entries of the SELL copy, padding included
+  char* dict = nullptr;            // row dictionary (see Csr), one allocation; sptr, scol and sval are then absent
+  unsigned char* pid = nullptr;
+  unsigned char* swid = nullptr;
+  double* pval = nullptr;
+  int* poff = nullptr;
+  int np = 0, pw = 0;
   int cert = 0;                    // rows of wide slices try the certified sum (see Csr)
   int unif = 0;                    // every dinv_i has the bits of du (see Csr)
   double du = 0.0;
@@ -72,7 +78,8 @@ inline bool records_fit(int64_t records, int64_t lanes, int fpe) {
 }
 
 inline Csr csr_of(const rpk_matrix* A) {
-  return Csr{A->sptr, A->scol, A->sval, A->dinv, (int)A->n, A->cert, 0, A->unif, A->du};
+  return Csr{A->sptr, A->scol, A->sval, A->dinv, (int)A->n, A->cert, 0, A->unif, A->du,
+             A->pid, A->swid, A->pval, A->poff, A->np, A->pw};
 }
 
 inline int nvec_of(int variant) { return variant == RPK_STD ? 8 : variant == RPK_PCG ? 4 : 16; }
@@ -84,8 +91,9 @@ constexpr double kInfinityCacheBytes = 256.0 * 1024 * 1024;
 // the matrix as fits in nine tenths of the Infinity Cache next to `nvec`
 // n-vectors (those one solver iteration touches, or x and y of a lone SpMV),
 // so that the next SpMV finds it there.  Slices are counted in proportion to
-// the SELL entries.
+// the SELL entries; none where a row dictionary replaces them.
 inline int keep_slices(const rpk_matrix* A, int nvec) {
+  if (A->np) return 0;
   const double vecs = (double)nvec * (double)A->n * 8.0;
   const double room = 0.9 * kInfinityCacheBytes - vecs;
   const double sell = (double)A->sell_entries * 12.0;

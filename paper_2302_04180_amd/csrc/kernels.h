@@ -65,7 +65,20 @@ struct Csr {
   // formed where it is read instead of being stored (the same values either way)
   int unif;
   double du;
+  // Row dictionary (np > 0): the matrix has few different rows, a row being its
+  // list of (column - row, value).  Row r is entry pid[r] of the dictionary,
+  // whose entry j of row p is (poff[j np + p], pval[j np + p]); swid[s] is the
+  // width of slice s.  A kernel copies the dictionary into LDS (pat_load) and
+  // reads one byte per row instead of 12 per entry; the SELL copy is then absent.
+  const unsigned char* pid;   // [64 nslices]
+  const unsigned char* swid;  // [nslices]
+  const double* pval;         // [pw np]
+  const int* poff;            // [pw np]
+  int np, pw;
 };
+// LDS bytes set aside for the dictionary (12 bytes an entry) in every kernel
+// that multiplies by the matrix
+constexpr int kPatEntries = 1024;
 
 // Device-resident solver state (one per solve, in the caller's workspace).
 // resumable: 1 = stopped at maxit with the next iteration's scalars in place,
@@ -101,18 +114,20 @@ __host__ __device__ inline int scat_rows(int block) { return block <= 512 ? 64 :
 constexpr int ROW_STRIDE = WIN + 1;
 
 __host__ __device__ inline size_t shm_bytes(int N, int K, bool rows, int block) {
-  (void)rows;
   const size_t nw = (size_t)block / 64;
   const size_t sa = (N > 0 && N != LW8) ? (size_t)K * SA_D * 8 : 0;
   // scatter rows (nw x rows x ROW_STRIDE); the row-fallback accumulators (nw x SA_D)
   // use the same space at other times
   const size_t scat = (N > 0) ? nw * scat_rows(block) * ROW_STRIDE * 8 : 0;
   const size_t wsum = (N > 0) ? nw * WIN * (K > 0 ? K : 1) * 8 : 0;
-  return sa + scat + wsum + 16 * 8 + 16 * MAX_DOTS * 4 + MAX_DOTS * 8 + MAX_DOTS * 4 + (4 + MAX_DOTS) * 4;
+  const size_t pat = rows ? (size_t)kPatEntries * 12 : 0;
+  return pat + sa + scat + wsum + 16 * 8 + 16 * MAX_DOTS * 4 + MAX_DOTS * 8 + MAX_DOTS * 4 + (4 + MAX_DOTS) * 4;
 }
 
 template <int N>
 struct Shm {
+  double* pv;       // row dictionary of the matrix: values, offsets (kernels with rows)
+  int* po;
   long long* sa;    // K * SA_D    long accumulators (rare path)
   long long* wsa;   // nw * SA_D   row fallback accumulators (aliases scat)
   long long* scat;  // nw * rows * ROW_STRIDE scatter rows
@@ -126,10 +141,13 @@ struct Shm {
 
 template <int N>
 __device__ __forceinline__ Shm<N> shm_carve(char* base, int K, bool rows) {
-  (void)rows;
   Shm<N> s;
   const size_t nw = blockDim.x / 64;
   size_t off = 0;
+  s.pv = (double*)(base + off);
+  off += rows ? (size_t)kPatEntries * 8 : 0;
+  s.po = (int*)(base + off);
+  off += rows ? (size_t)kPatEntries * 4 : 0;
   s.sa = (long long*)(base + off);
   off += (N > 0 && N != LW8) ? (size_t)K * SA_D * 8 : 0;
   s.scat = (long long*)(base + off);
@@ -147,6 +165,17 @@ __device__ __forceinline__ Shm<N> shm_carve(char* base, int K, bool rows) {
   off += MAX_DOTS * 4;
   s.misc = (int*)(base + off);
   return s;
+}
+
+// Copy A's row dictionary into LDS (nothing where it has none); a barrier must
+// follow before any row is computed.
+template <int N>
+__device__ __forceinline__ void pat_load(const Csr& A, const Shm<N>& s) {
+  const int cnt = A.np * A.pw;
+  for (int k = threadIdx.x; k < cnt; k += blockDim.x) {
+    s.pv[k] = A.pval[k];
+    s.po[k] = A.poff[k];
+  }
 }
 
 // zero the K long accumulators and flags of this block (must precede any deposit)
@@ -297,30 +326,67 @@ __device__ __forceinline__ T ld_entry(const T* p) {
   else return *p;
 }
 
+// Where a wavefront finds the entries of its 64 rows.  load(j, ..) gives the
+// value and column of entry j of this lane's row, at(l, j, ..) those of lane l's
+// row; j is below the slice's width.
+template <bool NT>
+struct SellSrc {  // the SELL-64 copy: sv, sc at entry 0 of the slice's first row
+  const double* sv;
+  const int* sc;
+  int lane;
+  __device__ __forceinline__ void load(int j, double& a, int& c) const {
+    a = ld_entry<NT>(sv + (size_t)j * 64 + lane);
+    c = ld_entry<NT>(sc + (size_t)j * 64 + lane);
+  }
+  __device__ __forceinline__ void at(int l, int j, double& a, int& c) const {
+    a = sv[(size_t)j * 64 + l];
+    c = sc[(size_t)j * 64 + l];
+  }
+};
+struct PatSrc {  // the row dictionary in LDS (Csr::pid): column = row + offset
+  const double* pv;
+  const int* po;
+  int np, row, pid;  // row: this lane's, at most n - 1
+  __device__ __forceinline__ void load(int j, double& a, int& c) const {
+    a = pv[j * np + pid];
+    c = row + po[j * np + pid];
+  }
+  __device__ __forceinline__ void at(int l, int j, double& a, int& c) const {
+    const int p = __builtin_amdgcn_readlane(pid, l);
+    a = pv[j * np + p];
+    c = __builtin_amdgcn_readlane(row, l) + po[j * np + p];
+  }
+};
+
+// The next B entries of every lane's row, from entry j0 on: all value / column
+// loads, then all gathers, so that a lane keeps many independent loads in
+// flight.  The width w is uniform over the wavefront; slots past it repeat the
+// last entry with a value of 0, so that no load waits for a branch.
+template <int B, class Src, class Gth>
+__device__ __forceinline__ void row_batch(const Src& src, const Gth& gx, int j0, int w, double (&a)[B], double (&b)[B]) {
+  int c[B];
+#pragma unroll
+  for (int u = 0; u < B; ++u) src.load(j0 + u < w ? j0 + u : w - 1, a[u], c[u]);
+#pragma unroll
+  for (int u = 0; u < B; ++u) b[u] = gx.load(c[u]);
+#pragma unroll
+  for (int u = 0; u < B; ++u) {
+    b[u] = gx.fin(b[u]);
+    if (j0 + u >= w) a[u] = 0.0;
+  }
+}
+
 // Exact fast path of one row in one lane: FPE of the twoprod terms of entries
-// j = 0..w-1 (stride 64 in the slice).  Sets `bad` when the FPE overflows or a
-// product needs the integer path.
-template <int N, bool NT, class Gth>
-__device__ __forceinline__ double row_fast(const double* __restrict__ sval, const int* __restrict__ scol,
-                                           const Gth& gx, int w, bool& bad) {
+// j = 0..w-1.  Sets `bad` when the FPE overflows or a product needs the
+// integer path.
+template <int N, class Src, class Gth>
+__device__ __forceinline__ double row_fast(const Src& src, const Gth& gx, int w, bool& bad) {
   Fpe<N> f;
   fpe_zero(f);
   bool ovf = false;
-  // entries in batches of 8: all value/column loads, then all gathers, then the
-  // arithmetic, so that a lane keeps many independent loads in flight
   for (int j0 = 0; j0 < w; j0 += 8) {
     double a[8], b[8];
-    int c[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const bool in = j0 + u < w;
-      a[u] = in ? ld_entry<NT>(sval + (size_t)(j0 + u) * 64) : 0.0;
-      c[u] = in ? ld_entry<NT>(scol + (size_t)(j0 + u) * 64) : -1;
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) b[u] = (c[u] >= 0) ? gx.load(c[u]) : 0.0;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) b[u] = (c[u] >= 0) ? gx.fin(b[u]) : 0.0;
+    row_batch<8>(src, gx, j0, w, a, b);
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
       const double p = a[u] * b[u];
@@ -364,74 +430,75 @@ __device__ __forceinline__ double tsum(double x, double y, double& err) {
 // huge.  When it returns true, y is the correctly rounded row sum: the same
 // bits as the FPE path.  The trees keep the dependent chains of a batch at
 // three and four additions instead of eight and sixteen.
-template <bool Track, bool NT, class Gth>
-__device__ __forceinline__ bool row_cert(const double* __restrict__ sval, const int* __restrict__ scol, const Gth& gx,
-                                         int w, double& y) {
+struct CertSum {
   double s = 0.0, q = 0.0, m = 0.0;
   bool ok = true, exactq = true;
-  int nb = 0;  // batches of eight entries
-  for (int j0 = 0; j0 < w; j0 += 8, ++nb) {
-    double a[8], b[8];
-    int c[8];
+};
+
+template <int B, bool Track, class Src, class Gth>
+__device__ __forceinline__ void cert_batch(const Src& src, const Gth& gx, int j0, int w, CertSum& c) {
+  double a[B], b[B];
+  row_batch<B>(src, gx, j0, w, a, b);
+  // v[0..B-1]: the errors t of the batch's additions, v[B..2B-1]: the products' e
+  double p[B], v[2 * B];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const bool in = j0 + u < w;
-      a[u] = in ? ld_entry<NT>(sval + (size_t)(j0 + u) * 64) : 0.0;
-      c[u] = in ? ld_entry<NT>(scol + (size_t)(j0 + u) * 64) : -1;
-    }
+  for (int u = 0; u < B; ++u) {
+    p[u] = a[u] * b[u];
+    const double ap = fabs(p[u]);
+    c.ok &= (ap >= kProdLo && ap < kProdHi) || (p[u] == 0.0 && (a[u] == 0.0 || b[u] == 0.0));
+    v[B + u] = fma(a[u], b[u], -p[u]);
+  }
+  int t = 0;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) b[u] = (c[u] >= 0) ? gx.load(c[u]) : 0.0;
+  for (int width = B / 2; width >= 1; width >>= 1)
 #pragma unroll
-    for (int u = 0; u < 8; ++u) b[u] = (c[u] >= 0) ? gx.fin(b[u]) : 0.0;
-    // v[0..7]: the errors t of the batch's additions, v[8..15]: the products' e
-    double p[8], v[16];
+    for (int i = 0; i < width; ++i) p[i] = tsum(p[2 * i], p[2 * i + 1], v[t++]);
+  if (j0 == 0) {
+    c.s = p[0];
+    v[B - 1] = 0.0;
+  } else {
+    c.s = tsum(c.s, p[0], v[B - 1]);
+  }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      p[u] = a[u] * b[u];
-      const double ap = fabs(p[u]);
-      ok &= (ap >= kProdLo && ap < kProdHi) || (p[u] == 0.0 && (a[u] == 0.0 || b[u] == 0.0));
-      v[8 + u] = fma(a[u], b[u], -p[u]);
-    }
-    double l1[4], l2[2];
+  for (int u = 0; u < 2 * B; ++u) c.m += fabs(v[u]);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) l1[i] = tsum(p[2 * i], p[2 * i + 1], v[i]);
+  for (int width = B; width >= 1; width >>= 1) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) l2[i] = tsum(l1[2 * i], l1[2 * i + 1], v[4 + i]);
-    const double sb = tsum(l2[0], l2[1], v[6]);
-    if (j0 == 0) {
-      s = sb;
-      v[7] = 0.0;
-    } else {
-      s = tsum(s, sb, v[7]);
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u) m += fabs(v[u]);
-#pragma unroll
-    for (int width = 8; width >= 1; width >>= 1) {
-#pragma unroll
-      for (int i = 0; i < width; ++i) {
-        if constexpr (Track) {
-          double err;
-          v[i] = tsum(v[i], v[i + width], err);
-          exactq &= (err == 0.0);
-        } else {
-          v[i] = v[i] + v[i + width];
-        }
+    for (int i = 0; i < width; ++i) {
+      if constexpr (Track) {
+        double err;
+        v[i] = tsum(v[i], v[i + width], err);
+        c.exactq &= (err == 0.0);
+      } else {
+        v[i] = v[i] + v[i + width];
       }
     }
-    if constexpr (Track) {
-      double err;
-      q = tsum(q, v[0], err);
-      exactq &= (err == 0.0);
-    } else {
-      q += v[0];
-    }
   }
+  if constexpr (Track) {
+    double err;
+    c.q = tsum(c.q, v[0], err);
+    c.exactq &= (err == 0.0);
+  } else {
+    c.q += v[0];
+  }
+}
+
+template <bool Track, class Src, class Gth>
+__device__ __forceinline__ bool row_cert(const Src& src, const Gth& gx, int w, double& y) {
+  CertSum c;
+  int j0 = 0;
+  for (; w - j0 > 4; j0 += 8) cert_batch<8, Track>(src, gx, j0, w, c);
+  if (j0 < w) {  // a remainder of up to four entries
+    cert_batch<4, Track>(src, gx, j0, w, c);
+    j0 += 4;
+  }
+  const double s = c.s, q = c.q, m = c.m;
+  const bool ok = c.ok, exactq = c.exactq;
   if (Track && ok && exactq) {  // q is the exact sum of the error terms
     y = s + q;
     return true;
   }
-  const double k = 16.0 * nb + 2.0;  // sixteen error terms per batch
+  const double k = 2.0 * j0 + 2.0;  // two error terms per entry
   const double E = (m * (k * 0x1p-53)) * (1.0 + 0x1p-28) + k * 0x1p-1074;
   const double y0 = s + q;
   if (ok && m == 0.0) {  // every error term is 0: the sum is s exactly (+0 for a zero row)
@@ -450,18 +517,20 @@ __device__ __forceinline__ bool row_cert(const double* __restrict__ sval, const 
   return (fabs(r) + E) * (1.0 + 0x1p-50) < half;
 }
 
-// Exact slow path: the whole wavefront sums one row (entries at sv[64 j],
-// sc[64 j]) in its private long accumulator through exact integer products;
-// lane 0 rounds it.
-template <class Gth>
-__device__ inline double row_slow(const double* sv, const int* sc, const Gth& gx, int w, long long* wsa) {
+// Exact slow path: the whole wavefront sums lane l's row in its private long
+// accumulator through exact integer products; lane 0 rounds it.
+template <class Src, class Gth>
+__device__ inline double row_slow(const Src& src, int l, const Gth& gx, int w, long long* wsa) {
   const int lane = threadIdx.x & 63;
   for (int k = lane; k < SA_D; k += 64) wsa[k] = 0;
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
   __builtin_amdgcn_wave_barrier();
   bool nf = false;
   for (int j = lane; j < w; j += 64) {
-    const double a = sv[(size_t)j * 64], b = gx(sc[(size_t)j * 64]);
+    double a;
+    int c;
+    src.at(l, j, a, c);
+    const double b = gx(c);
     if (!isfinite(a) || !isfinite(b)) nf = true;
     else sa_add_prod(wsa, a, b);
   }
@@ -476,35 +545,27 @@ __device__ inline double row_slow(const double* sv, const int* sc, const Gth& gx
   return r;
 }
 
-// Row values of the 64 rows of one wavefront (rows first..first+63, first a
-// multiple of 64, lane l holds row first+l); must be called by all 64 lanes.
-template <int N, bool NT, class Gth>
-__device__ __forceinline__ double rows_wave_nt(const Csr& A, const Gth& gx, int row, bool valid, long long* wsa_block) {
-  if (__ballot(valid) == 0ull) return 0.0;
-  const int lane = threadIdx.x & 63;
-  const int s = __builtin_amdgcn_readfirstlane(row) >> 6;
-  const long long off = A.sptr[s];
-  const int w = (int)((A.sptr[s + 1] - off) >> 6);
-  const double* sv = A.sval + off + lane;
-  const int* sc = A.scol + off + lane;
+// Row values of the 64 rows of one wavefront whose entries `src` gives (w
+// entries a row); must be called by all 64 lanes.
+template <int N, class Src, class Gth>
+__device__ __forceinline__ double rows_wave_src(const Csr& A, const Src& src, const Gth& gx, int w, bool valid,
+                                                long long* wsa_block) {
   if constexpr (N == 0) {
     double acc = 0.0;
-    for (int j0 = 0; j0 < w; j0 += 8) {
+    int j0 = 0;
+    for (; w - j0 > 4; j0 += 8) {
       double a[8], b[8];
-      int c[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const bool in = j0 + u < w;
-        a[u] = in ? ld_entry<NT>(sv + (size_t)(j0 + u) * 64) : 0.0;
-        c[u] = in ? ld_entry<NT>(sc + (size_t)(j0 + u) * 64) : -1;
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) b[u] = (c[u] >= 0) ? gx.load(c[u]) : 0.0;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) b[u] = (c[u] >= 0) ? gx.fin(b[u]) : 0.0;
+      row_batch<8>(src, gx, j0, w, a, b);
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (c[u] >= 0) acc = fma(a[u], b[u], acc);
+        if (j0 + u < w) acc = fma(a[u], b[u], acc);
+    }
+    if (j0 < w) {
+      double a[4], b[4];
+      row_batch<4>(src, gx, j0, w, a, b);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (j0 + u < w) acc = fma(a[u], b[u], acc);
     }
     return acc;
   } else {
@@ -513,11 +574,11 @@ __device__ __forceinline__ double rows_wave_nt(const Csr& A, const Gth& gx, int 
     // it: its dependency chain is a few additions per entry, an FPE
     // insertion's several twosums with a data-dependent exit after each
     if (A.cert) {
-      const bool cert = (A.cert == 2) ? row_cert<true, NT>(sv, sc, gx, w, y) : row_cert<false, NT>(sv, sc, gx, w, y);
+      const bool cert = (A.cert == 2) ? row_cert<true>(src, gx, w, y) : row_cert<false>(src, gx, w, y);
       if (__ballot(valid && !cert) == 0ull) return y;
     }
     bool bad = false;
-    y = row_fast<kRowN<N>, NT>(sv, sc, gx, w, bad);
+    y = row_fast<kRowN<N>>(src, gx, w, bad);
     bad = bad && valid;
     unsigned long long m = __ballot(bad);
     if (m) {
@@ -525,26 +586,39 @@ __device__ __forceinline__ double rows_wave_nt(const Csr& A, const Gth& gx, int 
       while (m) {
         const int l = __ffsll((long long)m) - 1;
         m &= m - 1ull;
-        const double val = row_slow(A.sval + off + l, A.scol + off + l, gx, w, wsa);
-        if (lane == l) y = val;
+        const double val = row_slow(src, l, gx, w, wsa);
+        if ((int)(threadIdx.x & 63) == l) y = val;
       }
     }
     return y;
   }
 }
 
-// The wavefront's slice decides the kind of matrix load (Csr::keep); the values
-// and so the results are the same either way.
+// Rows first..first+63 of one wavefront (first a multiple of 64, lane l holds
+// row first+l): from the row dictionary where the matrix has one, else from the
+// SELL copy, whose slice decides the kind of load (Csr::keep).  The values and
+// so the results are the same either way.
 template <int N, class Gth>
-__device__ __forceinline__ double rows_wave_g(const Csr& A, const Gth& gx, int row, bool valid, long long* wsa_block) {
-  if ((__builtin_amdgcn_readfirstlane(row) >> 6) < A.keep) return rows_wave_nt<N, false>(A, gx, row, valid, wsa_block);
-  return rows_wave_nt<N, true>(A, gx, row, valid, wsa_block);
+__device__ __forceinline__ double rows_wave_g(const Csr& A, const Gth& gx, int row, bool valid, const Shm<N>& s) {
+  if (__ballot(valid) == 0ull) return 0.0;
+  const int lane = threadIdx.x & 63;
+  const int sl = __builtin_amdgcn_readfirstlane(row) >> 6;
+  if (A.np) {
+    const int w = __builtin_amdgcn_readfirstlane((int)A.swid[sl]);
+    const PatSrc src{s.pv, s.po, A.np, row < A.n ? row : A.n - 1, (int)A.pid[(size_t)sl * 64 + lane]};
+    return rows_wave_src<N>(A, src, gx, w, valid, s.wsa);
+  }
+  const long long off = A.sptr[sl];
+  const int w = (int)((A.sptr[sl + 1] - off) >> 6);
+  if (sl < A.keep)
+    return rows_wave_src<N>(A, SellSrc<false>{A.sval + off, A.scol + off, lane}, gx, w, valid, s.wsa);
+  return rows_wave_src<N>(A, SellSrc<true>{A.sval + off, A.scol + off, lane}, gx, w, valid, s.wsa);
 }
 
 template <int N>
 __device__ __forceinline__ double rows_wave(const Csr& A, const double* __restrict__ x, int row, bool valid,
-                                            long long* wsa_block) {
-  return rows_wave_g<N>(A, GatherX{x}, row, valid, wsa_block);
+                                            const Shm<N>& s) {
+  return rows_wave_g<N>(A, GatherX{x}, row, valid, s);
 }
 
 // (A M^-1 v)_row: gathers the stored preconditioned vector vh, or, for a uniform
@@ -552,9 +626,9 @@ __device__ __forceinline__ double rows_wave(const Csr& A, const double* __restri
 template <int N, bool Unif>
 __device__ __forceinline__ double rows_wave_hat(const Csr& A, const double* __restrict__ v,
                                                 const double* __restrict__ vh, int row, bool valid,
-                                                long long* wsa_block) {
-  if constexpr (Unif) return rows_wave_g<N>(A, GatherScaled{A.du, v}, row, valid, wsa_block);
-  else return rows_wave_g<N>(A, GatherX{vh}, row, valid, wsa_block);
+                                                const Shm<N>& s) {
+  if constexpr (Unif) return rows_wave_g<N>(A, GatherScaled{A.du, v}, row, valid, s);
+  else return rows_wave_g<N>(A, GatherX{vh}, row, valid, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -1090,12 +1164,14 @@ template <int N>
 __global__ void __launch_bounds__(1024) k_spmv(Csr A, const double* __restrict__ x, double* __restrict__ y) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 0, true);
+  pat_load(A, s);
+  __syncthreads();
   const int L = xcd_block(blockIdx.x, gridDim.x);
   const Range R = block_rows(A.n, L, gridDim.x);
   for (int base = R.lo; base < R.hi; base += blockDim.x) {
     const int row = base + threadIdx.x;
     const bool valid = row < R.hi;
-    const double v = rows_wave<N>(A, x, row, valid, s.wsa);
+    const double v = rows_wave<N>(A, x, row, valid, s);
     if (valid) y[row] = v;
   }
 }

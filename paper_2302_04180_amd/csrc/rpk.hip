@@ -7,8 +7,10 @@
 // the stop are no-ops, so the result does not depend on the chunk size.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 #include <cmath>
+#include <cstddef>
 #include <cstdint>
 #include <cstring>
 #include <map>
@@ -286,88 +288,138 @@ static void free_matrix(rpk_matrix* A) {
   if (A->sptr) (void)hipFree(A->sptr);
   if (A->scol) (void)hipFree(A->scol);
   if (A->sval) (void)hipFree(A->sval);
+  if (A->dict) (void)hipFree(A->dict);
   delete A;
 }
 
-// SELL-64 copy of the validated CSR (slice widths, prefix sum, padded fill)
-static rpk_status build_sell(rpk_matrix* A, hipStream_t s) {
-  const int n = (int)A->n;
-  const int ns = (n + 63) / 64;
-  A->nslices = ns;
-  int* width = nullptr;
-  if (hipMalloc((void**)&width, (size_t)ns * sizeof(int)) != hipSuccess) return RPK_ERR_NOMEM;
-  if (hipMalloc((void**)&A->sptr, (size_t)(ns + 1) * sizeof(long long)) != hipSuccess) {
-    (void)hipFree(width);
-    return RPK_ERR_NOMEM;
-  }
-  rpk_status st = RPK_OK;
+// SELL-64 copy of the validated CSR (prefix sum of the slice widths, padded fill)
+static rpk_status build_sell(rpk_matrix* A, const int* width, hipStream_t s) {
+  const int n = (int)A->n, ns = A->nslices;
+  if (hipMalloc((void**)&A->sptr, (size_t)(ns + 1) * sizeof(long long)) != hipSuccess) return RPK_ERR_NOMEM;
   long long total = 0;
-  do {
-    hipLaunchKernelGGL(k_slice_width, dim3((ns + 255) / 256), dim3(256), 0, s, A->rp, n, ns, width);
-    if (hipGetLastError() != hipSuccess) { st = RPK_ERR_HIP; break; }
-    hipLaunchKernelGGL(k_slice_scan, dim3(1), dim3(1024), 0, s, width, ns, A->sptr);
-    if (hipGetLastError() != hipSuccess) { st = RPK_ERR_HIP; break; }
-    if (hipMemcpyAsync(&total, A->sptr + ns, sizeof(long long), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess) { st = RPK_ERR_HIP; break; }
-    A->sell_entries = total;
-    const size_t cnt = (size_t)(total > 0 ? total : 1);
-    if (hipMalloc((void**)&A->scol, cnt * sizeof(int)) != hipSuccess ||
-        hipMalloc((void**)&A->sval, cnt * sizeof(double)) != hipSuccess) { st = RPK_ERR_NOMEM; break; }
-    const long long rows = (long long)ns * 64;
-    hipLaunchKernelGGL(k_fill_sell, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, A->rp, A->ci, A->v, n,
-                       ns, (const long long*)A->sptr, A->scol, A->sval);
-    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) { st = RPK_ERR_HIP; break; }
-  } while (0);
-  (void)hipFree(width);
-  return st;
+  hipLaunchKernelGGL(k_slice_scan, dim3(1), dim3(1024), 0, s, width, ns, A->sptr);
+  HIPCHK(hipGetLastError());
+  HIPCHK(hipMemcpyAsync(&total, A->sptr + ns, sizeof(long long), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  A->sell_entries = total;
+  const size_t cnt = (size_t)(total > 0 ? total : 1);
+  if (hipMalloc((void**)&A->scol, cnt * sizeof(int)) != hipSuccess ||
+      hipMalloc((void**)&A->sval, cnt * sizeof(double)) != hipSuccess)
+    return RPK_ERR_NOMEM;
+  const long long rows = (long long)ns * 64;
+  hipLaunchKernelGGL(k_fill_sell, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, A->rp, A->ci, A->v, n, ns,
+                     (const long long*)A->sptr, A->scol, A->sval);
+  HIPCHK(hipGetLastError());
+  return RPK_OK;
 }
 
-// Whether and how rows should try the certified row sum first: probe it on a
-// pseudo-random vector and take the cheaper form (bound only, then with the
-// exactness check) under which at most one slice in eight has a row it cannot
-// certify; neither, when both fail more often (results are the same either way).
-// Also whether the Jacobi vector is uniform (Csr::unif).
-static rpk_status probe_cert(rpk_matrix* A, hipStream_t s) {
-  A->cert = 0;
-  double* x = nullptr;
-  unsigned* counts = nullptr;
-  if (hipMalloc((void**)&x, (size_t)A->n * sizeof(double)) != hipSuccess) return RPK_ERR_NOMEM;
-  if (hipMalloc((void**)&counts, 3 * sizeof(unsigned)) != hipSuccess) {
-    (void)hipFree(x);
-    return RPK_ERR_NOMEM;
+// Row dictionary (Csr::pid) where the matrix's rows are few different ones, as a
+// stencil's are; the SELL copy is then not made.  The dictionary must fit the
+// LDS set aside for it (kPatEntries) and a workgroup must read far fewer bytes
+// for it than for its rows: at least 32 rows for each distinct one.  Byte
+// offsets of a column and a slice's width must fit 32 bits and a byte.
+// `found`: the counters k_pat_find and k_slice_max left.
+static rpk_status build_dictionary(rpk_matrix* A, const PatHash& found, const int* width,
+                                   const unsigned long long* hash, PatHash* t, hipStream_t s) {
+  const int64_t np = (int64_t)found.count + 1, pw = found.wide;
+  if (found.count > kPatMax || pw > 255 || np * pw > kPatEntries || A->n < 32ll * found.count || A->n > (1ll << 28))
+    return RPK_OK;
+  const size_t o_swid = up((size_t)A->nslices * 64), o_val = o_swid + up((size_t)A->nslices);
+  const size_t o_off = o_val + up((size_t)(np * pw) * 8);
+  if (hipMalloc((void**)&A->dict, o_off + up((size_t)(np * pw) * 4)) != hipSuccess) return RPK_ERR_NOMEM;
+  A->pid = (unsigned char*)A->dict;
+  A->swid = (unsigned char*)(A->dict + o_swid);
+  A->pval = (double*)(A->dict + o_val);
+  A->poff = (int*)(A->dict + o_off);
+  const unsigned G = (unsigned)std::min<int64_t>(2048, (A->nslices + 3) / 4);
+  hipLaunchKernelGGL(k_pat_table, dim3(1), dim3(1024), 0, s, A->rp, A->ci, A->v, t, (int)np, (int)pw, A->pval, A->poff);
+  hipLaunchKernelGGL(k_pat_rows, dim3(G), dim3(256), 0, s, A->rp, A->ci, A->v, (int)A->n, A->nslices, width, hash, t,
+                     (int)np, (int)pw, A->pval, A->poff, A->pid, A->swid);
+  HIPCHK(hipGetLastError());
+  int fail = 0;
+  HIPCHK(hipMemcpyAsync(&fail, &t->fail, sizeof(int), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  if (fail) {  // two different rows with one hash: the SELL copy serves them
+    (void)hipFree(A->dict);
+    A->dict = nullptr;
+    A->pid = A->swid = nullptr;
+    A->pval = nullptr;
+    A->poff = nullptr;
+  } else {
+    A->np = (int)np;
+    A->pw = (int)pw;
   }
-  rpk_status st = RPK_OK;
+  return RPK_OK;
+}
+
+// Scratch of a creation (one allocation): flags and probe counts, hash table,
+// slice widths, and n + 64 words that hold the rows' hashes, then the probe's x.
+struct Setup {
+  int* flags;          // [0] row pointers, [1] entries
+  unsigned* counts;    // probe: [0..2]; [3] the Jacobi vector is not uniform
+  PatHash* t;
+  int* width;
+  unsigned long long* words;
+};
+
+static rpk_status check_and_lay_out(rpk_matrix* A, const Setup& u, hipStream_t s) {
+  const int n = (int)A->n, ns = A->nslices;
+  const int B = 256;
+  hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, (unsigned*)u.flags, 64ll);
+  hipLaunchKernelGGL(k_pat_clear, dim3(1), dim3(1024), 0, s, u.t);
+  hipLaunchKernelGGL(k_check_rowptr, dim3((unsigned)(((int64_t)n + 1 + B - 1) / B)), dim3(B), 0, s, A->rp, n,
+                     (int)A->nnz, u.flags);
+  HIPCHK(hipGetLastError());
+  int hflags[2] = {0, 0};
+  HIPCHK(hipMemcpyAsync(hflags, u.flags, sizeof(int), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  if (hflags[0]) return RPK_ERR_ARG;  // row_ptr unusable: do not read the rows
+  const unsigned G = (unsigned)std::min(4096, (ns + 3) / 4);
+  hipLaunchKernelGGL(k_setup_rows, dim3(G), dim3(256), 0, s, A->rp, A->ci, A->v, n, ns, A->dinv, u.width, u.words,
+                     u.flags + 1);
+  hipLaunchKernelGGL(k_slice_max, dim3(1), dim3(1024), 0, s, u.width, ns, &u.t->wide);
+  hipLaunchKernelGGL(k_pat_find, dim3((unsigned)std::min<int64_t>(1024, (A->n + 255) / 256)), dim3(256), 0, s, u.words,
+                     n, u.t);
+  // a uniform Jacobi vector (every dinv_i with the bits of dinv_0)
+  hipLaunchKernelGGL(k_dinv_uniform, dim3((unsigned)(((int64_t)n + B - 1) / B)), dim3(B), 0, s, A->dinv, n,
+                     u.counts + 3);
+  HIPCHK(hipGetLastError());
+  PatHash found;
+  unsigned differ = 0;
+  double d0 = 0.0;
+  constexpr size_t kTail = offsetof(PatHash, count);
+  HIPCHK(hipMemcpyAsync(hflags + 1, u.flags + 1, sizeof(int), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync((char*)&found + kTail, (char*)u.t + kTail, sizeof(PatHash) - kTail, hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(&differ, u.counts + 3, sizeof(unsigned), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(&d0, A->dinv, sizeof(double), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  if (hflags[1] & CHK_ARG) return RPK_ERR_ARG;
+  if (hflags[1] & CHK_NONFINITE) return RPK_ERR_NONFINITE;
+  if (hflags[1] & CHK_DIAG) return RPK_ERR_ZERO_DIAG;
+  A->unif = differ == 0u ? 1 : 0;
+  A->du = d0;
+  RET_IF(build_dictionary(A, found, u.width, u.words, u.t, s));
+  if (!A->np) RET_IF(build_sell(A, u.width, s));
+  // Whether and how rows should try the certified row sum first: probe it on a
+  // pseudo-random vector and take the cheaper form (bound only, then with the
+  // exactness check) under which at most one slice in eight has a row it cannot
+  // certify; neither, when both fail more often (results are the same either way).
+  double* x = (double*)u.words;
+  hipLaunchKernelGGL(k_fill_hash, dim3(1024), dim3(256), 0, s, x, (long long)n);
+  hipLaunchKernelGGL(k_cert_probe, dim3(G), dim3(256), 0, s, csr_of(A), (const double*)x, u.counts);
+  HIPCHK(hipGetLastError());
   unsigned h[3] = {0u, 0u, 0u};
-  do {
-    if (hipMemsetAsync(counts, 0, 3 * sizeof(unsigned), s) != hipSuccess) { st = RPK_ERR_HIP; break; }
-    hipLaunchKernelGGL(k_fill_hash, dim3(1024), dim3(256), 0, s, x, (long long)A->n);
-    const long long threads = (long long)A->nslices * 64;
-    hipLaunchKernelGGL(k_cert_probe, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, csr_of(A), x, counts);
-    if (hipGetLastError() != hipSuccess ||
-        hipMemcpyAsync(h, counts, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess) { st = RPK_ERR_HIP; break; }
-    A->cert = (h[2] > 0 && 8ull * h[0] <= h[2]) ? 1 : (h[2] > 0 && 8ull * h[1] <= h[2]) ? 2 : 0;
-    // a uniform Jacobi vector (every dinv_i with the bits of dinv_0)
-    if (hipMemsetAsync(counts, 0, sizeof(unsigned), s) != hipSuccess) { st = RPK_ERR_HIP; break; }
-    hipLaunchKernelGGL(k_dinv_uniform, dim3((unsigned)((A->n + 255) / 256)), dim3(256), 0, s, A->dinv, (int)A->n,
-                       counts);
-    double d0 = 0.0;
-    if (hipGetLastError() != hipSuccess ||
-        hipMemcpyAsync(h, counts, sizeof(unsigned), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(&d0, A->dinv, sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess) { st = RPK_ERR_HIP; break; }
-    A->unif = h[0] == 0u ? 1 : 0;
-    A->du = d0;
-  } while (0);
-  (void)hipFree(x);
-  (void)hipFree(counts);
-  return st;
+  HIPCHK(hipMemcpyAsync(h, u.counts, sizeof(h), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  A->cert = (h[2] > 0 && 8ull * h[0] <= h[2]) ? 1 : (h[2] > 0 && 8ull * h[1] <= h[2]) ? 2 : 0;
+  return RPK_OK;
 }
 
 static rpk_status create_impl(int64_t n, int64_t nnz, const int32_t* rp, const int32_t* ci, const double* v,
                               int32_t on_dev, hipStream_t s, rpk_matrix* A) {
   A->n = n;
   A->nnz = nnz;
+  A->nslices = (int)((n + 63) / 64);
   if (hipMalloc((void**)&A->rp, (size_t)(n + 1) * 4) != hipSuccess) return RPK_ERR_NOMEM;
   if (hipMalloc((void**)&A->ci, (size_t)(nnz > 0 ? nnz : 1) * 4) != hipSuccess) return RPK_ERR_NOMEM;
   if (hipMalloc((void**)&A->v, (size_t)(nnz > 0 ? nnz : 1) * 8) != hipSuccess) return RPK_ERR_NOMEM;
@@ -378,32 +430,15 @@ static rpk_status create_impl(int64_t n, int64_t nnz, const int32_t* rp, const i
     HIPCHK(hipMemcpyAsync(A->ci, ci, (size_t)nnz * 4, kind, s));
     HIPCHK(hipMemcpyAsync(A->v, v, (size_t)nnz * 8, kind, s));
   }
-  int* flags = nullptr;
-  if (hipMalloc((void**)&flags, 2 * sizeof(int)) != hipSuccess) return RPK_ERR_NOMEM;
-  int hflags[2] = {0, 0};
-  rpk_status st = RPK_OK;
-  do {
-    if (hipMemsetAsync(flags, 0, 2 * sizeof(int), s) != hipSuccess) { st = RPK_ERR_HIP; break; }
-    const int B = 256;
-    const int G1 = (int)((n + 1 + B - 1) / B);
-    hipLaunchKernelGGL(k_check_rowptr, dim3(G1), dim3(B), 0, s, A->rp, (int)n, (int)nnz, flags);
-    if (hipGetLastError() != hipSuccess) { st = RPK_ERR_HIP; break; }
-    if (hipMemcpyAsync(hflags, flags, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess) { st = RPK_ERR_HIP; break; }
-    if (hflags[0]) { st = RPK_ERR_ARG; break; }  // row_ptr unusable: do not read the rows
-    const int G2 = (int)((n + B - 1) / B);
-    hipLaunchKernelGGL(k_setup_rows, dim3(G2), dim3(B), 0, s, A->rp, A->ci, A->v, (int)n, A->dinv, flags + 1);
-    if (hipGetLastError() != hipSuccess) { st = RPK_ERR_HIP; break; }
-    if (hipMemcpyAsync(hflags + 1, flags + 1, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess) { st = RPK_ERR_HIP; break; }
-    if (hflags[1] & CHK_ARG) st = RPK_ERR_ARG;
-    else if (hflags[1] & CHK_NONFINITE) st = RPK_ERR_NONFINITE;
-    else if (hflags[1] & CHK_DIAG) st = RPK_ERR_ZERO_DIAG;
-  } while (0);
-  (void)hipFree(flags);
-  if (st != RPK_OK) return st;
-  RET_IF(build_sell(A, s));
-  return probe_cert(A, s);
+  char* buf = nullptr;
+  const size_t o_t = kAlign, o_width = o_t + up(sizeof(PatHash));
+  const size_t o_words = o_width + up((size_t)A->nslices * sizeof(int));
+  if (hipMalloc((void**)&buf, o_words + ((size_t)n + 64) * 8) != hipSuccess) return RPK_ERR_NOMEM;
+  const Setup u{(int*)buf, (unsigned*)buf + 4, (PatHash*)(buf + o_t), (int*)(buf + o_width),
+                (unsigned long long*)(buf + o_words)};
+  const rpk_status st = check_and_lay_out(A, u, s);
+  (void)hipFree(buf);
+  return st;
 }
 
 rpk_status rpk_matrix_create(int64_t n, int64_t nnz, const int32_t* row_ptr, const int32_t* col_idx,

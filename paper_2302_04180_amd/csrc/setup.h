@@ -19,25 +19,78 @@ __global__ void k_check_rowptr(const int* rp, int n, int nnz, int* flags) {
   if (bad) atomicOr(flags, CHK_ARG);
 }
 
-__global__ void k_setup_rows(const int* rp, const int* ci, const double* v, int n, double* dinv, int* flags) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int cnt = 0, fl = 0;
-  double d = 0.0;
-  for (int k = rp[i]; k < rp[i + 1]; ++k) {
-    const int c = ci[k];
-    if (c < 0 || c >= n) fl |= CHK_ARG;
-    if (!isfinite(v[k])) fl |= CHK_NONFINITE;
-    if (c == i) {
-      ++cnt;
-      d = v[k];
-    }
+__device__ __forceinline__ unsigned long long pat_mix(unsigned long long v) {
+  v *= 0x9E3779B97F4A7C15ull;
+  v ^= v >> 29;
+  v *= 0xBF58476D1CE4E5B9ull;
+  return v ^ (v >> 32);
+}
+
+// The 64 rows of one slice as its wavefront sees them: their row pointers in
+// LDS, and the row (0..63) that entry e of the CSR belongs to.
+struct SliceRows {
+  int rp[65];
+  __device__ __forceinline__ void load(const int* g, int n, int s) {
+    const int lane = threadIdx.x & 63;
+    const int r = 64 * s + lane;
+    rp[lane] = g[r < n ? r : n];
+    if (lane == 0) rp[64] = g[64 * s + 64 < n ? 64 * s + 64 : n];
   }
-  if (cnt != 1 || d == 0.0) {
-    fl |= CHK_DIAG;
-    dinv[i] = 0.0;
-  } else {
-    dinv[i] = 1.0 / d;
+  __device__ __forceinline__ int row_of(int e) const {
+    int lo = 0;  // the last row that starts at or before e
+#pragma unroll
+    for (int step = 32; step >= 1; step >>= 1)
+      if (rp[lo + step] <= e) lo += step;
+    return lo;
+  }
+};
+
+// One wavefront per slice, its lanes over the slice's entries (the loads
+// coalesce whatever the rows' lengths; one row a thread took 3.1 ms on the
+// 27-point 159^3 matrix): the checks of every entry, dinv, the slice's width
+// and, for the row dictionary, each row's hash over its (position, column - row,
+// value).  n + 64 entries of hash.
+__global__ void __launch_bounds__(256) k_setup_rows(const int* rp, const int* ci, const double* v, int n, int nslices,
+                                                    double* dinv, int* width, unsigned long long* hash, int* flags) {
+  __shared__ SliceRows R[4];
+  __shared__ unsigned long long h[4][64];
+  __shared__ double diag[4][64];
+  __shared__ int cnt[4][64];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  int fl = 0;
+  for (int s = blockIdx.x * 4 + w; s < nslices; s += gridDim.x * 4) {
+    R[w].load(rp, n, s);
+    h[w][lane] = 0ull;
+    cnt[w][lane] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    const int e1 = R[w].rp[64];
+    for (int e = R[w].rp[0] + lane; e < e1; e += 64) {
+      const int l = R[w].row_of(e), r = 64 * s + l;
+      const int c = ci[e];
+      const double val = v[e];
+      if (c < 0 || c >= n) fl |= CHK_ARG;
+      if (!isfinite(val)) fl |= CHK_NONFINITE;
+      if (c == r) {
+        atomicAdd(&cnt[w][l], 1);
+        diag[w][l] = val;
+      }
+      const unsigned long long at = ((unsigned long long)(unsigned)(e - R[w].rp[l]) << 32) | (unsigned)(c - r);
+      atomicAdd(&h[w][l], pat_mix(pat_mix(at) ^ (unsigned long long)__double_as_longlong(val)));
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    const int r = 64 * s + lane, len = R[w].rp[lane + 1] - R[w].rp[lane];
+    if (r < n) {
+      const bool one = cnt[w][lane] == 1 && diag[w][lane] != 0.0;
+      if (!one) fl |= CHK_DIAG;
+      dinv[r] = one ? 1.0 / diag[w][lane] : 0.0;
+      hash[r] = pat_mix(h[w][lane] ^ (unsigned)len) | 1ull;  // 0 marks a free slot
+    }
+    const int wide = wave_max_int(r < n ? len : 0);
+    if (lane == 0) width[s] = wide;
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
   }
   if (fl) atomicOr(flags, fl);
 }
@@ -45,24 +98,27 @@ __global__ void k_setup_rows(const int* rp, const int* ci, const double* v, int 
 // *differ = 1 when some dinv_i does not have the bits of dinv_0 (Csr::unif)
 __global__ void k_dinv_uniform(const double* dinv, int n, unsigned* differ) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  if (__double_as_longlong(dinv[i]) != __double_as_longlong(dinv[0])) atomicOr(differ, 1u);
+  const bool d = i < n && __double_as_longlong(dinv[i]) != __double_as_longlong(dinv[0]);
+  // one store for the first workgroups that find a difference, not one of every lane
+  if (__syncthreads_or(d) && threadIdx.x == 0 &&
+      __hip_atomic_load(differ, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
+    atomicOr(differ, 1u);
 }
 
-// SELL-64 construction (see Csr): width of each 64-row slice ...
-__global__ void k_slice_width(const int* rp, int n, int nslices, int* width) {
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= nslices) return;
-  int w = 0;
-  const int r1 = (s * 64 + 64 < n) ? s * 64 + 64 : n;
-  for (int r = s * 64; r < r1; ++r) {
-    const int len = rp[r + 1] - rp[r];
-    w = (len > w) ? len : w;
-  }
-  width[s] = w;
+// Largest of the slices' widths (one workgroup of 1024).
+__global__ void __launch_bounds__(1024) k_slice_max(const int* width, int nslices, int* out) {
+  __shared__ int wmax;
+  if (threadIdx.x == 0) wmax = 0;
+  __syncthreads();
+  int mine = 0;
+  for (int i = threadIdx.x; i < nslices; i += 1024) mine = width[i] > mine ? width[i] : mine;
+  atomicMax(&wmax, mine);
+  __syncthreads();
+  if (threadIdx.x == 0) *out = wmax;
 }
 
-// ... exclusive prefix sum of 64*width into sptr[0..nslices] (one workgroup of 1024) ...
+// SELL-64 construction (see Csr): exclusive prefix sum of 64*width into
+// sptr[0..nslices] (one workgroup of 1024) ...
 __global__ void __launch_bounds__(1024) k_slice_scan(const int* width, int nslices, long long* sptr) {
   __shared__ long long buf[1024];
   long long carry = 0;
@@ -104,30 +160,182 @@ __global__ void k_fill_sell(const int* rp, const int* ci, const double* v, int n
   }
 }
 
+// Row dictionary (Csr::pid).  A row is its list of (column - row, value) in CSR
+// order; every distinct one is found by the 64-bit hash k_setup_rows took, in an
+// open-addressing table, the lowest row with a hash represents it, and every
+// row is then compared with its representative entry by entry, so a hash
+// collision only costs the dictionary, never a value.
+constexpr int kPatMax = 255;    // distinct rows (an id is a byte; the last id is the empty row)
+constexpr int kPatSlots = 1024; // hash slots
+
+struct PatHash {
+  unsigned long long key[kPatSlots];  // 0 = free
+  int rep[kPatSlots];                 // lowest row with that hash; k_pat_table: -1 - id
+  int count;                          // distinct hashes so far (counts on past kPatMax)
+  int wide;                           // widest slice
+  int fail;                           // a row differs from its representative
+  int pad;
+};
+
+__global__ void __launch_bounds__(1024) k_pat_clear(PatHash* t) {
+  for (int i = threadIdx.x; i < kPatSlots; i += blockDim.x) {
+    t->key[i] = 0ull;
+    t->rep[i] = 0x7fffffff;
+  }
+  if (threadIdx.x == 0) t->count = t->wide = t->fail = t->pad = 0;
+}
+
+// One row per thread: enter the row's hash, note the lowest row.  A thread's
+// rows ascend, so a row with the hash of the thread's row before needs nothing.
+// Threads stop once more than kPatMax different rows have been seen (a matrix
+// without structure ends here after a few thousand rows).
+__global__ void __launch_bounds__(256) k_pat_find(const unsigned long long* hash, int n, PatHash* t) {
+  const int stride = gridDim.x * blockDim.x;
+  unsigned long long last = 0ull;
+  for (long long r = blockIdx.x * (long long)blockDim.x + threadIdx.x; r < n; r += stride) {
+    const unsigned long long h = hash[r];
+    if (h == last) continue;
+    last = h;
+    int i = (int)(h >> 32) & (kPatSlots - 1);
+    for (;; i = (i + 1) & (kPatSlots - 1)) {
+      unsigned long long k = __hip_atomic_load(&t->key[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (k == h) break;
+      if (__hip_atomic_load(&t->count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > kPatMax) return;
+      if (k == 0ull) {
+        k = atomicCAS(&t->key[i], 0ull, h);
+        if (k == 0ull) atomicAdd(&t->count, 1);
+        if (k == 0ull || k == h) break;
+      }
+    }
+    if (__hip_atomic_load(&t->rep[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > (int)r)
+      atomicMin(&t->rep[i], (int)r);
+  }
+}
+
+// One workgroup: number the distinct rows by their lowest row, and write the
+// dictionary, padded with (offset 0, value 0) to pw entries; id np - 1 is the
+// empty row.
+__global__ void __launch_bounds__(1024) k_pat_table(const int* rp, const int* ci, const double* v, PatHash* t, int np,
+                                                    int pw, double* pval, int* poff) {
+  __shared__ int rep[kPatMax + 1];
+  __shared__ int byid[kPatMax + 1];
+  __shared__ int cnt;
+  if (threadIdx.x == 0) cnt = 0;
+  __syncthreads();
+  for (int i = threadIdx.x; i < kPatSlots; i += blockDim.x)
+    if (t->key[i]) rep[atomicAdd(&cnt, 1)] = t->rep[i];  // np - 1 <= kPatMax of them
+  __syncthreads();
+  for (int i = threadIdx.x; i < kPatSlots; i += blockDim.x)
+    if (t->key[i]) {
+      const int r = t->rep[i];
+      int id = 0;
+      for (int k = 0; k < cnt; ++k) id += rep[k] < r;
+      byid[id] = r;
+      t->rep[i] = -1 - id;
+    }
+  __syncthreads();
+  for (int k = threadIdx.x; k < np * pw; k += blockDim.x) {
+    const int j = k / np, id = k - j * np;
+    const int r = id < np - 1 ? byid[id] : 0;
+    const int k0 = rp[r], len = id < np - 1 ? rp[r + 1] - k0 : 0;
+    pval[k] = j < len ? v[k0 + j] : 0.0;
+    poff[k] = j < len ? ci[k0 + j] - r : 0;
+  }
+}
+
+// One wavefront per slice: every row's id and a comparison of its entries with
+// that dictionary row, bit by bit; the slice's width.
+__global__ void __launch_bounds__(256) k_pat_rows(const int* rp, const int* ci, const double* v, int n, int nslices,
+                                                  const int* width, const unsigned long long* hash, PatHash* t, int np,
+                                                  int pw, const double* pval, const int* poff, unsigned char* pid,
+                                                  unsigned char* swid) {
+  __shared__ SliceRows R[4];
+  __shared__ int id[4][64];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  bool bad = false;
+  unsigned long long last = 0ull;
+  int last_id = 0;
+  for (int s = blockIdx.x * 4 + w; s < nslices; s += gridDim.x * 4) {
+    R[w].load(rp, n, s);
+    const int r = 64 * s + lane;
+    int mine = np - 1;
+    if (r < n) {
+      const unsigned long long hr = hash[r];
+      if (hr != last) {
+        int i = (int)(hr >> 32) & (kPatSlots - 1);
+        for (int probe = 0; probe < kPatSlots && t->key[i] != hr; ++probe) i = (i + 1) & (kPatSlots - 1);
+        last = hr;
+        last_id = t->key[i] == hr ? -1 - t->rep[i] : -1;
+      }
+      mine = last_id;
+      if (mine < 0 || mine >= np - 1) {
+        bad = true;
+        mine = np - 1;
+      } else {  // as long as the representative: it has an entry here and the padding behind it
+        const int len = rp[r + 1] - rp[r];
+        bad |= len > pw || (len < pw && (pval[len * np + mine] != 0.0 || poff[len * np + mine] != 0));
+      }
+    }
+    id[w][lane] = mine;
+    pid[(size_t)64 * s + lane] = (unsigned char)mine;
+    if (lane == 0) swid[s] = (unsigned char)width[s];
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    const int e1 = R[w].rp[64];
+    for (int e = R[w].rp[0] + lane; e < e1; e += 64) {
+      const int l = R[w].row_of(e);
+      const int j = e - R[w].rp[l];
+      const int at = (j < pw ? j : 0) * np + id[w][l];
+      bad |= j >= pw || ci[e] - (64 * s + l) != poff[at] ||
+             __double_as_longlong(v[e]) != __double_as_longlong(pval[at]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+  }
+  if (__ballot(bad) && lane == 0) atomicOr(&t->fail, 1);
+}
+
 // Probe at matrix creation: one wavefront per slice tries row_cert on x, by
 // the bound alone and with the exactness check; counts[0] / counts[1] += slices
 // where some row was not certified that way, counts[2] += slices.  Rows whose
 // sums often land exactly on a rounding midpoint fail the first, and rows the
 // certificate cannot help fail both; the matrix takes the cheapest way that
 // rarely fails.
+// Workgroups count in LDS first: one atomic of every wavefront on the same
+// three words took most of the probe's time (128^3: 755 us).
 __global__ void __launch_bounds__(256) k_cert_probe(Csr A, const double* __restrict__ x, unsigned* counts) {
+  __shared__ unsigned mine[3];
+  if (threadIdx.x < 3) mine[threadIdx.x] = 0u;
+  __syncthreads();
   const int nslices = (A.n + 63) >> 6;
-  const int s = (int)((blockIdx.x * (size_t)blockDim.x + threadIdx.x) >> 6);
-  if (s >= nslices) return;  // whole wavefronts (blockDim.x is a multiple of 64)
   const int lane = threadIdx.x & 63;
-  const long long off = A.sptr[s];
-  const int w = (int)((A.sptr[s + 1] - off) >> 6);
-  double y;
-  const bool valid = (s << 6) + lane < A.n;
-  const bool c1 = row_cert<false, true>(A.sval + off + lane, A.scol + off + lane, GatherX{x}, w, y);
-  const bool fail1 = __ballot(valid && !c1) != 0ull;
-  const bool c2 = row_cert<true, true>(A.sval + off + lane, A.scol + off + lane, GatherX{x}, w, y);
-  const bool fail2 = __ballot(valid && !c2) != 0ull;
-  if (lane == 0) {
-    atomicAdd(&counts[2], 1u);
-    if (fail1) atomicAdd(&counts[0], 1u);
-    if (fail2) atomicAdd(&counts[1], 1u);
+  for (int s = (int)((blockIdx.x * (size_t)blockDim.x + threadIdx.x) >> 6); s < nslices;
+       s += (int)((gridDim.x * (size_t)blockDim.x) >> 6)) {  // whole wavefronts
+    double y;
+    const bool valid = (s << 6) + lane < A.n;
+    bool c1, c2;
+    if (A.np) {  // the dictionary read from device memory
+      const int row = (s << 6) + lane;
+      const PatSrc src{A.pval, A.poff, A.np, row < A.n ? row : A.n - 1, (int)A.pid[row]};
+      c1 = row_cert<false>(src, GatherX{x}, A.swid[s], y);
+      c2 = row_cert<true>(src, GatherX{x}, A.swid[s], y);
+    } else {
+      const long long off = A.sptr[s];
+      const int w = (int)((A.sptr[s + 1] - off) >> 6);
+      const SellSrc<true> src{A.sval + off, A.scol + off, lane};
+      c1 = row_cert<false>(src, GatherX{x}, w, y);
+      c2 = row_cert<true>(src, GatherX{x}, w, y);
+    }
+    const bool fail1 = __ballot(valid && !c1) != 0ull;
+    const bool fail2 = __ballot(valid && !c2) != 0ull;
+    if (lane == 0) {
+      atomicAdd(&mine[2], 1u);
+      if (fail1) atomicAdd(&mine[0], 1u);
+      if (fail2) atomicAdd(&mine[1], 1u);
+    }
   }
+  __syncthreads();
+  if (threadIdx.x < 3 && mine[threadIdx.x]) atomicAdd(&counts[threadIdx.x], mine[threadIdx.x]);
 }
 
 // x[i] in [-1, 1) from a 64-bit mix of i (the certified-row probe's input)

@@ -464,7 +464,7 @@ __device__ __forceinline__ void std_init_body(const Csr& A, const Vecs& V, const
   for (int base = R.lo; base < R.hi; base += blockDim.x) {
     const int i = base + threadIdx.x;
     const bool ok = i < R.hi;
-    const double t = rows_wave<N>(A, V.x, i, ok, s.wsa);
+    const double t = rows_wave<N>(A, V.x, i, ok, s);
     if (ok) {
       const double ri = V.b[i] - t;
       V.r[i] = ri;
@@ -566,7 +566,7 @@ __device__ __forceinline__ void std_B_body(const Csr& A, const Vecs& V, const Re
     const int i = base + threadIdx.x;
     const bool ok = i < R.hi;
     const double r0 = ok ? V.r0[i] : 0.0;
-    const double si = rows_wave_hat<N, Unif>(A, V.p, V.ph, i, ok, s.wsa);
+    const double si = rows_wave_hat<N, Unif>(A, V.p, V.ph, i, ok, s);
     if (ok) {
       V.s[i] = si;
       d[0].add(r0, si, s.sa, &s.flag[0]);
@@ -629,7 +629,7 @@ __device__ __forceinline__ void std_D_body(const Csr& A, const Vecs& V, const Re
     const int i = base + threadIdx.x;
     const bool ok = i < R.hi;
     const double q = ok ? V.q[i] : 0.0;
-    const double yi = rows_wave_hat<N, Unif>(A, V.q, V.qh, i, ok, s.wsa);
+    const double yi = rows_wave_hat<N, Unif>(A, V.q, V.qh, i, ok, s);
     if (ok) {
       V.y[i] = yi;
       d[0].add(q, yi, s.sa, &s.flag[0]);
@@ -717,7 +717,7 @@ __device__ __forceinline__ void resid_body(const Csr& A, const Vecs& V, const Re
   for (int base = R.lo; base < R.hi; base += blockDim.x) {
     const int i = base + threadIdx.x;
     const bool ok = i < R.hi;
-    const double t = rows_wave<N>(A, V.x, i, ok, s.wsa);
+    const double t = rows_wave<N>(A, V.x, i, ok, s);
     if (ok) {
       const double e = V.b[i] - t;
       d[0].add(e, e, s.sa, &s.flag[0]);
@@ -735,7 +735,7 @@ __device__ __forceinline__ void pipe_init1_body(const Csr& A, const Vecs& V, con
   for (int base = R.lo; base < R.hi; base += blockDim.x) {
     const int i = base + threadIdx.x;
     const bool ok = i < R.hi;
-    const double t = rows_wave<N>(A, V.x, i, ok, s.wsa);
+    const double t = rows_wave<N>(A, V.x, i, ok, s);
     if (ok) {
       const double ri = V.b[i] - t;
       V.r[i] = ri;
@@ -757,7 +757,7 @@ __device__ __forceinline__ void pipe_init2_body(const Csr& A, const Vecs& V, con
   for (int base = R.lo; base < R.hi; base += blockDim.x) {
     const int i = base + threadIdx.x;
     const bool ok = i < R.hi;
-    const double wi = rows_wave<N>(A, V.rh, i, ok, s.wsa);
+    const double wi = rows_wave<N>(A, V.rh, i, ok, s);
     if (ok) {
       V.w[i] = wi;
       if constexpr (!Unif) V.wh[i] = A.dinv[i] * wi;
@@ -773,7 +773,7 @@ __device__ __forceinline__ void spmv_body(const Csr& A, const double* in, double
   for (int base = R.lo; base < R.hi; base += blockDim.x) {
     const int i = base + threadIdx.x;
     const bool ok = i < R.hi;
-    const double v = rows_wave<N>(A, in, i, ok, s.wsa);
+    const double v = rows_wave<N>(A, in, i, ok, s);
     if (ok) out[i] = v;
   }
 }
@@ -785,7 +785,7 @@ __device__ __forceinline__ void spmv_hat_body(const Csr& A, const double* v, con
   for (int base = R.lo; base < R.hi; base += blockDim.x) {
     const int i = base + threadIdx.x;
     const bool ok = i < R.hi;
-    const double y = rows_wave_hat<N, Unif>(A, v, vh, i, ok, s.wsa);
+    const double y = rows_wave_hat<N, Unif>(A, v, vh, i, ok, s);
     if (ok) out[i] = y;
   }
 }
@@ -882,7 +882,7 @@ __device__ __forceinline__ void pcg_init_body(const Csr& A, const Vecs& V, const
   for (int base = R.lo; base < R.hi; base += blockDim.x) {
     const int i = base + threadIdx.x;
     const bool ok = i < R.hi;
-    const double t = rows_wave<N>(A, V.x, i, ok, s.wsa);
+    const double t = rows_wave<N>(A, V.x, i, ok, s);
     if (ok) {
       const double ri = V.b[i] - t;
       const double yi = (Unif ? A.du : A.dinv[i]) * ri;
@@ -906,7 +906,7 @@ __device__ __forceinline__ void pcg_S1_body(const Csr& A, const Vecs& V, const R
     const int i = base + threadIdx.x;
     const bool ok = i < R.hi;
     const double pi = ok ? V.p[i] : 0.0;
-    const double di = rows_wave<N>(A, V.p, i, ok, s.wsa);
+    const double di = rows_wave<N>(A, V.p, i, ok, s);
     if (ok) {
       V.s[i] = di;
       d[0].add(pi, di, s.sa, &s.flag[0]);
@@ -978,6 +978,7 @@ template <int N>
 __global__ void __launch_bounds__(1024) k_std_init(Csr A, Vecs V, Red red) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
+  pat_load(A, s);
   shm_init(s, 1);
   std_init_body<N>(A, V, red, my_rows(A.n), blockIdx.x, s);
 }
@@ -1054,6 +1055,7 @@ __global__ void __launch_bounds__(1024) k_std_B(Csr A, Vecs V, Red red) {
   if (V.st->done) return;
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
+  pat_load(A, s);
   shm_init(s, 1);
   std_B_body<N, Unif, defer_std<N>()>(A, V, red, my_rows(A.n), blockIdx.x, s);
 }
@@ -1098,6 +1100,7 @@ __global__ void __launch_bounds__(1024) k_std_D(Csr A, Vecs V, Red red) {
   if (V.st->done) return;
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 2, true);
+  pat_load(A, s);
   shm_init(s, 2);
   std_D_body<N, Unif, defer_std<N>()>(A, V, red, my_rows(A.n), blockIdx.x, s);
 }
@@ -1149,6 +1152,7 @@ template <int N>
 __global__ void __launch_bounds__(1024) k_resid(Csr A, Vecs V, Red red) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
+  pat_load(A, s);
   shm_init(s, 1);
   resid_body<N>(A, V, red, my_rows(A.n), blockIdx.x, s);
 }
@@ -1157,6 +1161,7 @@ template <int N>
 __global__ void __launch_bounds__(1024) k_pipe_init1(Csr A, Vecs V, Red red) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
+  pat_load(A, s);
   shm_init(s, 1);
   pipe_init1_body<N>(A, V, red, my_rows(A.n), blockIdx.x, s);
 }
@@ -1165,6 +1170,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) k_pipe_init2(Csr A, Vecs V, Red red) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
+  pat_load(A, s);
   shm_init(s, 1);
   pipe_init2_body<N, Unif>(A, V, red, my_rows(A.n), blockIdx.x, s);
 }
@@ -1177,6 +1183,8 @@ __global__ void __launch_bounds__(1024) k_pipe_spmv(Csr A, Vecs V) {
   if (V.st->done && V.st->resumable != 1) return;
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 0, true);
+  pat_load(A, s);
+  __syncthreads();
   spmv_hat_body<N, Unif>(A, V.w, V.wh, V.t, my_rows(A.n), s);
 }
 
@@ -1223,6 +1231,8 @@ __global__ void __launch_bounds__(1024) k_pipe_spmv_fin(Csr A, Vecs V, Red red) 
   }
   if (!V.st->spmv_go) return;
   Shm<N> s = shm_carve<N>(smem, 0, true);
+  pat_load(A, s);
+  __syncthreads();
   const int G = gridDim.x - 1;
   const Range R = block_rows(A.n, xcd_block(blockIdx.x - 1, G), G);
   if (W == 0) spmv_hat_body<N, Unif>(A, V.w, V.wh, V.t, R, s);
@@ -1233,6 +1243,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) k_pcg_init(Csr A, Vecs V, Red red) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 2, true);
+  pat_load(A, s);
   shm_init(s, 2);
   pcg_init_body<N, Unif>(A, V, red, my_rows(A.n), blockIdx.x, s);
 }
@@ -1299,6 +1310,7 @@ __global__ void __launch_bounds__(1024) k_pcg_S1(Csr A, Vecs V, Red red) {
   if (V.st->done) return;
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
+  pat_load(A, s);
   shm_init(s, 1);
   pcg_S1_body<N, defer_std<N>()>(A, V, red, my_rows(A.n), blockIdx.x, s);
 }
@@ -1361,6 +1373,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) k_std_one(Csr A, Vecs V, Red red, int iters) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 2, true);
+  pat_load(A, s);  // shm_init's barrier comes before the first row
   const Range R{0, A.n};
   const State* st = V.st;
   for (int k = 0; k < iters; ++k) {
@@ -1385,6 +1398,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) k_pcg_one(Csr A, Vecs V, Red red, int iters) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 2, true);
+  pat_load(A, s);  // shm_init's barrier comes before the first row
   const Range R{0, A.n};
   const State* st = V.st;
   for (int k = 0; k < iters; ++k) {
