@@ -25,10 +25,10 @@ struct rpk_matrix {
   char* dict = nullptr;            // row dictionary (see Csr), one allocation; sptr, scol and sval are then absent
   unsigned char* pid = nullptr;
   unsigned char* swid = nullptr;
-  double* pval = nullptr;
-  int* poff = nullptr;
+  rpk::PatEnt* pat = nullptr;
   int np = 0, pw = 0;
-  int cert = 0;                    // rows of wide slices try the certified sum (see Csr)
+  int cert = 0;                    // rows try the certified sum (see Csr)
+  int xlo = 0, xhi = 0, xlsb = 0;
   int unif = 0;                    // every dinv_i has the bits of du (see Csr)
   double du = 0.0;
 };
@@ -78,8 +78,8 @@ inline bool records_fit(int64_t records, int64_t lanes, int fpe) {
 }
 
 inline Csr csr_of(const rpk_matrix* A) {
-  return Csr{A->sptr, A->scol, A->sval, A->dinv, (int)A->n, A->cert, 0, A->unif, A->du,
-             A->pid, A->swid, A->pval, A->poff, A->np, A->pw};
+  return Csr{A->sptr, A->scol, A->sval, A->dinv, (int)A->n, A->cert, A->xlo, A->xhi, A->xlsb, 0, A->unif, A->du,
+             A->pid, A->swid, A->pat, A->np, A->pw};
 }
 
 inline int nvec_of(int variant) { return variant == RPK_STD ? 8 : variant == RPK_PCG ? 4 : 16; }

@@ -39,6 +39,20 @@ constexpr int kRowN = (N == LW8) ? 4 : N;
 
 enum : int { ST_OK = 0, ST_NONFINITE = 5, ST_NOT_CONVERGED = 6, ST_BREAKDOWN = 7 };
 
+// An entry of the row dictionary (Csr::pid): value and 8 (column - row), the
+// distance in bytes between the operand's element and the row's own.
+struct __align__(16) PatEnt {
+  double a;
+  int off8, pad;
+};
+// Dictionary rows are padded with (0, own element) to a multiple of four
+// entries, so that a batch reads no entry behind them, and by one more, so that
+// different rows lie on different LDS banks.
+__host__ __device__ constexpr int pat_stride(int pw) { return ((pw + 3) & ~3) + 1; }
+// entries of the LDS set aside for the dictionary in every kernel that multiplies
+// by the matrix
+constexpr int kPatEntries = 1024;
+
 // Matrix as the kernels see it.  The CSR input is re-laid out at creation as
 // SELL-64: slices of 64 consecutive rows (one wavefront), each slice stored
 // column-major with the width of its longest row, so that lane l of a wave reads
@@ -52,10 +66,10 @@ struct Csr {
   const double* sval;     // [sptr[nslices]]
   const double* dinv;
   int n;
-  // rows first try the certified row sum: 0 = no, 1 = with the error bound,
-  // 2 = also accepting an exactly accumulated correction (decided once per
-  // matrix at creation by a probe; every path gives the same bits)
+  // rows first try the certified row sum (decided once per matrix at creation
+  // by a probe; every path gives the same bits); xlo, xhi, xlsb: see row_cert
   int cert;
+  int xlo, xhi, xlsb;
   // slices [0, keep) read their entries with ordinary loads, which leave them
   // in the Infinity Cache for the next SpMV; the rest with non-temporal loads,
   // which leave the cache to the vectors (the same values either way)
@@ -66,19 +80,15 @@ struct Csr {
   int unif;
   double du;
   // Row dictionary (np > 0): the matrix has few different rows, a row being its
-  // list of (column - row, value).  Row r is entry pid[r] of the dictionary,
-  // whose entry j of row p is (poff[j np + p], pval[j np + p]); swid[s] is the
-  // width of slice s.  A kernel copies the dictionary into LDS (pat_load) and
-  // reads one byte per row instead of 12 per entry; the SELL copy is then absent.
+  // list of (column - row, value).  Row r is row pid[r] of the dictionary, whose
+  // entry j is pat[pid[r] pat_stride(pw) + j]; swid[s] is the width of slice s,
+  // pw the largest.  A kernel copies the dictionary into LDS (pat_load) and reads
+  // one byte per row instead of 12 per entry; the SELL copy is then absent.
   const unsigned char* pid;   // [64 nslices]
   const unsigned char* swid;  // [nslices]
-  const double* pval;         // [pw np]
-  const int* poff;            // [pw np]
+  const PatEnt* pat;          // [np pat_stride(pw)]
   int np, pw;
 };
-// LDS bytes set aside for the dictionary (12 bytes an entry) in every kernel
-// that multiplies by the matrix
-constexpr int kPatEntries = 1024;
 
 // Device-resident solver state (one per solve, in the caller's workspace).
 // resumable: 1 = stopped at maxit with the next iteration's scalars in place,
@@ -120,14 +130,13 @@ __host__ __device__ inline size_t shm_bytes(int N, int K, bool rows, int block) 
   // use the same space at other times
   const size_t scat = (N > 0) ? nw * scat_rows(block) * ROW_STRIDE * 8 : 0;
   const size_t wsum = (N > 0) ? nw * WIN * (K > 0 ? K : 1) * 8 : 0;
-  const size_t pat = rows ? (size_t)kPatEntries * 12 : 0;
+  const size_t pat = rows ? (size_t)kPatEntries * sizeof(PatEnt) : 0;
   return pat + sa + scat + wsum + 16 * 8 + 16 * MAX_DOTS * 4 + MAX_DOTS * 8 + MAX_DOTS * 4 + (4 + MAX_DOTS) * 4;
 }
 
 template <int N>
 struct Shm {
-  double* pv;       // row dictionary of the matrix: values, offsets (kernels with rows)
-  int* po;
+  PatEnt* pat;      // row dictionary of the matrix (kernels with rows)
   long long* sa;    // K * SA_D    long accumulators (rare path)
   long long* wsa;   // nw * SA_D   row fallback accumulators (aliases scat)
   long long* scat;  // nw * rows * ROW_STRIDE scatter rows
@@ -144,10 +153,8 @@ __device__ __forceinline__ Shm<N> shm_carve(char* base, int K, bool rows) {
   Shm<N> s;
   const size_t nw = blockDim.x / 64;
   size_t off = 0;
-  s.pv = (double*)(base + off);
-  off += rows ? (size_t)kPatEntries * 8 : 0;
-  s.po = (int*)(base + off);
-  off += rows ? (size_t)kPatEntries * 4 : 0;
+  s.pat = (PatEnt*)(base + off);
+  off += rows ? (size_t)kPatEntries * sizeof(PatEnt) : 0;
   s.sa = (long long*)(base + off);
   off += (N > 0 && N != LW8) ? (size_t)K * SA_D * 8 : 0;
   s.scat = (long long*)(base + off);
@@ -171,11 +178,8 @@ __device__ __forceinline__ Shm<N> shm_carve(char* base, int K, bool rows) {
 // follow before any row is computed.
 template <int N>
 __device__ __forceinline__ void pat_load(const Csr& A, const Shm<N>& s) {
-  const int cnt = A.np * A.pw;
-  for (int k = threadIdx.x; k < cnt; k += blockDim.x) {
-    s.pv[k] = A.pval[k];
-    s.po[k] = A.poff[k];
-  }
+  const int cnt = A.np * pat_stride(A.pw);
+  for (int k = threadIdx.x; k < cnt; k += blockDim.x) ((int4*)s.pat)[k] = ((const int4*)A.pat)[k];
 }
 
 // zero the K long accumulators and flags of this block (must precede any deposit)
@@ -298,16 +302,16 @@ struct Dot<LW8> {
 // ---------------------------------------------------------------------------
 // CSR rows
 // ---------------------------------------------------------------------------
-// Gathers: the value the SpMV multiplies a_ij by, as a function of the column,
-// in two parts: load(c), the memory access, and fin(v), arithmetic on the loaded
-// value.  The row loops issue the loads of a batch of entries under their
-// column guards first and apply fin afterwards, outside the guards, so that no
-// load waits for the one before it.
+// Gathers: the value the SpMV multiplies a_ij by, in two parts: the memory
+// access, by column (load) or by a 32-bit byte offset (load8), and fin(v),
+// arithmetic on the loaded value.  The row loops issue the loads of a batch of
+// entries first and apply fin afterwards, so that no load waits for the one
+// before it.
 struct GatherX {  // plain vector
   const double* __restrict__ x;
   __device__ __forceinline__ double load(int c) const { return x[c]; }
+  __device__ __forceinline__ double load8(unsigned o) const { return *(const double*)((const char*)x + o); }
   __device__ __forceinline__ double fin(double v) const { return v; }
-  __device__ __forceinline__ double operator()(int c) const { return x[c]; }
 };
 // M^-1 v for a uniform Jacobi vector (Csr::unif), formed at the gather:
 // RN(du * v_c), the value a stored copy would hold.
@@ -315,8 +319,8 @@ struct GatherScaled {
   double du;
   const double* __restrict__ v;
   __device__ __forceinline__ double load(int c) const { return v[c]; }
+  __device__ __forceinline__ double load8(unsigned o) const { return *(const double*)((const char*)v + o); }
   __device__ __forceinline__ double fin(double x) const { return du * x; }
-  __device__ __forceinline__ double operator()(int c) const { return du * v[c]; }
 };
 
 // A matrix entry or column index: non-temporal (NT) or ordinary load.
@@ -326,55 +330,66 @@ __device__ __forceinline__ T ld_entry(const T* p) {
   else return *p;
 }
 
-// Where a wavefront finds the entries of its 64 rows.  load(j, ..) gives the
-// value and column of entry j of this lane's row, at(l, j, ..) those of lane l's
-// row; j is below the slice's width.
+// Where a wavefront finds the entries of its 64 rows.  batch() gives this lane's
+// entries j0..j0+B-1 as values a and gathered operands b: all value / column
+// loads, then all gathers, so that a lane keeps many independent loads in
+// flight; the width w is uniform over the wavefront, and slots from w on have
+// the value 0 and an operand of this row.  at(l, j, ..) gives entry j < w of
+// lane l's row.
 template <bool NT>
 struct SellSrc {  // the SELL-64 copy: sv, sc at entry 0 of the slice's first row
   const double* sv;
   const int* sc;
-  int lane;
-  __device__ __forceinline__ void load(int j, double& a, int& c) const {
-    a = ld_entry<NT>(sv + (size_t)j * 64 + lane);
-    c = ld_entry<NT>(sc + (size_t)j * 64 + lane);
+  template <int B, class Gth>
+  __device__ __forceinline__ void batch(const Gth& gx, int j0, int w, double (&a)[B], double (&b)[B]) const {
+    const unsigned lane = threadIdx.x & 63;
+    int c[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const size_t j = (size_t)(j0 + u < w ? j0 + u : w - 1) * 64;
+      a[u] = ld_entry<NT>((const double*)((const char*)(sv + j) + lane * 8u));
+      c[u] = ld_entry<NT>((const int*)((const char*)(sc + j) + lane * 4u));
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) b[u] = gx.load(c[u]);
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      b[u] = gx.fin(b[u]);
+      if (j0 + u >= w) a[u] = 0.0;
+    }
   }
-  __device__ __forceinline__ void at(int l, int j, double& a, int& c) const {
+  template <class Gth>
+  __device__ __forceinline__ void at(const Gth& gx, int l, int j, double& a, double& b) const {
     a = sv[(size_t)j * 64 + l];
-    c = sc[(size_t)j * 64 + l];
+    b = gx.fin(gx.load(sc[(size_t)j * 64 + l]));
   }
 };
-struct PatSrc {  // the row dictionary in LDS (Csr::pid): column = row + offset
-  const double* pv;
-  const int* po;
-  int np, row, pid;  // row: this lane's, at most n - 1
-  __device__ __forceinline__ void load(int j, double& a, int& c) const {
-    a = pv[j * np + pid];
-    c = row + po[j * np + pid];
+struct PatSrc {  // the row dictionary (Csr::pid) in LDS
+  const PatEnt* pat;
+  unsigned row8;  // byte offset of this lane's row (at most n - 1)
+  int at0;        // first entry of its dictionary row
+  template <int B, class Gth>
+  __device__ __forceinline__ void batch(const Gth& gx, int j0, int w, double (&a)[B], double (&b)[B]) const {
+    (void)w;
+    const PatEnt* e = pat + at0 + j0;
+    unsigned o[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      a[u] = e[u].a;
+      o[u] = row8 + (unsigned)e[u].off8;
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) b[u] = gx.load8(o[u]);
+#pragma unroll
+    for (int u = 0; u < B; ++u) b[u] = gx.fin(b[u]);
   }
-  __device__ __forceinline__ void at(int l, int j, double& a, int& c) const {
-    const int p = __builtin_amdgcn_readlane(pid, l);
-    a = pv[j * np + p];
-    c = __builtin_amdgcn_readlane(row, l) + po[j * np + p];
+  template <class Gth>
+  __device__ __forceinline__ void at(const Gth& gx, int l, int j, double& a, double& b) const {
+    const PatEnt* e = pat + __builtin_amdgcn_readlane(at0, l) + j;
+    a = e->a;
+    b = gx.fin(gx.load8((unsigned)__builtin_amdgcn_readlane((int)row8, l) + (unsigned)e->off8));
   }
 };
-
-// The next B entries of every lane's row, from entry j0 on: all value / column
-// loads, then all gathers, so that a lane keeps many independent loads in
-// flight.  The width w is uniform over the wavefront; slots past it repeat the
-// last entry with a value of 0, so that no load waits for a branch.
-template <int B, class Src, class Gth>
-__device__ __forceinline__ void row_batch(const Src& src, const Gth& gx, int j0, int w, double (&a)[B], double (&b)[B]) {
-  int c[B];
-#pragma unroll
-  for (int u = 0; u < B; ++u) src.load(j0 + u < w ? j0 + u : w - 1, a[u], c[u]);
-#pragma unroll
-  for (int u = 0; u < B; ++u) b[u] = gx.load(c[u]);
-#pragma unroll
-  for (int u = 0; u < B; ++u) {
-    b[u] = gx.fin(b[u]);
-    if (j0 + u >= w) a[u] = 0.0;
-  }
-}
 
 // Exact fast path of one row in one lane: FPE of the twoprod terms of entries
 // j = 0..w-1.  Sets `bad` when the FPE overflows or a product needs the
@@ -384,11 +399,11 @@ __device__ __forceinline__ double row_fast(const Src& src, const Gth& gx, int w,
   Fpe<N> f;
   fpe_zero(f);
   bool ovf = false;
-  for (int j0 = 0; j0 < w; j0 += 8) {
-    double a[8], b[8];
-    row_batch<8>(src, gx, j0, w, a, b);
+  for (int j0 = 0; j0 < w; j0 += 4) {
+    double a[4], b[4];
+    src.template batch<4>(gx, j0, w, a, b);
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < 4; ++u) {
       const double p = a[u] * b[u];
       const double ap = fabs(p);
       // no per-lane branch: an out-of-range product inserts 0 and flags the row
@@ -419,102 +434,99 @@ __device__ __forceinline__ double tsum(double x, double y, double& err) {
 // additions, the row sum is exactly T = s + sum(t + e), sixteen terms per
 // batch.  q = fl(sum(t + e)), also summed pairwise, is within
 // E = gamma_k * sum(|t| + |e|) of that sum for any order of the additions
-// (k at least the number of terms, plus an allowance for underflow).  With
-// (y, r) = twosum(s, q), T = y + r + d with |d| <= E, so y = RN(T) whenever
-// |r| + E is below half the gap from y to its neighbours.  Track: also check
-// with twosum that every addition into q was exact; then T = s + q and
-// y = RN(s + q) is RN(T) even when T is a rounding midpoint, which no bound can
-// settle (sums of a few exact products often are).  Returns false -- the
-// caller then takes the FPE path -- when neither shows it, or for a product
-// out of range or a sum that is non-finite or, for the bound, zero, tiny or
-// huge.  When it returns true, y is the correctly rounded row sum: the same
-// bits as the FPE path.  The trees keep the dependent chains of a batch at
-// three and four additions instead of eight and sixteen.
+// (k at least the number of terms).  With (y, r) = twosum(s, q), T = y + r + d
+// with |d| <= E, so y = RN(T) whenever |r| + E is below half the gap from y to
+// its neighbours.  No bound can settle a T that is a rounding midpoint itself,
+// and sums of a few short products often are (a quarter of the 7-point rows);
+// there the additions into q are usually exact, because all their operands are
+// multiples of one power of two: a_j is an odd multiple of at least 2^lsb (the
+// matrix's smallest, Csr::xlsb = lsb - 1), x_j a multiple of 2^(ex_j - 53) with
+// ex_j its binary exponent, so every p, e and t, and every partial sum of them,
+// is a multiple of U = 2^(lsb + min ex - 53).  A partial sum is at most
+// m = sum(|t| + |e|) in magnitude; where m < 2^52 U (the computed m is within
+// 2^-40 of it), it is below 2^53 U and hence a double: q is the exact sum, T =
+// s + q, and y = RN(s + q) = RN(T) whatever it is.  The products are in range
+// by the same exponents (Csr::xlo, xhi), which costs three integer operations
+// an entry instead of four comparisons; an x_j = 0 counts as exponent 0, which
+// can only make the tests stricter.  Returns false -- the caller then takes the
+// FPE path -- when neither shows it, or for a product out of range or a sum that
+// is non-finite or, for the bound, zero, tiny or huge.  When it returns true, y
+// is the correctly rounded row sum: the same bits as the FPE path.  Checking
+// every addition into q for exactness by a twosum instead cost 105 more
+// operations a row: with it the kernels B and D of the 128^3 standard loop took
+// 34.9 and 40.2 us, with the exponents 27.2 and 32.5 (the 27-point 159^3 SpMV 127
+// and 81).
 struct CertSum {
   double s = 0.0, q = 0.0, m = 0.0;
-  bool ok = true, exactq = true;
+  int elo = INT_MAX, ehi = INT_MIN;  // binary exponents of the x_j
 };
 
-template <int B, bool Track, class Src, class Gth>
+template <int B, class Src, class Gth>
 __device__ __forceinline__ void cert_batch(const Src& src, const Gth& gx, int j0, int w, CertSum& c) {
   double a[B], b[B];
-  row_batch<B>(src, gx, j0, w, a, b);
-  // v[0..B-1]: the errors t of the batch's additions, v[B..2B-1]: the products' e
-  double p[B], v[2 * B];
+  src.template batch<B>(gx, j0, w, a, b);
+  // pairs are added as soon as their operands exist, which keeps the live
+  // values of a batch few
+  double p[B / 2], q[B / 2], m[B / 2];
 #pragma unroll
-  for (int u = 0; u < B; ++u) {
-    p[u] = a[u] * b[u];
-    const double ap = fabs(p[u]);
-    c.ok &= (ap >= kProdLo && ap < kProdHi) || (p[u] == 0.0 && (a[u] == 0.0 || b[u] == 0.0));
-    v[B + u] = fma(a[u], b[u], -p[u]);
-  }
-  int t = 0;
-#pragma unroll
-  for (int width = B / 2; width >= 1; width >>= 1)
-#pragma unroll
-    for (int i = 0; i < width; ++i) p[i] = tsum(p[2 * i], p[2 * i + 1], v[t++]);
-  if (j0 == 0) {
-    c.s = p[0];
-    v[B - 1] = 0.0;
-  } else {
-    c.s = tsum(c.s, p[0], v[B - 1]);
+  for (int i = 0; i < B / 2; ++i) {
+    const int e0 = __builtin_amdgcn_frexp_exp(b[2 * i]), e1 = __builtin_amdgcn_frexp_exp(b[2 * i + 1]);
+    c.elo = min(c.elo, min(e0, e1));
+    c.ehi = max(c.ehi, max(e0, e1));
+    const double p0 = a[2 * i] * b[2 * i], p1 = a[2 * i + 1] * b[2 * i + 1];
+    const double r0 = fma(a[2 * i], b[2 * i], -p0), r1 = fma(a[2 * i + 1], b[2 * i + 1], -p1);
+    double t;
+    p[i] = tsum(p0, p1, t);
+    q[i] = (r0 + r1) + t;
+    m[i] = (fabs(r0) + fabs(r1)) + fabs(t);
   }
 #pragma unroll
-  for (int u = 0; u < 2 * B; ++u) c.m += fabs(v[u]);
-#pragma unroll
-  for (int width = B; width >= 1; width >>= 1) {
+  for (int width = B / 4; width >= 1; width >>= 1)
 #pragma unroll
     for (int i = 0; i < width; ++i) {
-      if constexpr (Track) {
-        double err;
-        v[i] = tsum(v[i], v[i + width], err);
-        c.exactq &= (err == 0.0);
-      } else {
-        v[i] = v[i] + v[i + width];
-      }
+      double t;
+      p[i] = tsum(p[2 * i], p[2 * i + 1], t);
+      q[i] = (q[2 * i] + q[2 * i + 1]) + t;
+      m[i] = (m[2 * i] + m[2 * i + 1]) + fabs(t);
     }
-  }
-  if constexpr (Track) {
-    double err;
-    c.q = tsum(c.q, v[0], err);
-    c.exactq &= (err == 0.0);
+  if (j0 == 0) {
+    c.s = p[0];
+    c.q = q[0];
+    c.m = m[0];
   } else {
-    c.q += v[0];
+    double t;
+    c.s = tsum(c.s, p[0], t);
+    c.q += q[0] + t;
+    c.m += m[0] + fabs(t);
   }
 }
 
-template <bool Track, class Src, class Gth>
-__device__ __forceinline__ bool row_cert(const Src& src, const Gth& gx, int w, double& y) {
+template <class Src, class Gth>
+__device__ __forceinline__ bool row_cert(const Csr& A, const Src& src, const Gth& gx, int w, double& y) {
   CertSum c;
   int j0 = 0;
-  for (; w - j0 > 4; j0 += 8) cert_batch<8, Track>(src, gx, j0, w, c);
+  for (; w - j0 > 4; j0 += 8) cert_batch<8>(src, gx, j0, w, c);
   if (j0 < w) {  // a remainder of up to four entries
-    cert_batch<4, Track>(src, gx, j0, w, c);
+    cert_batch<4>(src, gx, j0, w, c);
     j0 += 4;
   }
   const double s = c.s, q = c.q, m = c.m;
-  const bool ok = c.ok, exactq = c.exactq;
-  if (Track && ok && exactq) {  // q is the exact sum of the error terms
-    y = s + q;
-    return true;
-  }
+  y = s + (q + 0.0);  // +0 where both are zero
+  const double ay = fabs(y);
+  const bool in = c.elo >= A.xlo && c.ehi <= A.xhi && ay < 0x1p1020;  // false for a NaN y
+  // every error term is 0 (the sum is s exactly, +0 for a zero row), or every
+  // addition into q was exact
+  const bool exactq = m == 0.0 || __builtin_amdgcn_frexp_exp(m) <= c.elo + A.xlsb;
   const double k = 2.0 * j0 + 2.0;  // two error terms per entry
   const double E = (m * (k * 0x1p-53)) * (1.0 + 0x1p-28) + k * 0x1p-1074;
-  const double y0 = s + q;
-  if (ok && m == 0.0) {  // every error term is 0: the sum is s exactly (+0 for a zero row)
-    y = y0;
-    return true;
-  }
-  const double z = y0 - s;
-  const double r = (s - (y0 - z)) + (q - z);
-  y = y0;
-  const double ay = fabs(y0);
-  if (!ok || !(ay >= 0x1p-960) || !(ay < 0x1p1020)) return false;
+  const double z = y - s;
+  const double r = (s - (y - z)) + (q - z);
   const unsigned long long bits = (unsigned long long)__double_as_longlong(ay);
   const double up = __longlong_as_double((long long)(bits + 1ull)) - ay;  // spacing above |y|
   const bool pow2 = (bits & ((1ull << 52) - 1ull)) == 0ull;               // then the spacing below is up / 2
   const double half = pow2 ? 0.25 * up : 0.5 * up;
-  return (fabs(r) + E) * (1.0 + 0x1p-50) < half;
+  const bool bound = ay >= 0x1p-960 && (fabs(r) + E) * (1.0 + 0x1p-50) < half;
+  return in && (exactq || bound);
 }
 
 // Exact slow path: the whole wavefront sums lane l's row in its private long
@@ -527,10 +539,8 @@ __device__ inline double row_slow(const Src& src, int l, const Gth& gx, int w, l
   __builtin_amdgcn_wave_barrier();
   bool nf = false;
   for (int j = lane; j < w; j += 64) {
-    double a;
-    int c;
-    src.at(l, j, a, c);
-    const double b = gx(c);
+    double a, b;
+    src.at(gx, l, j, a, b);
     if (!isfinite(a) || !isfinite(b)) nf = true;
     else sa_add_prod(wsa, a, b);
   }
@@ -545,74 +555,90 @@ __device__ inline double row_slow(const Src& src, int l, const Gth& gx, int w, l
   return r;
 }
 
-// Row values of the 64 rows of one wavefront whose entries `src` gives (w
-// entries a row); must be called by all 64 lanes.
-template <int N, class Src, class Gth>
-__device__ __forceinline__ double rows_wave_src(const Csr& A, const Src& src, const Gth& gx, int w, bool valid,
-                                                long long* wsa_block) {
-  if constexpr (N == 0) {
-    double acc = 0.0;
-    int j0 = 0;
-    for (; w - j0 > 4; j0 += 8) {
-      double a[8], b[8];
-      row_batch<8>(src, gx, j0, w, a, b);
+// Plain rows: a chain of fmas in entry order.
+template <class Src, class Gth>
+__device__ __forceinline__ double row_plain(const Src& src, const Gth& gx, int w) {
+  double acc = 0.0;
+  int j0 = 0;
+  for (; w - j0 > 4; j0 += 8) {
+    double a[8], b[8];
+    src.template batch<8>(gx, j0, w, a, b);
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (j0 + u < w) acc = fma(a[u], b[u], acc);
-    }
-    if (j0 < w) {
-      double a[4], b[4];
-      row_batch<4>(src, gx, j0, w, a, b);
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (j0 + u < w) acc = fma(a[u], b[u], acc);
-    }
-    return acc;
-  } else {
-    double y = 0.0;
-    // try the certified compensated sum first where the matrix's probe chose
-    // it: its dependency chain is a few additions per entry, an FPE
-    // insertion's several twosums with a data-dependent exit after each
-    if (A.cert) {
-      const bool cert = (A.cert == 2) ? row_cert<true>(src, gx, w, y) : row_cert<false>(src, gx, w, y);
-      if (__ballot(valid && !cert) == 0ull) return y;
-    }
-    bool bad = false;
-    y = row_fast<kRowN<N>>(src, gx, w, bad);
-    bad = bad && valid;
-    unsigned long long m = __ballot(bad);
-    if (m) {
-      long long* wsa = wsa_block + (size_t)(threadIdx.x >> 6) * SA_D;
-      while (m) {
-        const int l = __ffsll((long long)m) - 1;
-        m &= m - 1ull;
-        const double val = row_slow(src, l, gx, w, wsa);
-        if ((int)(threadIdx.x & 63) == l) y = val;
-      }
-    }
-    return y;
+    for (int u = 0; u < 8; ++u)
+      if (j0 + u < w) acc = fma(a[u], b[u], acc);
   }
+  if (j0 < w) {
+    double a[4], b[4];
+    src.template batch<4>(gx, j0, w, a, b);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (j0 + u < w) acc = fma(a[u], b[u], acc);
+  }
+  return acc;
+}
+
+// Exact rows of a wavefront without the certificate: the FPE, then the integer
+// path for the rows that need it.
+template <int N, class Src, class Gth>
+__device__ __forceinline__ double rows_fpe(const Src& src, const Gth& gx, int w, bool valid, long long* wsa_block) {
+  bool bad = false;
+  double y = row_fast<kRowN<N>>(src, gx, w, bad);
+  bad = bad && valid;
+  unsigned long long m = __ballot(bad);
+  if (m) {
+    long long* wsa = wsa_block + (size_t)(threadIdx.x >> 6) * SA_D;
+    while (m) {
+      const int l = __ffsll((long long)m) - 1;
+      m &= m - 1ull;
+      const double val = row_slow(src, l, gx, w, wsa);
+      if ((int)(threadIdx.x & 63) == l) y = val;
+    }
+  }
+  return y;
 }
 
 // Rows first..first+63 of one wavefront (first a multiple of 64, lane l holds
-// row first+l): from the row dictionary where the matrix has one, else from the
-// SELL copy, whose slice decides the kind of load (Csr::keep).  The values and
-// so the results are the same either way.
+// row first+l); must be called by all 64 lanes.  The entries come from the row
+// dictionary where the matrix has one, else from the SELL copy, whose slice
+// decides the kind of load (Csr::keep).  Exact rows try the certified
+// compensated sum first where the matrix's probe chose it: its dependency chain
+// is a few additions per entry, an FPE insertion's several twosums with a
+// data-dependent exit after each; a wavefront with a row that is not certified
+// takes all its rows the other way (its entries are in the caches by then).
+// Every path gives the same values.
 template <int N, class Gth>
 __device__ __forceinline__ double rows_wave_g(const Csr& A, const Gth& gx, int row, bool valid, const Shm<N>& s) {
   if (__ballot(valid) == 0ull) return 0.0;
   const int lane = threadIdx.x & 63;
   const int sl = __builtin_amdgcn_readfirstlane(row) >> 6;
+  double y = 0.0;
   if (A.np) {
     const int w = __builtin_amdgcn_readfirstlane((int)A.swid[sl]);
-    const PatSrc src{s.pv, s.po, A.np, row < A.n ? row : A.n - 1, (int)A.pid[(size_t)sl * 64 + lane]};
-    return rows_wave_src<N>(A, src, gx, w, valid, s.wsa);
+    const PatSrc src{s.pat, (unsigned)(row < A.n ? row : A.n - 1) * 8u,
+                     (int)A.pid[(size_t)sl * 64 + lane] * pat_stride(A.pw)};
+    if constexpr (N == 0) {
+      return row_plain(src, gx, w);
+    } else {
+      if (A.cert) {
+        const bool cert = row_cert(A, src, gx, w, y);
+        if (__ballot(valid && !cert) == 0ull) return y;
+      }
+      return rows_fpe<N>(src, gx, w, valid, s.wsa);
+    }
   }
   const long long off = A.sptr[sl];
   const int w = (int)((A.sptr[sl + 1] - off) >> 6);
-  if (sl < A.keep)
-    return rows_wave_src<N>(A, SellSrc<false>{A.sval + off, A.scol + off, lane}, gx, w, valid, s.wsa);
-  return rows_wave_src<N>(A, SellSrc<true>{A.sval + off, A.scol + off, lane}, gx, w, valid, s.wsa);
+  const SellSrc<false> kept{A.sval + off, A.scol + off};
+  const SellSrc<true> passing{A.sval + off, A.scol + off};
+  if constexpr (N == 0) {
+    return sl < A.keep ? row_plain(kept, gx, w) : row_plain(passing, gx, w);
+  } else {
+    if (A.cert) {
+      const bool cert = sl < A.keep ? row_cert(A, kept, gx, w, y) : row_cert(A, passing, gx, w, y);
+      if (__ballot(valid && !cert) == 0ull) return y;
+    }
+    return rows_fpe<N>(kept, gx, w, valid, s.wsa);
+  }
 }
 
 template <int N>

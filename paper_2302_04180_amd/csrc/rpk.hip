@@ -322,19 +322,18 @@ static rpk_status build_sell(rpk_matrix* A, const int* width, hipStream_t s) {
 static rpk_status build_dictionary(rpk_matrix* A, const PatHash& found, const int* width,
                                    const unsigned long long* hash, PatHash* t, hipStream_t s) {
   const int64_t np = (int64_t)found.count + 1, pw = found.wide;
-  if (found.count > kPatMax || pw > 255 || np * pw > kPatEntries || A->n < 32ll * found.count || A->n > (1ll << 28))
+  if (found.count > kPatMax || pw > 252 || np * pat_stride((int)pw) > kPatEntries || A->n < 32ll * found.count || A->n > (1ll << 28))
     return RPK_OK;
   const size_t o_swid = up((size_t)A->nslices * 64), o_val = o_swid + up((size_t)A->nslices);
-  const size_t o_off = o_val + up((size_t)(np * pw) * 8);
-  if (hipMalloc((void**)&A->dict, o_off + up((size_t)(np * pw) * 4)) != hipSuccess) return RPK_ERR_NOMEM;
+  if (hipMalloc((void**)&A->dict, o_val + (size_t)np * pat_stride((int)pw) * sizeof(PatEnt)) != hipSuccess)
+    return RPK_ERR_NOMEM;
   A->pid = (unsigned char*)A->dict;
   A->swid = (unsigned char*)(A->dict + o_swid);
-  A->pval = (double*)(A->dict + o_val);
-  A->poff = (int*)(A->dict + o_off);
+  A->pat = (PatEnt*)(A->dict + o_val);
   const unsigned G = (unsigned)std::min<int64_t>(2048, (A->nslices + 3) / 4);
-  hipLaunchKernelGGL(k_pat_table, dim3(1), dim3(1024), 0, s, A->rp, A->ci, A->v, t, (int)np, (int)pw, A->pval, A->poff);
+  hipLaunchKernelGGL(k_pat_table, dim3(1), dim3(1024), 0, s, A->rp, A->ci, A->v, t, (int)np, (int)pw, A->pat);
   hipLaunchKernelGGL(k_pat_rows, dim3(G), dim3(256), 0, s, A->rp, A->ci, A->v, (int)A->n, A->nslices, width, hash, t,
-                     (int)np, (int)pw, A->pval, A->poff, A->pid, A->swid);
+                     (int)np, (int)pw, A->pat, A->pid, A->swid);
   HIPCHK(hipGetLastError());
   int fail = 0;
   HIPCHK(hipMemcpyAsync(&fail, &t->fail, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -343,8 +342,7 @@ static rpk_status build_dictionary(rpk_matrix* A, const PatHash& found, const in
     (void)hipFree(A->dict);
     A->dict = nullptr;
     A->pid = A->swid = nullptr;
-    A->pval = nullptr;
-    A->poff = nullptr;
+    A->pat = nullptr;
   } else {
     A->np = (int)np;
     A->pw = (int)pw;
@@ -356,7 +354,7 @@ static rpk_status build_dictionary(rpk_matrix* A, const PatHash& found, const in
 // slice widths, and n + 64 words that hold the rows' hashes, then the probe's x.
 struct Setup {
   int* flags;          // [0] row pointers, [1] entries
-  unsigned* counts;    // probe: [0..2]; [3] the Jacobi vector is not uniform
+  unsigned* counts;    // [0], [1] probe; [2] the Jacobi vector is not uniform
   PatHash* t;
   int* width;
   unsigned long long* words;
@@ -376,21 +374,21 @@ static rpk_status check_and_lay_out(rpk_matrix* A, const Setup& u, hipStream_t s
   if (hflags[0]) return RPK_ERR_ARG;  // row_ptr unusable: do not read the rows
   const unsigned G = (unsigned)std::min(4096, (ns + 3) / 4);
   hipLaunchKernelGGL(k_setup_rows, dim3(G), dim3(256), 0, s, A->rp, A->ci, A->v, n, ns, A->dinv, u.width, u.words,
-                     u.flags + 1);
+                     u.flags + 1, u.t);
   hipLaunchKernelGGL(k_slice_max, dim3(1), dim3(1024), 0, s, u.width, ns, &u.t->wide);
-  hipLaunchKernelGGL(k_pat_find, dim3((unsigned)std::min<int64_t>(1024, (A->n + 255) / 256)), dim3(256), 0, s, u.words,
+  hipLaunchKernelGGL(k_pat_find, dim3((unsigned)std::min<int64_t>(512, (A->n + 255) / 256)), dim3(256), 0, s, u.words,
                      n, u.t);
   // a uniform Jacobi vector (every dinv_i with the bits of dinv_0)
   hipLaunchKernelGGL(k_dinv_uniform, dim3((unsigned)(((int64_t)n + B - 1) / B)), dim3(B), 0, s, A->dinv, n,
-                     u.counts + 3);
+                     u.counts + 2);
   HIPCHK(hipGetLastError());
   PatHash found;
   unsigned differ = 0;
   double d0 = 0.0;
-  constexpr size_t kTail = offsetof(PatHash, count);
+  constexpr size_t kTail = offsetof(PatHash, elo);
   HIPCHK(hipMemcpyAsync(hflags + 1, u.flags + 1, sizeof(int), hipMemcpyDeviceToHost, s));
   HIPCHK(hipMemcpyAsync((char*)&found + kTail, (char*)u.t + kTail, sizeof(PatHash) - kTail, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(&differ, u.counts + 3, sizeof(unsigned), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(&differ, u.counts + 2, sizeof(unsigned), hipMemcpyDeviceToHost, s));
   HIPCHK(hipMemcpyAsync(&d0, A->dinv, sizeof(double), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   if (hflags[1] & CHK_ARG) return RPK_ERR_ARG;
@@ -400,18 +398,22 @@ static rpk_status check_and_lay_out(rpk_matrix* A, const Setup& u, hipStream_t s
   A->du = d0;
   RET_IF(build_dictionary(A, found, u.width, u.words, u.t, s));
   if (!A->np) RET_IF(build_sell(A, u.width, s));
-  // Whether and how rows should try the certified row sum first: probe it on a
-  // pseudo-random vector and take the cheaper form (bound only, then with the
-  // exactness check) under which at most one slice in eight has a row it cannot
-  // certify; neither, when both fail more often (results are the same either way).
+  // x_j for which every product is in the exact range of twoprod (kProdLo,
+  // kProdHi): 2^(ea + ex - 2) <= |a x| < 2^(ea + ex)
+  A->xlo = -966 - found.elo;
+  A->xhi = 989 - found.ehi;
+  A->xlsb = found.lsb - 1;
+  // Whether rows should try the certified row sum first: probe it on a
+  // pseudo-random vector; not when more than one slice in eight has a row that it
+  // cannot certify (results are the same either way).
   double* x = (double*)u.words;
   hipLaunchKernelGGL(k_fill_hash, dim3(1024), dim3(256), 0, s, x, (long long)n);
   hipLaunchKernelGGL(k_cert_probe, dim3(G), dim3(256), 0, s, csr_of(A), (const double*)x, u.counts);
   HIPCHK(hipGetLastError());
-  unsigned h[3] = {0u, 0u, 0u};
+  unsigned h[2] = {0u, 0u};
   HIPCHK(hipMemcpyAsync(h, u.counts, sizeof(h), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
-  A->cert = (h[2] > 0 && 8ull * h[0] <= h[2]) ? 1 : (h[2] > 0 && 8ull * h[1] <= h[2]) ? 2 : 0;
+  A->cert = 8ull * h[0] <= h[1] ? 1 : 0;
   return RPK_OK;
 }
 

@@ -19,6 +19,19 @@ __global__ void k_check_rowptr(const int* rp, int n, int nnz, int* flags) {
   if (bad) atomicOr(flags, CHK_ARG);
 }
 
+// What a creation learns of the matrix: its distinct rows and the range of its values.
+constexpr int kPatMax = 255;    // distinct rows (an id is a byte; the last id is the empty row)
+constexpr int kPatSlots = 1024; // hash slots
+
+struct PatHash {
+  unsigned long long key[kPatSlots];  // 0 = free
+  int rep[kPatSlots];                 // lowest row with that hash; k_pat_table: -1 - id
+  int elo, ehi, lsb;                  // of the non-zero values: smallest / largest binary exponent, lowest set bit
+  int count;                          // distinct hashes so far (counts on past kPatMax)
+  int wide;                           // widest slice
+  int fail;                           // a row differs from its representative
+};
+
 __device__ __forceinline__ unsigned long long pat_mix(unsigned long long v) {
   v *= 0x9E3779B97F4A7C15ull;
   v ^= v >> 29;
@@ -51,13 +64,14 @@ struct SliceRows {
 // and, for the row dictionary, each row's hash over its (position, column - row,
 // value).  n + 64 entries of hash.
 __global__ void __launch_bounds__(256) k_setup_rows(const int* rp, const int* ci, const double* v, int n, int nslices,
-                                                    double* dinv, int* width, unsigned long long* hash, int* flags) {
+                                                    double* dinv, int* width, unsigned long long* hash, int* flags,
+                                                    PatHash* t) {
   __shared__ SliceRows R[4];
   __shared__ unsigned long long h[4][64];
   __shared__ double diag[4][64];
   __shared__ int cnt[4][64];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  int fl = 0;
+  int fl = 0, elo = INT_MAX, ehi = INT_MIN, lsb = INT_MAX;
   for (int s = blockIdx.x * 4 + w; s < nslices; s += gridDim.x * 4) {
     R[w].load(rp, n, s);
     h[w][lane] = 0ull;
@@ -70,7 +84,17 @@ __global__ void __launch_bounds__(256) k_setup_rows(const int* rp, const int* ci
       const int c = ci[e];
       const double val = v[e];
       if (c < 0 || c >= n) fl |= CHK_ARG;
-      if (!isfinite(val)) fl |= CHK_NONFINITE;
+      if (!isfinite(val)) {
+        fl |= CHK_NONFINITE;
+      } else if (val != 0.0) {
+        bool neg;
+        unsigned long long mant;
+        int e2;
+        decode(val, neg, mant, e2);
+        lsb = min(lsb, e2 + __ffsll((long long)mant) - 1);
+        elo = min(elo, e2 + 64 - __clzll((long long)mant));
+        ehi = max(ehi, e2 + 64 - __clzll((long long)mant));
+      }
       if (c == r) {
         atomicAdd(&cnt[w][l], 1);
         diag[w][l] = val;
@@ -93,6 +117,15 @@ __global__ void __launch_bounds__(256) k_setup_rows(const int* rp, const int* ci
     __builtin_amdgcn_wave_barrier();
   }
   if (fl) atomicOr(flags, fl);
+  elo = -wave_max_int(-elo);
+  ehi = wave_max_int(ehi);
+  lsb = -wave_max_int(-lsb);
+  // most wavefronts have nothing new for the three words
+  if (lane == 0) {
+    if (elo < __hip_atomic_load(&t->elo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&t->elo, elo);
+    if (ehi > __hip_atomic_load(&t->ehi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&t->ehi, ehi);
+    if (lsb < __hip_atomic_load(&t->lsb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&t->lsb, lsb);
+  }
 }
 
 // *differ = 1 when some dinv_i does not have the bits of dinv_0 (Csr::unif)
@@ -165,58 +198,63 @@ __global__ void k_fill_sell(const int* rp, const int* ci, const double* v, int n
 // open-addressing table, the lowest row with a hash represents it, and every
 // row is then compared with its representative entry by entry, so a hash
 // collision only costs the dictionary, never a value.
-constexpr int kPatMax = 255;    // distinct rows (an id is a byte; the last id is the empty row)
-constexpr int kPatSlots = 1024; // hash slots
-
-struct PatHash {
-  unsigned long long key[kPatSlots];  // 0 = free
-  int rep[kPatSlots];                 // lowest row with that hash; k_pat_table: -1 - id
-  int count;                          // distinct hashes so far (counts on past kPatMax)
-  int wide;                           // widest slice
-  int fail;                           // a row differs from its representative
-  int pad;
-};
-
 __global__ void __launch_bounds__(1024) k_pat_clear(PatHash* t) {
   for (int i = threadIdx.x; i < kPatSlots; i += blockDim.x) {
     t->key[i] = 0ull;
     t->rep[i] = 0x7fffffff;
   }
-  if (threadIdx.x == 0) t->count = t->wide = t->fail = t->pad = 0;
+  if (threadIdx.x == 0) {
+    t->count = t->wide = t->fail = 0;
+    t->elo = t->lsb = INT_MAX;
+    t->ehi = INT_MIN;
+  }
 }
 
-// One row per thread: enter the row's hash, note the lowest row.  A thread's
-// rows ascend, so a row with the hash of the thread's row before needs nothing.
-// Threads stop once more than kPatMax different rows have been seen (a matrix
-// without structure ends here after a few thousand rows).
+// Enter every row's hash and note the lowest row seen with it.  Each workgroup
+// takes a contiguous chunk of rows; a hash goes to the device's table once per
+// wavefront that meets it first (its lowest lane) and then never again from
+// that workgroup, which keeps the hashes it has entered in LDS: with every
+// thread looking for itself, the hot words took 2.6 ms at 128^3.  Wavefronts
+// stop once more than kPatMax different rows have been seen (a matrix without
+// structure ends here after a few thousand rows).
 __global__ void __launch_bounds__(256) k_pat_find(const unsigned long long* hash, int n, PatHash* t) {
-  const int stride = gridDim.x * blockDim.x;
-  unsigned long long last = 0ull;
-  for (long long r = blockIdx.x * (long long)blockDim.x + threadIdx.x; r < n; r += stride) {
+  __shared__ unsigned long long seen[512];
+  for (int i = threadIdx.x; i < 512; i += blockDim.x) seen[i] = 0ull;
+  __syncthreads();
+  const long long chunk = ((long long)n + gridDim.x - 1) / gridDim.x;
+  const long long lo = blockIdx.x * chunk, hi = lo + chunk < n ? lo + chunk : n;
+  for (long long r = lo + threadIdx.x; r < hi; r += blockDim.x) {
     const unsigned long long h = hash[r];
-    if (h == last) continue;
-    last = h;
-    int i = (int)(h >> 32) & (kPatSlots - 1);
-    for (;; i = (i + 1) & (kPatSlots - 1)) {
-      unsigned long long k = __hip_atomic_load(&t->key[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (k == h) break;
-      if (__hip_atomic_load(&t->count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > kPatMax) return;
-      if (k == 0ull) {
-        k = atomicCAS(&t->key[i], 0ull, h);
-        if (k == 0ull) atomicAdd(&t->count, 1);
-        if (k == 0ull || k == h) break;
+    unsigned long long todo = __ballot(seen[(h >> 8) & 511] != h);
+    while (todo) {  // one lane for each different hash that is new here
+      const int l = __ffsll((long long)todo) - 1;
+      const unsigned long long hl = __shfl(h, l, 64);
+      todo &= ~__ballot(h == hl);
+      bool many = false;
+      if ((int)(threadIdx.x & 63) == l) {
+        int i = (int)(h >> 32) & (kPatSlots - 1);
+        for (;; i = (i + 1) & (kPatSlots - 1)) {
+          many = __hip_atomic_load(&t->count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > kPatMax;
+          if (many) break;  // also when the table is full
+          unsigned long long k = __hip_atomic_load(&t->key[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (k == 0ull) {
+            k = atomicCAS(&t->key[i], 0ull, h);
+            if (k == 0ull) atomicAdd(&t->count, 1);
+          }
+          if (k == 0ull || k == h) break;
+        }
+        if (!many) atomicMin(&t->rep[i], (int)r);
+        seen[(h >> 8) & 511] = h;
       }
+      if (__ballot(many)) return;
     }
-    if (__hip_atomic_load(&t->rep[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > (int)r)
-      atomicMin(&t->rep[i], (int)r);
   }
 }
 
 // One workgroup: number the distinct rows by their lowest row, and write the
-// dictionary, padded with (offset 0, value 0) to pw entries; id np - 1 is the
-// empty row.
+// dictionary, its rows padded with (0, own element); id np - 1 is the empty row.
 __global__ void __launch_bounds__(1024) k_pat_table(const int* rp, const int* ci, const double* v, PatHash* t, int np,
-                                                    int pw, double* pval, int* poff) {
+                                                    int pw, PatEnt* pat) {
   __shared__ int rep[kPatMax + 1];
   __shared__ int byid[kPatMax + 1];
   __shared__ int cnt;
@@ -234,12 +272,12 @@ __global__ void __launch_bounds__(1024) k_pat_table(const int* rp, const int* ci
       t->rep[i] = -1 - id;
     }
   __syncthreads();
-  for (int k = threadIdx.x; k < np * pw; k += blockDim.x) {
-    const int j = k / np, id = k - j * np;
+  const int stride = pat_stride(pw);
+  for (int k = threadIdx.x; k < np * stride; k += blockDim.x) {
+    const int id = k / stride, j = k - id * stride;
     const int r = id < np - 1 ? byid[id] : 0;
     const int k0 = rp[r], len = id < np - 1 ? rp[r + 1] - k0 : 0;
-    pval[k] = j < len ? v[k0 + j] : 0.0;
-    poff[k] = j < len ? ci[k0 + j] - r : 0;
+    pat[k] = j < len ? PatEnt{v[k0 + j], 8 * (ci[k0 + j] - r), 0} : PatEnt{0.0, 0, 0};
   }
 }
 
@@ -247,11 +285,11 @@ __global__ void __launch_bounds__(1024) k_pat_table(const int* rp, const int* ci
 // that dictionary row, bit by bit; the slice's width.
 __global__ void __launch_bounds__(256) k_pat_rows(const int* rp, const int* ci, const double* v, int n, int nslices,
                                                   const int* width, const unsigned long long* hash, PatHash* t, int np,
-                                                  int pw, const double* pval, const int* poff, unsigned char* pid,
-                                                  unsigned char* swid) {
+                                                  int pw, const PatEnt* pat, unsigned char* pid, unsigned char* swid) {
   __shared__ SliceRows R[4];
   __shared__ int id[4][64];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int stride = pat_stride(pw);
   bool bad = false;
   unsigned long long last = 0ull;
   int last_id = 0;
@@ -273,7 +311,12 @@ __global__ void __launch_bounds__(256) k_pat_rows(const int* rp, const int* ci, 
         mine = np - 1;
       } else {  // as long as the representative: it has an entry here and the padding behind it
         const int len = rp[r + 1] - rp[r];
-        bad |= len > pw || (len < pw && (pval[len * np + mine] != 0.0 || poff[len * np + mine] != 0));
+        if (len > pw) {
+          bad = true;
+        } else {
+          const PatEnt behind = pat[mine * stride + len];
+          bad |= behind.a != 0.0 || behind.off8 != 0;
+        }
       }
     }
     id[w][lane] = mine;
@@ -285,9 +328,9 @@ __global__ void __launch_bounds__(256) k_pat_rows(const int* rp, const int* ci, 
     for (int e = R[w].rp[0] + lane; e < e1; e += 64) {
       const int l = R[w].row_of(e);
       const int j = e - R[w].rp[l];
-      const int at = (j < pw ? j : 0) * np + id[w][l];
-      bad |= j >= pw || ci[e] - (64 * s + l) != poff[at] ||
-             __double_as_longlong(v[e]) != __double_as_longlong(pval[at]);
+      const PatEnt p = pat[id[w][l] * stride + (j < pw ? j : 0)];
+      bad |= j >= pw || 8 * (ci[e] - (64 * s + l)) != p.off8 ||
+             __double_as_longlong(v[e]) != __double_as_longlong(p.a);
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     __builtin_amdgcn_wave_barrier();
@@ -295,47 +338,37 @@ __global__ void __launch_bounds__(256) k_pat_rows(const int* rp, const int* ci, 
   if (__ballot(bad) && lane == 0) atomicOr(&t->fail, 1);
 }
 
-// Probe at matrix creation: one wavefront per slice tries row_cert on x, by
-// the bound alone and with the exactness check; counts[0] / counts[1] += slices
-// where some row was not certified that way, counts[2] += slices.  Rows whose
-// sums often land exactly on a rounding midpoint fail the first, and rows the
-// certificate cannot help fail both; the matrix takes the cheapest way that
-// rarely fails.
-// Workgroups count in LDS first: one atomic of every wavefront on the same
-// three words took most of the probe's time (128^3: 755 us).
+// Probe at matrix creation: counts[0] += slices where row_cert did not certify
+// some row on x, counts[1] += slices.  Workgroups count in LDS first: an atomic
+// of every wavefront on the same words took most of the probe's time (128^3:
+// 755 us).
 __global__ void __launch_bounds__(256) k_cert_probe(Csr A, const double* __restrict__ x, unsigned* counts) {
-  __shared__ unsigned mine[3];
-  if (threadIdx.x < 3) mine[threadIdx.x] = 0u;
+  __shared__ unsigned mine[2];
+  if (threadIdx.x < 2) mine[threadIdx.x] = 0u;
   __syncthreads();
   const int nslices = (A.n + 63) >> 6;
   const int lane = threadIdx.x & 63;
   for (int s = (int)((blockIdx.x * (size_t)blockDim.x + threadIdx.x) >> 6); s < nslices;
        s += (int)((gridDim.x * (size_t)blockDim.x) >> 6)) {  // whole wavefronts
     double y;
-    const bool valid = (s << 6) + lane < A.n;
-    bool c1, c2;
+    const int row = (s << 6) + lane;
+    bool c;
     if (A.np) {  // the dictionary read from device memory
-      const int row = (s << 6) + lane;
-      const PatSrc src{A.pval, A.poff, A.np, row < A.n ? row : A.n - 1, (int)A.pid[row]};
-      c1 = row_cert<false>(src, GatherX{x}, A.swid[s], y);
-      c2 = row_cert<true>(src, GatherX{x}, A.swid[s], y);
+      const PatSrc src{A.pat, (unsigned)(row < A.n ? row : A.n - 1) * 8u, (int)A.pid[row] * pat_stride(A.pw)};
+      c = row_cert(A, src, GatherX{x}, A.swid[s], y);
     } else {
       const long long off = A.sptr[s];
-      const int w = (int)((A.sptr[s + 1] - off) >> 6);
-      const SellSrc<true> src{A.sval + off, A.scol + off, lane};
-      c1 = row_cert<false>(src, GatherX{x}, w, y);
-      c2 = row_cert<true>(src, GatherX{x}, w, y);
+      const SellSrc<true> src{A.sval + off, A.scol + off};
+      c = row_cert(A, src, GatherX{x}, (int)((A.sptr[s + 1] - off) >> 6), y);
     }
-    const bool fail1 = __ballot(valid && !c1) != 0ull;
-    const bool fail2 = __ballot(valid && !c2) != 0ull;
+    const bool fail = __ballot(row < A.n && !c) != 0ull;
     if (lane == 0) {
-      atomicAdd(&mine[2], 1u);
-      if (fail1) atomicAdd(&mine[0], 1u);
-      if (fail2) atomicAdd(&mine[1], 1u);
+      atomicAdd(&mine[1], 1u);
+      if (fail) atomicAdd(&mine[0], 1u);
     }
   }
   __syncthreads();
-  if (threadIdx.x < 3 && mine[threadIdx.x]) atomicAdd(&counts[threadIdx.x], mine[threadIdx.x]);
+  if (threadIdx.x < 2 && mine[threadIdx.x]) atomicAdd(&counts[threadIdx.x], mine[threadIdx.x]);
 }
 
 // x[i] in [-1, 1) from a 64-bit mix of i (the certified-row probe's input)
