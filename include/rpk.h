@@ -180,7 +180,7 @@ rpk_status rpk_exdot(int64_t n, const double* x, const double* y, double* out_de
 /* rpk_exdot for callers that cannot allocate device memory -- code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc: the same
  * kernels and results (bit for bit) as rpk_exdot with this n, dots and launch,
- * but no workspace argument: the reduction scratch is a 1 MiB array in device
+ * but no workspace argument: the reduction scratch is an array of 1,088 KiB in device
  * memory that the library holds on every device it runs on until the process
  * ends.  The call itself allocates nothing (no hipMalloc / hipFree, no
  * allocating library routine); it clears the scratch's counters with a small

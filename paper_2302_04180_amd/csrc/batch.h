@@ -252,7 +252,7 @@ __global__ void __launch_bounds__(1024) kb_pipe_spmv_fin(Batch B) {
     const SysDesc& D = B.sys[T.sys];
     if (!D.V.st->spmv_go) continue;
     if (T.rec == 0) {
-      block_finalize_last<N, K>(s, D.red, 0);
+      block_finalize<N, K, FIN_CLEAR>(s, D.red, 0);
       if (threadIdx.x == 0) finish_step<N, K, F>(s, D.V);
     }
     pat_load(D.A, s);

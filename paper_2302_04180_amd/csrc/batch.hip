@@ -96,6 +96,7 @@ SysDesc make_desc(const rpk_matrix* A, const double* b, double* x, char* base, i
   r.gsa = (long long*)(base + up(kFlagsBytes));
   r.partials = (double*)(base + up(kFlagsBytes) + up((size_t)MAX_DOTS * SA_D * 8));
   r.G = G;
+  r.copies = 1;  // a system's tiles are few
   char* vec = (char*)r.partials + up((size_t)MAX_DOTS * gcap * 8);
   const size_t step = up((size_t)A->n * 8);
   double* p[16];

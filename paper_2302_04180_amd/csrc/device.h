@@ -180,17 +180,16 @@ __device__ __forceinline__ void sa_add_int(long long* acc, bool neg, unsigned lo
                                            unsigned long long lo, int e) {
   const int pos = e - SA_LSB;
   const int d = pos >> 5, sh = pos & 31;
-  const unsigned long long w0 = lo << sh;
-  const unsigned long long w1 = (hi << sh) | (sh ? (lo >> (64 - sh)) : 0ull);
-  const unsigned long long w2 = sh ? (hi >> (64 - sh)) : 0ull;
-  const unsigned int ch[5] = {(unsigned int)w0, (unsigned int)(w0 >> 32), (unsigned int)w1,
-                              (unsigned int)(w1 >> 32), (unsigned int)w2};
-#pragma unroll
+  unsigned long long w0 = lo << sh;
+  unsigned long long w1 = (hi << sh) | (sh ? (lo >> (64 - sh)) : 0ull);
+  unsigned long long w2 = sh ? (hi >> (64 - sh)) : 0ull;
+#pragma unroll 1  // a rare path: kept small, it is inlined wherever a dot is accumulated
   for (int j = 0; j < 5; ++j) {
-    if (ch[j]) {
-      const long long add = neg ? -(long long)ch[j] : (long long)ch[j];
-      atomicAdd((unsigned long long*)&acc[d + j], (unsigned long long)add);
-    }
+    const long long ch = (long long)(w0 & 0xffffffffull);
+    if (ch) atomicAdd((unsigned long long*)&acc[d + j], (unsigned long long)(neg ? -ch : ch));
+    w0 = (w0 >> 32) | (w1 << 32);
+    w1 = (w1 >> 32) | (w2 << 32);
+    w2 >>= 32;
   }
 }
 
@@ -207,15 +206,6 @@ __device__ __forceinline__ void decode(double x, bool& neg, unsigned long long& 
     m = fr | (1ull << 52);
     e = f - 1075;
   }
-}
-
-__device__ __forceinline__ void sa_add_double(long long* acc, double x) {
-  if (x == 0.0) return;
-  bool neg;
-  unsigned long long m;
-  int e;
-  decode(x, neg, m, e);
-  sa_add_int(acc, neg, 0ull, m, e);
 }
 
 // exact a*b of finite doubles through the 106-bit integer product
@@ -292,74 +282,76 @@ __device__ inline double window_round(long long* w, int lo, int hi, int base) {
   return __longlong_as_double((long long)bits);
 }
 
-// Same rounding for a window of W digits copied into registers first (one thread;
-// static indexing only, so no memory latency in the carry chain).  The window's
-// top two digits must be zero on entry (carry room).
-template <int W>
-__device__ inline double window_round_reg(const long long* win, int base) {
-  long long d[W];
-#pragma unroll
-  for (int k = 0; k < W; ++k) d[k] = win[k];
-  long long carry = 0;
-#pragma unroll
-  for (int k = 0; k < W - 1; ++k) {
-    const long long v = d[k] + carry;
-    d[k] = v & 0xffffffffll;
-    carry = v >> 32;
-  }
-  long long top = d[W - 1] + carry;
-  const bool neg = top < 0;
+// lane l of the result: v of lane l - 1 (lane 0: 0)
+__device__ __forceinline__ unsigned wave_up1(unsigned v) {
+  return (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x138, 0xf, 0xf, false);  // wave_shr:1
+}
+
+// Lanes that receive a carry (or borrow), given the lanes `t` that receive one
+// from the lane below at once and the lanes `p` that pass one on.
+__device__ __forceinline__ unsigned long long carry_lanes(unsigned long long t, unsigned long long p) {
+  return (t + p) ^ p;
+}
+
+// Whole wavefront: the same rounding of the digits base + l held by lanes l
+// (signed 64-bit, carries not propagated, lanes 62 and 63 zero).  One digit a
+// lane: two shifts of the high words bring every digit to at most 2^32, one
+// 64-bit addition of lane masks then carries through all of them at once, and the
+// leading bits are read from at most three lanes.  In one thread the carry chain
+// and the selections of a 16-digit window were some 1,500 cycles at the start of
+// every kernel that takes a reduction.  The digits are made non-negative by
+// adding 2^63 to each (S = sum of 2^(63 + 32 l)), which is taken off again
+// afterwards, so that carries have one sign.  Every lane returns the result.
+__device__ __forceinline__ double round_lanes(long long v, int base) {
+  const int lane = threadIdx.x & 63;
+  unsigned long long u = (unsigned long long)v ^ 0x8000000000000000ull;  // v + 2^63
+  u = (u & 0xffffffffull) + wave_up1((unsigned)(u >> 32));
+  u = (u & 0xffffffffull) + wave_up1((unsigned)(u >> 32));  // at most 2^32
+  unsigned d = (unsigned)u;
+  unsigned long long g = __ballot((u >> 32) != 0ull);
+  unsigned long long in = carry_lanes(g << 1, __ballot(d == 0xffffffffu));
+  d += (unsigned)((in >> lane) & 1ull);
+  const unsigned sub = lane ? 0x80000000u : 0u;  // digit l of S, modulo 2^(32 * 64)
+  g = __ballot(d < sub);
+  in = carry_lanes(g << 1, __ballot(d == sub));
+  d = d - sub - (unsigned)((in >> lane) & 1ull);
+  const bool neg = (__builtin_amdgcn_readlane((int)d, 63) < 0);  // two's complement over the 64 digits
   if (neg) {
-    long long borrow = 0;
-#pragma unroll
-    for (int k = 0; k < W - 1; ++k) {
-      const long long v = -d[k] - borrow;
-      d[k] = v & 0xffffffffll;
-      borrow = (v < 0) ? 1 : 0;
-    }
-    top = -top - borrow;
+    d = ~d;
+    in = carry_lanes(1ull, __ballot(d == 0xffffffffu));
+    d += (unsigned)((in >> lane) & 1ull);
   }
-  d[W - 1] = top;
-  int t = -1;
-#pragma unroll
-  for (int k = 0; k < W; ++k)
-    if (d[k] != 0) t = k;
-  if (t < 0) return 0.0;
-  long long dt = 0;
-#pragma unroll
-  for (int k = 0; k < W; ++k)
-    if (k == t) dt = d[k];
-  const int lead = 32 * (base + t) + (63 - __clzll((unsigned long long)dt));
-  const int low = (lead - 52 > SA_SUB_BIT) ? lead - 52 : SA_SUB_BIT;
-  const int nbits = lead - low + 1;
-  const int a = (low >> 5) - base, sh = low & 31;  // window index of the digit holding bit `low`
-  unsigned long long x0 = 0, x1 = 0, x2 = 0;
-#pragma unroll
-  for (int k = 0; k < W; ++k) {
-    x0 = (k == a) ? (unsigned long long)d[k] : x0;
-    x1 = (k == a + 1) ? (unsigned long long)d[k] : x1;
-    x2 = (k == a + 2) ? (unsigned long long)d[k] : x2;
+  const unsigned long long nz = __ballot(d != 0u);
+  if (nz == 0ull) return 0.0;
+  const int t = 63 - __clzll((long long)nz);
+  const unsigned d0 = (unsigned)__builtin_amdgcn_readlane((int)d, t);
+  const unsigned d1 = t >= 1 ? (unsigned)__builtin_amdgcn_readlane((int)d, t - 1) : 0u;
+  const unsigned d2 = t >= 2 ? (unsigned)__builtin_amdgcn_readlane((int)d, t - 2) : 0u;
+  const bool below = t >= 3 && (nz & ((1ull << (t - 2)) - 1ull)) != 0ull;
+  const unsigned long long hi = ((unsigned long long)d0 << 32) | d1;
+  const int gb = 32 * (base + t - 2);                               // grid bit of d2's lowest bit
+  const int lead = gb + 127 - __clzll((long long)hi) - 32;          // grid bit of the leading 1
+  const int low = (lead - 52 > SA_SUB_BIT) ? lead - 52 : SA_SUB_BIT;  // grid bit of the last kept bit
+  const int drop = low - gb;  // bits of the 96-bit hi:d2 below it, at least 12
+  unsigned long long mant, rest;
+  bool guard;
+  if (drop > 96) {  // less than half the smallest subnormal
+    mant = 0ull;
+    guard = false;
+    rest = 1ull;
+  } else if (drop >= 33) {
+    const int s = drop - 32;  // bits of hi below the last kept one: 1 .. 64
+    mant = s < 64 ? hi >> s : 0ull;
+    guard = ((hi >> (s - 1)) & 1ull) != 0ull;
+    rest = (hi & ((1ull << (s - 1)) - 1ull)) | d2;
+  } else {
+    mant = (hi << (32 - drop)) | ((unsigned long long)d2 >> drop);
+    guard = ((d2 >> (drop - 1)) & 1u) != 0u;
+    rest = d2 & ((1u << (drop - 1)) - 1u);
   }
-  unsigned long long mant = 0;
-  if (nbits > 0) {
-    mant = (x0 | (x1 << 32)) >> sh;
-    if (64 - sh < nbits) mant |= x2 << (64 - sh);
-    mant &= (1ull << nbits) - 1ull;
-  }
-  const int g = low - 1;
-  const int gi = (g >> 5) - base, gb = g & 31;
-  unsigned long long gdig = 0;
-  int sticky = 0;
-#pragma unroll
-  for (int k = 0; k < W; ++k) {
-    gdig = (k == gi) ? (unsigned long long)d[k] : gdig;
-    sticky |= (k < gi && d[k] != 0) ? 1 : 0;
-  }
-  const int guard = (int)((gdig >> gb) & 1ull);
-  sticky |= (gdig & ((1ull << gb) - 1ull)) != 0ull;
-  if (guard && (sticky || (mant & 1ull))) mant += 1ull;
-  const long long q = (long long)low + SA_LSB;
-  unsigned long long bits = ((unsigned long long)(q + 1074) << 52) + mant;
+  if (guard && (rest != 0ull || below || (mant & 1ull))) mant += 1ull;
+  // value = mant * 2^q, q = low + SA_LSB >= -1074; IEEE bits = ((q + 1074) << 52) + mant
+  unsigned long long bits = ((unsigned long long)(low + SA_LSB + 1074) << 52) + mant;
   if (bits >= 0x7ff0000000000000ull) bits = 0x7ff0000000000000ull;
   if (neg) bits |= 0x8000000000000000ull;
   return __longlong_as_double((long long)bits);
@@ -435,18 +427,27 @@ __device__ __forceinline__ void acc_prod(Fpe<N>& f, double a, double b, long lon
   const double l2 = fpe_add_all<N, (N > 1 ? 1 : 0)>(f, e);
   const bool extreme = !ok && !(p == 0.0 && (a == 0.0 || b == 0.0));
   if (l1 != 0.0 || l2 != 0.0 || extreme) {
-    if (l1 != 0.0 || l2 != 0.0) {
-      sa_add_double(sa, l1);
-      sa_add_double(sa, l2);
-      atomicOr(flag, F_SA);
-    }
-    if (extreme) {
-      if (!isfinite(a) || !isfinite(b)) {
-        atomicOr(flag, F_NONFINITE);
-      } else {
-        sa_add_prod(sa, a, b);
-        atomicOr(flag, F_SA);
+    const bool finite = isfinite(a) && isfinite(b);
+    atomicOr(flag, extreme && !finite ? F_NONFINITE : F_SA);
+#pragma unroll 1  // one body for l1, l2 and the product (rare, inlined often)
+    for (int k = 0; k < 3; ++k) {
+      const double x = k == 0 ? l1 : k == 1 ? l2 : (extreme && finite) ? a : 0.0;
+      if (x == 0.0) continue;
+      bool neg;
+      unsigned long long m, hi = 0ull;
+      int e;
+      decode(x, neg, m, e);
+      if (k == 2) {  // the exact product
+        bool nb;
+        unsigned long long mb;
+        int eb;
+        decode(b, nb, mb, eb);
+        hi = __umul64hi(m, mb);
+        m *= mb;
+        neg = neg != nb;
+        e += eb;
       }
+      sa_add_int(sa, neg, hi, m, e);
     }
   }
 }

@@ -108,41 +108,48 @@ struct State {
 // Reduction scratch in the caller's workspace (left zeroed after every use).
 struct Red {
   double* partials;    // plain mode: [slot][G] workgroup sums
-  long long* gsa;      // [slot][SA_D] global long accumulators
+  long long* gsa;      // [copies][MAX_DOTS slots][SA_D] global long accumulators
   int* gflags;         // [slot]
   unsigned* tickets;   // [8] arrival counters
   int G;               // number of workgroups (or tiles) that publish
+  int copies;          // of each accumulator: workgroup b adds into copy b % copies (red_copies)
 };
+// Additions of many workgroups into one address are performed one after another
+// (about 10 ns each), which the end of a kernel waits for: with 512 workgroups
+// and one copy of each accumulator, kernel B of a 64^3 solve took 12.8 us, with
+// eight 9.1 (128^3: 29.4 and 27.6).  Fewer workgroups queue less, and with few
+// copies the threads of a small workgroup load all of them at once (DCAP).
+constexpr int kMaxCopies = 8;
+__host__ __device__ constexpr int red_copies(int grid) { return grid >= 256 ? kMaxCopies : grid >= 64 ? 4 : 1; }
 
 // ---------------------------------------------------------------------------
 // LDS layout
 // ---------------------------------------------------------------------------
-// lanes per scatter round: all 64 for workgroups of up to 512 threads, 32 for larger ones
-__host__ __device__ inline int scat_rows(int block) { return block <= 512 ? 64 : 32; }
-// LDS stride of the scatter rows (digits): one digit of padding puts the rows of
-// 16 consecutive lanes on distinct banks
+// The window of an exact reduction: 64 rows of WIN digits per dot, row l shared
+// by lane l of every wavefront.  One digit of padding puts the rows of 16
+// consecutive lanes on distinct banks.
 constexpr int ROW_STRIDE = WIN + 1;
 
 __host__ __device__ inline size_t shm_bytes(int N, int K, bool rows, int block) {
-  const size_t nw = (size_t)block / 64;
-  const size_t sa = (N > 0 && N != LW8) ? (size_t)K * SA_D * 8 : 0;
-  // scatter rows (nw x rows x ROW_STRIDE); the row-fallback accumulators (nw x SA_D)
-  // use the same space at other times
-  const size_t scat = (N > 0) ? nw * scat_rows(block) * ROW_STRIDE * 8 : 0;
-  const size_t wsum = (N > 0) ? nw * WIN * (K > 0 ? K : 1) * 8 : 0;
+  const size_t nw = (size_t)block / 64, k1 = K > 0 ? K : 1;
+  const bool exact = N > 0 && N != LW8;
+  const size_t sa = exact ? (size_t)K * SA_D * 8 : 0;
+  const size_t scat = exact ? (size_t)K * 64 * ROW_STRIDE * 8 : 0;
+  const size_t wsa = N > 0 && rows ? nw * SA_D * 8 : 0;
+  const size_t wsum = exact ? k1 * WIN * 8 : N == LW8 ? nw * k1 * LW_REC * 8 : 0;
   const size_t pat = rows ? (size_t)kPatEntries * sizeof(PatEnt) : 0;
-  return pat + sa + scat + wsum + 16 * 8 + 16 * MAX_DOTS * 4 + MAX_DOTS * 8 + MAX_DOTS * 4 + (4 + MAX_DOTS) * 4;
+  return pat + sa + scat + wsa + wsum + 16 * 8 + MAX_DOTS * 4 + MAX_DOTS * 8 + MAX_DOTS * 4 + (4 + MAX_DOTS) * 4;
 }
 
 template <int N>
 struct Shm {
   PatEnt* pat;      // row dictionary of the matrix (kernels with rows)
   long long* sa;    // K * SA_D    long accumulators (rare path)
-  long long* wsa;   // nw * SA_D   row fallback accumulators (aliases scat)
-  long long* scat;  // nw * rows * ROW_STRIDE scatter rows
-  long long* wsum;  // nw * K * WIN  per-wave window sums (lightweight: nw * K * LW_REC doubles)
+  long long* scat;  // K * 64 * ROW_STRIDE window rows
+  long long* wsa;   // nw * SA_D   row fallback accumulators (kernels with rows)
+  long long* wsum;  // K * WIN     window sums (lightweight: nw * K * LW_REC doubles)
   double* pbuf;     // 16          plain per-wave sums
-  int* imax;        // 16 * MAX_DOTS per-wave maxima
+  int* imax;        // MAX_DOTS    highest digit of the workgroup's components, -1: none
   double* res;      // MAX_DOTS
   int* flag;        // MAX_DOTS
   int* misc;        // 4 + MAX_DOTS  ([1..K] flags, [10] last-arrival, [11] sink)
@@ -151,21 +158,23 @@ struct Shm {
 template <int N>
 __device__ __forceinline__ Shm<N> shm_carve(char* base, int K, bool rows) {
   Shm<N> s;
-  const size_t nw = blockDim.x / 64;
+  const size_t nw = blockDim.x / 64, k1 = K > 0 ? K : 1;
+  constexpr bool exact = N > 0 && N != LW8;
   size_t off = 0;
   s.pat = (PatEnt*)(base + off);
   off += rows ? (size_t)kPatEntries * sizeof(PatEnt) : 0;
   s.sa = (long long*)(base + off);
-  off += (N > 0 && N != LW8) ? (size_t)K * SA_D * 8 : 0;
+  off += exact ? (size_t)K * SA_D * 8 : 0;
   s.scat = (long long*)(base + off);
-  s.wsa = s.scat;
-  off += (N > 0) ? nw * scat_rows(blockDim.x) * ROW_STRIDE * 8 : 0;
+  off += exact ? (size_t)K * 64 * ROW_STRIDE * 8 : 0;
+  s.wsa = (long long*)(base + off);
+  off += N > 0 && rows ? nw * SA_D * 8 : 0;
   s.wsum = (long long*)(base + off);
-  off += (N > 0) ? nw * WIN * (K > 0 ? K : 1) * 8 : 0;
+  off += exact ? k1 * WIN * 8 : N == LW8 ? nw * k1 * LW_REC * 8 : 0;
   s.pbuf = (double*)(base + off);
   off += 16 * 8;
   s.imax = (int*)(base + off);
-  off += 16 * MAX_DOTS * 4;
+  off += MAX_DOTS * 4;
   s.res = (double*)(base + off);
   off += MAX_DOTS * 8;
   s.flag = (int*)(base + off);
@@ -182,12 +191,17 @@ __device__ __forceinline__ void pat_load(const Csr& A, const Shm<N>& s) {
   for (int k = threadIdx.x; k < cnt; k += blockDim.x) ((int4*)s.pat)[k] = ((const int4*)A.pat)[k];
 }
 
-// zero the K long accumulators and flags of this block (must precede any deposit)
+// zero the K long accumulators, window rows and flags of this block (must precede any deposit)
 template <int N>
 __device__ __forceinline__ void shm_init(const Shm<N>& s, int K) {
-  if (N > 0 && N != LW8)
+  if (N > 0 && N != LW8) {
     for (int k = threadIdx.x; k < K * SA_D; k += blockDim.x) s.sa[k] = 0;
-  if (threadIdx.x < MAX_DOTS) s.flag[threadIdx.x] = 0;
+    for (int k = threadIdx.x; k < K * 64 * ROW_STRIDE; k += blockDim.x) s.scat[k] = 0;
+  }
+  if (threadIdx.x < MAX_DOTS) {
+    s.flag[threadIdx.x] = 0;
+    s.imax[threadIdx.x] = -1;
+  }
   __syncthreads();
 }
 
@@ -461,6 +475,27 @@ struct CertSum {
   int elo = INT_MAX, ehi = INT_MIN;  // binary exponents of the x_j
 };
 
+// Whether the sums prove y = RN(T) (terms: entries summed, padding included).
+__device__ __forceinline__ bool cert_finish(const Csr& A, const CertSum& c, int terms, double& y) {
+  const double s = c.s, q = c.q, m = c.m;
+  y = s + (q + 0.0);  // +0 where both are zero
+  const double ay = fabs(y);
+  const bool in = c.elo >= A.xlo && c.ehi <= A.xhi && ay < 0x1p1020;  // false for a NaN y
+  // every error term is 0 (the sum is s exactly, +0 for a zero row), or every
+  // addition into q was exact
+  const bool exactq = m == 0.0 || __builtin_amdgcn_frexp_exp(m) <= c.elo + A.xlsb;
+  const double k = 2.0 * terms + 2.0;  // two error terms per entry
+  const double E = (m * (k * 0x1p-53)) * (1.0 + 0x1p-28) + k * 0x1p-1074;
+  const double z = y - s;
+  const double r = (s - (y - z)) + (q - z);
+  const unsigned long long bits = (unsigned long long)__double_as_longlong(ay);
+  const double up = __longlong_as_double((long long)(bits + 1ull)) - ay;  // spacing above |y|
+  const bool pow2 = (bits & ((1ull << 52) - 1ull)) == 0ull;               // then the spacing below is up / 2
+  const double half = pow2 ? 0.25 * up : 0.5 * up;
+  const bool bound = ay >= 0x1p-960 && (fabs(r) + E) * (1.0 + 0x1p-50) < half;
+  return in && (exactq || bound);
+}
+
 template <int B, class Src, class Gth>
 __device__ __forceinline__ void cert_batch(const Src& src, const Gth& gx, int j0, int w, CertSum& c) {
   double a[B], b[B];
@@ -510,23 +545,7 @@ __device__ __forceinline__ bool row_cert(const Csr& A, const Src& src, const Gth
     cert_batch<4>(src, gx, j0, w, c);
     j0 += 4;
   }
-  const double s = c.s, q = c.q, m = c.m;
-  y = s + (q + 0.0);  // +0 where both are zero
-  const double ay = fabs(y);
-  const bool in = c.elo >= A.xlo && c.ehi <= A.xhi && ay < 0x1p1020;  // false for a NaN y
-  // every error term is 0 (the sum is s exactly, +0 for a zero row), or every
-  // addition into q was exact
-  const bool exactq = m == 0.0 || __builtin_amdgcn_frexp_exp(m) <= c.elo + A.xlsb;
-  const double k = 2.0 * j0 + 2.0;  // two error terms per entry
-  const double E = (m * (k * 0x1p-53)) * (1.0 + 0x1p-28) + k * 0x1p-1074;
-  const double z = y - s;
-  const double r = (s - (y - z)) + (q - z);
-  const unsigned long long bits = (unsigned long long)__double_as_longlong(ay);
-  const double up = __longlong_as_double((long long)(bits + 1ull)) - ay;  // spacing above |y|
-  const bool pow2 = (bits & ((1ull << 52) - 1ull)) == 0ull;               // then the spacing below is up / 2
-  const double half = pow2 ? 0.25 * up : 0.5 * up;
-  const bool bound = ay >= 0x1p-960 && (fabs(r) + E) * (1.0 + 0x1p-50) < half;
-  return in && (exactq || bound);
+  return cert_finish(A, c, j0, y);
 }
 
 // Exact slow path: the whole wavefront sums lane l's row in its private long
@@ -597,64 +616,63 @@ __device__ __forceinline__ double rows_fpe(const Src& src, const Gth& gx, int w,
   return y;
 }
 
-// Rows first..first+63 of one wavefront (first a multiple of 64, lane l holds
-// row first+l); must be called by all 64 lanes.  The entries come from the row
-// dictionary where the matrix has one, else from the SELL copy, whose slice
-// decides the kind of load (Csr::keep).  Exact rows try the certified
-// compensated sum first where the matrix's probe chose it: its dependency chain
-// is a few additions per entry, an FPE insertion's several twosums with a
-// data-dependent exit after each; a wavefront with a row that is not certified
-// takes all its rows the other way (its entries are in the caches by then).
-// Every path gives the same values.
-template <int N, class Gth>
-__device__ __forceinline__ double rows_wave_g(const Csr& A, const Gth& gx, int row, bool valid, const Shm<N>& s) {
-  if (__ballot(valid) == 0ull) return 0.0;
-  const int lane = threadIdx.x & 63;
-  const int sl = __builtin_amdgcn_readfirstlane(row) >> 6;
-  double y = 0.0;
-  if (A.np) {
-    const int w = __builtin_amdgcn_readfirstlane((int)A.swid[sl]);
-    const PatSrc src{s.pat, (unsigned)(row < A.n ? row : A.n - 1) * 8u,
-                     (int)A.pid[(size_t)sl * 64 + lane] * pat_stride(A.pw)};
-    if constexpr (N == 0) {
-      return row_plain(src, gx, w);
-    } else {
-      if (A.cert) {
-        const bool cert = row_cert(A, src, gx, w, y);
-        if (__ballot(valid && !cert) == 0ull) return y;
+// This workgroup's rows R (R.lo a multiple of 64), one a thread at a time:
+// pre(i) loads what the kernel needs of its own row i (called for rows of R
+// only), use(i, ok, v, p) takes the row value v = (A g)_i and p = pre(i).  The
+// entries come from the row dictionary where the matrix has one, else from the
+// SELL copy, whose slice decides the kind of load (Csr::keep).  Exact rows try
+// the certified compensated sum first where the matrix's probe chose it: its
+// dependency chain is a few additions per entry, an FPE insertion's several
+// twosums with a data-dependent exit after each; a wavefront with a row that is
+// not certified takes all its rows the other way (its entries are in the caches
+// by then).  Every path gives the same values.  With the dictionary the loop is
+// bound by its arithmetic (about 290 vector operations a row in D); loading the
+// next row's id, operands and own values ahead of this row's sums was slower (D
+// 32.9 instead of 27.4 us at 128^3), and so was a second pass for the rows that
+// are not certified.
+template <int N, class Gth, class Pre, class Use>
+__device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, const Shm<N>& s, Pre pre, Use use) {
+  // the wavefront's 64 rows (one slice)
+  for (int first = __builtin_amdgcn_readfirstlane(R.lo + (int)(threadIdx.x & ~63u)); first < R.hi;
+       first += blockDim.x) {
+    const int i = first + (int)(threadIdx.x & 63), sl = first >> 6;
+    const bool ok = i < R.hi;
+    double y = 0.0;
+    if (A.np) {
+      const int w = __builtin_amdgcn_readfirstlane((int)A.swid[sl]);
+      const PatSrc src{s.pat, (unsigned)(i < A.n ? i : A.n - 1) * 8u, (int)A.pid[i] * pat_stride(A.pw)};
+      const auto p = pre(ok ? i : R.hi - 1);
+      if constexpr (N == 0) {
+        y = row_plain(src, gx, w);
+      } else {
+        const bool cert = A.cert && row_cert(A, src, gx, w, y);
+        if (__ballot(ok && !cert) != 0ull) y = rows_fpe<N>(src, gx, w, ok, s.wsa);
       }
-      return rows_fpe<N>(src, gx, w, valid, s.wsa);
+      use(i, ok, y, p);
+    } else {
+      const long long off = A.sptr[sl];
+      const int w = (int)((A.sptr[sl + 1] - off) >> 6);
+      const SellSrc<false> kept{A.sval + off, A.scol + off};
+      const SellSrc<true> passing{A.sval + off, A.scol + off};
+      const auto p = pre(ok ? i : R.hi - 1);
+      if constexpr (N == 0) {
+        y = sl < A.keep ? row_plain(kept, gx, w) : row_plain(passing, gx, w);
+      } else {
+        const bool cert = A.cert && (sl < A.keep ? row_cert(A, kept, gx, w, y) : row_cert(A, passing, gx, w, y));
+        if (__ballot(ok && !cert) != 0ull) y = rows_fpe<N>(kept, gx, w, ok, s.wsa);
+      }
+      use(i, ok, y, p);
     }
-  }
-  const long long off = A.sptr[sl];
-  const int w = (int)((A.sptr[sl + 1] - off) >> 6);
-  const SellSrc<false> kept{A.sval + off, A.scol + off};
-  const SellSrc<true> passing{A.sval + off, A.scol + off};
-  if constexpr (N == 0) {
-    return sl < A.keep ? row_plain(kept, gx, w) : row_plain(passing, gx, w);
-  } else {
-    if (A.cert) {
-      const bool cert = sl < A.keep ? row_cert(A, kept, gx, w, y) : row_cert(A, passing, gx, w, y);
-      if (__ballot(valid && !cert) == 0ull) return y;
-    }
-    return rows_fpe<N>(kept, gx, w, valid, s.wsa);
   }
 }
 
-template <int N>
-__device__ __forceinline__ double rows_wave(const Csr& A, const double* __restrict__ x, int row, bool valid,
-                                            const Shm<N>& s) {
-  return rows_wave_g<N>(A, GatherX{x}, row, valid, s);
-}
-
-// (A M^-1 v)_row: gathers the stored preconditioned vector vh, or, for a uniform
+// (A M^-1 v): gathers the stored preconditioned vector vh, or, for a uniform
 // Jacobi vector (Unif), v itself scaled at the gather (same values)
-template <int N, bool Unif>
-__device__ __forceinline__ double rows_wave_hat(const Csr& A, const double* __restrict__ v,
-                                                const double* __restrict__ vh, int row, bool valid,
-                                                const Shm<N>& s) {
-  if constexpr (Unif) return rows_wave_g<N>(A, GatherScaled{A.du, v}, row, valid, s);
-  else return rows_wave_g<N>(A, GatherX{vh}, row, valid, s);
+template <int N, bool Unif, class Pre, class Use>
+__device__ __forceinline__ void for_rows_hat(const Csr& A, const double* __restrict__ v, const double* __restrict__ vh,
+                                             Range R, const Shm<N>& s, Pre pre, Use use) {
+  if constexpr (Unif) for_rows<N>(A, GatherScaled{A.du, v}, R, s, pre, use);
+  else for_rows<N>(A, GatherX{vh}, R, s, pre, use);
 }
 
 // ---------------------------------------------------------------------------
@@ -675,23 +693,23 @@ __device__ __forceinline__ int wave_max_int(int v) {
   return __builtin_amdgcn_readlane(v, 63);
 }
 
-// Block-wide max of K values per thread (all threads get them).  Uses s.imax; ends with a barrier.
-template <int N, int K>
-__device__ __forceinline__ void block_max_k(int (&v)[K], const Shm<N>& s) {
-  const int nw = blockDim.x >> 6, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int j = 0; j < K; ++j) {
-    v[j] = wave_max_int(v[j]);
-    if ((threadIdx.x & 63) == 0) s.imax[w * K + j] = v[j];
+// Sum of v over the wavefront, in lane 63: DPP within rows of 16 lanes, then the
+// row broadcasts of lanes 15 and 31 (lanes a step does not write add 0).
+__device__ __forceinline__ long long wave_sum_i64(long long v) {
+#define RPK_STEP(ctrl, rows)                                                                          \
+  {                                                                                                   \
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xf, false);                    \
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), ctrl, rows, 0xf, false);            \
+    v += (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);                        \
   }
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < K; ++j) {
-    int m = s.imax[j];
-    for (int i = 1; i < nw; ++i) m = (s.imax[i * K + j] > m) ? s.imax[i * K + j] : m;
-    v[j] = m;
-  }
-  __syncthreads();
+  RPK_STEP(0x111, 0xf)  // row_shr:1
+  RPK_STEP(0x112, 0xf)  // row_shr:2
+  RPK_STEP(0x114, 0xf)  // row_shr:4
+  RPK_STEP(0x118, 0xf)  // row_shr:8
+  RPK_STEP(0x142, 0xa)  // row_bcast:15
+  RPK_STEP(0x143, 0xc)  // row_bcast:31
+#undef RPK_STEP
+  return v;
 }
 
 // The exact value of a finite double c as three digit values on the long-
@@ -726,65 +744,77 @@ __device__ __forceinline__ void lds_add(long long* p, long long v) {
                          __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Wavefront part of the window reduction of one dot: every lane adds the
-// digits3 values of its FPE components into a private LDS row of WIN digits
-// (digit 0 = grid digit d0; d0 + WIN - 1 is at or above every component's top
-// digit; digits below d0 go to the long accumulator `sa`), then the rows are
-// summed column-wise (4 lanes per column, combined with shuffles).  Returns the
-// wavefront's sum of window digit `lane` in lanes 0..WIN-1.
+// This lane's FPE into its window row (digit 0 = grid digit d0; d0 + WIN - 1 is
+// at or above every component's top digit; digits below d0 go to the long
+// accumulator `sa`): the digits3 values of each component, by LDS atomics, as
+// lane l of every wavefront shares row l.
 template <int N>
-__device__ __forceinline__ long long wave_window(const Fpe<N>& f, int d0, const Shm<N>& s, long long* sa, int* flag) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int rows = scat_rows(blockDim.x);
-  long long* R = s.scat + (size_t)w * rows * ROW_STRIDE;
-  const int col = lane % WIN, part = lane / WIN;  // lanes < 4*WIN: column, every 4th row from `part`
-  long long colsum = 0;
-  for (int q = 0; q < 64 / rows; ++q) {
-    if (lane / rows == q) {
-      long long* row = R + (lane % rows) * ROW_STRIDE;
+__device__ __forceinline__ void lane_deposit(const Fpe<N>& f, int d0, long long* row, long long* sa, int* flag) {
+  bool below = false;
 #pragma unroll
-      for (int i = 0; i < WIN; ++i) row[i] = 0;
-      bool below = false;
+  for (int k = 0; k < N; ++k) {
+    long long D[3];
+    int idx = digits3(f.c[k], D) - d0;
+    if (f.c[k] == 0.0) idx = 0;  // three zeros, added anywhere in the row
+    if (idx >= 0) {
 #pragma unroll
-      for (int k = 0; k < N; ++k) {
-        long long D[3];
-        int idx = digits3(f.c[k], D) - d0;
-        if (f.c[k] == 0.0) idx = 0;  // three zeros, added anywhere in the row
-        if (idx >= 0) {
+      for (int j = 0; j < 3; ++j) lds_add(row + idx + j, D[j]);
+    } else {
+      below = true;
+    }
+  }
+  if (below) {  // rare: components whose low digits lie below the window
 #pragma unroll
-          for (int j = 0; j < 3; ++j) lds_add(row + idx + j, D[j]);
-        } else {
-          below = true;
-        }
-      }
-      if (below) {  // rare: components whose low digits lie below the window
+    for (int k = 0; k < N; ++k) {
+      long long D[3];
+      const int dg = digits3(f.c[k], D);
+      if (f.c[k] == 0.0 || dg >= d0) continue;
 #pragma unroll
-        for (int k = 0; k < N; ++k) {
-          long long D[3];
-          const int dg = digits3(f.c[k], D);
-          if (f.c[k] == 0.0 || dg >= d0) continue;
-#pragma unroll
-          for (int j = 0; j < 3; ++j) {
-            if (dg + j >= d0) {
-              lds_add(row + (dg + j - d0), D[j]);
-            } else if (D[j] != 0) {
-              lds_add(sa + dg + j, D[j]);
-              atomicOr(flag, F_SA);
-            }
-          }
+      for (int j = 0; j < 3; ++j) {
+        if (dg + j >= d0) {
+          lds_add(row + (dg + j - d0), D[j]);
+        } else if (D[j] != 0) {
+          lds_add(sa + dg + j, D[j]);
+          atomicOr(flag, F_SA);
         }
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    if (lane < 4 * WIN)
-      for (int r = part; r < rows; r += 4) colsum += R[r * ROW_STRIDE + col];
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    __builtin_amdgcn_wave_barrier();
   }
-  colsum += __shfl(colsum, (lane + WIN) & 63, 64) + __shfl(colsum, (lane + 2 * WIN) & 63, 64) +
-            __shfl(colsum, (lane + 3 * WIN) & 63, 64);
-  return colsum;
+}
+
+// The K dots of the workgroup as windows: dot j's sum is that of the digits
+// s.wsum[j WIN + k] at grid digits s.imax[j] - (WIN - 1) + k (nothing where
+// s.imax[j] < 0) and of the long accumulator s.sa + j SA_D where s.flag[j] says
+// F_SA.  Every thread calls it, after shm_init; ends with a barrier.  All
+// wavefronts share one set of 64 rows per dot, cleared ahead of the kernel's main
+// loop, and each sums whole columns, one row a lane; with 64 rows to clear, fill
+// and sum for every wavefront (37 LDS operations a lane and dot instead of 12)
+// this took about 4 us of kernel B at 128^3 (29.4 us; 25.1 without it).
+template <int N, int K>
+__device__ __forceinline__ void block_window(Dot<N> (&d)[K], const Shm<N>& s) {
+  const int nw = blockDim.x >> 6, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    double mx = 0.0;
+#pragma unroll
+    for (int k = 0; k < N; ++k) mx = fmax(mx, fabs(d[j].f.c[k]));
+    const int top = wave_max_int((mx != 0.0) ? digits3_top(mx) : -1);
+    if (lane == 0 && top >= 0) atomicMax(&s.imax[j], top);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    const int top = s.imax[j];
+    if (top >= 0)  // else the workgroup's sum of this dot is zero
+      lane_deposit(d[j].f, top - (WIN - 1), s.scat + (j * 64 + lane) * ROW_STRIDE, s.sa + (size_t)j * SA_D, &s.flag[j]);
+  }
+  __syncthreads();
+  for (int c = w; c < K * WIN; c += nw) {
+    const int j = c / WIN, k = c - j * WIN;
+    const long long v = wave_sum_i64(s.scat[(j * 64 + lane) * ROW_STRIDE + k]);
+    if (lane == 63) s.wsum[c] = v;
+  }
+  __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
@@ -869,37 +899,13 @@ __device__ __forceinline__ unsigned long long block_publish(Dot<N> (&d)[K], cons
       }
     }
   } else if constexpr (N > 0) {
-    // the K windows together: one block-wide max for all dots, wavefront-local
-    // scatters, one barrier, then the cross-wave sums feed the atomics directly
-    const int nw = blockDim.x >> 6, w = tid >> 6, lane = tid & 63;
-    int top[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      double mx = 0.0;
-#pragma unroll
-      for (int k = 0; k < N; ++k) mx = fmax(mx, fabs(d[j].f.c[k]));
-      top[j] = (mx != 0.0) ? digits3_top(mx) : -1;
-    }
-    block_max_k<N, K>(top, s);
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      if (top[j] < 0) continue;  // the workgroup's sum of this dot is zero
-      const long long cs = wave_window(d[j].f, top[j] - (WIN - 1), s, s.sa + (size_t)j * SA_D, &s.flag[j]);
-      if (lane < WIN) s.wsum[(w * K + j) * WIN + lane] = cs;
-    }
-    __syncthreads();
+    block_window<N, K>(d, s);
+    long long* gsa = red.gsa + (size_t)(b & (red.copies - 1)) * (MAX_DOTS * SA_D);
     if (tid < K * WIN) {
       const int j = tid / WIN, k = tid % WIN;
-      int tj = top[0];
-#pragma unroll
-      for (int jj = 1; jj < K; ++jj)
-        if (jj == j) tj = top[jj];
-      if (tj >= 0) {
-        long long v = 0;
-        for (int i = 0; i < nw; ++i) v += s.wsum[(i * K + j) * WIN + k];
-        const int g = tj - (WIN - 1) + k;
-        if (v != 0 && g >= 0 && g < SA_D) sink += dev_add(red.gsa + (size_t)(slot0 + j) * SA_D + g, v);
-      }
+      const int g = s.imax[j] - (WIN - 1) + k;
+      const long long v = s.wsum[tid];
+      if (s.imax[j] >= 0 && v != 0 && g >= 0 && g < SA_D) sink += dev_add(gsa + (size_t)(slot0 + j) * SA_D + g, v);
     }
     // rare: this workgroup's own long accumulators, and the non-finite flags
     if (tid < 64) {
@@ -912,7 +918,7 @@ __device__ __forceinline__ unsigned long long block_publish(Dot<N> (&d)[K], cons
           long long* sa = s.sa + (size_t)j * SA_D;
           int lo, hi;
           sa_normalize_wave(sa, lo, hi);
-          long long* g = red.gsa + (size_t)(slot0 + j) * SA_D;
+          long long* g = gsa + (size_t)(slot0 + j) * SA_D;
           for (int k = lo + tid; k <= hi; k += 64)
             if (sa[k]) sink += dev_add(g + k, sa[k]);
         }
@@ -956,38 +962,41 @@ __device__ __forceinline__ bool block_publish_last(Dot<N> (&d)[K], const Shm<N>&
 // s.misc[1..K]) into s.res[0..K-1]; one wavefront per dot.  All threads call it.
 template <int N, int K>
 __device__ __forceinline__ void block_round_sa(const Shm<N>& s) {
-  const int tid = threadIdx.x, bd = blockDim.x;
-  const int nw = bd >> 6, w = tid >> 6, lane = tid & 63;
+  const int nw = blockDim.x >> 6, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   for (int j = w; j < K; j += nw) {  // one wave per dot
     long long* tot = s.sa + (size_t)j * SA_D;
     int lo, hi;
     wave_digit_range(tot, SA_D, lo, hi);
     double r = 0.0;
     if (hi >= 0) {
-      constexpr int RW = 16;  // register window (digits) of the common case
-      const int start = (lo < SA_D - RW) ? lo : SA_D - RW;
-      if (hi + 2 <= start + RW - 1) {
-        if (lane == 0) r = window_round_reg<RW>(tot + start, start);
-      } else {
-        r = sa_round_wave(tot);
-      }
+      if (hi - lo <= 61) r = round_lanes(lane <= hi - lo ? tot[lo + lane] : 0ll, lo);
+      else r = sa_round_wave(tot);  // digits further apart than a wavefront holds
     }
-    if (lane == 0) s.res[j] = r;
+    if (lane == 0) s.res[j] = (s.misc[1 + j] & F_NONFINITE) ? __longlong_as_double(0x7ff8000000000000ll) : r;
   }
-  __syncthreads();
-  if (tid < K && (s.misc[1 + tid] & F_NONFINITE)) s.res[tid] = __longlong_as_double(0x7ff8000000000000ll);
   __syncthreads();
 }
 
+// Item i of the K accumulators from slot0 on, all copies (0 <= i < K SA_D
+// copies): its address, and the digit of s.sa it belongs to.
+template <int K>
+__device__ __forceinline__ unsigned long long* slot_item(const Red& red, int slot0, int i, int& digit) {
+  const int c = i / (K * SA_D);
+  digit = i - c * (K * SA_D);
+  return (unsigned long long*)&red.gsa[(size_t)(c * MAX_DOTS + slot0) * SA_D + digit];
+}
+
+// How block_finalize reads the exact accumulators and flags.
+enum : int {
+  FIN_EXCHANGE = 0,  // the last workgroup to arrive: exchanges that leave them zeroed for the next use
+  FIN_CLEAR = 1,     // a kernel after the one that published: loads, then stores of zero
+  FIN_READ = 2       // the same, left for a later kernel to clear (block_clear_slots)
+};
+
 // Round the K dots of slots slot0.. into s.res[0..K-1] (their flags into
-// s.misc[1..K]).  Clear (the last workgroup to arrive): read the exact
-// accumulators and flags with exchanges that leave them zeroed for the next use.
-// !Clear (every workgroup of the kernel after the one that published, exact and
-// plain dots only): read them with device-scope loads and leave them; a later
-// kernel clears them (block_clear_slots).
-template <int N, int K, bool Clear = true>
+// s.misc[1..K]).
+template <int N, int K, int Mode>
 __device__ __forceinline__ void block_finalize(const Shm<N>& s, const Red& red, int slot0) {
-  static_assert(Clear || N != LW8, "lightweight records are always finished by the last workgroup");
   const int tid = threadIdx.x, bd = blockDim.x;
   if constexpr (N == LW8) {
     const int nw = bd >> 6, w = tid >> 6, lane = tid & 63;
@@ -1024,15 +1033,41 @@ __device__ __forceinline__ void block_finalize(const Shm<N>& s, const Red& red, 
     }
     __syncthreads();
   } else if constexpr (N > 0) {
-    for (int i = tid; i < K * SA_D; i += bd) {
-      unsigned long long* g = (unsigned long long*)&red.gsa[(size_t)slot0 * SA_D + i];
-      s.sa[i] = Clear ? (long long)__hip_atomic_exchange(g, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                      : (long long)__hip_atomic_load(g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int i = tid; i < K * SA_D; i += bd) s.sa[i] = 0;
+    if (tid < K) {
+      int* f = &red.gflags[slot0 + tid];
+      if constexpr (Mode == FIN_EXCHANGE) {
+        s.misc[1 + tid] = __hip_atomic_exchange(f, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } else {
+        s.misc[1 + tid] = __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (Mode == FIN_CLEAR) __hip_atomic_store(f, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
     }
-    if (tid < K)
-      s.misc[1 + tid] = Clear ? __hip_atomic_exchange(&red.gflags[slot0 + tid], 0, __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_AGENT)
-                              : __hip_atomic_load(&red.gflags[slot0 + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    constexpr int U = 4;  // items of a thread in flight
+    for (int i0 = tid; i0 < K * SA_D * red.copies; i0 += U * bd) {
+      unsigned long long v[U];
+      int digit[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = i0 + u * bd;
+        v[u] = 0ull;
+        if (i < K * SA_D * red.copies) {
+          unsigned long long* g = slot_item<K>(red, slot0, i, digit[u]);
+          if constexpr (Mode == FIN_EXCHANGE)
+            v[u] = __hip_atomic_exchange(g, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          else v[u] = __hip_atomic_load(g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (v[u] != 0ull) {
+          lds_add(&s.sa[digit[u]], (long long)v[u]);
+          if constexpr (Mode == FIN_CLEAR)
+            __hip_atomic_store(slot_item<K>(red, slot0, i0 + u * bd, digit[u]), 0ull, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
     __syncthreads();
     block_round_sa<N, K>(s);
   } else {
@@ -1056,7 +1091,7 @@ __device__ __forceinline__ void block_finalize(const Shm<N>& s, const Red& red, 
 
 template <int N, int K>
 __device__ __forceinline__ void block_finalize_last(const Shm<N>& s, const Red& red, int slot0) {
-  block_finalize<N, K, true>(s, red, slot0);
+  block_finalize<N, K, FIN_EXCHANGE>(s, red, slot0);
 }
 
 // The only workgroup of a reduction (G = 1): round its K dots into
@@ -1070,35 +1105,12 @@ __device__ __forceinline__ void block_reduce_local(Dot<N> (&d)[K], const Shm<N>&
   static_assert(N != LW8, "lightweight records are merged through the partials");
   const int tid = threadIdx.x;
   if constexpr (N > 0) {
-    const int nw = blockDim.x >> 6, w = tid >> 6, lane = tid & 63;
-    int top[K];
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      double mx = 0.0;
-#pragma unroll
-      for (int k = 0; k < N; ++k) mx = fmax(mx, fabs(d[j].f.c[k]));
-      top[j] = (mx != 0.0) ? digits3_top(mx) : -1;
-    }
-    block_max_k<N, K>(top, s);
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      if (top[j] < 0) continue;
-      const long long cs = wave_window(d[j].f, top[j] - (WIN - 1), s, s.sa + (size_t)j * SA_D, &s.flag[j]);
-      if (lane < WIN) s.wsum[(w * K + j) * WIN + lane] = cs;
-    }
-    __syncthreads();
+    block_window<N, K>(d, s);
     if (tid < K * WIN) {  // one (dot, digit) per thread: no two write one digit
       const int j = tid / WIN, k = tid % WIN;
-      int tj = top[0];
-#pragma unroll
-      for (int jj = 1; jj < K; ++jj)
-        if (jj == j) tj = top[jj];
-      if (tj >= 0) {
-        long long v = 0;
-        for (int i = 0; i < nw; ++i) v += s.wsum[(i * K + j) * WIN + k];
-        const int g = tj - (WIN - 1) + k;
-        if (v != 0 && g >= 0 && g < SA_D) s.sa[(size_t)j * SA_D + g] += v;
-      }
+      const int g = s.imax[j] - (WIN - 1) + k;
+      const long long v = s.wsum[tid];
+      if (s.imax[j] >= 0 && v != 0 && g >= 0 && g < SA_D) s.sa[(size_t)j * SA_D + g] += v;
     }
     if (tid < K) s.misc[1 + tid] = s.flag[tid] & F_NONFINITE;
     __syncthreads();
@@ -1119,9 +1131,10 @@ __device__ __forceinline__ void block_reduce_local(Dot<N> (&d)[K], const Shm<N>&
 template <int N, int K>
 __device__ __forceinline__ void block_clear_slots(const Red& red, int slot0) {
   if constexpr (N > 0 && N != LW8) {
-    for (int i = threadIdx.x; i < K * SA_D; i += blockDim.x)
-      __hip_atomic_store((unsigned long long*)&red.gsa[(size_t)slot0 * SA_D + i], 0ull, __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
+    for (int i = threadIdx.x; i < K * SA_D * red.copies; i += blockDim.x) {
+      int digit;
+      __hip_atomic_store(slot_item<K>(red, slot0, i, digit), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (threadIdx.x < K)
       __hip_atomic_store(&red.gflags[slot0 + threadIdx.x], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -1130,31 +1143,39 @@ __device__ __forceinline__ void block_clear_slots(const Red& red, int slot0) {
 // A reduction published by the kernel before (exact dots), read by every
 // workgroup of the next one: issue() starts the device-scope loads of the
 // digits and flags into registers, so that the caller can start its own loads
-// behind them; store() puts them in s.sa / s.misc[1..K] ahead of a barrier and
-// block_round_sa.
-constexpr int DCAP = (2 * SA_D + 63) / 64;  // digits per thread: K <= 2, at least 64 threads
+// behind them; store() adds the copies up in s.sa and puts the flags in
+// s.misc[1..K], ahead of a barrier and block_round_sa.
+constexpr int DCAP = 5;  // items a thread loads ahead: all of two dots with 64 threads a copy
 template <int N, int K>
 struct Published {
   long long dg[DCAP];
   int fl;
-  __device__ __forceinline__ void issue(const Red& red, int slot0) {
-    static_assert(K * SA_D <= DCAP * 64, "Published holds at most two dots");
+  __device__ __forceinline__ void issue(const Shm<N>& s, const Red& red, int slot0) {
+    const int items = K * SA_D * red.copies;
 #pragma unroll
     for (int r = 0; r < DCAP; ++r) {
       const int i = threadIdx.x + r * blockDim.x;
-      dg[r] = (i < K * SA_D) ? (long long)__hip_atomic_load((unsigned long long*)&red.gsa[(size_t)slot0 * SA_D + i],
-                                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                             : 0ll;
+      int digit;
+      dg[r] = (i < items) ? (long long)__hip_atomic_load(slot_item<K>(red, slot0, i, digit), __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT)
+                          : 0ll;
     }
     fl = (threadIdx.x < K) ? __hip_atomic_load(&red.gflags[slot0 + threadIdx.x], __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT)
                            : 0;
+    for (int i = threadIdx.x; i < K * SA_D; i += blockDim.x) s.sa[i] = 0;
   }
-  __device__ __forceinline__ void store(const Shm<N>& s) const {
+  __device__ __forceinline__ void store(const Shm<N>& s, const Red& red, int slot0) const {
+    const int items = K * SA_D * red.copies;
+    __syncthreads();  // s.sa is cleared
 #pragma unroll
-    for (int r = 0; r < DCAP; ++r) {
-      const int i = threadIdx.x + r * blockDim.x;
-      if (i < K * SA_D) s.sa[i] = dg[r];
+    for (int r = 0; r < DCAP; ++r)
+      if (dg[r] != 0) lds_add(&s.sa[(threadIdx.x + r * blockDim.x) % (K * SA_D)], dg[r]);
+    for (int i = threadIdx.x + DCAP * blockDim.x; i < items; i += blockDim.x) {  // workgroups below 512 threads
+      int digit;
+      const long long v = (long long)__hip_atomic_load(slot_item<K>(red, slot0, i, digit), __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT);
+      if (v != 0) lds_add(&s.sa[digit], v);
     }
     if (threadIdx.x < K) s.misc[1 + threadIdx.x] = fl;
   }
@@ -1194,12 +1215,9 @@ __global__ void __launch_bounds__(1024) k_spmv(Csr A, const double* __restrict__
   __syncthreads();
   const int L = xcd_block(blockIdx.x, gridDim.x);
   const Range R = block_rows(A.n, L, gridDim.x);
-  for (int base = R.lo; base < R.hi; base += blockDim.x) {
-    const int row = base + threadIdx.x;
-    const bool valid = row < R.hi;
-    const double v = rows_wave<N>(A, x, row, valid, s);
-    if (valid) y[row] = v;
-  }
+  for_rows<N>(A, GatherX{x}, R, s, [](int) { return 0; }, [&](int i, bool ok, double v, int) {
+    if (ok) y[i] = v;
+  });
 }
 
 }  // namespace rpk

@@ -29,8 +29,9 @@ using namespace rpkhost;
 // device address: it is a host-side stand-in.  The address of each device's
 // copy comes from hipGetSymbolAddress, taken once per device (noalloc_scratch).
 // Holds the exdot workspace layout (header + per-workgroup partial records) of
-// grids up to 1,624 workgroups.
-constexpr size_t kScratchBytes = size_t(1) << 20;
+// grids up to kScratchGrid workgroups.
+constexpr size_t kScratchBytes = (size_t(1) << 20) + (size_t(1) << 16);
+constexpr int kScratchGrid = 1624;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
@@ -82,7 +83,9 @@ Layout layout(int grid, int64_t n, int nvec) {
   l.gflags = off + 8 * sizeof(unsigned);
   off += up(8 * sizeof(unsigned) + MAX_DOTS * sizeof(int));
   l.gsa = off;
-  off += up((size_t)MAX_DOTS * SA_D * sizeof(long long));
+  // room for every launch shape's copies: a workspace serves calls of different
+  // shapes, and the partials of one must not lie on the accumulators of another
+  off += up((size_t)kMaxCopies * MAX_DOTS * SA_D * sizeof(long long));
   l.partials = off;
   off += up((size_t)MAX_DOTS * grid * LW_REC * sizeof(double));  // plain sums / lightweight records per workgroup
   l.vecs = off;
@@ -98,6 +101,7 @@ Red make_red(char* ws, const Layout& l, int grid) {
   r.gflags = (int*)(ws + l.gflags);
   r.tickets = (unsigned*)(ws + l.tickets);
   r.G = grid;
+  r.copies = red_copies(grid);
   return r;
 }
 
@@ -511,13 +515,13 @@ rpk_status rpk_exdot_noalloc(int64_t n, const double* x, const double* y, double
   Cfg c;
   RET_IF(resolve(launch_cfg, n, &c));
   const Layout l = layout(c.grid, 0, 0);
-  if (l.total > kScratchBytes) return RPK_ERR_ARG;  // grid beyond what the scratch array holds
+  if (c.grid > kScratchGrid || l.total > kScratchBytes) return RPK_ERR_ARG;  // beyond what the scratch array holds
   char* ws = nullptr;
   RET_IF(noalloc_scratch(&ws));
   hipStream_t s = (hipStream_t)stream;
   // tickets, flags and long accumulators start at zero (the kernel leaves them
   // zeroed; cleared all the same, by a kernel rather than a memset node)
-  hipLaunchKernelGGL(k_zero_words, dim3(4), dim3(256), 0, s, (unsigned*)ws,
+  hipLaunchKernelGGL(k_zero_words, dim3(32), dim3(256), 0, s, (unsigned*)ws,
                      (long long)(l.partials / sizeof(unsigned)));
   if (hipGetLastError() != hipSuccess) return RPK_ERR_HIP;
   Red red = make_red(ws, l, c.grid);

@@ -382,15 +382,15 @@ struct Deferred {
   Published<N, K> pub;
   State S;
   int pend;
-  __device__ __forceinline__ void issue(const Red& red, int slot0, const State* st) {
-    if constexpr (N > 0) pub.issue(red, slot0);
+  __device__ __forceinline__ void issue(const Shm<N>& s, const Red& red, int slot0, const State* st) {
+    if constexpr (N > 0) pub.issue(s, red, slot0);
     if (threadIdx.x == 0) {
       state_load(S, st);
       pend = st->pend;
     }
   }
-  __device__ __forceinline__ int flags(const Shm<N>& s) {
-    if constexpr (N > 0) pub.store(s);
+  __device__ __forceinline__ int flags(const Shm<N>& s, const Red& red, int slot0) {
+    if constexpr (N > 0) pub.store(s, red, slot0);
     if (threadIdx.x == 0) s.misc[9] = S.done | (pend << 1);
     __syncthreads();
     return s.misc[9];
@@ -398,7 +398,7 @@ struct Deferred {
   template <int F>
   __device__ __forceinline__ bool step(const Shm<N>& s, const Vecs& V, const Red& red, int slot0, double& out) {
     if constexpr (N > 0) block_round_sa<N, K>(s);
-    else block_finalize<N, K, false>(s, red, slot0);
+    else block_finalize<N, K, FIN_READ>(s, red, slot0);
     if (threadIdx.x == 0) {
       State* st = V.st;
       const bool w0 = blockIdx.x == 0;
@@ -461,18 +461,15 @@ __device__ __forceinline__ void std_init_body(const Csr& A, const Vecs& V, const
                                               const Shm<N>& s) {
   Dot<N> d[1];
   d[0].zero();
-  for (int base = R.lo; base < R.hi; base += blockDim.x) {
-    const int i = base + threadIdx.x;
-    const bool ok = i < R.hi;
-    const double t = rows_wave<N>(A, V.x, i, ok, s);
+  for_rows<N>(A, GatherX{V.x}, R, s, [&](int i) { return V.b[i]; }, [&](int i, bool ok, double t, double b) {
     if (ok) {
-      const double ri = V.b[i] - t;
+      const double ri = b - t;
       V.r[i] = ri;
       V.r0[i] = ri;
       V.p[i] = ri;
       d[0].add(ri, ri, s.sa, &s.flag[0]);
     }
-  }
+  });
   publish_step<N, 1, FIN_ENTRY>(d, s, V, red, rec);
 }
 
@@ -562,16 +559,13 @@ __device__ __forceinline__ void std_B_body(const Csr& A, const Vecs& V, const Re
                                            const Shm<N>& s) {
   Dot<N> d[1];
   d[0].zero();
-  for (int base = R.lo; base < R.hi; base += blockDim.x) {
-    const int i = base + threadIdx.x;
-    const bool ok = i < R.hi;
-    const double r0 = ok ? V.r0[i] : 0.0;
-    const double si = rows_wave_hat<N, Unif>(A, V.p, V.ph, i, ok, s);
-    if (ok) {
-      V.s[i] = si;
-      d[0].add(r0, si, s.sa, &s.flag[0]);
-    }
-  }
+  for_rows_hat<N, Unif>(A, V.p, V.ph, R, s, [&](int i) { return V.r0[i]; },
+                        [&](int i, bool ok, double si, double r0) {
+                          if (ok) {
+                            V.s[i] = si;
+                            d[0].add(r0, si, s.sa, &s.flag[0]);
+                          }
+                        });
   if constexpr (Defer) (void)block_publish<N, 1>(d, s, red, SLOT_SIGMA, rec);
   else publish_step<N, 1, FIN_ALPHA>(d, s, V, red, rec);
 }
@@ -625,17 +619,14 @@ __device__ __forceinline__ void std_D_body(const Csr& A, const Vecs& V, const Re
   Dot<N> d[2];
   d[0].zero();
   d[1].zero();
-  for (int base = R.lo; base < R.hi; base += blockDim.x) {
-    const int i = base + threadIdx.x;
-    const bool ok = i < R.hi;
-    const double q = ok ? V.q[i] : 0.0;
-    const double yi = rows_wave_hat<N, Unif>(A, V.q, V.qh, i, ok, s);
-    if (ok) {
-      V.y[i] = yi;
-      d[0].add(q, yi, s.sa, &s.flag[0]);
-      d[1].add(yi, yi, s.sa + SA_D, &s.flag[1]);
-    }
-  }
+  for_rows_hat<N, Unif>(A, V.q, V.qh, R, s, [&](int i) { return V.q[i]; },
+                        [&](int i, bool ok, double yi, double q) {
+                          if (ok) {
+                            V.y[i] = yi;
+                            d[0].add(q, yi, s.sa, &s.flag[0]);
+                            d[1].add(yi, yi, s.sa + SA_D, &s.flag[1]);
+                          }
+                        });
   if constexpr (Defer) (void)block_publish<N, 2>(d, s, red, SLOT_THETA, rec);
   else publish_step<N, 2, FIN_OMEGA>(d, s, V, red, rec);
 }
@@ -714,15 +705,12 @@ __device__ __forceinline__ void resid_body(const Csr& A, const Vecs& V, const Re
                                            const Shm<N>& s) {
   Dot<N> d[1];
   d[0].zero();
-  for (int base = R.lo; base < R.hi; base += blockDim.x) {
-    const int i = base + threadIdx.x;
-    const bool ok = i < R.hi;
-    const double t = rows_wave<N>(A, V.x, i, ok, s);
+  for_rows<N>(A, GatherX{V.x}, R, s, [&](int i) { return V.b[i]; }, [&](int, bool ok, double t, double b) {
     if (ok) {
-      const double e = V.b[i] - t;
+      const double e = b - t;
       d[0].add(e, e, s.sa, &s.flag[0]);
     }
-  }
+  });
   publish_step<N, 1, FIN_RESID>(d, s, V, red, rec);
 }
 
@@ -732,18 +720,15 @@ __device__ __forceinline__ void pipe_init1_body(const Csr& A, const Vecs& V, con
                                                 const Shm<N>& s) {
   Dot<N> d[1];
   d[0].zero();
-  for (int base = R.lo; base < R.hi; base += blockDim.x) {
-    const int i = base + threadIdx.x;
-    const bool ok = i < R.hi;
-    const double t = rows_wave<N>(A, V.x, i, ok, s);
+  for_rows<N>(A, GatherX{V.x}, R, s, [&](int i) { return V.b[i]; }, [&](int i, bool ok, double t, double b) {
     if (ok) {
-      const double ri = V.b[i] - t;
+      const double ri = b - t;
       V.r[i] = ri;
       V.r0[i] = ri;
       V.rh[i] = A.dinv[i] * ri;
       d[0].add(ri, ri, s.sa, &s.flag[0]);
     }
-  }
+  });
   publish_step<N, 1, FIN_PENTRY1>(d, s, V, red, rec);
 }
 
@@ -754,40 +739,23 @@ __device__ __forceinline__ void pipe_init2_body(const Csr& A, const Vecs& V, con
                                                 const Shm<N>& s) {
   Dot<N> d[1];
   d[0].zero();
-  for (int base = R.lo; base < R.hi; base += blockDim.x) {
-    const int i = base + threadIdx.x;
-    const bool ok = i < R.hi;
-    const double wi = rows_wave<N>(A, V.rh, i, ok, s);
+  for_rows<N>(A, GatherX{V.rh}, R, s, [&](int i) { return V.r0[i]; }, [&](int i, bool ok, double wi, double r0) {
     if (ok) {
       V.w[i] = wi;
       if constexpr (!Unif) V.wh[i] = A.dinv[i] * wi;
-      d[0].add(V.r0[i], wi, s.sa, &s.flag[0]);
+      d[0].add(r0, wi, s.sa, &s.flag[0]);
     }
-  }
+  });
   publish_step<N, 1, FIN_PENTRY2>(d, s, V, red, rec);
-}
-
-// out = A in on rows R (the SpMVs of the pipelined loop)
-template <int N>
-__device__ __forceinline__ void spmv_body(const Csr& A, const double* in, double* out, Range R, const Shm<N>& s) {
-  for (int base = R.lo; base < R.hi; base += blockDim.x) {
-    const int i = base + threadIdx.x;
-    const bool ok = i < R.hi;
-    const double v = rows_wave<N>(A, in, i, ok, s);
-    if (ok) out[i] = v;
-  }
 }
 
 // out = A M^-1 v on rows R: gathers the stored M^-1 v (vh), or v scaled by du
 template <int N, bool Unif>
 __device__ __forceinline__ void spmv_hat_body(const Csr& A, const double* v, const double* vh, double* out, Range R,
                                               const Shm<N>& s) {
-  for (int base = R.lo; base < R.hi; base += blockDim.x) {
-    const int i = base + threadIdx.x;
-    const bool ok = i < R.hi;
-    const double y = rows_wave_hat<N, Unif>(A, v, vh, i, ok, s);
+  for_rows_hat<N, Unif>(A, v, vh, R, s, [](int) { return 0; }, [&](int i, bool ok, double y, int) {
     if (ok) out[i] = y;
-  }
+  });
 }
 
 // P1: S1..S7, S9, the partials of S8 (slots 0, 1) and of <r0,s>, <r0,z> (slots 2, 3).
@@ -879,12 +847,9 @@ __device__ __forceinline__ void pcg_init_body(const Csr& A, const Vecs& V, const
   Dot<N> d[2];
   d[0].zero();
   d[1].zero();
-  for (int base = R.lo; base < R.hi; base += blockDim.x) {
-    const int i = base + threadIdx.x;
-    const bool ok = i < R.hi;
-    const double t = rows_wave<N>(A, V.x, i, ok, s);
+  for_rows<N>(A, GatherX{V.x}, R, s, [&](int i) { return V.b[i]; }, [&](int i, bool ok, double t, double b) {
     if (ok) {
-      const double ri = V.b[i] - t;
+      const double ri = b - t;
       const double yi = (Unif ? A.du : A.dinv[i]) * ri;
       V.r[i] = ri;
       if constexpr (!Unif) V.y[i] = yi;
@@ -892,7 +857,7 @@ __device__ __forceinline__ void pcg_init_body(const Csr& A, const Vecs& V, const
       d[0].add(yi, ri, s.sa, &s.flag[0]);
       d[1].add(ri, ri, s.sa + SA_D, &s.flag[1]);
     }
-  }
+  });
   publish_step<N, 2, FIN_PCG_ENTRY>(d, s, V, red, rec);
 }
 
@@ -902,16 +867,12 @@ __device__ __forceinline__ void pcg_S1_body(const Csr& A, const Vecs& V, const R
                                             const Shm<N>& s) {
   Dot<N> d[1];
   d[0].zero();
-  for (int base = R.lo; base < R.hi; base += blockDim.x) {
-    const int i = base + threadIdx.x;
-    const bool ok = i < R.hi;
-    const double pi = ok ? V.p[i] : 0.0;
-    const double di = rows_wave<N>(A, V.p, i, ok, s);
+  for_rows<N>(A, GatherX{V.p}, R, s, [&](int i) { return V.p[i]; }, [&](int i, bool ok, double di, double pi) {
     if (ok) {
       V.s[i] = di;
       d[0].add(pi, di, s.sa, &s.flag[0]);
     }
-  }
+  });
   if constexpr (Defer) (void)block_publish<N, 1>(d, s, red, SLOT_PD, rec);
   else publish_step<N, 1, FIN_PCG_RHO>(d, s, V, red, rec);
 }
@@ -1004,7 +965,7 @@ __global__ void __launch_bounds__(1024) k_std_A(Csr A, Vecs V, Red red) {
     Shm<N> s = shm_carve<N>(smem, 2, false);
     const Range R = my_rows(A.n);
     Deferred<N, 2> q;
-    q.issue(red, SLOT_RHO, V.st);
+    q.issue(s, red, SLOT_RHO, V.st);
     RowsA<Far, Unif> pf[pf_a<Unif>()];
 #pragma unroll
     for (int k = 0; k < pf_a<Unif>(); ++k) {
@@ -1012,7 +973,7 @@ __global__ void __launch_bounds__(1024) k_std_A(Csr A, Vecs V, Red red) {
       if (i < R.hi) pf[k].load(A, V, i, R.hi);
     }
     if (blockIdx.x == 0) block_clear_slots<N, 2>(red, SLOT_THETA);
-    const int fl = q.flags(s);
+    const int fl = q.flags(s, red, SLOT_RHO);
     if (fl & 1) return;
     double beta = V.st->beta;
     bool upd = V.st->iter > 0;
@@ -1067,14 +1028,14 @@ __global__ void __launch_bounds__(1024) k_std_C(Csr A, Vecs V, Red red) {
     Shm<N> s = shm_carve<N>(smem, 1, false);
     const Range R = my_rows(A.n);
     Deferred<N, 1> q;
-    q.issue(red, SLOT_SIGMA, V.st);
+    q.issue(s, red, SLOT_SIGMA, V.st);
     RowsC<Far, Unif> pf[PF_C];
 #pragma unroll
     for (int k = 0; k < PF_C; ++k) {
       const int i = R.lo + threadIdx.x + 2 * k * blockDim.x;
       if (i < R.hi) pf[k].load(A, V, i, R.hi);
     }
-    if (q.flags(s) & 1) return;
+    if (q.flags(s, red, SLOT_SIGMA) & 1) return;
     double alpha;
     if (q.template step<FIN_ALPHA>(s, V, red, SLOT_SIGMA, alpha)) return;  // S3
 #pragma unroll
@@ -1112,14 +1073,14 @@ __global__ void __launch_bounds__(1024) k_std_E(Csr A, Vecs V, Red red) {
   if constexpr (defer_std<N>()) {
     const Range R = my_rows(A.n);
     Deferred<N, 2> q;
-    q.issue(red, SLOT_THETA, V.st);
+    q.issue(s, red, SLOT_THETA, V.st);
     RowsE<N, Far, Unif> pf[PF_E];
 #pragma unroll
     for (int k = 0; k < PF_E; ++k) {
       const int i = R.lo + threadIdx.x + 2 * k * blockDim.x;
       if (i < R.hi) pf[k].load(V, i, R.hi);
     }
-    if (q.flags(s) & 1) return;
+    if (q.flags(s, red, SLOT_THETA) & 1) return;
     double omega;
     if (q.template step<FIN_OMEGA>(s, V, red, SLOT_THETA, omega)) return;  // S7
     shm_init(s, 2);
@@ -1225,7 +1186,7 @@ __global__ void __launch_bounds__(1024) k_pipe_spmv_fin(Csr A, Vecs V, Red red) 
   if (blockIdx.x == 0) {
     if (V.st->done) return;
     Shm<N> s = shm_carve<N>(smem, K, true);
-    block_finalize_last<N, K>(s, red, 0);
+    block_finalize<N, K, FIN_CLEAR>(s, red, 0);
     if (threadIdx.x == 0) finish_step<N, K, F>(s, V);
     return;
   }
@@ -1259,7 +1220,7 @@ __global__ void __launch_bounds__(1024) k_pcg_S10(Csr A, Vecs V, Red red) {
     Shm<N> s = shm_carve<N>(smem, 2, false);
     const Range R = my_rows(A.n);
     Deferred<N, 2> q;
-    q.issue(red, SLOT_YR, V.st);
+    q.issue(s, red, SLOT_YR, V.st);
     constexpr int PF = 8;  // a thread's rows at two workgroups per CU on 2M rows
     double pp[PF], py[PF];
 #pragma unroll
@@ -1271,7 +1232,7 @@ __global__ void __launch_bounds__(1024) k_pcg_S10(Csr A, Vecs V, Red red) {
       }
     }
     if (blockIdx.x == 0) block_clear_slots<N, 1>(red, SLOT_PD);
-    const int fl = q.flags(s);
+    const int fl = q.flags(s, red, SLOT_YR);
     if (fl & 1) return;
     double alpha = V.st->alpha;
     bool has = V.st->iter > 0;
@@ -1322,7 +1283,7 @@ __global__ void __launch_bounds__(1024) k_pcg_S3(Csr A, Vecs V, Red red) {
   if constexpr (defer_std<N>()) {
     const Range R = my_rows(A.n);
     Deferred<N, 1> q;
-    q.issue(red, SLOT_PD, V.st);
+    q.issue(s, red, SLOT_PD, V.st);
     constexpr int PF = 4;
     RowsP3<Unif> pf[PF];
 #pragma unroll
@@ -1330,7 +1291,7 @@ __global__ void __launch_bounds__(1024) k_pcg_S3(Csr A, Vecs V, Red red) {
       const int i = R.lo + threadIdx.x + k * blockDim.x;
       if (i < R.hi) pf[k].load(A, V, i);
     }
-    if (q.flags(s) & 1) return;
+    if (q.flags(s, red, SLOT_PD) & 1) return;
     double rho;
     if (q.template step<FIN_PCG_RHO>(s, V, red, SLOT_PD, rho)) return;  // S2
     shm_init(s, 2);
