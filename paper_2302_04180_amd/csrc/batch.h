@@ -2,8 +2,8 @@
 //
 // Each system keeps its own matrix, vectors, device state and reduction slots
 // (a SysDesc).  The rows of all systems are cut into tiles of consecutive rows
-// of one system; a phase launch walks the tile table (workgroup b takes tiles
-// b, b + gridDim.x, ...) and runs the same phase bodies as the single-system
+// of one system; a phase launch covers the tile table (workgroup b takes tile
+// Batch::t0 + b) and runs the same phase bodies as the single-system
 // kernels on each tile, publishing the tile's record into its own system's
 // slots; the workgroup that finishes a system's last tile rounds that system's
 // dot products and takes its scalar step.  Every system therefore computes exactly
@@ -35,6 +35,8 @@ struct Batch {
   const Tile* tiles;
   const int* order;  // [count[1]] system indices visited by the finishing workgroups
   const int* count;  // [0] number of tiles, [1] number of systems in `order`
+  int nt;            // number of tiles (host copy of count[0]: the launchers cover them)
+  int t0;            // first tile of a launch (set by the launchers)
   int far;           // the batch's vectors do not fit in the Infinity Cache: the host
                      // launches the Far / Mid instantiations (streamed vectors)
   int unif;          // every system's Jacobi vector is uniform (Csr::unif): the host
@@ -48,42 +50,40 @@ __device__ __forceinline__ Tile tile_at(const Batch& B, int t) {
               __builtin_amdgcn_readfirstlane(B.tiles[t].hi), __builtin_amdgcn_readfirstlane(B.tiles[t].rec)};
 }
 
-// Run body(desc, rows, rec) on every tile of the table assigned to this
-// workgroup (logical index b out of G).  CHECK: skip systems that have stopped.
-// Rows: the body multiplies by the system's matrix.
+// Run body(desc, rows, rec) on this workgroup's tile.  CHECK: not when its system
+// has stopped.  Rows: the body multiplies by the system's matrix.  One tile a
+// workgroup and no loop over tiles: what the compiler kept across such a loop
+// came on top of the bodies' registers (kb_std_D: 176 bytes of spills a lane, 233
+// us on the 9.08M rows of the 256-system batch).
 template <int N, int K, bool CHECK, bool Rows, class Body>
-__device__ __forceinline__ void tile_loop(const Batch& B, const Shm<N>& s, int b, int G, Body body) {
-  const int nt = B.count[0];
-  for (int t = b; t < nt; t += G) {
-    const Tile T = tile_at(B, t);
-    if (T.sys < 0) continue;
-    const SysDesc& D = B.sys[T.sys];
-    if (CHECK && D.V.st->done) continue;
-    if (Rows) pat_load(D.A, s);
-    if (K > 0) shm_init(s, K);
-    else if (Rows) __syncthreads();
-    body(D, Range{T.lo, T.hi}, T.rec);
-    __syncthreads();
-  }
+__device__ __forceinline__ void on_tile(const Batch& B, const Shm<N>& s, Body body) {
+  const int t = B.t0 + blockIdx.x;
+  if (t >= B.count[0]) return;
+  const Tile T = tile_at(B, t);
+  if (T.sys < 0) return;
+  const SysDesc& D = B.sys[T.sys];
+  if (CHECK && D.V.st->done) return;
+  if (Rows) pat_load(D.A, s);
+  if (K > 0) shm_init(s, K);
+  else if (Rows) __syncthreads();
+  body(D, Range{T.lo, T.hi}, T.rec);
 }
 
 // P1 / P3 of the pipelined loop: the tiles only publish their partial sums (the
 // SpMV kernel after them finishes each system's reduction), and the workgroup of
 // a system's first tile records whether the system ran, for that SpMV kernel.
 template <int N, int K, class Body>
-__device__ __forceinline__ void tile_loop_publish(const Batch& B, const Shm<N>& s, int b, int G, Body body) {
-  const int nt = B.count[0];
-  for (int t = b; t < nt; t += G) {
-    const Tile T = tile_at(B, t);
-    if (T.sys < 0) continue;
-    const SysDesc& D = B.sys[T.sys];
-    const int done = D.V.st->done;
-    if (T.rec == 0 && threadIdx.x == 0) D.V.st->spmv_go = !done;
-    if (done) continue;
-    shm_init(s, K);
-    body(D, Range{T.lo, T.hi}, T.rec);
-    __syncthreads();
-  }
+__device__ __forceinline__ void on_tile_publish(const Batch& B, const Shm<N>& s, Body body) {
+  const int t = B.t0 + blockIdx.x;
+  if (t >= B.count[0]) return;
+  const Tile T = tile_at(B, t);
+  if (T.sys < 0) return;
+  const SysDesc& D = B.sys[T.sys];
+  const int done = D.V.st->done;
+  if (T.rec == 0 && threadIdx.x == 0) D.V.st->spmv_go = !done;
+  if (done) return;
+  shm_init(s, K);
+  body(D, Range{T.lo, T.hi}, T.rec);
 }
 
 // ---------------------------------------------------------------------------
@@ -136,7 +136,7 @@ template <int N>
 __global__ void __launch_bounds__(1024) kb_std_init(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
-  tile_loop<N, 1, false, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  on_tile<N, 1, false, true>(B, s, [&](const SysDesc& D, Range R, int rec) {
     std_init_body<N>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -145,8 +145,7 @@ template <int N, bool Far, bool Unif>
 __global__ void __launch_bounds__(1024) kb_std_A(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 0, false);
-  tile_loop<N, 0, true, false>(B, s, blockIdx.x, gridDim.x,
-                        [&](const SysDesc& D, Range R, int) {
+  on_tile<N, 0, true, false>(B, s, [&](const SysDesc& D, Range R, int) {
                           const State* st = D.V.st;
                           std_A_body<Far, Unif>(D.A, D.V, R, st->beta, st->omega, st->iter > 0);
                         });
@@ -156,7 +155,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) kb_std_B(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
-  tile_loop<N, 1, true, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  on_tile<N, 1, true, true>(B, s, [&](const SysDesc& D, Range R, int rec) {
     std_B_body<N, Unif, false>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -165,15 +164,14 @@ template <int N, bool Far, bool Unif>
 __global__ void __launch_bounds__(1024) kb_std_C(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 0, false);
-  tile_loop<N, 0, true, false>(B, s, blockIdx.x, gridDim.x,
-                        [&](const SysDesc& D, Range R, int) { std_C_body<Far, Unif>(D.A, D.V, R, D.V.st->alpha); });
+  on_tile<N, 0, true, false>(B, s, [&](const SysDesc& D, Range R, int) { std_C_body<Far, Unif>(D.A, D.V, R, D.V.st->alpha); });
 }
 
 template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) kb_std_D(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 2, true);
-  tile_loop<N, 2, true, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  on_tile<N, 2, true, true>(B, s, [&](const SysDesc& D, Range R, int rec) {
     std_D_body<N, Unif, false>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -182,7 +180,7 @@ template <int N, bool Far, bool Unif>
 __global__ void __launch_bounds__(1024) kb_std_E(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 2, false);
-  tile_loop<N, 2, true, false>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  on_tile<N, 2, true, false>(B, s, [&](const SysDesc& D, Range R, int rec) {
     const State* st = D.V.st;
     std_E_body<N, Far, Unif>(D.A, D.V, D.red, R, rec, s, st->alpha, st->omega, st->iter);
   });
@@ -192,7 +190,7 @@ template <int N>
 __global__ void __launch_bounds__(1024) kb_resid(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
-  tile_loop<N, 1, false, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  on_tile<N, 1, false, true>(B, s, [&](const SysDesc& D, Range R, int rec) {
     resid_body<N>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -204,7 +202,7 @@ template <int N>
 __global__ void __launch_bounds__(1024) kb_pipe_init1(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
-  tile_loop<N, 1, false, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  on_tile<N, 1, false, true>(B, s, [&](const SysDesc& D, Range R, int rec) {
     pipe_init1_body<N>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -213,7 +211,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) kb_pipe_init2(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
-  tile_loop<N, 1, false, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  on_tile<N, 1, false, true>(B, s, [&](const SysDesc& D, Range R, int rec) {
     pipe_init2_body<N, Unif>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -222,7 +220,7 @@ template <int N, bool Mid, bool Unif>
 __global__ void __launch_bounds__(1024) kb_pipe_P1(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 4, false);
-  tile_loop_publish<N, 4>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  on_tile_publish<N, 4>(B, s, [&](const SysDesc& D, Range R, int rec) {
     pipe_P1_body<N, true, Mid, Unif>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -231,7 +229,7 @@ template <int N, bool Mid, bool Unif>
 __global__ void __launch_bounds__(1024) kb_pipe_P3(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 3, false);
-  tile_loop_publish<N, 3>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  on_tile_publish<N, 3>(B, s, [&](const SysDesc& D, Range R, int rec) {
     pipe_P3_body<N, true, Mid, Unif>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -245,22 +243,20 @@ template <int N, int W, int K, int F, bool Unif>
 __global__ void __launch_bounds__(1024) kb_pipe_spmv_fin(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, K, true);
-  const int nt = B.count[0];
-  for (int t = blockIdx.x; t < nt; t += gridDim.x) {
-    const Tile T = tile_at(B, t);
-    if (T.sys < 0) continue;
-    const SysDesc& D = B.sys[T.sys];
-    if (!D.V.st->spmv_go) continue;
-    if (T.rec == 0) {
-      block_finalize<N, K, FIN_CLEAR>(s, D.red, 0);
-      if (threadIdx.x == 0) finish_step<N, K, F>(s, D.V);
-    }
-    pat_load(D.A, s);
-    __syncthreads();
-    if (W == 0) spmv_hat_body<N, Unif>(D.A, D.V.w, D.V.wh, D.V.t, Range{T.lo, T.hi}, s);
-    else spmv_hat_body<N, Unif>(D.A, D.V.z, D.V.zh, D.V.v, Range{T.lo, T.hi}, s);
-    __syncthreads();
+  const int t = B.t0 + blockIdx.x;
+  if (t >= B.count[0]) return;
+  const Tile T = tile_at(B, t);
+  if (T.sys < 0) return;
+  const SysDesc& D = B.sys[T.sys];
+  if (!D.V.st->spmv_go) return;
+  if (T.rec == 0) {
+    block_finalize<N, K, FIN_CLEAR>(s, D.red, 0);
+    if (threadIdx.x == 0) finish_step<N, K, F>(s, D.V);
   }
+  pat_load(D.A, s);
+  __syncthreads();
+  if (W == 0) spmv_hat_body<N, Unif>(D.A, D.V.w, D.V.wh, D.V.t, Range{T.lo, T.hi}, s);
+  else spmv_hat_body<N, Unif>(D.A, D.V.z, D.V.zh, D.V.v, Range{T.lo, T.hi}, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -270,7 +266,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) kb_pcg_init(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 2, true);
-  tile_loop<N, 2, false, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  on_tile<N, 2, false, true>(B, s, [&](const SysDesc& D, Range R, int rec) {
     pcg_init_body<N, Unif>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -279,7 +275,7 @@ template <int N>
 __global__ void __launch_bounds__(1024) kb_pcg_S1(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 1, true);
-  tile_loop<N, 1, true, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  on_tile<N, 1, true, true>(B, s, [&](const SysDesc& D, Range R, int rec) {
     pcg_S1_body<N, false>(D.A, D.V, D.red, R, rec, s);
   });
 }
@@ -288,7 +284,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) kb_pcg_S3(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 2, false);
-  tile_loop<N, 2, true, false>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int rec) {
+  on_tile<N, 2, true, false>(B, s, [&](const SysDesc& D, Range R, int rec) {
     pcg_S3_body<N, Unif, false>(D.A, D.V, D.red, R, rec, s, D.V.st->rho, D.V.st->iter);
   });
 }
@@ -297,8 +293,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) kb_pcg_S10(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 0, false);
-  tile_loop<N, 0, true, false>(B, s, blockIdx.x, gridDim.x,
-                        [&](const SysDesc& D, Range R, int) { pcg_S10_body<Unif>(D.A, D.V, R, D.V.st->alpha); });
+  on_tile<N, 0, true, false>(B, s, [&](const SysDesc& D, Range R, int) { pcg_S10_body<Unif>(D.A, D.V, R, D.V.st->alpha); });
 }
 
 // Third set-up step of the pipelined loop over all tiles: t = A w^ (the loop's
@@ -307,7 +302,7 @@ template <int N, bool Unif>
 __global__ void __launch_bounds__(1024) kb_pipe_spmv(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 0, true);
-  tile_loop<N, 0, true, true>(B, s, blockIdx.x, gridDim.x, [&](const SysDesc& D, Range R, int) {
+  on_tile<N, 0, true, true>(B, s, [&](const SysDesc& D, Range R, int) {
     spmv_hat_body<N, Unif>(D.A, D.V.w, D.V.wh, D.V.t, R, s);
   });
 }

@@ -9,8 +9,9 @@
 //   trial  : one x per system (only when the autotuner may run)
 // The header is written with one host-to-device copy per call; everything the
 // kernels need is found through it, so a cached graph only depends on the
-// workspace address, the launch shape and whether the batch's far vectors are
-// streamed (which picks the kernel instantiations captured).
+// workspace address, the launch shape, the number of tiles, whether the batch's
+// far vectors are streamed and whether its Jacobi vectors are uniform (which pick
+// the kernel instantiations captured).
 #include <algorithm>
 #include <cstring>
 #include <numeric>
@@ -209,8 +210,10 @@ struct Ctx {
   BLayout L;
 };
 
-Batch batch_of(const Ctx& c) {
+Batch batch_of(const Ctx& c, const Plan& plan) {
   Batch B;
+  B.nt = (int)plan.tiles.size();
+  B.t0 = 0;
   B.count = (const int*)(c.ws + c.L.count);
   B.sys = (const SysDesc*)(c.ws + c.L.descs);
   B.order = (const int*)(c.ws + c.L.order);
@@ -261,7 +264,7 @@ struct Shape {
 Shape shape_of(const Ctx& c, const BCfg& cfg, const Plan& plan) {
   Shape sh;
   const int nt = (int)plan.tiles.size();  // a multiple of 8
-  const int cap = cfg.grid_cap ? std::min((cfg.grid_cap + 7) & ~7, 64000) : 64000;
+  const int cap = cfg.grid_cap ? (cfg.grid_cap + 7) & ~7 : kMaxTileGrid;
   sh.G = std::max(8, std::min(nt, cap));
   sh.Gf = std::min((c.ns + 7) & ~7, 1024);
   sh.B = cfg.block;
@@ -290,7 +293,7 @@ bool all_done(const State* h, int ns) {
 rpk_status start(const Ctx& c, const BCfg& cfg, const Plan& plan, bool trial, Shape* out) {
   RET_IF(upload(c, plan, trial));
   const Shape sh = shape_of(c, cfg, plan);
-  const Batch bt = batch_of(c);
+  const Batch bt = batch_of(c, plan);
   if (trial) {
     size_t off = c.L.trial;
     for (int k = 0; k < c.ns; ++k) {
@@ -306,8 +309,8 @@ rpk_status start(const Ctx& c, const BCfg& cfg, const Plan& plan, bool trial, Sh
   return RPK_OK;
 }
 
-rpk_status iterate_direct(const Ctx& c, const Shape& sh, int iters) {
-  const Batch bt = batch_of(c);
+rpk_status iterate_direct(const Ctx& c, const Plan& plan, const Shape& sh, int iters) {
+  const Batch bt = batch_of(c, plan);
   for (int k = 0; k < iters; ++k)
     for (int ph = 0; ph < sh.nph; ++ph) RET_IF(by_fpe<BPhaseF>(sh.N, c.o->variant, ph, sh.G, sh.Gf, sh.B, c.s, bt));
   return RPK_OK;
@@ -319,7 +322,7 @@ rpk_status trial_time(const Ctx& c, const BCfg& cfg, float* ms) {
   const Plan plan = make_plan(c.n, cfg.tile);
   Shape sh;
   RET_IF(start(c, cfg, plan, true, &sh));
-  RET_IF(iterate_direct(c, sh, 1));
+  RET_IF(iterate_direct(c, plan, sh, 1));
   hipEvent_t e0 = nullptr, e1 = nullptr;
   HIPCHK(hipEventCreate(&e0));
   if (hipEventCreate(&e1) != hipSuccess) {
@@ -329,7 +332,7 @@ rpk_status trial_time(const Ctx& c, const BCfg& cfg, float* ms) {
   constexpr int kIters = 3;
   rpk_status st = RPK_OK;
   if (hipEventRecord(e0, c.s) != hipSuccess) st = RPK_ERR_HIP;
-  if (st == RPK_OK) st = iterate_direct(c, sh, kIters);
+  if (st == RPK_OK) st = iterate_direct(c, plan, sh, kIters);
   if (st == RPK_OK && (hipEventRecord(e1, c.s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess))
     st = RPK_ERR_HIP;
   float t = 0.f;
@@ -428,7 +431,7 @@ rpk_status run(const Ctx& c, const BCfg& cfg, rpk_info* infos) {
     infos[0].phase_launches[slot] += 1;
   };
   State* h = nullptr;
-  const int bt_far = batch_of(c).far;
+  const int bt_far = batch_of(c, plan).far;
   do {
     if (st != RPK_OK) break;
     if (timing && hipEventRecord(ev[0], c.s) != hipSuccess) { st = RPK_ERR_HIP; break; }
@@ -438,8 +441,9 @@ rpk_status run(const Ctx& c, const BCfg& cfg, rpk_info* infos) {
       if (hipEventRecord(ev[1], c.s) != hipSuccess || hipEventSynchronize(ev[1]) != hipSuccess) { st = RPK_ERR_HIP; break; }
       elapsed(0, 1, 8);
     }
-    const Batch bt = batch_of(c);
-    const bool use_graph = !timing && cfg.graph >= 0;
+    const Batch bt = batch_of(c, plan);
+    // a grid so small that a phase takes many launches is not captured
+    const bool use_graph = !timing && cfg.graph >= 0 && bt.nt <= 8ll * sh.G;
     int chunk = cfg.graph > 0 ? cfg.graph : 4;
     long long launched = 0;
     for (;;) {
@@ -462,7 +466,8 @@ rpk_status run(const Ctx& c, const BCfg& cfg, rpk_info* infos) {
         const std::vector<uint64_t> key{0, (uint64_t)(uintptr_t)c.ws, (uint64_t)c.L.count, (uint64_t)c.L.descs,
                                         (uint64_t)c.L.order, (uint64_t)c.L.tiles, (uint64_t)c.o->variant,
                                         (uint64_t)sh.N, (uint64_t)sh.G, (uint64_t)sh.Gf, (uint64_t)sh.B,
-                                        (uint64_t)chunk, (uint64_t)bt.far, 0xba7c4ull};
+                                        (uint64_t)chunk, (uint64_t)bt.nt, (uint64_t)bt.far, (uint64_t)bt.unif,
+                                        0xba7c4ull};
         hipGraphExec_t exec = nullptr;
         st = graph_get(key, [&](hipStream_t cs) {
           rpk_status cst = RPK_OK;
@@ -476,7 +481,7 @@ rpk_status run(const Ctx& c, const BCfg& cfg, rpk_info* infos) {
         launched += chunk;
         if (cfg.graph == 0 && chunk < 32) chunk *= 2;
       } else {
-        st = iterate_direct(c, sh, chunk);
+        st = iterate_direct(c, plan, sh, chunk);
         if (st != RPK_OK) break;
         launched += chunk;
       }

@@ -72,6 +72,9 @@ constexpr int64_t kOneGroupRows = 512;
 constexpr int64_t kSmallBlockRows = 65536;
 // Largest automatic chunk of iterations between two looks at a solve's state
 constexpr int kMaxChunk = 64;
+// Workgroups of one launch over a tile table (the rest take further launches):
+// with 1,024 threads each, well inside a launch's 2^32 threads
+constexpr int kMaxTileGrid = 1 << 20;
 constexpr int64_t kCarryChunks = (int64_t(1) << 31) - 1;
 inline bool records_fit(int64_t records, int64_t lanes, int fpe) {
   return records * (lanes * (int64_t)fpe + 1) <= kCarryChunks;

@@ -28,8 +28,8 @@ struct Kern {
   static rpk_status one(int variant, int B, hipStream_t s, Csr A, Vecs V, Red red, int iters);
 };
 
-// Batched launchers: G = workgroups of the tile-walking kernels, Gf = workgroups
-// of the per-system set-up kernel.
+// Batched launchers: G = workgroups a launch of the kernels that take one tile
+// each (b.nt tiles are covered), Gf = workgroups of the per-system set-up kernel.
 template <int N>
 struct KernB {
   static rpk_status setup(int Gf, hipStream_t s, Batch b, double tol, int maxit, int variant);

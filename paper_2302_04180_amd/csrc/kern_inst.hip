@@ -11,6 +11,14 @@ static rpk_status launch(K kernel, int grid, int block, size_t shm, hipStream_t 
   return hipGetLastError() == hipSuccess ? RPK_OK : RPK_ERR_HIP;
 }
 
+// a kernel that takes one tile a workgroup, over all tiles, G at a time
+template <typename K>
+static rpk_status launch_tiles(K kernel, int G, int block, size_t shm, hipStream_t s, Batch b) {
+  for (b.t0 = 0; b.t0 < b.nt; b.t0 += G)
+    RET_IF(launch(kernel, G < b.nt - b.t0 ? G : b.nt - b.t0, block, shm, s, b));
+  return RPK_OK;
+}
+
 template <int N>
 rpk_status Kern<N>::dot(int G, int B, hipStream_t s, long long n, const double* x, const double* y, double* out,
                         int* lost, Red red) {
@@ -138,23 +146,23 @@ rpk_status KernB<N>::setup(int Gf, hipStream_t s, Batch b, double tol, int maxit
 template <int N>
 rpk_status KernB<N>::init(int variant, int G, int Gf, int B, hipStream_t s, Batch b) {
   (void)Gf;
-  if (variant == RPK_STD) return launch(kb_std_init<N>, G, B, shm_bytes(N, 1, true, B), s, b);
+  if (variant == RPK_STD) return launch_tiles(kb_std_init<N>, G, B, shm_bytes(N, 1, true, B), s, b);
   if (variant == RPK_PCG)
-    return b.unif ? launch(kb_pcg_init<N, true>, G, B, shm_bytes(N, 2, true, B), s, b)
-                  : launch(kb_pcg_init<N, false>, G, B, shm_bytes(N, 2, true, B), s, b);
-  RET_IF(launch(kb_pipe_init1<N>, G, B, shm_bytes(N, 1, true, B), s, b));
+    return b.unif ? launch_tiles(kb_pcg_init<N, true>, G, B, shm_bytes(N, 2, true, B), s, b)
+                  : launch_tiles(kb_pcg_init<N, false>, G, B, shm_bytes(N, 2, true, B), s, b);
+  RET_IF(launch_tiles(kb_pipe_init1<N>, G, B, shm_bytes(N, 1, true, B), s, b));
   if (b.unif) {
-    RET_IF(launch(kb_pipe_init2<N, true>, G, B, shm_bytes(N, 1, true, B), s, b));
-    return launch(kb_pipe_spmv<N, true>, G, B, shm_bytes(N, 0, true, B), s, b);
+    RET_IF(launch_tiles(kb_pipe_init2<N, true>, G, B, shm_bytes(N, 1, true, B), s, b));
+    return launch_tiles(kb_pipe_spmv<N, true>, G, B, shm_bytes(N, 0, true, B), s, b);
   }
-  RET_IF(launch(kb_pipe_init2<N, false>, G, B, shm_bytes(N, 1, true, B), s, b));
-  return launch(kb_pipe_spmv<N, false>, G, B, shm_bytes(N, 0, true, B), s, b);
+  RET_IF(launch_tiles(kb_pipe_init2<N, false>, G, B, shm_bytes(N, 1, true, B), s, b));
+  return launch_tiles(kb_pipe_spmv<N, false>, G, B, shm_bytes(N, 0, true, B), s, b);
 }
 
 template <int N>
 rpk_status KernB<N>::resid(int G, int Gf, int B, hipStream_t s, Batch b) {
   (void)Gf;
-  return launch(kb_resid<N>, G, B, shm_bytes(N, 1, true, B), s, b);
+  return launch_tiles(kb_resid<N>, G, B, shm_bytes(N, 1, true, B), s, b);
 }
 
 template <int N>
@@ -165,37 +173,37 @@ rpk_status KernB<N>::phase(int variant, int ph, int G, int Gf, int B, hipStream_
     const size_t s1e = shm_bytes(N, 1, false, B);
     if (b.unif) {
       switch (ph) {
-        case 0: return launch(kb_std_A<N, false, true>, G, B, 0, s, b);
-        case 1: return launch(kb_std_B<N, true>, G, B, s1, s, b);
-        case 2: return launch(kb_std_C<N, false, true>, G, B, 0, s, b);
-        case 3: return launch(kb_std_D<N, true>, G, B, s2, s, b);
+        case 0: return launch_tiles(kb_std_A<N, false, true>, G, B, 0, s, b);
+        case 1: return launch_tiles(kb_std_B<N, true>, G, B, s1, s, b);
+        case 2: return launch_tiles(kb_std_C<N, false, true>, G, B, 0, s, b);
+        case 3: return launch_tiles(kb_std_D<N, true>, G, B, s2, s, b);
         default:
-          return b.far ? launch(kb_std_E<N, true, true>, G, B, s2e, s, b)
-                       : launch(kb_std_E<N, false, true>, G, B, s2e, s, b);
+          return b.far ? launch_tiles(kb_std_E<N, true, true>, G, B, s2e, s, b)
+                       : launch_tiles(kb_std_E<N, false, true>, G, B, s2e, s, b);
       }
     }
     switch (ph) {
       case 0:
-        return b.far ? launch(kb_std_A<N, true, false>, G, B, 0, s, b)
-                     : launch(kb_std_A<N, false, false>, G, B, 0, s, b);
-      case 1: return launch(kb_std_B<N, false>, G, B, s1, s, b);
+        return b.far ? launch_tiles(kb_std_A<N, true, false>, G, B, 0, s, b)
+                     : launch_tiles(kb_std_A<N, false, false>, G, B, 0, s, b);
+      case 1: return launch_tiles(kb_std_B<N, false>, G, B, s1, s, b);
       case 2:
-        return b.far ? launch(kb_std_C<N, true, false>, G, B, 0, s, b)
-                     : launch(kb_std_C<N, false, false>, G, B, 0, s, b);
-      case 3: return launch(kb_std_D<N, false>, G, B, s2, s, b);
+        return b.far ? launch_tiles(kb_std_C<N, true, false>, G, B, 0, s, b)
+                     : launch_tiles(kb_std_C<N, false, false>, G, B, 0, s, b);
+      case 3: return launch_tiles(kb_std_D<N, false>, G, B, s2, s, b);
       default:
-        return b.far ? launch(kb_std_E<N, true, false>, G, B, s2e, s, b)
-                     : launch(kb_std_E<N, false, false>, G, B, s2e, s, b);
+        return b.far ? launch_tiles(kb_std_E<N, true, false>, G, B, s2e, s, b)
+                     : launch_tiles(kb_std_E<N, false, false>, G, B, s2e, s, b);
     }
   }
   if (variant == RPK_PCG) {
     switch (ph) {
-      case 0: return launch(kb_pcg_S1<N>, G, B, shm_bytes(N, 1, true, B), s, b);
+      case 0: return launch_tiles(kb_pcg_S1<N>, G, B, shm_bytes(N, 1, true, B), s, b);
       case 1:
-        return b.unif ? launch(kb_pcg_S3<N, true>, G, B, shm_bytes(N, 2, false, B), s, b)
-                      : launch(kb_pcg_S3<N, false>, G, B, shm_bytes(N, 2, false, B), s, b);
+        return b.unif ? launch_tiles(kb_pcg_S3<N, true>, G, B, shm_bytes(N, 2, false, B), s, b)
+                      : launch_tiles(kb_pcg_S3<N, false>, G, B, shm_bytes(N, 2, false, B), s, b);
       default:
-        return b.unif ? launch(kb_pcg_S10<N, true>, G, B, 0, s, b) : launch(kb_pcg_S10<N, false>, G, B, 0, s, b);
+        return b.unif ? launch_tiles(kb_pcg_S10<N, true>, G, B, 0, s, b) : launch_tiles(kb_pcg_S10<N, false>, G, B, 0, s, b);
     }
   }
   const size_t s4 = shm_bytes(N, 4, false, B), s4t = shm_bytes(N, 4, true, B);
@@ -203,24 +211,24 @@ rpk_status KernB<N>::phase(int variant, int ph, int G, int Gf, int B, hipStream_
   if (b.unif) {
     switch (ph) {
       case 0:
-        return b.far ? launch(kb_pipe_P1<N, true, true>, G, B, s4, s, b)
-                     : launch(kb_pipe_P1<N, false, true>, G, B, s4, s, b);
-      case 1: return launch(kb_pipe_spmv_fin<N, 1, 4, FIN_POMEGA, true>, G, B, s4t, s, b);
+        return b.far ? launch_tiles(kb_pipe_P1<N, true, true>, G, B, s4, s, b)
+                     : launch_tiles(kb_pipe_P1<N, false, true>, G, B, s4, s, b);
+      case 1: return launch_tiles(kb_pipe_spmv_fin<N, 1, 4, FIN_POMEGA, true>, G, B, s4t, s, b);
       case 2:
-        return b.far ? launch(kb_pipe_P3<N, true, true>, G, B, s3, s, b)
-                     : launch(kb_pipe_P3<N, false, true>, G, B, s3, s, b);
-      default: return launch(kb_pipe_spmv_fin<N, 0, 3, FIN_S19, true>, G, B, s3t, s, b);
+        return b.far ? launch_tiles(kb_pipe_P3<N, true, true>, G, B, s3, s, b)
+                     : launch_tiles(kb_pipe_P3<N, false, true>, G, B, s3, s, b);
+      default: return launch_tiles(kb_pipe_spmv_fin<N, 0, 3, FIN_S19, true>, G, B, s3t, s, b);
     }
   }
   switch (ph) {
     case 0:
-      return b.far ? launch(kb_pipe_P1<N, true, false>, G, B, s4, s, b)
-                   : launch(kb_pipe_P1<N, false, false>, G, B, s4, s, b);
-    case 1: return launch(kb_pipe_spmv_fin<N, 1, 4, FIN_POMEGA, false>, G, B, s4t, s, b);
+      return b.far ? launch_tiles(kb_pipe_P1<N, true, false>, G, B, s4, s, b)
+                   : launch_tiles(kb_pipe_P1<N, false, false>, G, B, s4, s, b);
+    case 1: return launch_tiles(kb_pipe_spmv_fin<N, 1, 4, FIN_POMEGA, false>, G, B, s4t, s, b);
     case 2:
-      return b.far ? launch(kb_pipe_P3<N, true, false>, G, B, s3, s, b)
-                   : launch(kb_pipe_P3<N, false, false>, G, B, s3, s, b);
-    default: return launch(kb_pipe_spmv_fin<N, 0, 3, FIN_S19, false>, G, B, s3t, s, b);
+      return b.far ? launch_tiles(kb_pipe_P3<N, true, false>, G, B, s3, s, b)
+                   : launch_tiles(kb_pipe_P3<N, false, false>, G, B, s3, s, b);
+    default: return launch_tiles(kb_pipe_spmv_fin<N, 0, 3, FIN_S19, false>, G, B, s3t, s, b);
   }
 }
 

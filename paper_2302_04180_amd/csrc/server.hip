@@ -159,6 +159,8 @@ rpk_status layout_header(rpk_server* S, int64_t tile_cap) {
 
 Batch view(const rpk_server* S, int v) {
   Batch B;
+  B.nt = ((const int*)S->h_hdr.data())[2 * v];
+  B.t0 = 0;
   B.count = (const int*)(S->hdr) + 2 * v;
   B.sys = (const SysDesc*)(S->hdr + S->off_descs);
   B.order = (const int*)(S->hdr + S->off_order) + (size_t)v * S->o.max_slots;
@@ -211,8 +213,8 @@ rpk_status upload(rpk_server* S) {
 }
 
 int gf_of(size_t ns) { return (int)std::min<size_t>((ns + 7) & ~size_t(7), 1024); }
-// tile-walking workgroups: one per tile up to a limit
-int g_of(int ntiles) { return std::min(ntiles, 64000); }
+// workgroups of the kernels that take a tile each
+int g_of(int ntiles) { return std::min(ntiles, kMaxTileGrid); }
 
 template <int N>
 struct SPhaseF {
