@@ -95,7 +95,8 @@ typedef enum { RPK_DOT_EXACT = 0, RPK_DOT_PLAIN = 1, RPK_DOT_FPE = 2 } rpk_dotmo
  * grid 1, block 1024); other solves of fewer than 65536 rows use workgroups of
  * 256 threads.  Exact results are the same bits either way. */
 typedef struct {
-  int32_t block;  /* workgroup size, a multiple of 64 in [64, 1024]; 0 = 512 */
+  int32_t block;  /* workgroup size, a multiple of 64 in [64, 1024]; 0 = 512, or
+                     1024 from 262,144 rows on when the grid is automatic too */
   int32_t grid;   /* workgroups of the streaming kernels, 1 .. 65535; 0 = automatic */
   int32_t fpe;    /* FPE length 1, 2, 3, 4 or 8 (1 sends almost every term to
                      the long accumulator); 0 = 3 */

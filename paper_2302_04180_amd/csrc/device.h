@@ -417,15 +417,18 @@ enum : int { F_SA = 1, F_NONFINITE = 2, F_LOST = 4 };
 // accumulator `sa`; `flag` collects F_SA / F_NONFINITE.
 template <int N>
 __device__ __forceinline__ void acc_prod(Fpe<N>& f, double a, double b, long long* sa, int* flag) {
-  const double p = a * b;
+  double p = a * b;
+  double e = fma(a, b, -p);
   const double ap = fabs(p);
-  // common case without per-lane branches: out-of-range products insert 0 here
-  // and are handled below
   const bool ok = ap >= kProdLo && ap < kProdHi;
-  const double e = ok ? fma(a, b, -p) : 0.0;
-  const double l1 = fpe_add_all<N, 0>(f, ok ? p : 0.0);
+  bool extreme = false;
+  if (__ballot(!ok)) {  // out-of-range products insert 0 and are handled below; zeros need nothing
+    extreme = !ok && !(p == 0.0 && (a == 0.0 || b == 0.0));
+    p = ok ? p : 0.0;
+    e = ok ? e : 0.0;
+  }
+  const double l1 = fpe_add_all<N, 0>(f, p);
   const double l2 = fpe_add_all<N, (N > 1 ? 1 : 0)>(f, e);
-  const bool extreme = !ok && !(p == 0.0 && (a == 0.0 || b == 0.0));
   if (l1 != 0.0 || l2 != 0.0 || extreme) {
     const bool finite = isfinite(a) && isfinite(b);
     atomicOr(flag, extreme && !finite ? F_NONFINITE : F_SA);

@@ -70,6 +70,14 @@ constexpr int64_t kOneGroupRows = 512;
 // threads instead of 512: measured 3-12 % faster from 1,728 to 32,768 rows
 // (7-point Poisson, all three loops), slower from 110,592 on
 constexpr int64_t kSmallBlockRows = 65536;
+// Dots of at most this many elements with the automatic launch shape run in one
+// workgroup: 1,000 elements 4.3 us against 5.4 in two workgroups of 512
+constexpr int64_t kOneGroupDot = 4096;
+// From this many rows on the automatic shape is 256 workgroups of 1,024 threads
+// instead of 512 of 512: as many wavefronts, but half the partial sums that
+// queue on the accumulators (128^3 solve: B 25.0 and 23.5, D 30.6 and 28.0 us,
+// 101^3 PCG: S1 15.8 and 14.6, S3 17.5 and 16.6 us)
+constexpr int64_t kBigBlockRows = 262144;
 // Largest automatic chunk of iterations between two looks at a solve's state
 constexpr int kMaxChunk = 64;
 // Workgroups of one launch over a tile table (the rest take further launches):

@@ -43,7 +43,8 @@ struct Cfg {
 
 rpk_status resolve(const rpk_launch* L, int64_t n, Cfg* c) {
   c->one = 0;
-  c->block = (L && L->block) ? L->block : 512;
+  const bool automatic = !L || (L->block == 0 && L->grid == 0);
+  c->block = (L && L->block) ? L->block : (automatic && n >= kBigBlockRows) ? 1024 : 512;
   c->fpe = (L && L->fpe) ? L->fpe : 3;
   c->graph = L ? L->graph : 0;
   if (c->block < 64 || c->block > 1024 || (c->block % 64) != 0) return RPK_ERR_ARG;
@@ -53,12 +54,13 @@ rpk_status resolve(const rpk_launch* L, int64_t n, Cfg* c) {
     if (L->grid < 1 || L->grid > 65535) return RPK_ERR_ARG;
     c->grid = L->grid;
   } else {
-    // about two workgroups per CU of 256 CUs: few enough partial records for
-    // the workgroup that finishes a reduction, enough waves in flight for the
-    // streams (measured best among 256..1024 workgroups of 256..1024 threads)
+    // 1,024 threads per CU of 256 CUs: few enough workgroups for their partial
+    // sums to queue little, enough waves in flight for the streams (measured best
+    // among 256..2048 workgroups of 256..1024 threads)
     int64_t need = (n + c->block - 1) / c->block;
+    const int64_t most = automatic && n >= kBigBlockRows ? 256 : 512;
     if (need < 1) need = 1;
-    if (need > 512) need = 512;
+    if (need > most) need = most;
     if (need >= 8) need &= ~7ll;
     c->grid = (int)need;
   }
@@ -66,6 +68,18 @@ rpk_status resolve(const rpk_launch* L, int64_t n, Cfg* c) {
   // cannot take a huge n)
   if ((n + c->grid - 1) / c->grid > kMaxPerGroup) return RPK_ERR_ARG;
   if (!records_fit(c->grid, c->block, c->fpe)) return RPK_ERR_ARG;
+  return RPK_OK;
+}
+
+// Launch shape of a dot: that of the streaming kernels, but with the automatic
+// shape one workgroup for short vectors, which reduces in LDS with no
+// accumulator, ticket or second workgroup to wait for.
+rpk_status dot_shape(const rpk_launch* L, int64_t n, Cfg* c) {
+  RET_IF(resolve(L, n, c));
+  if (n <= kOneGroupDot && (!L || (L->block == 0 && L->grid == 0))) {
+    c->block = 1024;
+    c->grid = 1;
+  }
   return RPK_OK;
 }
 
@@ -500,7 +514,7 @@ rpk_status rpk_exdot(int64_t n, const double* x, const double* y, double* out_de
   if (n < 0 || n >= (1ll << 32) || !out_dev || !ws || (n > 0 && (!x || !y))) return RPK_ERR_ARG;
   if (dots != RPK_DOT_EXACT && dots != RPK_DOT_PLAIN) return RPK_ERR_ARG;
   Cfg c;
-  RET_IF(resolve(launch_cfg, n, &c));
+  RET_IF(dot_shape(launch_cfg, n, &c));
   const Layout l = layout(c.grid, 0, 0);
   if (ws_bytes < l.total) return RPK_ERR_ARG;
   Red red = make_red((char*)ws, l, c.grid);
@@ -513,17 +527,20 @@ rpk_status rpk_exdot_noalloc(int64_t n, const double* x, const double* y, double
   if (n < 0 || n >= (1ll << 32) || !out_dev || (n > 0 && (!x || !y))) return RPK_ERR_ARG;
   if (dots != RPK_DOT_EXACT && dots != RPK_DOT_PLAIN) return RPK_ERR_ARG;
   Cfg c;
-  RET_IF(resolve(launch_cfg, n, &c));
+  RET_IF(dot_shape(launch_cfg, n, &c));
   const Layout l = layout(c.grid, 0, 0);
   if (c.grid > kScratchGrid || l.total > kScratchBytes) return RPK_ERR_ARG;  // beyond what the scratch array holds
   char* ws = nullptr;
   RET_IF(noalloc_scratch(&ws));
   hipStream_t s = (hipStream_t)stream;
   // tickets, flags and long accumulators start at zero (the kernel leaves them
-  // zeroed; cleared all the same, by a kernel rather than a memset node)
-  hipLaunchKernelGGL(k_zero_words, dim3(32), dim3(256), 0, s, (unsigned*)ws,
-                     (long long)(l.partials / sizeof(unsigned)));
-  if (hipGetLastError() != hipSuccess) return RPK_ERR_HIP;
+  // zeroed; cleared all the same, by a kernel rather than a memset node); a
+  // single workgroup uses none of them
+  if (c.grid > 1) {
+    hipLaunchKernelGGL(k_zero_words, dim3(32), dim3(256), 0, s, (unsigned*)ws,
+                       (long long)(l.partials / sizeof(unsigned)));
+    if (hipGetLastError() != hipSuccess) return RPK_ERR_HIP;
+  }
   Red red = make_red(ws, l, c.grid);
   return by_dot<DotF>(kernel_n(dots, c.fpe), c.grid, c.block, s, (long long)n, x, y, out_dev, (int*)nullptr, red);
 }

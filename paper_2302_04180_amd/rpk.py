@@ -5,6 +5,7 @@ memory and streams.  If the shared library is missing the import of this module
 fails: there is no CPU fallback.
 """
 import ctypes
+import functools
 import os
 import warnings
 
@@ -116,8 +117,13 @@ def _check(code, where):
         raise RpkError(code, where)
 
 
+def _raw_stream():
+    """The current stream as an integer (torch.cuda.current_stream() builds an object, 3 us)."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream())
 
 
 def _ptr(t):
@@ -131,6 +137,21 @@ def _launch(block=0, grid=0, fpe=0, graph=0, tile=0):
 def _dev(t):
     assert t.is_cuda and t.dtype == torch.float64 and t.is_contiguous()
     return t
+
+
+@functools.lru_cache(maxsize=1024)
+def _dot_bytes(n, block, grid, fpe):
+    """Workspace size of a dot of n elements (a function of its arguments alone)."""
+    L = _launch(block, grid, fpe)
+    nb = ctypes.c_size_t()
+    _check(load().rpk_exdot_workspace_bytes(n, ctypes.byref(L), ctypes.byref(nb)), "workspace")
+    return nb.value
+
+
+@functools.lru_cache(maxsize=256)
+def _launch_ref(block, grid, fpe):
+    """A launch argument that is only read (None: the defaults)."""
+    return ctypes.byref(_launch(block, grid, fpe)) if block or grid or fpe else None
 
 
 _ws_cache = {}
@@ -226,16 +247,18 @@ def solve_workspace_bytes(A, variant=STD, dots=EXACT, block=0, grid=0, fpe=0):
 
 def exdot(x, y, dots=EXACT, block=0, grid=0, fpe=0):
     """Correctly rounded <x, y> (exact mode) as a 0-dim device tensor."""
-    lib = load()
+    # short dots are bound by this call: sizes and launch arguments are looked up,
+    # pointers passed as plain integers
+    lib = _lib or load()
     x, y = _dev(x), _dev(y)
-    assert x.numel() == y.numel()
-    L = _launch(block, grid, fpe)
-    nb = ctypes.c_size_t()
-    _check(lib.rpk_exdot_workspace_bytes(x.numel(), ctypes.byref(L), ctypes.byref(nb)), "workspace")
-    ws = _workspace(nb.value, ("dot", x.device.index))
-    out = torch.empty((), dtype=torch.float64, device=x.device)
-    _check(lib.rpk_exdot(x.numel(), _ptr(x), _ptr(y), _ptr(out), int(dots), ctypes.byref(L), _ptr(ws),
-                         ws.numel(), _stream()), "rpk_exdot")
+    n = x.numel()
+    assert n == y.numel()
+    ws = _workspace(_dot_bytes(n, block, grid, fpe), ("dot", x.device.index))
+    out = x.new_empty(())
+    code = lib.rpk_exdot(n, x.data_ptr(), y.data_ptr(), out.data_ptr(), int(dots), _launch_ref(block, grid, fpe),
+                         ws.data_ptr(), ws.numel(), _raw_stream())
+    if code:
+        _check(code, "rpk_exdot")
     return out
 
 
