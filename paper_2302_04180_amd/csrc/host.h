@@ -115,8 +115,23 @@ inline int keep_slices(const rpk_matrix* A, int nvec) {
 
 // Vectors one standard iteration touches: its eight work vectors, x and the
 // Jacobi vector; with a uniform Jacobi vector p^ and q^ are never stored and
-// dinv is a scalar, which leaves seven.
+// dinv is a scalar, which leaves seven.  (The three-kernel loop has a second p and
+// s; it runs where all fit.)
 inline int std_vectors(bool unif) { return unif ? 7 : nvec_of(RPK_STD) + 2; }
+// Loop of a single standard solve (Vecs::loop).  The shorter loops need a uniform
+// Jacobi vector and a row dictionary, and the deferred reduction points.  They save
+// a launch and a pass over vectors and pay with one (D3) or two (B3) more gathers
+// per entry: about 0.37 us for a million entries in D3 against 4 us and 3.4 us for
+// a million rows in C.  Measured, us: D3 and D + C 34.9 and 40.6 (128^3, 7 points),
+// 17.2 and 19.2 (64^3, 27 points), 26.2 and 25.4 (80^3, 27), 76.4 and 68.4
+// (128^3, 27); B3 and A + B, with 1 us for the gap between two kernels, 11.6 and
+// 13.8 (64^3, 7), 16.8 and 17.4 (80^3, 7: 3.6M entries), 14.2 and 14.0 (48^3, 27:
+// 3.0M), 43.4 and 39.2 (128^3, 7).
+inline int std_loop(const rpk_matrix* A, int variant, int dots) {
+  if (variant != RPK_STD || dots == RPK_DOT_FPE || A->unif == 0 || A->np == 0) return LOOP5;
+  if (A->nnz <= 3000000) return LOOP3;
+  return A->nnz <= 8000000 + 9 * (int64_t)A->n ? LOOP4 : LOOP5;
+}
 // Vectors the pipelined loop keeps cached when they fit: p^, q, q^, y, r, r^, w,
 // t, v and z^, w^ (its other six, s, s^, z, x, r0 and dinv, are always
 // streamed); with a uniform Jacobi vector z^ and w^ are never stored and z

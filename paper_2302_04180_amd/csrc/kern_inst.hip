@@ -58,6 +58,25 @@ rpk_status Kern<N>::phase(int variant, int ph, int G, int B, hipStream_t s, Csr 
     const bool far = V.far != 0;
     const size_t s1 = shm_bytes(N, 1, true, B), s2 = shm_bytes(N, 2, true, B), s2e = shm_bytes(N, 2, false, B);
     const size_t s1e = shm_bytes(N, 1, false, B);
+    if constexpr (defer_std<N>()) {
+      if (V.loop != LOOP5) {
+        const bool three = V.loop == LOOP3;
+        switch (ph) {
+          case 0: return three ? RPK_OK : launch(k_std_A<N, false, true>, G, B, s2e, s, A, V, red);
+          case 1:
+            return three ? launch(k_std_B3<N>, G, B, s2, s, A, V, red)
+                         : launch(k_std_B<N, true>, G, B, s1, s, A, V, red);
+          case 2: return RPK_OK;  // part of 3
+          case 3:
+            return three ? launch(k_std_D3<N, LOOP3>, G, B, s2, s, A, V, red)
+                         : launch(k_std_D3<N, LOOP4>, G, B, s2, s, A, V, red);
+          default:
+            return three ? launch(k_std_E<N, false, true, LOOP3>, G, B, s2e, s, A, V, red)
+                   : far ? launch(k_std_E<N, true, true, LOOP4>, G, B, s2e, s, A, V, red)
+                         : launch(k_std_E<N, false, true, LOOP4>, G, B, s2e, s, A, V, red);
+        }
+      }
+    }
     if (A.unif) {
       switch (ph) {
         case 0: return launch(k_std_A<N, false, true>, G, B, s2e, s, A, V, red);

@@ -322,7 +322,11 @@ struct Dot<LW8> {
 // arithmetic on the loaded value.  The row loops issue the loads of a batch of
 // entries first and apply fin afterwards, so that no load waits for the one
 // before it.
+// Raw is what the access gives; kDict marks gathers used with a row dictionary
+// only.
 struct GatherX {  // plain vector
+  using Raw = double;
+  static constexpr bool kDict = false;
   const double* __restrict__ x;
   __device__ __forceinline__ double load(int c) const { return x[c]; }
   __device__ __forceinline__ double load8(unsigned o) const { return *(const double*)((const char*)x + o); }
@@ -331,11 +335,44 @@ struct GatherX {  // plain vector
 // M^-1 v for a uniform Jacobi vector (Csr::unif), formed at the gather:
 // RN(du * v_c), the value a stored copy would hold.
 struct GatherScaled {
+  using Raw = double;
+  static constexpr bool kDict = false;
   double du;
   const double* __restrict__ v;
   __device__ __forceinline__ double load(int c) const { return v[c]; }
   __device__ __forceinline__ double load8(unsigned o) const { return *(const double*)((const char*)v + o); }
   __device__ __forceinline__ double fin(double x) const { return du * x; }
+};
+
+// M^-1 of a vector that is itself an update of others, formed at the gather (a
+// uniform Jacobi vector and a row dictionary): S4 + S5, q = fma(-alpha, s, r) ...
+struct GatherQ {
+  struct Raw {
+    double s, r;
+  };
+  static constexpr bool kDict = true;
+  double du, alpha;
+  const double *__restrict__ s, *__restrict__ r;
+  __device__ __forceinline__ Raw load8(unsigned o) const {
+    return Raw{*(const double*)((const char*)s + o), *(const double*)((const char*)r + o)};
+  }
+  __device__ __forceinline__ double own(Raw v) const { return fma(-alpha, v.s, v.r); }
+  __device__ __forceinline__ double fin(Raw v) const { return du * own(v); }
+};
+// ... and S12 + S1, p = fma(beta, fma(-omega, s, p), r)
+struct GatherP {
+  struct Raw {
+    double p, s, r;
+  };
+  static constexpr bool kDict = true;
+  double du, beta, omega;
+  const double *__restrict__ p, *__restrict__ s, *__restrict__ r;
+  __device__ __forceinline__ Raw load8(unsigned o) const {
+    return Raw{*(const double*)((const char*)p + o), *(const double*)((const char*)s + o),
+               *(const double*)((const char*)r + o)};
+  }
+  __device__ __forceinline__ double own(Raw v) const { return fma(beta, fma(-omega, v.s, v.p), v.r); }
+  __device__ __forceinline__ double fin(Raw v) const { return du * own(v); }
 };
 
 // A matrix entry or column index: non-temporal (NT) or ordinary load.
@@ -388,15 +425,16 @@ struct PatSrc {  // the row dictionary (Csr::pid) in LDS
     (void)w;
     const PatEnt* e = pat + at0 + j0;
     unsigned o[B];
+    typename Gth::Raw v[B];
 #pragma unroll
     for (int u = 0; u < B; ++u) {
       a[u] = e[u].a;
       o[u] = row8 + (unsigned)e[u].off8;
     }
 #pragma unroll
-    for (int u = 0; u < B; ++u) b[u] = gx.load8(o[u]);
+    for (int u = 0; u < B; ++u) v[u] = gx.load8(o[u]);
 #pragma unroll
-    for (int u = 0; u < B; ++u) b[u] = gx.fin(b[u]);
+    for (int u = 0; u < B; ++u) b[u] = gx.fin(v[u]);
   }
   template <class Gth>
   __device__ __forceinline__ void at(const Gth& gx, int l, int j, double& a, double& b) const {
@@ -644,7 +682,7 @@ __device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, c
     const int i = first + (int)(threadIdx.x & 63), sl = first >> 6;
     const bool ok = i < R.hi;
     double y = 0.0;
-    if (A.np) {
+    if (Gth::kDict || A.np) {
       const int w = __builtin_amdgcn_readfirstlane((int)A.swid[sl]);
       const PatSrc src{s.pat, (unsigned)(i < A.n ? i : A.n - 1) * 8u, (int)A.pid[i] * pat_stride(A.pw)};
       const auto p = pre(ok ? i : R.hi - 1);
@@ -655,7 +693,7 @@ __device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, c
         if (__ballot(ok && !cert) != 0ull) y = rows_fpe<N>(src, gx, w, ok, s.wsa);
       }
       use(i, ok, y, p);
-    } else {
+    } else if constexpr (!Gth::kDict) {
       const long long off = A.sptr[sl];
       const int w = (int)((A.sptr[sl + 1] - off) >> 6);
       const SellSrc<false> kept{A.sval + off, A.scol + off};

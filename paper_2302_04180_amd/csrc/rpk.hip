@@ -635,6 +635,7 @@ rpk_status rpk_solve(const rpk_matrix* A, const double* b, double* x, const rpk_
   info->used.grid = c.grid;
   info->used.fpe = (o->dots == RPK_DOT_PLAIN) ? 0 : (o->dots == RPK_DOT_FPE) ? LW_N : c.fpe;
   info->used.graph = c.graph;
+  const int loop = c.one ? LOOP5 : std_loop(A, o->variant, o->dots);
   info->streamed = streams_far(A, o->variant) ? 1 : 0;
   hipStream_t s = (hipStream_t)stream;
   std::lock_guard<std::mutex> lk(g_mu);
@@ -648,7 +649,8 @@ rpk_status rpk_solve(const rpk_matrix* A, const double* b, double* x, const rpk_
   Red red = make_red(w, l, G);
   Vecs V = carve_vecs(w, l, A->n, variant, x, b, o);
   Csr Ac = csr_of(A);
-  V.far = streams_far(A, variant) ? 1 : 0;
+  V.loop = loop;
+  V.far = info->streamed;
   Ac.keep = keep_slices(A, cached_vectors(variant, V.far != 0, A->unif != 0));
 
   const bool resume = o->resume != 0;
@@ -668,6 +670,10 @@ rpk_status rpk_solve(const rpk_matrix* A, const double* b, double* x, const rpk_
     const size_t step = up((size_t)A->n * sizeof(double));
     hipLaunchKernelGGL(k_fill, dim3(1024), dim3(256), 0, s, (double*)(w + l.vecs),
                        (long long)(16 * step / sizeof(double)), 0.0);
+    HIPCHK(hipGetLastError());
+  }
+  if (resume && loop == LOOP3) {
+    hipLaunchKernelGGL(k_std_pair, dim3(256), dim3(256), 0, s, A->n, V, true);
     HIPCHK(hipGetLastError());
   }
   if (resume) hipLaunchKernelGGL(k_resume, dim3(1), dim3(64), 0, s, V.st, o->maxit);
@@ -708,6 +714,7 @@ rpk_status rpk_solve(const rpk_matrix* A, const double* b, double* x, const rpk_
       // chunk after the one that ran the last iteration at the latest
       if (launched > (long long)o->maxit + 8) { st = RPK_ERR_HIP; break; }
       if (timing) {
+        auto absent = [&](int ph) { return (loop == LOOP3 && ph == 0) || (loop != LOOP5 && ph == 2); };
         for (int ph = 0; ph < nph && st == RPK_OK; ++ph) {
           if (hipEventRecord(ev[ph], s) != hipSuccess) st = RPK_ERR_HIP;
           if (st == RPK_OK) st = by_dot<PhaseF>(N, variant, ph, G, B, s, Ac, V, red);
@@ -718,6 +725,7 @@ rpk_status rpk_solve(const rpk_matrix* A, const double* b, double* x, const rpk_
           break;
         }
         for (int ph = 0; ph < nph; ++ph) {
+          if (absent(ph)) continue;
           float ms = 0.f;
           hipEventElapsedTime(&ms, ev[ph], ev[ph + 1]);
           info->phase_ms[ph] += ms;
@@ -770,6 +778,10 @@ rpk_status rpk_solve(const rpk_matrix* A, const double* b, double* x, const rpk_
       }
     }
     if (st != RPK_OK) break;
+    if (loop == LOOP3 && g_pinned->status == RPK_NOT_CONVERGED) {  // a checkpoint keeps p and s in place
+      hipLaunchKernelGGL(k_std_pair, dim3(256), dim3(256), 0, s, A->n, V, false);
+      if (hipGetLastError() != hipSuccess) { st = RPK_ERR_HIP; break; }
+    }
     // reduction slots that a stop left published but not cleared (the kernels
     // that clear them did not run), so that the residual and a resumed solve
     // start from zeroed accumulators

@@ -410,6 +410,35 @@ __global__ void k_state_setup(State* st, double tol, int maxit, int variant) {
   }
 }
 
+// Between a checkpoint, where p and s are in place and p = r0 before the first
+// iteration, as in the other loops, and the buffers of the three-kernel loop:
+// enter before k_resume, leave at the iteration limit
+__global__ void k_std_pair(int n, Vecs V, bool enter) {
+  State* st = V.st;
+  const int it = st->iter;
+  const bool odd = (it & 1) != 0;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    if (enter) {
+      if (odd) {
+        V.ph[i] = V.p[i];
+        V.qh[i] = V.s[i];
+      } else if (it == 0) {
+        V.p[i] = 0.0;
+        V.s[i] = 0.0;
+      }
+    } else if (odd) {
+      V.p[i] = V.ph[i];
+      V.s[i] = V.qh[i];
+    } else if (it == 0) {
+      V.p[i] = V.r[i];
+    }
+  }
+  if (enter && blockIdx.x == 0 && threadIdx.x == 0) {
+    st->iter_n = it;
+    st->stg = st->rho;
+  }
+}
+
 // Resume a solve stopped at its iteration limit (device state from the same
 // workspace): continue up to `maxit` iterations in total.  A solve that stopped
 // for any other reason keeps its status; one whose next step breaks down now

@@ -20,6 +20,14 @@
 //   E: [omega] S8 + S9, <r0,r>, <r,r> of S10/S11  -> published
 // ([..]: the deferred scalar step, taken at the kernel's start; with
 // lightweight dots the last workgroup of B, D, E takes alpha, omega, beta.)
+// With a uniform Jacobi vector and a row dictionary (single solves, exact or plain
+// dots: Vecs::loop) the matrix costs no traffic, and C and, in small solves, A are
+// formed at the gathers of D and B as well, whose extra operands come from L1 and
+// L2: four kernels, A, B, D3, E, or three, B3, D3, E:
+//   B3: [tau, stop test, beta] S12 + S1 at the gathers, S2 + <r0,s>
+//   D3: [alpha] S4 + S5 at the gathers, S6 + <q,y>, <y,y>
+// B3 reads p and s of its rows' neighbours while it writes its own, so they
+// alternate between two buffers.
 // PCG, three kernels per iteration: S10 [beta, tau, stop test, alpha of the
 // iteration before], S1 SpMV + <p,d>, S3 [rho] + S4, S5 + <y,r>, <r,r>.
 // Pipelined loop, four kernels per iteration.  Each reduction of Fig. 3 is
@@ -46,6 +54,10 @@ namespace rpk {
 
 __device__ __forceinline__ double qnan() { return __longlong_as_double(0x7ff8000000000000ll); }
 
+// Kernels of a standard iteration: A, B, C, D, E; A, B, D3, E; B3, D3, E.  In the
+// last p alternates between p and ph, s between s and qh.
+enum : int { LOOP5 = 0, LOOP4 = 1, LOOP3 = 2 };
+
 struct Vecs {
   // standard: r0 r p ph s q qh y ; pipelined: r0 r ph s q qh y rh w wh t sh z zh v
   double *r0, *r, *p, *ph, *s, *q, *qh, *y;
@@ -55,6 +67,7 @@ struct Vecs {
   State* st;
   double* hist;  // [maxit][HIST_W] or null
   double* xr;    // [maxit][2][n] or null
+  int loop;      // standard loop: LOOP5, LOOP4 or LOOP3, set by the host
   int far;       // vectors that do not fit are streamed (ld_v): set by the host, which
                  // then launches the Far / Mid instantiations of the standard /
                  // pipelined kernels
@@ -105,7 +118,7 @@ __device__ __forceinline__ void step_entry(State* st, double rho) {
     stop(st, ST_NONFINITE);
     return;
   }
-  st->rho = rho;
+  st->rho = st->stg = rho;
   st->tau0 = sqrt(rho);
   st->tau = st->tau0;
   if (st->tau0 == 0.0) stop(st, ST_OK);
@@ -377,7 +390,9 @@ constexpr bool defer_std() {
 // thread, whether the step stopped the solve, with the step's scalar in `out`.
 // The state may change under the kernel only in fields the step does not read,
 // or in done, which the step would set the same way.
-template <int N, int K>
+// Staged (D3 and E of the three-kernel loop): the iteration and rho are those that
+// B3 left in iter_n and stg; E moves them to iter and rho, which D3 and E do not read.
+template <int N, int K, bool Staged = false>
 struct Deferred {
   Published<N, K> pub;
   State S;
@@ -386,6 +401,10 @@ struct Deferred {
     if constexpr (N > 0) pub.issue(s, red, slot0);
     if (threadIdx.x == 0) {
       state_load(S, st);
+      if constexpr (Staged) {
+        S.iter = st->iter_n;
+        S.rho = st->stg;
+      }
       pend = st->pend;
     }
   }
@@ -466,7 +485,8 @@ __device__ __forceinline__ void std_init_body(const Csr& A, const Vecs& V, const
       const double ri = b - t;
       V.r[i] = ri;
       V.r0[i] = ri;
-      V.p[i] = ri;
+      V.p[i] = V.loop == LOOP3 ? 0.0 : ri;
+      if (V.loop == LOOP3) V.s[i] = 0.0;
       d[0].add(ri, ri, s.sa, &s.flag[0]);
     }
   });
@@ -1066,26 +1086,124 @@ __global__ void __launch_bounds__(1024) k_std_D(Csr A, Vecs V, Red red) {
   std_D_body<N, Unif, defer_std<N>()>(A, V, red, my_rows(A.n), blockIdx.x, s);
 }
 
-template <int N, bool Far, bool Unif>
+// The three-kernel loop.  Buffers of p and s by iteration: it reads number it & 1
+// and writes the other, `it` iterations being complete.
+__device__ __forceinline__ double* buf_p(const Vecs& V, int k) { return (k & 1) ? V.ph : V.p; }
+__device__ __forceinline__ double* buf_s(const Vecs& V, int k) { return (k & 1) ? V.qh : V.s; }
+
+// B3: S10, S11, the stop test and beta on the dots E published; S12 + S1 + S2 and
+// <r0,s>.  In the first iteration p = r0: with p = s = +0 from the set-up,
+// omega = +0 and beta = -1, fma(-1, fma(-0, 0, 0), r) is r, its sign included.
+template <int N>
+__global__ void __launch_bounds__(1024) k_std_B3(Csr A, Vecs V, Red red) {
+  extern __shared__ __align__(16) char smem[];
+  Shm<N> s = shm_carve<N>(smem, 2, true);
+  Deferred<N, 2> q;
+  q.issue(s, red, SLOT_RHO, V.st);
+  pat_load(A, s);
+  if (blockIdx.x == 0) block_clear_slots<N, 2>(red, SLOT_THETA);
+  const int fl = q.flags(s, red, SLOT_RHO);
+  if (fl & 1) return;
+  int it = V.st->iter;
+  double beta = V.st->beta, omega = V.st->omega;
+  if (fl & 2) {
+    if (q.template step<FIN_BETA>(s, V, red, SLOT_RHO, beta)) return;
+    ++it;
+  } else {
+    if (it == 0) {
+      beta = -1.0;
+      omega = 0.0;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      V.st->stg = V.st->rho;
+      V.st->iter_n = it;
+    }
+  }
+  shm_init(s, 1);
+  const GatherP g{A.du, beta, omega, buf_p(V, it), buf_s(V, it), V.r};
+  double *pn = buf_p(V, it + 1), *sn = buf_s(V, it + 1);
+  struct Own {
+    double p, r0;
+  };
+  Dot<N> d[1];
+  d[0].zero();
+  for_rows<N>(A, g, my_rows(A.n), s,
+              [&](int i) { return Own{g.own(g.load8((unsigned)i * 8u)), V.r0[i]}; },
+              [&](int i, bool ok, double si, Own o) {
+                if (ok) {
+                  pn[i] = o.p;
+                  sn[i] = si;
+                  d[0].add(o.r0, si, s.sa, &s.flag[0]);
+                }
+              });
+  (void)block_publish<N, 1>(d, s, red, SLOT_SIGMA, blockIdx.x);
+}
+
+// D3: S3 on the dot B or B3 published; S4 + S5 + S6 and <q,y>, <y,y>
+template <int N, int Loop>
+__global__ void __launch_bounds__(1024) k_std_D3(Csr A, Vecs V, Red red) {
+  extern __shared__ __align__(16) char smem[];
+  Shm<N> s = shm_carve<N>(smem, 2, true);
+  Deferred<N, 1, Loop == LOOP3> a;
+  a.issue(s, red, SLOT_SIGMA, V.st);
+  pat_load(A, s);
+  if constexpr (Loop == LOOP3) {
+    if (blockIdx.x == 0) {  // B3 has taken E's dots
+      block_clear_slots<N, 2>(red, SLOT_RHO);
+      if (threadIdx.x == 0) V.st->pend = 0;
+    }
+  }
+  if (a.flags(s, red, SLOT_SIGMA) & 1) return;
+  double alpha;
+  if (a.template step<FIN_ALPHA>(s, V, red, SLOT_SIGMA, alpha)) return;  // S3
+  shm_init(s, 2);
+  const GatherQ g{A.du, alpha, Loop == LOOP3 ? buf_s(V, V.st->iter_n + 1) : V.s, V.r};
+  Dot<N> d[2];
+  d[0].zero();
+  d[1].zero();
+  for_rows<N>(A, g, my_rows(A.n), s,
+              [&](int i) { return g.own(g.load8((unsigned)i * 8u)); },
+              [&](int i, bool ok, double yi, double q) {
+                if (ok) {
+                  V.q[i] = q;
+                  V.y[i] = yi;
+                  d[0].add(q, yi, s.sa, &s.flag[0]);
+                  d[1].add(yi, yi, s.sa + SA_D, &s.flag[1]);
+                }
+              });
+  (void)block_publish<N, 2>(d, s, red, SLOT_THETA, blockIdx.x);
+}
+
+template <int N, bool Far, bool Unif, int Loop = LOOP5>
 __global__ void __launch_bounds__(1024) k_std_E(Csr A, Vecs V, Red red) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 2, false);
   if constexpr (defer_std<N>()) {
     const Range R = my_rows(A.n);
-    Deferred<N, 2> q;
+    Deferred<N, 2, Loop == LOOP3> q;
     q.issue(s, red, SLOT_THETA, V.st);
+    const int iter = Loop == LOOP3 ? V.st->iter_n : V.st->iter;
+    if constexpr (Loop == LOOP3) V.p = buf_p(V, iter + 1);
     RowsE<N, Far, Unif> pf[PF_E];
 #pragma unroll
     for (int k = 0; k < PF_E; ++k) {
       const int i = R.lo + threadIdx.x + 2 * k * blockDim.x;
       if (i < R.hi) pf[k].load(V, i, R.hi);
     }
+    if constexpr (Loop != LOOP5) {
+      if (blockIdx.x == 0) {  // D3 has taken the dot of B or B3: clear it
+        block_clear_slots<N, 1>(red, SLOT_SIGMA);
+        if (Loop == LOOP3 && threadIdx.x == 0) {
+          V.st->iter = iter;
+          V.st->rho = V.st->stg;
+        }
+      }
+    }
     if (q.flags(s, red, SLOT_THETA) & 1) return;
     double omega;
     if (q.template step<FIN_OMEGA>(s, V, red, SLOT_THETA, omega)) return;  // S7
     shm_init(s, 2);
     const double alpha = V.st->alpha;
-    const int iter = V.st->iter;
     Dot<N> d[2];
     d[0].zero();
     d[1].zero();
