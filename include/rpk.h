@@ -323,7 +323,8 @@ rpk_status rpk_server_get_stats(const rpk_server* s, rpk_server_stats* out);
 rpk_status rpk_server_destroy(rpk_server* s);
 
 /* Test hook (host only, no device work): the tile table rpk_solve_batched
- * builds for systems of n[0..nsys-1] rows and `tile` rows per tile.  tiles
+ * builds for systems of n[0..nsys-1] rows and `tile` rows per tile, every system
+ * on one XCD (the solver cuts systems over several where this leaves XCDs idle).  tiles
  * receives 4 int32 per tile (system, first row, end row, index of the tile in
  * its system; system -1 for padding); tile t runs on XCD t % 8.  *ntiles is the
  * table length; RPK_ERR_ARG if it exceeds cap. */

@@ -41,7 +41,13 @@ namespace rpkhost {
 // fewest tiles so far) so that a system's SpMV gathers stay in one L2, and
 // interleave the 8 lists so that tile t lands on XCD t % 8 (workgroups are
 // dispatched to XCDs round-robin).  Short lists are padded with empty tiles.
-Plan make_plan(const std::vector<int64_t>& n, int T, const std::vector<int>* ids) {
+// spread: where the longest list is more than a sixteenth longer than the
+// average (a system with more than its share of an XCD), systems that no XCD has
+// room for are cut into contiguous ranges over several, each filled up to the
+// average.  16 systems of 5,832 to 1,685,159 rows, tiles of 4,096: 148 tiles an
+// XCD instead of 412 on one; P1, P2, P3, P4 117, 66, 90, 66 us instead of
+// 202, 146, 162, 145.
+Plan make_plan(const std::vector<int64_t>& n, int T, const std::vector<int>* ids, bool spread) {
   const int ns = (int)n.size();
   Plan p;
   p.G.resize(ns);
@@ -54,21 +60,37 @@ Plan make_plan(const std::vector<int64_t>& n, int T, const std::vector<int>* ids
   std::vector<int> idx(ns);
   std::iota(idx.begin(), idx.end(), 0);
   std::stable_sort(idx.begin(), idx.end(), [&](int a, int b) { return p.G[a] > p.G[b]; });
+  struct Run {  // tiles j0 .. j1 - 1 of system k
+    int k, j0, j1;
+  };
   std::vector<int64_t> load(8, 0);
-  std::vector<std::vector<int>> bins(8);
-  for (int k : idx) {
-    const int bin = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-    load[bin] += p.G[k];
-    bins[bin].push_back(k);
+  std::vector<std::vector<Run>> bins(8);
+  const auto least = [&] { return (int)(std::min_element(load.begin(), load.end()) - load.begin()); };
+  const auto put = [&](int k, int j0, int j1) {
+    const int bin = least();
+    load[bin] += j1 - j0;
+    bins[bin].push_back(Run{k, j0, j1});
+  };
+  for (int k : idx) put(k, 0, p.G[k]);
+  const int64_t share = cdiv(std::accumulate(load.begin(), load.end(), (int64_t)0), 8);
+  if (spread && 16 * *std::max_element(load.begin(), load.end()) > 17 * share) {
+    load.assign(8, 0);
+    bins.assign(8, {});
+    for (int k : idx)
+      for (int j = 0; j < p.G[k];) {  // share * 8 tiles have room for all
+        const int end = (int)std::min<int64_t>(p.G[k], j + share - load[least()]);
+        put(k, j, end);
+        j = end;
+      }
   }
   const int64_t rows = *std::max_element(load.begin(), load.end());
   p.tiles.assign((size_t)(8 * rows), Tile{-1, 0, 0, 0});
   for (int bin = 0; bin < 8; ++bin) {
     int64_t pos = 0;
-    for (int k : bins[bin])
-      for (int j = 0; j < p.G[k]; ++j, ++pos) {
-        const int64_t lo = j * chunk[k], hi = std::min<int64_t>(n[k], lo + chunk[k]);
-        p.tiles[(size_t)(8 * pos + bin)] = Tile{ids ? (*ids)[k] : k, (int)lo, (int)hi, j};
+    for (const Run& r : bins[bin])
+      for (int j = r.j0; j < r.j1; ++j, ++pos) {
+        const int64_t lo = j * chunk[r.k], hi = std::min<int64_t>(n[r.k], lo + chunk[r.k]);
+        p.tiles[(size_t)(8 * pos + bin)] = Tile{ids ? (*ids)[r.k] : r.k, (int)lo, (int)hi, j};
       }
   }
   return p;
@@ -542,7 +564,7 @@ rpk_status rpk_plan_tiles(int32_t nsys, const int64_t* n, int32_t tile, int32_t*
   std::vector<int64_t> nv(n, n + nsys);
   for (int64_t v : nv)
     if (v < 1 || v >= (1ll << 31)) return RPK_ERR_ARG;
-  const Plan p = make_plan(nv, tile);
+  const Plan p = make_plan(nv, tile, nullptr, false);
   *ntiles = (int64_t)p.tiles.size();
   if ((int64_t)p.tiles.size() > cap) return RPK_ERR_ARG;
   for (size_t t = 0; t < p.tiles.size(); ++t) {

@@ -181,7 +181,8 @@ struct Plan {
 
 // Tiles of at most T rows for the listed systems (sizes n); Tile.sys is ids[k]
 // (or k when ids is null) and Tile.rec the tile's index inside its system.
-Plan make_plan(const std::vector<int64_t>& n, int T, const std::vector<int>* ids = nullptr);
+// spread: a system may be cut over several XCDs where whole ones leave XCDs idle.
+Plan make_plan(const std::vector<int64_t>& n, int T, const std::vector<int>* ids = nullptr, bool spread = true);
 // upper bound of make_plan(n, T).tiles.size() for every T >= Tcap
 int64_t tile_capacity(const std::vector<int64_t>& n, int Tcap);
 

@@ -470,7 +470,8 @@ class Server:
 
 
 def plan_tiles(sizes, tile):
-    """Host-only: the batched solver's tile table for systems of these sizes, as an
+    """Host-only: the batched solver's tile table for systems of these sizes, every
+    system on one XCD (large ones are cut over several when a batch runs), as an
     int32 array of rows (system, first row, end row, tile index in its system)."""
     n = np.ascontiguousarray(sizes, dtype=np.int64)
     cap = 8 * (int(np.sum(-(-n // tile))) // 8 + int(np.max(-(-n // tile))) + 2)
