@@ -38,7 +38,8 @@ struct Batch {
   int nt;            // number of tiles (host copy of count[0]: the launchers cover them)
   int t0;            // first tile of a launch (set by the launchers)
   int far;           // the batch's vectors do not fit in the Infinity Cache: the host
-                     // launches the Far / Mid instantiations (streamed vectors)
+                     // launches the Far / Str = 2 instantiations (streamed vectors)
+  int near;          // pipelined: all of them fit (Str = 0)
   int unif;          // every system's Jacobi vector is uniform (Csr::unif): the host
                      // launches the Unif instantiations of the standard loop
 };
@@ -216,21 +217,21 @@ __global__ void __launch_bounds__(1024) kb_pipe_init2(Batch B) {
   });
 }
 
-template <int N, bool Mid, bool Unif>
+template <int N, int Str, bool Unif>
 __global__ void __launch_bounds__(1024) kb_pipe_P1(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 4, false);
   on_tile_publish<N, 4>(B, s, [&](const SysDesc& D, Range R, int rec) {
-    pipe_P1_body<N, true, Mid, Unif>(D.A, D.V, D.red, R, rec, s);
+    pipe_P1_body<N, true, Str, Unif>(D.A, D.V, D.red, R, rec, s);
   });
 }
 
-template <int N, bool Mid, bool Unif>
+template <int N, int Str, bool Unif>
 __global__ void __launch_bounds__(1024) kb_pipe_P3(Batch B) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 3, false);
   on_tile_publish<N, 3>(B, s, [&](const SysDesc& D, Range R, int rec) {
-    pipe_P3_body<N, true, Mid, Unif>(D.A, D.V, D.red, R, rec, s);
+    pipe_P3_body<N, true, Str, Unif>(D.A, D.V, D.red, R, rec, s);
   });
 }
 

@@ -247,6 +247,7 @@ Batch batch_of(const Ctx& c, const Plan& plan) {
     unif = unif && c.A[k]->unif != 0;
   }
   B.far = rows_stream_far(rows, c.o->variant, unif) ? 1 : 0;
+  B.near = rows_stay_near(rows, c.o->variant, unif) ? 1 : 0;
   B.unif = unif ? 1 : 0;
   return B;
 }
@@ -488,8 +489,8 @@ rpk_status run(const Ctx& c, const BCfg& cfg, rpk_info* infos) {
         const std::vector<uint64_t> key{0, (uint64_t)(uintptr_t)c.ws, (uint64_t)c.L.count, (uint64_t)c.L.descs,
                                         (uint64_t)c.L.order, (uint64_t)c.L.tiles, (uint64_t)c.o->variant,
                                         (uint64_t)sh.N, (uint64_t)sh.G, (uint64_t)sh.Gf, (uint64_t)sh.B,
-                                        (uint64_t)chunk, (uint64_t)bt.nt, (uint64_t)bt.far, (uint64_t)bt.unif,
-                                        0xba7c4ull};
+                                        (uint64_t)chunk, (uint64_t)bt.nt, (uint64_t)bt.far, (uint64_t)bt.near,
+                                        (uint64_t)bt.unif, 0xba7c4ull};
         hipGraphExec_t exec = nullptr;
         st = graph_get(key, [&](hipStream_t cs) {
           rpk_status cst = RPK_OK;

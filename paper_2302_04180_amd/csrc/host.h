@@ -133,13 +133,13 @@ inline int std_loop(const rpk_matrix* A, int variant, int dots) {
   return A->nnz <= 8000000 + 9 * (int64_t)A->n ? LOOP4 : LOOP5;
 }
 // Vectors the pipelined loop keeps cached when they fit: p^, q, q^, y, r, r^, w,
-// t, v and z^, w^ (its other six, s, s^, z, x, r0 and dinv, are always
-// streamed); with a uniform Jacobi vector z^ and w^ are never stored and z
+// t, v and z^, w^ (its other six, s, s^, z, x, r0 and dinv, are streamed unless
+// all fit); with a uniform Jacobi vector z^ and w^ are never stored and z
 // (gathered by P2) is kept instead: ten.
 inline int pipe_kept(bool unif) { return unif ? 10 : 11; }
 
-// Whether a solve streams vectors past the Infinity Cache beyond what it always
-// does (Vecs::far): the standard loop when the vectors it touches do not fit in
+// Whether a solve streams vectors past the Infinity Cache, in the pipelined loop
+// beyond the six (Vecs::far): the standard loop when the vectors it touches do not fit in
 // nine tenths of the cache, the pipelined loop when the eleven it otherwise
 // keeps do not.  A batch of systems decides the same way on its total number of
 // rows (unif: every system's Jacobi vector is uniform).
@@ -148,12 +148,21 @@ inline bool rows_stream_far(int64_t rows, int variant, bool unif) {
   return kept > 0 && (double)kept * (double)rows * 8.0 > 0.9 * kInfinityCacheBytes;
 }
 inline bool streams_far(const rpk_matrix* A, int variant) { return rows_stream_far(A->n, variant, A->unif != 0); }
+// Whether the pipelined loop streams nothing (Vecs::near): all the vectors it
+// touches, seventeen, or fourteen with a uniform Jacobi vector, fit in nine tenths
+// of the cache.  P1 and P3 without and with the six always-streamed ones kept, us:
+// 96^3 28.3 + 21.4 and 25.2 + 20.5, 128^3 (88% of the cache) 53.0 + 40.6 and 49.4 +
+// 39.5, 112^3 with a varying diagonal 43.1 + 33.2 and 41.6 + 32.0.
+inline int pipe_vectors(bool unif) { return unif ? 14 : 17; }
+inline bool rows_stay_near(int64_t rows, int variant, bool unif) {
+  return variant == RPK_PIPELINED && (double)pipe_vectors(unif) * (double)rows * 8.0 <= 0.9 * kInfinityCacheBytes;
+}
 
 // Vectors of one iteration that stay in the Infinity Cache (those it touches,
 // less those streamed past it: x, p, r0 and dinv in the standard loop, x and r0
 // with a uniform Jacobi vector)
-inline int cached_vectors(int variant, bool far, bool unif) {
-  if (variant == RPK_PIPELINED) return far ? 4 : pipe_kept(unif);
+inline int cached_vectors(int variant, bool near, bool far, bool unif) {
+  if (variant == RPK_PIPELINED) return near ? pipe_vectors(unif) : far ? 4 : pipe_kept(unif);
   if (variant == RPK_STD) return std_vectors(unif) - (far ? (unif ? 2 : 4) : 0);
   return unif ? nvec_of(variant) : nvec_of(variant) + 2;  // PCG: r, p, d, y, x, dinv (r, p, d, x)
 }

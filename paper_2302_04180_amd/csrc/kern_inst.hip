@@ -122,23 +122,27 @@ rpk_status Kern<N>::phase(int variant, int ph, int G, int B, hipStream_t s, Csr 
   if (A.unif) {
     switch (ph) {
       case 0:
-        return V.far ? launch(k_pipe_P1<N, true, true>, G, B, s4, s, A, V, red)
-                     : launch(k_pipe_P1<N, false, true>, G, B, s4, s, A, V, red);
+        return V.near ? launch(k_pipe_P1<N, 0, true>, G, B, s4, s, A, V, red)
+               : V.far ? launch(k_pipe_P1<N, 2, true>, G, B, s4, s, A, V, red)
+                       : launch(k_pipe_P1<N, 1, true>, G, B, s4, s, A, V, red);
       case 1: return launch(k_pipe_spmv_fin<N, 1, 4, FIN_POMEGA, true>, Gs, B, s4t, s, A, V, red);
       case 2:
-        return V.far ? launch(k_pipe_P3<N, true, true>, G, B, s3, s, A, V, red)
-                     : launch(k_pipe_P3<N, false, true>, G, B, s3, s, A, V, red);
+        return V.near ? launch(k_pipe_P3<N, 0, true>, G, B, s3, s, A, V, red)
+               : V.far ? launch(k_pipe_P3<N, 2, true>, G, B, s3, s, A, V, red)
+                       : launch(k_pipe_P3<N, 1, true>, G, B, s3, s, A, V, red);
       default: return launch(k_pipe_spmv_fin<N, 0, 3, FIN_S19, true>, Gs, B, s3t, s, A, V, red);
     }
   }
   switch (ph) {
     case 0:
-      return V.far ? launch(k_pipe_P1<N, true, false>, G, B, s4, s, A, V, red)
-                   : launch(k_pipe_P1<N, false, false>, G, B, s4, s, A, V, red);
+      return V.near ? launch(k_pipe_P1<N, 0, false>, G, B, s4, s, A, V, red)
+               : V.far ? launch(k_pipe_P1<N, 2, false>, G, B, s4, s, A, V, red)
+                       : launch(k_pipe_P1<N, 1, false>, G, B, s4, s, A, V, red);
     case 1: return launch(k_pipe_spmv_fin<N, 1, 4, FIN_POMEGA, false>, Gs, B, s4t, s, A, V, red);
     case 2:
-      return V.far ? launch(k_pipe_P3<N, true, false>, G, B, s3, s, A, V, red)
-                   : launch(k_pipe_P3<N, false, false>, G, B, s3, s, A, V, red);
+      return V.near ? launch(k_pipe_P3<N, 0, false>, G, B, s3, s, A, V, red)
+               : V.far ? launch(k_pipe_P3<N, 2, false>, G, B, s3, s, A, V, red)
+                       : launch(k_pipe_P3<N, 1, false>, G, B, s3, s, A, V, red);
     default: return launch(k_pipe_spmv_fin<N, 0, 3, FIN_S19, false>, Gs, B, s3t, s, A, V, red);
   }
 }
@@ -230,23 +234,27 @@ rpk_status KernB<N>::phase(int variant, int ph, int G, int Gf, int B, hipStream_
   if (b.unif) {
     switch (ph) {
       case 0:
-        return b.far ? launch_tiles(kb_pipe_P1<N, true, true>, G, B, s4, s, b)
-                     : launch_tiles(kb_pipe_P1<N, false, true>, G, B, s4, s, b);
+        return b.near ? launch_tiles(kb_pipe_P1<N, 0, true>, G, B, s4, s, b)
+               : b.far ? launch_tiles(kb_pipe_P1<N, 2, true>, G, B, s4, s, b)
+                       : launch_tiles(kb_pipe_P1<N, 1, true>, G, B, s4, s, b);
       case 1: return launch_tiles(kb_pipe_spmv_fin<N, 1, 4, FIN_POMEGA, true>, G, B, s4t, s, b);
       case 2:
-        return b.far ? launch_tiles(kb_pipe_P3<N, true, true>, G, B, s3, s, b)
-                     : launch_tiles(kb_pipe_P3<N, false, true>, G, B, s3, s, b);
+        return b.near ? launch_tiles(kb_pipe_P3<N, 0, true>, G, B, s3, s, b)
+               : b.far ? launch_tiles(kb_pipe_P3<N, 2, true>, G, B, s3, s, b)
+                       : launch_tiles(kb_pipe_P3<N, 1, true>, G, B, s3, s, b);
       default: return launch_tiles(kb_pipe_spmv_fin<N, 0, 3, FIN_S19, true>, G, B, s3t, s, b);
     }
   }
   switch (ph) {
     case 0:
-      return b.far ? launch_tiles(kb_pipe_P1<N, true, false>, G, B, s4, s, b)
-                   : launch_tiles(kb_pipe_P1<N, false, false>, G, B, s4, s, b);
+      return b.near ? launch_tiles(kb_pipe_P1<N, 0, false>, G, B, s4, s, b)
+             : b.far ? launch_tiles(kb_pipe_P1<N, 2, false>, G, B, s4, s, b)
+                     : launch_tiles(kb_pipe_P1<N, 1, false>, G, B, s4, s, b);
     case 1: return launch_tiles(kb_pipe_spmv_fin<N, 1, 4, FIN_POMEGA, false>, G, B, s4t, s, b);
     case 2:
-      return b.far ? launch_tiles(kb_pipe_P3<N, true, false>, G, B, s3, s, b)
-                   : launch_tiles(kb_pipe_P3<N, false, false>, G, B, s3, s, b);
+      return b.near ? launch_tiles(kb_pipe_P3<N, 0, false>, G, B, s3, s, b)
+             : b.far ? launch_tiles(kb_pipe_P3<N, 2, false>, G, B, s3, s, b)
+                     : launch_tiles(kb_pipe_P3<N, 1, false>, G, B, s3, s, b);
     default: return launch_tiles(kb_pipe_spmv_fin<N, 0, 3, FIN_S19, false>, G, B, s3t, s, b);
   }
 }

@@ -651,7 +651,8 @@ rpk_status rpk_solve(const rpk_matrix* A, const double* b, double* x, const rpk_
   Csr Ac = csr_of(A);
   V.loop = loop;
   V.far = info->streamed;
-  Ac.keep = keep_slices(A, cached_vectors(variant, V.far != 0, A->unif != 0));
+  V.near = rows_stay_near(A->n, variant, A->unif != 0) ? 1 : 0;
+  Ac.keep = keep_slices(A, cached_vectors(variant, V.near != 0, V.far != 0, A->unif != 0));
 
   const bool resume = o->resume != 0;
   // reduction scratch to zero; caller-visible histories to zero (not when resuming)

@@ -121,6 +121,7 @@ struct rpk_server {
   std::vector<Req*> slots;
   std::vector<int> free_slots;
   int view_far[NVIEW] = {};   // per view: its systems' vectors do not fit in the Infinity Cache
+  int view_near[NVIEW] = {};  // per view: its systems' vectors all fit
   int view_unif[NVIEW] = {};  // per view: every system's Jacobi vector is uniform
 
   mutable std::mutex mu;
@@ -166,17 +167,19 @@ Batch view(const rpk_server* S, int v) {
   B.order = (const int*)(S->hdr + S->off_order) + (size_t)v * S->o.max_slots;
   B.tiles = (const Tile*)(S->hdr + S->off_tiles) + (size_t)v * S->tile_cap;
   B.far = S->view_far[v];
+  B.near = S->view_near[v];
   B.unif = S->view_unif[v];
   return B;
 }
 
 // Fill view v of the host header image with the systems in `slots_v` (launched
-// with the Unif / Far instantiations when unif / far); returns the number of
+// with the instantiations for unif, far and near); returns the number of
 // tiles (a multiple of 8) through *ntiles.
-rpk_status set_view(rpk_server* S, int v, const std::vector<int>& slots_v, bool unif, bool far, int* ntiles) {
+rpk_status set_view(rpk_server* S, int v, const std::vector<int>& slots_v, bool unif, bool far, bool near, int* ntiles) {
   std::vector<int64_t> n;
   for (int k : slots_v) n.push_back(S->slots[k]->n);
   S->view_far[v] = far ? 1 : 0;
+  S->view_near[v] = near ? 1 : 0;
   S->view_unif[v] = unif ? 1 : 0;
   Plan p;
   if (!slots_v.empty()) p = make_plan(n, S->tile, &slots_v);
@@ -250,10 +253,11 @@ rpk_status round(rpk_server* S, const std::vector<int>& fresh, const std::vector
   }
   // the two views share the Infinity Cache: one decision on all rows in flight
   const bool far = rows_stream_far(rows, variant, run_v[1].empty());
+  const bool near = rows_stay_near(rows, variant, run_v[1].empty());
   int nt_new[2] = {0, 0}, nt_run[2] = {0, 0};
   for (int u = 0; u < 2; ++u) {
-    RET_IF(set_view(S, V_NEW_U + u, fresh_v[u], u == 0, far, &nt_new[u]));
-    RET_IF(set_view(S, V_RUN_U + u, run_v[u], u == 0, far, &nt_run[u]));
+    RET_IF(set_view(S, V_NEW_U + u, fresh_v[u], u == 0, far, near, &nt_new[u]));
+    RET_IF(set_view(S, V_RUN_U + u, run_v[u], u == 0, far, near, &nt_run[u]));
   }
   if (far)
     for (int k : running) S->slots[k]->streamed = true;
@@ -280,7 +284,7 @@ rpk_status round(rpk_server* S, const std::vector<int>& fresh, const std::vector
   if (stopped->empty()) return RPK_OK;
   // exact true residual of the stopped systems
   int nt_fin = 0;
-  RET_IF(set_view(S, V_FIN, *stopped, false, false, &nt_fin));
+  RET_IF(set_view(S, V_FIN, *stopped, false, false, false, &nt_fin));
   RET_IF(upload(S));
   RET_IF(KernB<4>::resid(g_of(nt_fin), gf_of(stopped->size()), S->block, S->stream, view(S, V_FIN)));
   HIPCHK(hipMemcpyAsync(S->h_states, S->d_states, (size_t)S->o.max_slots * sizeof(State),

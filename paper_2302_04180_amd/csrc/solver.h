@@ -69,8 +69,9 @@ struct Vecs {
   double* xr;    // [maxit][2][n] or null
   int loop;      // standard loop: LOOP5, LOOP4 or LOOP3, set by the host
   int far;       // vectors that do not fit are streamed (ld_v): set by the host, which
-                 // then launches the Far / Mid instantiations of the standard /
+                 // then launches the Far / Str = 2 instantiations of the standard /
                  // pipelined kernels
+  int near;      // pipelined: every vector fits, none is streamed (set by the host)
 };
 
 __device__ __forceinline__ double* hist_row(const Vecs& V, int iter) {
@@ -498,9 +499,9 @@ __device__ __forceinline__ void std_init_body(const Csr& A, const Vecs& V, const
 // vectors do not all fit in the Infinity Cache: the cache is then left to the
 // vectors that the next kernel or two read back, and to the part of the matrix
 // that fits beside them (the same values either way).  The pipelined loop
-// always streams s, s^, z, x, r0 and the Jacobi vector (its 18 vectors never
-// fit), and when the other eleven do not fit either (Vecs::far, the Mid
-// instantiations of P1 and P3), also p^, q, q^, y, r, r^ and w, which the
+// streams nothing when its vectors fit (Vecs::near, Str = 0 in P1 and P3); else s,
+// s^, z, x, r0 and the Jacobi vector (Str = 1), and when the other eleven do not
+// fit either (Vecs::far, Str = 2), also p^, q, q^, y, r, r^ and w, which the
 // kernel after next reads back, keeping only z^, v, w^ and t; the standard
 // loop streams x, p, r0 and the Jacobi vector when its ten do not fit
 // (Vecs::far, the Far instantiations of A, C and E).
@@ -514,8 +515,6 @@ __device__ __forceinline__ void st_v(double* p, double v) {
   if constexpr (Far) __builtin_nontemporal_store(v, p);
   else *p = v;
 }
-__device__ __forceinline__ double ld_far(const double* p) { return ld_v<true>(p); }
-__device__ __forceinline__ void st_far(double* p, double v) { st_v<true>(p, v); }
 
 // A: S12 (iterations after the first) and S1 (not stored for a uniform Jacobi
 // vector: B and E form p^ themselves), on the rows i0 and i1 = i0 + blockDim.x:
@@ -781,7 +780,7 @@ __device__ __forceinline__ void spmv_hat_body(const Csr& A, const double* v, con
 // P1: S1..S7, S9, the partials of S8 (slots 0, 1) and of <r0,s>, <r0,z> (slots 2, 3).
 // Unif: w^ = RN(du w) and the old z^ = RN(du z) are formed here (S3), z^ is not
 // stored (P2 gathers z), and z and w stay cached for P2 / P3.
-template <int N, bool Defer, bool Mid, bool Unif>
+template <int N, bool Defer, int Str, bool Unif>
 __device__ __forceinline__ void pipe_P1_body(const Csr& A, const Vecs& V, const Red& red, Range R, int rec,
                                              const Shm<N>& s) {
   const State* st = V.st;
@@ -790,27 +789,27 @@ __device__ __forceinline__ void pipe_P1_body(const Csr& A, const Vecs& V, const 
 #pragma unroll
   for (int j = 0; j < 4; ++j) d[j].zero();
   for (int i = R.lo + threadIdx.x; i < R.hi; i += blockDim.x) {
-    const double rh = ld_v<Mid>(&V.rh[i]), r0 = ld_far(&V.r0[i]);
-    const double w = Unif ? V.w[i] : ld_v<Mid>(&V.w[i]);
+    const double rh = ld_v<Str >= 2>(&V.rh[i]), r0 = ld_v<Str >= 1>(&V.r0[i]);
+    const double w = Unif ? V.w[i] : ld_v<Str >= 2>(&V.w[i]);
     const double wh = Unif ? du * w : V.wh[i];
-    const double sh_old = ld_far(&V.sh[i]), z_old = Unif ? V.z[i] : ld_far(&V.z[i]);
+    const double sh_old = ld_v<Str >= 1>(&V.sh[i]), z_old = Unif ? V.z[i] : ld_v<Str >= 1>(&V.z[i]);
     const double zh_old = Unif ? du * z_old : V.zh[i];
-    const double ph = fma(beta, fma(-omega, sh_old, ld_v<Mid>(&V.ph[i])), rh);  // S1
-    const double sv = fma(beta, fma(-omega, z_old, ld_far(&V.s[i])), w);  // S2
+    const double ph = fma(beta, fma(-omega, sh_old, ld_v<Str >= 2>(&V.ph[i])), rh);  // S1
+    const double sv = fma(beta, fma(-omega, z_old, ld_v<Str >= 1>(&V.s[i])), w);  // S2
     const double sh = fma(beta, fma(-omega, zh_old, sh_old), wh);       // S3
     const double z = fma(beta, fma(-omega, V.v[i], z_old), V.t[i]);     // S4
-    const double q = fma(-alpha, sv, ld_v<Mid>(&V.r[i]));               // S5
+    const double q = fma(-alpha, sv, ld_v<Str >= 2>(&V.r[i]));               // S5
     const double qh = fma(-alpha, sh, rh);                              // S6
     const double y = fma(-alpha, z, w);                                 // S7
-    st_v<Mid>(&V.ph[i], ph);
-    st_far(&V.s[i], sv);
-    st_far(&V.sh[i], sh);
+    st_v<Str >= 2>(&V.ph[i], ph);
+    st_v<Str >= 1>(&V.s[i], sv);
+    st_v<Str >= 1>(&V.sh[i], sh);
     if constexpr (Unif) V.z[i] = z;
-    else st_far(&V.z[i], z);
-    st_v<Mid>(&V.q[i], q);
-    st_v<Mid>(&V.qh[i], qh);
-    st_v<Mid>(&V.y[i], y);
-    if constexpr (!Unif) V.zh[i] = ld_far(&A.dinv[i]) * z;              // S9
+    else st_v<Str >= 1>(&V.z[i], z);
+    st_v<Str >= 2>(&V.q[i], q);
+    st_v<Str >= 2>(&V.qh[i], qh);
+    st_v<Str >= 2>(&V.y[i], y);
+    if constexpr (!Unif) V.zh[i] = ld_v<Str >= 1>(&A.dinv[i]) * z;              // S9
     d[0].add(q, y, s.sa, &s.flag[0]);                                 // S8
     d[1].add(y, y, s.sa + SA_D, &s.flag[1]);
     d[2].add(r0, sv, s.sa + 2 * SA_D, &s.flag[2]);                    // S16: <r0,s>
@@ -822,7 +821,7 @@ __device__ __forceinline__ void pipe_P1_body(const Csr& A, const Vecs& V, const 
 // P3: S12..S15, S17 and the partials of <r0,r>, <r0,w> (S16) and <r,r> (slots 0..2).
 // Unif: z^ = RN(du z) and the old w^ = RN(du w) are formed here (S14), w^ is not
 // stored (P4 gathers w), and w stays cached for P4.
-template <int N, bool Defer, bool Mid, bool Unif>
+template <int N, bool Defer, int Str, bool Unif>
 __device__ __forceinline__ void pipe_P3_body(const Csr& A, const Vecs& V, const Red& red, Range R, int rec,
                                              const Shm<N>& s) {
   const State* st = V.st;
@@ -832,20 +831,20 @@ __device__ __forceinline__ void pipe_P3_body(const Csr& A, const Vecs& V, const 
 #pragma unroll
   for (int j = 0; j < 3; ++j) d[j].zero();
   for (int i = R.lo + threadIdx.x; i < R.hi; i += blockDim.x) {
-    const double qh = ld_v<Mid>(&V.qh[i]), y = ld_v<Mid>(&V.y[i]), r0 = ld_far(&V.r0[i]);
-    const double x = fma(omega, qh, fma(alpha, ld_v<Mid>(&V.ph[i]), ld_far(&V.x[i])));  // S12
-    const double r = fma(-omega, y, ld_v<Mid>(&V.q[i]));                               // S13
+    const double qh = ld_v<Str >= 2>(&V.qh[i]), y = ld_v<Str >= 2>(&V.y[i]), r0 = ld_v<Str >= 1>(&V.r0[i]);
+    const double x = fma(omega, qh, fma(alpha, ld_v<Str >= 2>(&V.ph[i]), ld_v<Str >= 1>(&V.x[i])));  // S12
+    const double r = fma(-omega, y, ld_v<Str >= 2>(&V.q[i]));                               // S13
     const double zh = Unif ? du * V.z[i] : V.zh[i], wh_old = Unif ? du * V.w[i] : V.wh[i];
     const double rh = fma(-omega, fma(-alpha, zh, wh_old), qh);            // S14
     const double w = fma(-omega, fma(-alpha, V.v[i], V.t[i]), y);          // S15
-    st_far(&V.x[i], x);
-    st_v<Mid>(&V.r[i], r);
-    st_v<Mid>(&V.rh[i], rh);
+    st_v<Str >= 1>(&V.x[i], x);
+    st_v<Str >= 2>(&V.r[i], r);
+    st_v<Str >= 2>(&V.rh[i], rh);
     if constexpr (Unif) {
       V.w[i] = w;
     } else {
-      st_v<Mid>(&V.w[i], w);
-      V.wh[i] = ld_far(&A.dinv[i]) * w;                                    // S17
+      st_v<Str >= 2>(&V.w[i], w);
+      V.wh[i] = ld_v<Str >= 1>(&A.dinv[i]) * w;                                    // S17
     }
     record_xr(V, iter, A.n, i, x, r);
     d[0].add(r0, r, s.sa, &s.flag[0]);                                 // S16
@@ -1269,7 +1268,7 @@ __global__ void __launch_bounds__(1024) k_pipe_spmv(Csr A, Vecs V) {
 
 // P1 and P3 leave their reduction to the SpMV kernel that follows them
 // (k_pipe_spmv_fin), and tell its SpMV workgroups whether they ran.
-template <int N, bool Mid, bool Unif>
+template <int N, int Str, bool Unif>
 __global__ void __launch_bounds__(1024) k_pipe_P1(Csr A, Vecs V, Red red) {
   const int done = V.st->done;
   if (blockIdx.x == 0 && threadIdx.x == 0) V.st->spmv_go = !done;
@@ -1277,10 +1276,10 @@ __global__ void __launch_bounds__(1024) k_pipe_P1(Csr A, Vecs V, Red red) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 4, false);
   shm_init(s, 4);
-  pipe_P1_body<N, true, Mid, Unif>(A, V, red, my_rows(A.n), blockIdx.x, s);
+  pipe_P1_body<N, true, Str, Unif>(A, V, red, my_rows(A.n), blockIdx.x, s);
 }
 
-template <int N, bool Mid, bool Unif>
+template <int N, int Str, bool Unif>
 __global__ void __launch_bounds__(1024) k_pipe_P3(Csr A, Vecs V, Red red) {
   const int done = V.st->done;
   if (blockIdx.x == 0 && threadIdx.x == 0) V.st->spmv_go = !done;
@@ -1288,7 +1287,7 @@ __global__ void __launch_bounds__(1024) k_pipe_P3(Csr A, Vecs V, Red red) {
   extern __shared__ __align__(16) char smem[];
   Shm<N> s = shm_carve<N>(smem, 3, false);
   shm_init(s, 3);
-  pipe_P3_body<N, true, Mid, Unif>(A, V, red, my_rows(A.n), blockIdx.x, s);
+  pipe_P3_body<N, true, Str, Unif>(A, V, red, my_rows(A.n), blockIdx.x, s);
 }
 
 // P2 (W = 1: v = A z^, after P1, finishing S11) and P4 (W = 0: t = A w^, after
