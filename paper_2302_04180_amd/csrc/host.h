@@ -22,6 +22,8 @@ struct rpk_matrix {
   int* scol = nullptr;
   double* sval = nullptr;
   long long sell_entries = 0;      // entries of the SELL copy, padding included
+  unsigned short* sdif = nullptr;  // distances for the operand window (see Csr), absent where none pays
+  int wlo = 0, whi = 0;
   char* dict = nullptr;            // row dictionary (see Csr), one allocation; sptr, scol and sval are then absent
   unsigned char* pid = nullptr;
   unsigned char* swid = nullptr;
@@ -90,7 +92,24 @@ inline bool records_fit(int64_t records, int64_t lanes, int fpe) {
 
 inline Csr csr_of(const rpk_matrix* A) {
   return Csr{A->sptr, A->scol, A->sval, A->dinv, (int)A->n, A->cert, A->xlo, A->xhi, A->xlsb, 0, A->unif, A->du,
-             A->pid, A->swid, A->pat, A->np, A->pw};
+             A->pid, A->swid, A->pat, A->np, A->pw, A->sdif, A->wlo, A->whi, 0};
+}
+
+// Operand window (Csr::win) for G workgroups of B threads that share the rows in
+// a kernel of K dots: where the matrix has distances, the window fits a CU's LDS
+// with all workgroups resident at once, and each of its elements is gathered once
+// on average.  20 scattered entries a row, SpMV, without and with it, us: 270,000
+// rows 17.4 and 13.3, 500,000 27.0 and 19.6, 1,000,000 76.4 and 35.6; 200,000 rows
+// in 512 workgroups, which would not all be resident, 16.7 and 20.0.
+constexpr size_t kLdsBytes = 160 * 1024;
+inline int window_for(const rpk_matrix* A, int N, int K, int G, int B) {
+  if (!A->sdif) return 0;
+  const int64_t chunk = (A->n + G - 1) / G;
+  const int64_t win = ((chunk + 63) & ~63ll) + A->wlo + A->whi;
+  if (win > (int64_t)(kLdsBytes / 8) || win * G > A->nnz) return 0;
+  const size_t shm = shm_bytes(N, K, true, B, (int)win);
+  if (shm > kLdsBytes || G > (int64_t)(256 * (kLdsBytes / shm))) return 0;
+  return (int)win;
 }
 
 inline int nvec_of(int variant) { return variant == RPK_STD ? 8 : variant == RPK_PCG ? 4 : 16; }
@@ -103,11 +122,11 @@ constexpr double kInfinityCacheBytes = 256.0 * 1024 * 1024;
 // n-vectors (those one solver iteration touches, or x and y of a lone SpMV),
 // so that the next SpMV finds it there.  Slices are counted in proportion to
 // the SELL entries; none where a row dictionary replaces them.
-inline int keep_slices(const rpk_matrix* A, int nvec) {
+inline int keep_slices(const rpk_matrix* A, int nvec, bool win) {
   if (A->np) return 0;
   const double vecs = (double)nvec * (double)A->n * 8.0;
   const double room = 0.9 * kInfinityCacheBytes - vecs;
-  const double sell = (double)A->sell_entries * 12.0;
+  const double sell = (double)A->sell_entries * (win ? 10.0 : 12.0);
   if (room <= 0.0 || sell <= 0.0) return 0;
   if (room >= sell) return A->nslices;
   return (int)((double)A->nslices * (room / sell));

@@ -27,7 +27,8 @@ rpk_status Kern<N>::dot(int G, int B, hipStream_t s, long long n, const double* 
 
 template <int N>
 rpk_status Kern<N>::spmv(int G, int B, hipStream_t s, Csr A, const double* x, double* y) {
-  return launch(k_spmv<N>, G, B, shm_bytes(N, 0, true, B), s, A, x, y);
+  return A.win ? launch(k_spmv<N, true>, G, B, shm_bytes(N, 0, true, B, A.win), s, A, x, y)
+               : launch(k_spmv<N, false>, G, B, shm_bytes(N, 0, true, B), s, A, x, y);
 }
 
 template <int N>
@@ -77,12 +78,17 @@ rpk_status Kern<N>::phase(int variant, int ph, int G, int B, hipStream_t s, Csr 
         }
       }
     }
+    const size_t s1w = shm_bytes(N, 1, true, B, A.win), s2w = shm_bytes(N, 2, true, B, A.win);
     if (A.unif) {
       switch (ph) {
         case 0: return launch(k_std_A<N, false, true>, G, B, s2e, s, A, V, red);
-        case 1: return launch(k_std_B<N, true>, G, B, s1, s, A, V, red);
+        case 1:
+          return A.win ? launch(k_std_B<N, true, true>, G, B, s1w, s, A, V, red)
+                       : launch(k_std_B<N, true>, G, B, s1, s, A, V, red);
         case 2: return launch(k_std_C<N, false, true>, G, B, s1e, s, A, V, red);
-        case 3: return launch(k_std_D<N, true>, G, B, s2, s, A, V, red);
+        case 3:
+          return A.win ? launch(k_std_D<N, true, true>, G, B, s2w, s, A, V, red)
+                       : launch(k_std_D<N, true>, G, B, s2, s, A, V, red);
         default:
           return far ? launch(k_std_E<N, true, true>, G, B, s2e, s, A, V, red)
                      : launch(k_std_E<N, false, true>, G, B, s2e, s, A, V, red);
@@ -92,11 +98,15 @@ rpk_status Kern<N>::phase(int variant, int ph, int G, int B, hipStream_t s, Csr 
       case 0:
         return far ? launch(k_std_A<N, true, false>, G, B, s2e, s, A, V, red)
                    : launch(k_std_A<N, false, false>, G, B, s2e, s, A, V, red);
-      case 1: return launch(k_std_B<N, false>, G, B, s1, s, A, V, red);
+      case 1:
+          return A.win ? launch(k_std_B<N, false, true>, G, B, s1w, s, A, V, red)
+                       : launch(k_std_B<N, false>, G, B, s1, s, A, V, red);
       case 2:
         return far ? launch(k_std_C<N, true, false>, G, B, s1e, s, A, V, red)
                    : launch(k_std_C<N, false, false>, G, B, s1e, s, A, V, red);
-      case 3: return launch(k_std_D<N, false>, G, B, s2, s, A, V, red);
+      case 3:
+          return A.win ? launch(k_std_D<N, false, true>, G, B, s2w, s, A, V, red)
+                       : launch(k_std_D<N, false>, G, B, s2, s, A, V, red);
       default:
         return far ? launch(k_std_E<N, true, false>, G, B, s2e, s, A, V, red)
                    : launch(k_std_E<N, false, false>, G, B, s2e, s, A, V, red);
@@ -108,7 +118,9 @@ rpk_status Kern<N>::phase(int variant, int ph, int G, int B, hipStream_t s, Csr 
       case 0:
         return A.unif ? launch(k_pcg_S10<N, true>, G, B, s2e, s, A, V, red)
                       : launch(k_pcg_S10<N, false>, G, B, s2e, s, A, V, red);
-      case 1: return launch(k_pcg_S1<N>, G, B, shm_bytes(N, 1, true, B), s, A, V, red);
+      case 1:
+        return A.win ? launch(k_pcg_S1<N, true>, G, B, shm_bytes(N, 1, true, B, A.win), s, A, V, red)
+                     : launch(k_pcg_S1<N>, G, B, shm_bytes(N, 1, true, B), s, A, V, red);
       default:
         return A.unif ? launch(k_pcg_S3<N, true>, G, B, s2e, s, A, V, red)
                       : launch(k_pcg_S3<N, false>, G, B, s2e, s, A, V, red);
@@ -119,18 +131,24 @@ rpk_status Kern<N>::phase(int variant, int ph, int G, int B, hipStream_t s, Csr 
   const int Gs = G < 2 ? 2 : G;
   const size_t s4 = shm_bytes(N, 4, false, B), s4t = shm_bytes(N, 4, true, B);
   const size_t s3 = shm_bytes(N, 3, false, B), s3t = shm_bytes(N, 3, true, B);
+  const size_t s0w = shm_bytes(N, 0, true, B, A.win);
+  const size_t s4w = s0w > s4t ? s0w : s4t, s3w = s0w > s3t ? s0w : s3t;
   if (A.unif) {
     switch (ph) {
       case 0:
         return V.near ? launch(k_pipe_P1<N, 0, true>, G, B, s4, s, A, V, red)
                : V.far ? launch(k_pipe_P1<N, 2, true>, G, B, s4, s, A, V, red)
                        : launch(k_pipe_P1<N, 1, true>, G, B, s4, s, A, V, red);
-      case 1: return launch(k_pipe_spmv_fin<N, 1, 4, FIN_POMEGA, true>, Gs, B, s4t, s, A, V, red);
+      case 1:
+        return A.win ? launch(k_pipe_spmv_fin<N, 1, 4, FIN_POMEGA, true, true>, Gs, B, s4w, s, A, V, red)
+                     : launch(k_pipe_spmv_fin<N, 1, 4, FIN_POMEGA, true, false>, Gs, B, s4t, s, A, V, red);
       case 2:
         return V.near ? launch(k_pipe_P3<N, 0, true>, G, B, s3, s, A, V, red)
                : V.far ? launch(k_pipe_P3<N, 2, true>, G, B, s3, s, A, V, red)
                        : launch(k_pipe_P3<N, 1, true>, G, B, s3, s, A, V, red);
-      default: return launch(k_pipe_spmv_fin<N, 0, 3, FIN_S19, true>, Gs, B, s3t, s, A, V, red);
+      default:
+        return A.win ? launch(k_pipe_spmv_fin<N, 0, 3, FIN_S19, true, true>, Gs, B, s3w, s, A, V, red)
+                     : launch(k_pipe_spmv_fin<N, 0, 3, FIN_S19, true, false>, Gs, B, s3t, s, A, V, red);
     }
   }
   switch (ph) {
@@ -138,12 +156,16 @@ rpk_status Kern<N>::phase(int variant, int ph, int G, int B, hipStream_t s, Csr 
       return V.near ? launch(k_pipe_P1<N, 0, false>, G, B, s4, s, A, V, red)
                : V.far ? launch(k_pipe_P1<N, 2, false>, G, B, s4, s, A, V, red)
                        : launch(k_pipe_P1<N, 1, false>, G, B, s4, s, A, V, red);
-    case 1: return launch(k_pipe_spmv_fin<N, 1, 4, FIN_POMEGA, false>, Gs, B, s4t, s, A, V, red);
+    case 1:
+        return A.win ? launch(k_pipe_spmv_fin<N, 1, 4, FIN_POMEGA, false, true>, Gs, B, s4w, s, A, V, red)
+                     : launch(k_pipe_spmv_fin<N, 1, 4, FIN_POMEGA, false, false>, Gs, B, s4t, s, A, V, red);
     case 2:
       return V.near ? launch(k_pipe_P3<N, 0, false>, G, B, s3, s, A, V, red)
                : V.far ? launch(k_pipe_P3<N, 2, false>, G, B, s3, s, A, V, red)
                        : launch(k_pipe_P3<N, 1, false>, G, B, s3, s, A, V, red);
-    default: return launch(k_pipe_spmv_fin<N, 0, 3, FIN_S19, false>, Gs, B, s3t, s, A, V, red);
+    default:
+        return A.win ? launch(k_pipe_spmv_fin<N, 0, 3, FIN_S19, false, true>, Gs, B, s3w, s, A, V, red)
+                     : launch(k_pipe_spmv_fin<N, 0, 3, FIN_S19, false, false>, Gs, B, s3t, s, A, V, red);
   }
 }
 

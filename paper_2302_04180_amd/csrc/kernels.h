@@ -88,6 +88,13 @@ struct Csr {
   const unsigned char* swid;  // [nslices]
   const PatEnt* pat;          // [np pat_stride(pw)]
   int np, pw;
+  // Operand window (win > 0): every row's columns lie between wlo before and whi
+  // behind it, and scattered, so that one gather of a wavefront touches about as
+  // many cache lines as it has lanes.  A workgroup then stages the operand of its
+  // rows and the band around them, win doubles, in LDS and gathers there, with
+  // 16-bit distances, sdif = column - row + wlo, in place of the columns.
+  const unsigned short* sdif;  // [sptr[nslices]]
+  int wlo, whi, win;
 };
 
 // Device-resident solver state (one per solve, in the caller's workspace).
@@ -131,20 +138,26 @@ __host__ __device__ constexpr int red_copies(int grid) { return grid >= 256 ? kM
 // consecutive lanes on distinct banks.
 constexpr int ROW_STRIDE = WIN + 1;
 
-__host__ __device__ inline size_t shm_bytes(int N, int K, bool rows, int block) {
+// room for the row dictionary or the operand window
+__host__ __device__ inline size_t pat_bytes(int win) {
+  const size_t d = (size_t)kPatEntries * sizeof(PatEnt), w = (((size_t)win + 1) & ~(size_t)1) * 8;
+  return w > d ? w : d;
+}
+
+__host__ __device__ inline size_t shm_bytes(int N, int K, bool rows, int block, int win = 0) {
   const size_t nw = (size_t)block / 64, k1 = K > 0 ? K : 1;
   const bool exact = N > 0 && N != LW8;
   const size_t sa = exact ? (size_t)K * SA_D * 8 : 0;
   const size_t scat = exact ? (size_t)K * 64 * ROW_STRIDE * 8 : 0;
   const size_t wsa = N > 0 && rows ? nw * SA_D * 8 : 0;
   const size_t wsum = exact ? k1 * WIN * 8 : N == LW8 ? nw * k1 * LW_REC * 8 : 0;
-  const size_t pat = rows ? (size_t)kPatEntries * sizeof(PatEnt) : 0;
+  const size_t pat = rows ? pat_bytes(win) : 0;
   return pat + sa + scat + wsa + wsum + 16 * 8 + MAX_DOTS * 4 + MAX_DOTS * 8 + MAX_DOTS * 4 + (4 + MAX_DOTS) * 4;
 }
 
 template <int N>
 struct Shm {
-  PatEnt* pat;      // row dictionary of the matrix (kernels with rows)
+  PatEnt* pat;      // row dictionary of the matrix or operand window (kernels with rows)
   long long* sa;    // K * SA_D    long accumulators (rare path)
   long long* scat;  // K * 64 * ROW_STRIDE window rows
   long long* wsa;   // nw * SA_D   row fallback accumulators (kernels with rows)
@@ -157,13 +170,13 @@ struct Shm {
 };
 
 template <int N>
-__device__ __forceinline__ Shm<N> shm_carve(char* base, int K, bool rows) {
+__device__ __forceinline__ Shm<N> shm_carve(char* base, int K, bool rows, int win = 0) {
   Shm<N> s;
   const size_t nw = blockDim.x / 64, k1 = K > 0 ? K : 1;
   constexpr bool exact = N > 0 && N != LW8;
   size_t off = 0;
   s.pat = (PatEnt*)(base + off);
-  off += rows ? (size_t)kPatEntries * sizeof(PatEnt) : 0;
+  off += rows ? pat_bytes(win) : 0;
   s.sa = (long long*)(base + off);
   off += exact ? (size_t)K * SA_D * 8 : 0;
   s.scat = (long long*)(base + off);
@@ -443,6 +456,59 @@ struct PatSrc {  // the row dictionary (Csr::pid) in LDS
     b = gx.fin(gx.load8((unsigned)__builtin_amdgcn_readlane((int)row8, l) + (unsigned)e->off8));
   }
 };
+template <bool NT>
+struct WinSrc {  // the SELL-64 copy with the operand window: w0 at the wavefront's first row, wlo before
+  const double* sv;
+  const unsigned short* sd;
+  const double* w0;
+  template <int B, class Gth>
+  __device__ __forceinline__ void batch(const Gth&, int j0, int w, double (&a)[B], double (&b)[B]) const {
+    const unsigned lane = threadIdx.x & 63;
+    unsigned c[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const size_t j = (size_t)(j0 + u < w ? j0 + u : w - 1) * 64;
+      a[u] = ld_entry<NT>((const double*)((const char*)(sv + j) + lane * 8u));
+      c[u] = ld_entry<NT>((const unsigned short*)((const char*)(sd + j) + lane * 2u));
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      b[u] = w0[lane + c[u]];
+      if (j0 + u >= w) a[u] = 0.0;
+    }
+  }
+  template <class Gth>
+  __device__ __forceinline__ void at(const Gth&, int l, int j, double& a, double& b) const {
+    a = sv[(size_t)j * 64 + l];
+    b = w0[l + sd[(size_t)j * 64 + l]];
+  }
+};
+
+// Stage the operand window of rows R (Csr::win): gathered and finished once an
+// element, zero outside the matrix.  Four loads in flight a thread.  Ends with a
+// barrier.
+template <int N, class Gth>
+__device__ __forceinline__ void win_load(const Csr& A, const Gth& gx, Range R, const Shm<N>& s) {
+  double* win = (double*)s.pat;
+  const int n = R.hi > R.lo ? R.hi - R.lo + A.wlo + A.whi : 0;
+  const int c0 = R.lo - A.wlo;
+  for (int k0 = threadIdx.x; k0 < n; k0 += 4 * blockDim.x) {
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int c = c0 + k0 + u * (int)blockDim.x;
+      v[u] = gx.load(c < 0 ? 0 : c < A.n ? c : A.n - 1);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int k = k0 + u * (int)blockDim.x, c = c0 + k;
+      if (k < n) win[k] = c >= 0 && c < A.n ? gx.fin(v[u]) : 0.0;
+    }
+  }
+  // rows of the last slice behind R
+  for (int k = n + threadIdx.x; k < A.win; k += blockDim.x) win[k] = 0.0;
+  __syncthreads();
+}
 
 // Exact fast path of one row in one lane: FPE of the twoprod terms of entries
 // j = 0..w-1.  Sets `bad` when the FPE overflows or a product needs the
@@ -674,15 +740,31 @@ __device__ __forceinline__ double rows_fpe(const Src& src, const Gth& gx, int w,
 // next row's id, operands and own values ahead of this row's sums was slower (D
 // 32.9 instead of 27.4 us at 128^3), and so was a second pass for the rows that
 // are not certified.
-template <int N, class Gth, class Pre, class Use>
+// Win: the operand comes from LDS (Csr::win).
+template <int N, bool Win = false, class Gth, class Pre, class Use>
 __device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, const Shm<N>& s, Pre pre, Use use) {
+  if constexpr (Win) win_load(A, gx, R, s);
   // the wavefront's 64 rows (one slice)
   for (int first = __builtin_amdgcn_readfirstlane(R.lo + (int)(threadIdx.x & ~63u)); first < R.hi;
        first += blockDim.x) {
     const int i = first + (int)(threadIdx.x & 63), sl = first >> 6;
     const bool ok = i < R.hi;
     double y = 0.0;
-    if (Gth::kDict || A.np) {
+    if constexpr (Win) {
+      const long long off = A.sptr[sl];
+      const int w = (int)((A.sptr[sl + 1] - off) >> 6);
+      const double* w0 = (const double*)s.pat + (first - R.lo);
+      const WinSrc<false> kept{A.sval + off, A.sdif + off, w0};
+      const WinSrc<true> passing{A.sval + off, A.sdif + off, w0};
+      const auto p = pre(ok ? i : R.hi - 1);
+      if constexpr (N == 0) {
+        y = sl < A.keep ? row_plain(kept, gx, w) : row_plain(passing, gx, w);
+      } else {
+        const bool cert = A.cert && (sl < A.keep ? row_cert(A, kept, gx, w, y) : row_cert(A, passing, gx, w, y));
+        if (__ballot(ok && !cert) != 0ull) y = rows_fpe<N>(kept, gx, w, ok, s.wsa);
+      }
+      use(i, ok, y, p);
+    } else if (Gth::kDict || A.np) {
       const int w = __builtin_amdgcn_readfirstlane((int)A.swid[sl]);
       const PatSrc src{s.pat, (unsigned)(i < A.n ? i : A.n - 1) * 8u, (int)A.pid[i] * pat_stride(A.pw)};
       const auto p = pre(ok ? i : R.hi - 1);
@@ -712,11 +794,11 @@ __device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, c
 
 // (A M^-1 v): gathers the stored preconditioned vector vh, or, for a uniform
 // Jacobi vector (Unif), v itself scaled at the gather (same values)
-template <int N, bool Unif, class Pre, class Use>
+template <int N, bool Unif, bool Win = false, class Pre, class Use>
 __device__ __forceinline__ void for_rows_hat(const Csr& A, const double* __restrict__ v, const double* __restrict__ vh,
                                              Range R, const Shm<N>& s, Pre pre, Use use) {
-  if constexpr (Unif) for_rows<N>(A, GatherScaled{A.du, v}, R, s, pre, use);
-  else for_rows<N>(A, GatherX{vh}, R, s, pre, use);
+  if constexpr (Unif) for_rows<N, Win>(A, GatherScaled{A.du, v}, R, s, pre, use);
+  else for_rows<N, Win>(A, GatherX{vh}, R, s, pre, use);
 }
 
 // ---------------------------------------------------------------------------
@@ -1280,15 +1362,17 @@ __global__ void __launch_bounds__(1024) k_dot(long long n, const double* __restr
   }
 }
 
-template <int N>
+template <int N, bool Win>
 __global__ void __launch_bounds__(1024) k_spmv(Csr A, const double* __restrict__ x, double* __restrict__ y) {
   extern __shared__ __align__(16) char smem[];
-  Shm<N> s = shm_carve<N>(smem, 0, true);
-  pat_load(A, s);
-  __syncthreads();
+  Shm<N> s = shm_carve<N>(smem, 0, true, Win ? A.win : 0);
+  if constexpr (!Win) {
+    pat_load(A, s);
+    __syncthreads();
+  }
   const int L = xcd_block(blockIdx.x, gridDim.x);
   const Range R = block_rows(A.n, L, gridDim.x);
-  for_rows<N>(A, GatherX{x}, R, s, [](int) { return 0; }, [&](int i, bool ok, double v, int) {
+  for_rows<N, Win>(A, GatherX{x}, R, s, [](int) { return 0; }, [&](int i, bool ok, double v, int) {
     if (ok) y[i] = v;
   });
 }

@@ -306,12 +306,16 @@ static void free_matrix(rpk_matrix* A) {
   if (A->sptr) (void)hipFree(A->sptr);
   if (A->scol) (void)hipFree(A->scol);
   if (A->sval) (void)hipFree(A->sval);
+  if (A->sdif) (void)hipFree(A->sdif);
   if (A->dict) (void)hipFree(A->dict);
   delete A;
 }
 
+// Widest band (columns before and behind the row) of an operand window: 128 KB
+constexpr int64_t kMaxBand = 16384;
+
 // SELL-64 copy of the validated CSR (prefix sum of the slice widths, padded fill)
-static rpk_status build_sell(rpk_matrix* A, const int* width, hipStream_t s) {
+static rpk_status build_sell(rpk_matrix* A, const int* width, Band* band, hipStream_t s) {
   const int n = (int)A->n, ns = A->nslices;
   if (hipMalloc((void**)&A->sptr, (size_t)(ns + 1) * sizeof(long long)) != hipSuccess) return RPK_ERR_NOMEM;
   long long total = 0;
@@ -327,6 +331,20 @@ static rpk_status build_sell(rpk_matrix* A, const int* width, hipStream_t s) {
   const long long rows = (long long)ns * 64;
   hipLaunchKernelGGL(k_fill_sell, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, A->rp, A->ci, A->v, n, ns,
                      (const long long*)A->sptr, A->scol, A->sval);
+  hipLaunchKernelGGL(k_band, dim3((unsigned)std::min(512, (ns + 3) / 4)), dim3(256), 0, s, n, ns,
+                     (const long long*)A->sptr, (const int*)A->scol, band);
+  HIPCHK(hipGetLastError());
+  // operand window: where a gather touches at least 16 cache lines and a band of
+  // columns leaves room for rows in LDS
+  Band h;
+  HIPCHK(hipMemcpyAsync(&h, band, sizeof(h), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipStreamSynchronize(s));
+  if (h.gathers == 0 || h.lines < 16 * (uint64_t)h.gathers || (int64_t)h.lo + h.hi > kMaxBand) return RPK_OK;
+  if (hipMalloc((void**)&A->sdif, cnt * sizeof(unsigned short)) != hipSuccess) return RPK_ERR_NOMEM;
+  A->wlo = h.lo;
+  A->whi = h.hi;
+  hipLaunchKernelGGL(k_fill_dif, dim3((unsigned)std::min(4096, (ns + 3) / 4)), dim3(256), 0, s, n, ns,
+                     (const long long*)A->sptr, (const int*)A->scol, h.lo, A->sdif);
   HIPCHK(hipGetLastError());
   return RPK_OK;
 }
@@ -415,7 +433,7 @@ static rpk_status check_and_lay_out(rpk_matrix* A, const Setup& u, hipStream_t s
   A->unif = differ == 0u ? 1 : 0;
   A->du = d0;
   RET_IF(build_dictionary(A, found, u.width, u.words, u.t, s));
-  if (!A->np) RET_IF(build_sell(A, u.width, s));
+  if (!A->np) RET_IF(build_sell(A, u.width, (Band*)(u.counts + 4), s));
   // x_j for which every product is in the exact range of twoprod (kProdLo,
   // kProdHi): 2^(ea + ex - 2) <= |a x| < 2^(ea + ex)
   A->xlo = -966 - found.elo;
@@ -564,7 +582,8 @@ rpk_status rpk_exspmv(const rpk_matrix* A, const double* x, double* y, int32_t d
   RET_IF(resolve(launch_cfg, A->n, &c));
   const int N = (dots == RPK_DOT_PLAIN) ? 0 : c.fpe;  // the lightweight mode keeps the exact rows
   Csr Ac = csr_of(A);
-  Ac.keep = keep_slices(A, 2);  // repeated SpMVs of a matrix that fits reuse it from the cache
+  Ac.win = window_for(A, N, 0, c.grid, c.block);
+  Ac.keep = keep_slices(A, 2, Ac.win != 0);  // repeated SpMVs of a matrix that fits reuse it from the cache
   return by_fpe<SpmvF>(N, c.grid, c.block, (hipStream_t)stream, Ac, x, y);
 }
 
@@ -650,9 +669,13 @@ rpk_status rpk_solve(const rpk_matrix* A, const double* b, double* x, const rpk_
   Vecs V = carve_vecs(w, l, A->n, variant, x, b, o);
   Csr Ac = csr_of(A);
   V.loop = loop;
+  // the pipelined products have one more workgroup, which finishes the reduction before them
+  if (!c.one)
+    Ac.win = window_for(A, N, variant == RPK_STD ? 2 : variant == RPK_PCG ? 1 : 0,
+                        std::max(1, G - (variant == RPK_PIPELINED ? 1 : 0)), B);
   V.far = info->streamed;
   V.near = rows_stay_near(A->n, variant, A->unif != 0) ? 1 : 0;
-  Ac.keep = keep_slices(A, cached_vectors(variant, V.near != 0, V.far != 0, A->unif != 0));
+  Ac.keep = keep_slices(A, cached_vectors(variant, V.near != 0, V.far != 0, A->unif != 0), Ac.win != 0);
 
   const bool resume = o->resume != 0;
   // reduction scratch to zero; caller-visible histories to zero (not when resuming)

@@ -193,6 +193,58 @@ __global__ void k_fill_sell(const int* rp, const int* ci, const double* v, int n
   }
 }
 
+// For the operand window (Csr::win): how far columns lie before and behind their
+// rows; the gathers of the SELL copy, and the lanes of them that leave the cache
+// line of the lane before (or are the first).
+struct Band {
+  int lo, hi;
+  unsigned lines, gathers;  // of every sixteenth slice
+};
+__global__ void __launch_bounds__(256) k_band(int n, int nslices, const long long* sptr, const int* scol, Band* band) {
+  __shared__ Band sum;
+  if (threadIdx.x == 0) sum = Band{0, 0, 0u, 0u};
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  int lo = 0, hi = 0;
+  unsigned lines = 0, gathers = 0;
+  for (int s = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; s < nslices; s += gridDim.x * blockDim.x >> 6) {
+    const int r = 64 * s + lane;
+    for (long long at = sptr[s] + lane; at < sptr[s + 1]; at += 64) {
+      const int c = r < n ? scol[at] : r;
+      lo = max(lo, r - c);
+      hi = max(hi, c - r);
+      if ((s & 15) == 0) {
+        const int before = __shfl_up(c, 1);
+        lines += __popcll(__ballot(lane == 0 || (c >> 4) != (before >> 4)));
+        ++gathers;
+      }
+    }
+  }
+  atomicMax(&sum.lo, lo);
+  atomicMax(&sum.hi, hi);
+  if (lane == 0) {
+    atomicAdd(&sum.lines, lines);
+    atomicAdd(&sum.gathers, gathers);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {  // one of each a workgroup
+    atomicMax(&band->lo, sum.lo);
+    atomicMax(&band->hi, sum.hi);
+    atomicAdd(&band->lines, sum.lines);
+    atomicAdd(&band->gathers, sum.gathers);
+  }
+}
+
+// 16-bit distances of the entries for the operand window (padding: the own row)
+__global__ void k_fill_dif(int n, int nslices, const long long* sptr, const int* scol, int wlo, unsigned short* sdif) {
+  const int lane = threadIdx.x & 63;
+  for (int s = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; s < nslices; s += gridDim.x * blockDim.x >> 6) {
+    const int r = 64 * s + lane;
+    for (long long at = sptr[s] + lane; at < sptr[s + 1]; at += 64)
+      sdif[at] = (unsigned short)(r < n ? scol[at] - r + wlo : wlo);
+  }
+}
+
 // Row dictionary (Csr::pid).  A row is its list of (column - row, value) in CSR
 // order; every distinct one is found by the 64-bit hash k_setup_rows took, in an
 // open-addressing table, the lowest row with a hash represents it, and every

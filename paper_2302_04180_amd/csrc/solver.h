@@ -573,12 +573,12 @@ __device__ __forceinline__ void std_A_body(const Csr& A, const Vecs& V, Range R,
 }
 
 // B: S2 + S3 partial
-template <int N, bool Unif, bool Defer>
+template <int N, bool Unif, bool Defer, bool Win = false>
 __device__ __forceinline__ void std_B_body(const Csr& A, const Vecs& V, const Red& red, Range R, int rec,
                                            const Shm<N>& s) {
   Dot<N> d[1];
   d[0].zero();
-  for_rows_hat<N, Unif>(A, V.p, V.ph, R, s, [&](int i) { return V.r0[i]; },
+  for_rows_hat<N, Unif, Win>(A, V.p, V.ph, R, s, [&](int i) { return V.r0[i]; },
                         [&](int i, bool ok, double si, double r0) {
                           if (ok) {
                             V.s[i] = si;
@@ -632,13 +632,13 @@ __device__ __forceinline__ void std_C_body(const Csr& A, const Vecs& V, Range R,
 }
 
 // D: S6 + S7 partials
-template <int N, bool Unif, bool Defer>
+template <int N, bool Unif, bool Defer, bool Win = false>
 __device__ __forceinline__ void std_D_body(const Csr& A, const Vecs& V, const Red& red, Range R, int rec,
                                            const Shm<N>& s) {
   Dot<N> d[2];
   d[0].zero();
   d[1].zero();
-  for_rows_hat<N, Unif>(A, V.q, V.qh, R, s, [&](int i) { return V.q[i]; },
+  for_rows_hat<N, Unif, Win>(A, V.q, V.qh, R, s, [&](int i) { return V.q[i]; },
                         [&](int i, bool ok, double yi, double q) {
                           if (ok) {
                             V.y[i] = yi;
@@ -769,10 +769,10 @@ __device__ __forceinline__ void pipe_init2_body(const Csr& A, const Vecs& V, con
 }
 
 // out = A M^-1 v on rows R: gathers the stored M^-1 v (vh), or v scaled by du
-template <int N, bool Unif>
+template <int N, bool Unif, bool Win = false>
 __device__ __forceinline__ void spmv_hat_body(const Csr& A, const double* v, const double* vh, double* out, Range R,
                                               const Shm<N>& s) {
-  for_rows_hat<N, Unif>(A, v, vh, R, s, [](int) { return 0; }, [&](int i, bool ok, double y, int) {
+  for_rows_hat<N, Unif, Win>(A, v, vh, R, s, [](int) { return 0; }, [&](int i, bool ok, double y, int) {
     if (ok) out[i] = y;
   });
 }
@@ -881,12 +881,12 @@ __device__ __forceinline__ void pcg_init_body(const Csr& A, const Vecs& V, const
 }
 
 // S1 d = A p + partial <p,d> (S2)
-template <int N, bool Defer>
+template <int N, bool Defer, bool Win = false>
 __device__ __forceinline__ void pcg_S1_body(const Csr& A, const Vecs& V, const Red& red, Range R, int rec,
                                             const Shm<N>& s) {
   Dot<N> d[1];
   d[0].zero();
-  for_rows<N>(A, GatherX{V.p}, R, s, [&](int i) { return V.p[i]; }, [&](int i, bool ok, double di, double pi) {
+  for_rows<N, Win>(A, GatherX{V.p}, R, s, [&](int i) { return V.p[i]; }, [&](int i, bool ok, double di, double pi) {
     if (ok) {
       V.s[i] = di;
       d[0].add(pi, di, s.sa, &s.flag[0]);
@@ -1020,7 +1020,7 @@ __global__ void __launch_bounds__(1024) k_std_A(Csr A, Vecs V, Red red) {
   }
 }
 
-template <int N, bool Unif>
+template <int N, bool Unif, bool Win = false>
 __global__ void __launch_bounds__(1024) k_std_B(Csr A, Vecs V, Red red) {
   if constexpr (defer_std<N>()) {
     if (blockIdx.x == 0) {  // A has taken E's dots: clear them, move iter and rho
@@ -1034,10 +1034,10 @@ __global__ void __launch_bounds__(1024) k_std_B(Csr A, Vecs V, Red red) {
   }
   if (V.st->done) return;
   extern __shared__ __align__(16) char smem[];
-  Shm<N> s = shm_carve<N>(smem, 1, true);
-  pat_load(A, s);
+  Shm<N> s = shm_carve<N>(smem, 1, true, Win ? A.win : 0);
+  if constexpr (!Win) pat_load(A, s);
   shm_init(s, 1);
-  std_B_body<N, Unif, defer_std<N>()>(A, V, red, my_rows(A.n), blockIdx.x, s);
+  std_B_body<N, Unif, defer_std<N>(), Win>(A, V, red, my_rows(A.n), blockIdx.x, s);
 }
 
 template <int N, bool Far, bool Unif>
@@ -1073,16 +1073,16 @@ __global__ void __launch_bounds__(1024) k_std_C(Csr A, Vecs V, Red red) {
   }
 }
 
-template <int N, bool Unif>
+template <int N, bool Unif, bool Win = false>
 __global__ void __launch_bounds__(1024) k_std_D(Csr A, Vecs V, Red red) {
   if constexpr (defer_std<N>())
     if (blockIdx.x == 0) block_clear_slots<N, 1>(red, SLOT_SIGMA);  // C has taken B's dot
   if (V.st->done) return;
   extern __shared__ __align__(16) char smem[];
-  Shm<N> s = shm_carve<N>(smem, 2, true);
-  pat_load(A, s);
+  Shm<N> s = shm_carve<N>(smem, 2, true, Win ? A.win : 0);
+  if constexpr (!Win) pat_load(A, s);
   shm_init(s, 2);
-  std_D_body<N, Unif, defer_std<N>()>(A, V, red, my_rows(A.n), blockIdx.x, s);
+  std_D_body<N, Unif, defer_std<N>(), Win>(A, V, red, my_rows(A.n), blockIdx.x, s);
 }
 
 // The three-kernel loop.  Buffers of p and s by iteration: it reads number it & 1
@@ -1297,7 +1297,7 @@ __global__ void __launch_bounds__(1024) k_pipe_P3(Csr A, Vecs V, Red red) {
 // kernel before wrote: `done` may change under them here.  So a P4 whose step
 // stops the solve at its iteration limit still computes the whole t (S18 of the
 // next iteration) that a resumed solve needs.
-template <int N, int W, int K, int F, bool Unif>
+template <int N, int W, int K, int F, bool Unif, bool Win>
 __global__ void __launch_bounds__(1024) k_pipe_spmv_fin(Csr A, Vecs V, Red red) {
   extern __shared__ __align__(16) char smem[];
   if (blockIdx.x == 0) {
@@ -1308,13 +1308,15 @@ __global__ void __launch_bounds__(1024) k_pipe_spmv_fin(Csr A, Vecs V, Red red) 
     return;
   }
   if (!V.st->spmv_go) return;
-  Shm<N> s = shm_carve<N>(smem, 0, true);
-  pat_load(A, s);
-  __syncthreads();
+  Shm<N> s = shm_carve<N>(smem, 0, true, Win ? A.win : 0);
+  if constexpr (!Win) {
+    pat_load(A, s);
+    __syncthreads();
+  }
   const int G = gridDim.x - 1;
   const Range R = block_rows(A.n, xcd_block(blockIdx.x - 1, G), G);
-  if (W == 0) spmv_hat_body<N, Unif>(A, V.w, V.wh, V.t, R, s);
-  else spmv_hat_body<N, Unif>(A, V.z, V.zh, V.v, R, s);
+  if (W == 0) spmv_hat_body<N, Unif, Win>(A, V.w, V.wh, V.t, R, s);
+  else spmv_hat_body<N, Unif, Win>(A, V.z, V.zh, V.v, R, s);
 }
 
 template <int N, bool Unif>
@@ -1373,7 +1375,7 @@ __global__ void __launch_bounds__(1024) k_pcg_S10(Csr A, Vecs V, Red red) {
   }
 }
 
-template <int N>
+template <int N, bool Win = false>
 __global__ void __launch_bounds__(1024) k_pcg_S1(Csr A, Vecs V, Red red) {
   if constexpr (defer_std<N>()) {
     if (blockIdx.x == 0) {  // S10 has taken S3's dots: clear them, move iter and beta
@@ -1387,10 +1389,10 @@ __global__ void __launch_bounds__(1024) k_pcg_S1(Csr A, Vecs V, Red red) {
   }
   if (V.st->done) return;
   extern __shared__ __align__(16) char smem[];
-  Shm<N> s = shm_carve<N>(smem, 1, true);
-  pat_load(A, s);
+  Shm<N> s = shm_carve<N>(smem, 1, true, Win ? A.win : 0);
+  if constexpr (!Win) pat_load(A, s);
   shm_init(s, 1);
-  pcg_S1_body<N, defer_std<N>()>(A, V, red, my_rows(A.n), blockIdx.x, s);
+  pcg_S1_body<N, defer_std<N>(), Win>(A, V, red, my_rows(A.n), blockIdx.x, s);
 }
 
 template <int N, bool Unif>
