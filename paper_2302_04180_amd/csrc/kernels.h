@@ -977,6 +977,13 @@ __device__ __forceinline__ void lw_store(double* r, const Dot<LW8>& a) {
   for (int k = 0; k < LW_REC; ++k) r[k] = v[k];
 }
 
+// lanes that a merge of n records spans: a power of two
+__device__ __forceinline__ int lw_width(int n) {
+  int width = 1;
+  while (width < n && width < 64) width <<= 1;
+  return width;
+}
+
 // One wavefront merges the per-wave records (wave i at rec[(i*K + j)*LW_REC])
 // of dot j; lane 0 ends with the workgroup's value.
 __device__ __forceinline__ void lw_gather_waves(Dot<LW8>& a, const double* rec, int j, int K, int nw, int lane) {
@@ -986,9 +993,40 @@ __device__ __forceinline__ void lw_gather_waves(Dot<LW8>& a, const double* rec, 
   for (int k = 0; k < LW_N; ++k) a.f.c[k] = in ? r[k] : 0.0;
   a.tail = in ? r[LW_N] : 0.0;
   a.fl = in ? (int)r[LW_N + 1] : 0;
-  int width = 1;
-  while (width < nw) width <<= 1;
-  a.wave_merge(width);
+  a.wave_merge(lw_width(nw));
+}
+
+// Every wavefront's record of each dot to LDS, then a barrier
+template <int K>
+__device__ __forceinline__ void lw_wave_records(Dot<LW8> (&d)[K], double* rec) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    d[j].wave_merge(64);
+    if (lane == 0) lw_store(rec + (size_t)(w * K + j) * LW_REC, d[j]);
+  }
+  __syncthreads();
+}
+
+// Record b of dot j, published by another workgroup
+__device__ __forceinline__ void lw_record(Dot<LW8>& a, const Red& red, int slot, int b) {
+  const double* g = red.partials + ((size_t)slot * red.G + b) * LW_REC;
+  double v[LW_REC];
+#pragma unroll
+  for (int k = 0; k < LW_REC; ++k)
+    v[k] = __longlong_as_double(
+        (long long)__hip_atomic_load((unsigned long long*)&g[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+#pragma unroll
+  for (int k = 0; k < LW_N; ++k) a.f.c[k] = v[k];
+  a.tail = v[LW_N];
+  a.fl = (int)v[LW_N + 1];
+}
+
+// The rounded dot of a merged record (one thread)
+__device__ __forceinline__ double lw_round(const Dot<LW8>& a) {
+  double r = fpe_round(a.f);
+  if (a.fl & F_LOST) r += a.tail;
+  return (a.fl & F_NONFINITE) ? __longlong_as_double(0x7ff8000000000000ll) : r;
 }
 
 // Adds this workgroup's part of the K dots into the reduction slots slot0..
@@ -1005,12 +1043,7 @@ __device__ __forceinline__ unsigned long long block_publish(Dot<N> (&d)[K], cons
     // one wave per dot); lane 0 publishes the workgroup's record of each dot
     const int nw = blockDim.x >> 6, w = tid >> 6, lane = tid & 63;
     double* rec = (double*)s.wsum;
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      d[j].wave_merge(64);
-      if (lane == 0) lw_store(rec + (size_t)(w * K + j) * LW_REC, d[j]);
-    }
-    __syncthreads();
+    lw_wave_records<K>(d, rec);
     for (int j = w; j < K; j += nw) {
       Dot<LW8> a;
       lw_gather_waves(a, rec, j, K, nw, lane);
@@ -1136,35 +1169,48 @@ template <int N, int K, int Mode>
 __device__ __forceinline__ void block_finalize(const Shm<N>& s, const Red& red, int slot0) {
   const int tid = threadIdx.x, bd = blockDim.x;
   if constexpr (N == LW8) {
+    // A level of a merge is a chain of some 50 twosums (0.5 us), so records go
+    // straight into lanes and only as many levels follow as there are records:
+    // up to 64 of them in one wavefront a dot (n = 57 of a dot, one record: 13.3
+    // us with all wavefronts merging all lanes, 8.0 in LDS; 1,000, two: 16.5, 11.7)
     const int nw = bd >> 6, w = tid >> 6, lane = tid & 63;
-    double* rec = (double*)s.wsum;
-    for (int j = 0; j < K; ++j) {
-      Dot<LW8> a;
-      a.zero();
-      for (int b = tid; b < red.G; b += bd) {
-        const double* g = red.partials + ((size_t)(slot0 + j) * red.G + b) * LW_REC;
-        double v[LW_REC];
-#pragma unroll
-        for (int k = 0; k < LW_REC; ++k)
-          v[k] = __longlong_as_double((long long)__hip_atomic_load((unsigned long long*)&g[k], __ATOMIC_RELAXED,
-                                                                   __HIP_MEMORY_SCOPE_AGENT));
-        double c[LW_N];
-#pragma unroll
-        for (int k = 0; k < LW_N; ++k) c[k] = v[k];
-        a.absorb(c, v[LW_N], (int)v[LW_N + 1]);
+    if (red.G <= 64) {
+      for (int j = w; j < K; j += nw) {
+        Dot<LW8> a;
+        a.zero();
+        if (lane < red.G) lw_record(a, red, slot0 + j, lane);
+        a.wave_merge(lw_width(red.G));
+        if (lane == 0) {
+          s.res[j] = lw_round(a);
+          s.misc[1 + j] = a.fl;
+        }
       }
-      a.wave_merge(64);
-      if (lane == 0) lw_store(rec + (size_t)(w * K + j) * LW_REC, a);
+      __syncthreads();
+      return;
+    }
+    double* rec = (double*)s.wsum;
+    const int held = min(nw, (red.G + 63) >> 6);  // wavefronts that hold records
+    if (w < held) {
+      for (int j = 0; j < K; ++j) {
+        Dot<LW8> a;
+        a.zero();
+        if (tid < red.G) lw_record(a, red, slot0 + j, tid);
+        for (int b0 = bd; b0 < red.G; b0 += bd) {  // all lanes absorb together
+          Dot<LW8> c;
+          c.zero();
+          if (b0 + tid < red.G) lw_record(c, red, slot0 + j, b0 + tid);
+          a.absorb(c.f.c, c.tail, c.fl);
+        }
+        a.wave_merge(64);
+        if (lane == 0) lw_store(rec + (size_t)(w * K + j) * LW_REC, a);
+      }
     }
     __syncthreads();
     for (int j = w; j < K; j += nw) {
       Dot<LW8> a;
-      lw_gather_waves(a, rec, j, K, nw, lane);
+      lw_gather_waves(a, rec, j, K, held, lane);
       if (lane == 0) {
-        double r = fpe_round(a.f);
-        if (a.fl & F_LOST) r += a.tail;
-        if (a.fl & F_NONFINITE) r = __longlong_as_double(0x7ff8000000000000ll);
-        s.res[j] = r;
+        s.res[j] = lw_round(a);
         s.misc[1 + j] = a.fl;
       }
     }
@@ -1236,12 +1282,23 @@ __device__ __forceinline__ void block_finalize_last(const Shm<N>& s, const Red& 
 // device memory.  The same bits as block_publish followed by
 // block_finalize_last: an exact dot is the same integer (the window sums added
 // to this workgroup's long accumulator instead of the global one) rounded
-// once, a plain one the workgroup's sum plus zero.  Exact and plain dots.
+// once, a plain one the workgroup's sum plus zero, a lightweight one its record.
 template <int N, int K>
 __device__ __forceinline__ void block_reduce_local(Dot<N> (&d)[K], const Shm<N>& s) {
-  static_assert(N != LW8, "lightweight records are merged through the partials");
   const int tid = threadIdx.x;
-  if constexpr (N > 0) {
+  if constexpr (N == LW8) {
+    const int nw = blockDim.x >> 6, w = tid >> 6, lane = tid & 63;
+    lw_wave_records<K>(d, (double*)s.wsum);
+    for (int j = w; j < K; j += nw) {
+      Dot<LW8> a;
+      lw_gather_waves(a, (const double*)s.wsum, j, K, nw, lane);
+      if (lane == 0) {
+        s.res[j] = lw_round(a);
+        s.misc[1 + j] = a.fl;
+      }
+    }
+    __syncthreads();
+  } else if constexpr (N > 0) {
     block_window<N, K>(d, s);
     if (tid < K * WIN) {  // one (dot, digit) per thread: no two write one digit
       const int j = tid / WIN, k = tid % WIN;
@@ -1350,8 +1407,8 @@ __global__ void __launch_bounds__(1024) k_dot(long long n, const double* __restr
     for (int u = 0; u < U; ++u) d[0].add(a[u], b[u], s.sa, &s.flag[0]);
   }
   for (; i < hi; i += blockDim.x) d[0].add(x[i], y[i], s.sa, &s.flag[0]);
-  if (N != LW8 && gridDim.x == 1) {
-    if constexpr (N != LW8) block_reduce_local<N, 1>(d, s);
+  if (gridDim.x == 1) {
+    block_reduce_local<N, 1>(d, s);
   } else {
     if (!block_publish_last<N, 1>(d, s, red, 0, blockIdx.x, 0)) return;
     block_finalize_last<N, 1>(s, red, 0);
