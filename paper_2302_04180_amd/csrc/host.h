@@ -68,18 +68,36 @@ constexpr int64_t kMaxPerGroup = int64_t(1) << 29;
 // the exact rows and dots outweighs the launches it saves (the pipelined loop
 // ran slower in one workgroup already at 512 rows)
 constexpr int64_t kOneGroupRows = 512;
-// Solves of fewer rows with the automatic launch shape use workgroups of 256
-// threads instead of 512: measured 3-12 % faster from 1,728 to 32,768 rows
-// (7-point Poisson, all three loops), slower from 110,592 on
-constexpr int64_t kSmallBlockRows = 65536;
+// Solves of fewer than kBigBlockRows rows with the automatic launch shape take
+// workgroups of 512 threads for 256 rows each (128 up to 4,096 rows), at most 248
+// of them: the threads beyond the rows shorten the fixed parts of a kernel
+// (clearing and reducing accumulators, the partial sums of the deferred points),
+// one workgroup a CU has few partial sums to queue, and below 256 workgroups the
+// accumulators have four copies to read instead of eight.  Fewer than 1,024 rows
+// keep 256 threads, for 128 rows each.  40 iterations, pipelined / standard / PCG,
+// us, in 256 threads for 256 rows (512 for 512 rows from 65,536 on, at most 512
+// workgroups) and in this shape: 9^3 1,065 / 1,211 / 791 and 1,030 / 1,185 / 784,
+// 16^3 1,121 / 1,091 / 789 and 1,005 / 1,036 / 764, 28^3 1,248 / 1,207 / 862 and
+// 1,079 / 1,073 / 789, 56^3 1,598 / 1,482 / 982 and 1,400 / 1,287 / 911; 68^3 1,649 /
+// 1,524 / 989 (256 of 1,024) and 1,752 / 1,499 / 991.
+constexpr int64_t kTinySolveRows = 1024;
+constexpr int64_t kShortSolveRows = 4096;
+constexpr int64_t kSmallSolveGroups = 248;
 // Dots of at most this many elements with the automatic launch shape run in one
 // workgroup: 1,000 elements 4.3 us against 5.4 in two workgroups of 512
 constexpr int64_t kOneGroupDot = 4096;
 // From this many rows on the automatic shape is 256 workgroups of 1,024 threads
-// instead of 512 of 512: as many wavefronts, but half the partial sums that
+// instead of 512 of 512 (solves: see kSmallSolveGroups): as many wavefronts, but half the partial sums that
 // queue on the accumulators (128^3 solve: B 25.0 and 23.5, D 30.6 and 28.0 us,
 // 101^3 PCG: S1 15.8 and 14.6, S3 17.5 and 16.6 us)
 constexpr int64_t kBigBlockRows = 262144;
+// Matrices of scattered columns (rpk_matrix::sdif) of at least kTinySolveRows rows
+// take 256 workgroups, of 512 threads and from this many rows on of 1,024: their gathers keep a
+// CU's L1 or LDS busy, so all CUs must share them, and one workgroup a CU leaves
+// room for the operand window.  SpMV in the shape above and in this one, us:
+// 30,000 rows (20 entries each) 8.6 and 5.5, 66,000 7.9 and 5.6, 130,000 10.2 and
+// 7.5, 200,000 16.7 and 11.5 (with 512 threads 12.8)
+constexpr int64_t kBigScatteredRows = 131073;
 // Largest automatic chunk of iterations between two looks at a solve's state
 constexpr int kMaxChunk = 64;
 // Workgroups of one launch over a tile table (the rest take further launches):

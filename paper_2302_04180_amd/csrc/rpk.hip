@@ -41,10 +41,11 @@ struct Cfg {
   int one;  // solve: every iteration in one workgroup (k_std_one / k_pcg_one)
 };
 
-rpk_status resolve(const rpk_launch* L, int64_t n, Cfg* c) {
+rpk_status resolve(const rpk_launch* L, int64_t n, Cfg* c, bool scattered = false) {
   c->one = 0;
   const bool automatic = !L || (L->block == 0 && L->grid == 0);
-  c->block = (L && L->block) ? L->block : (automatic && n >= kBigBlockRows) ? 1024 : 512;
+  scattered = scattered && n >= kTinySolveRows;
+  c->block = (L && L->block) ? L->block : (automatic && n >= (scattered ? kBigScatteredRows : kBigBlockRows)) ? 1024 : 512;
   c->fpe = (L && L->fpe) ? L->fpe : 3;
   c->graph = L ? L->graph : 0;
   if (c->block < 64 || c->block > 1024 || (c->block % 64) != 0) return RPK_ERR_ARG;
@@ -58,7 +59,8 @@ rpk_status resolve(const rpk_launch* L, int64_t n, Cfg* c) {
     // sums to queue little, enough waves in flight for the streams (measured best
     // among 256..2048 workgroups of 256..1024 threads)
     int64_t need = (n + c->block - 1) / c->block;
-    const int64_t most = automatic && n >= kBigBlockRows ? 256 : 512;
+    const int64_t most = automatic && (scattered || n >= kBigBlockRows) ? 256 : 512;
+    if (automatic && scattered) need = most;
     if (need < 1) need = 1;
     if (need > most) need = most;
     if (need >= 8) need &= ~7ll;
@@ -579,7 +581,7 @@ rpk_status rpk_exspmv(const rpk_matrix* A, const double* x, double* y, int32_t d
   if (!A || !x || !y || x == y) return RPK_ERR_ARG;
   if (dots != RPK_DOT_EXACT && dots != RPK_DOT_PLAIN && dots != RPK_DOT_FPE) return RPK_ERR_ARG;
   Cfg c;
-  RET_IF(resolve(launch_cfg, A->n, &c));
+  RET_IF(resolve(launch_cfg, A->n, &c, A->sdif != nullptr));
   const int N = (dots == RPK_DOT_PLAIN) ? 0 : c.fpe;  // the lightweight mode keeps the exact rows
   Csr Ac = csr_of(A);
   Ac.win = window_for(A, N, 0, c.grid, c.block);
@@ -588,16 +590,22 @@ rpk_status rpk_exspmv(const rpk_matrix* A, const double* x, double* y, int32_t d
 }
 
 // Launch shape of a solve: that of the streaming kernels, except with the
-// automatic shape (block and grid 0) on small systems: a standard or PCG solve
-// with exact or plain dots of up to kOneGroupRows rows runs all its iterations
-// in one workgroup of 1024 threads and one launch, and other solves of fewer
-// than kSmallBlockRows rows take workgroups of 256 threads (twice as many
-// workgroups: latency-bound iterations spread over more CUs).
+// automatic shape (block and grid 0) on systems of fewer than kBigBlockRows rows: a
+// standard or PCG solve with exact or plain dots of up to kOneGroupRows rows runs
+// all its iterations in one workgroup of 1024 threads and one launch, and other
+// solves, of matrices without scattered columns, take few large workgroups
+// (kSmallSolveGroups).
 static rpk_status solve_shape(const rpk_matrix* A, const rpk_opts* o, Cfg* c) {
   const bool automatic = o->launch.grid == 0 && o->launch.block == 0;
   rpk_launch L = o->launch;
-  if (automatic && A->n < kSmallBlockRows) L.block = 256;
-  RET_IF(resolve(&L, A->n, c));
+  const bool scattered = A->sdif != nullptr && A->n >= kTinySolveRows;
+  if (automatic && A->n < kBigBlockRows && !scattered) {
+    const int64_t rows = A->n <= kShortSolveRows ? 128 : 256;
+    const int64_t need = (A->n + rows - 1) / rows;
+    L.block = A->n < kTinySolveRows ? 256 : 512;
+    L.grid = (int32_t)std::min<int64_t>(kSmallSolveGroups, need < 8 ? need : (need + 7) & ~7ll);
+  }
+  RET_IF(resolve(&L, A->n, c, scattered));
   if (automatic && A->n <= kOneGroupRows && (o->variant == RPK_STD || o->variant == RPK_PCG) &&
       o->dots != RPK_DOT_FPE) {
     c->grid = 1;
