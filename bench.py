@@ -38,11 +38,11 @@ MAXIT = 5000
 # each scaled by what the same counter reads for the plain copy kernel of that
 # workload (512 MiB read + 512 MiB written), and the kernel's average duration in
 # the rocprofv3 kernel trace of the bench (launches of the 128^3 section longer
-# than 8 us).  Valid only while the kernel sources still have the digest they
+# than 4 us).  Valid only while the kernel sources still have the digest they
 # had when the profiles were taken and the solve runs the same FPE length.
-TRAFFIC = {"phase": 3, "kernel": "k_std_D<3, true>", "fpe": 3, "bytes": 212855288,
-           "fetch_scale": 1.9999, "write_scale": 1.0000, "trace_busy_avg_us": 48.6,
-           "src_sha256": "0923a99ac026297f1b4475119d33eb811fe726b7cc9e389aa1302ebca15a61d4"}
+TRAFFIC = {"phase": 3, "kernel": "k_std_D3<3, 1>", "fpe": 3, "bytes": 74073316,
+           "fetch_scale": 1.9999, "write_scale": 1.0000, "trace_busy_avg_us": 35.2,
+           "src_sha256": "cff43a9e6d084ea5dd3547928c82724284ab214c5fb5b5e95e880c7adb5cfd37"}
 
 
 KERNEL_SOURCES = ("device.h", "kernels.h", "solver.h")
@@ -67,8 +67,9 @@ def algorithmic_bytes(n, nnz):
     output; dots fused into their producers).  CSR = 12 nnz + 4 (n + 1).
     The reference counts keep every Fig. 2 / Fig. 3 operand, p^ and q^ included;
     with a uniform Jacobi vector (every diagonal entry equal, as in the Poisson
-    and convection-diffusion systems) the standard loop forms p^ and q^ where it
-    reads them and moves 19 vectors per iteration instead of 25."""
+    and convection-diffusion systems) and few different rows (read through a
+    dictionary, one byte a row) the standard loop forms p^, q and q^ where it
+    reads them and moves 18 vectors per iteration instead of 25, and no matrix."""
     V = 8 * n
     csr = 12 * nnz + 4 * (n + 1)
     return {
@@ -81,11 +82,11 @@ def algorithmic_bytes(n, nnz):
         # A: p s r dinv -> p p^ ; B: CSR + gather p^ + r0 -> s ; C: s r dinv -> q q^
         # D: CSR + gather q^ + q -> y ; E: x p^ q^ y q r0 -> x r
         "std_kernel": {0: 6 * V, 1: csr + 3 * V, 2: 5 * V, 3: csr + 3 * V, 4: 8 * V},
-        # the same with a uniform Jacobi vector (p^ = du p, q^ = du q formed where read):
-        # A: p s r -> p ; B: CSR + gather p + r0 -> s ; C: s r -> q
-        # D: CSR + gather q (its own element gives <q, y>) -> y ; E: x p q y r0 -> x r
-        "std_kernel_unif": {0: 4 * V, 1: csr + 3 * V, 2: 3 * V, 3: csr + 2 * V, 4: 7 * V},
-        "std_iteration_unif": 2 * csr + 19 * V,
+        # what the four kernels move on the 128^3 Poisson system (p^ = du p, q^ = du q
+        # formed where read, a byte a row for the matrix): A: p s r -> p ;
+        # B: gather p + r0 -> s ; D: gather s, r -> q y (C is part of it) ; E: x p q y r0 -> x r
+        "std_kernel_unif": {0: 4 * V, 1: n + 3 * V, 2: 0, 3: n + 4 * V, 4: 7 * V},
+        "std_iteration_unif": 2 * n + 18 * V,
     }
 
 
@@ -608,7 +609,7 @@ def main():
     tinfo = solve(timing=True)
     names = ["A: S12+S1", "B: S2 SpMV + S3 dot", "C: S4+S5", "D: S6 SpMV + S7 dots",
              "E: S8+S9 + S10/S11 dots"]
-    phase = {}
+    phase = {}  # C is part of D where it has no launches of its own
     for k, nm in enumerate(names):
         if tinfo["phase_launches"][k]:
             phase[nm] = round(1e3 * tinfo["phase_ms"][k] / tinfo["phase_launches"][k], 2)  # us per launch
@@ -627,7 +628,8 @@ def main():
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                 "kernel": names[dom], "bytes_per_launch": dom_bytes,
-                # what the kernel moves with the uniform Jacobi vector of the 7-point Poisson
+                # what the kernel moves (bytes_per_launch counts the CSR matrix, which the row
+                # dictionary replaces)
                 "moved_bytes_per_launch": by["std_kernel_unif"][dom], "avg_launch_us": round(avg_s * 1e6, 2),
                 # HIP events around direct launches include the dispatch of each kernel (a few us);
                 # the kernel trace of the same sources times the kernels alone
@@ -645,7 +647,7 @@ def main():
         "iterations_per_solve": it_exact,
         "algorithmic_GBps_iteration": round(exact_ips * by["std_iteration"] / 1e9, 1),
         "iteration_roofline_frac": round(exact_ips * by["std_iteration"] / 1e9 / HBM_PEAK_GBS, 4),
-        # what the kernels move (19 vector streams with the uniform Jacobi vector)
+        # what the kernels move (18 vector streams and a byte a row twice)
         "moved_bytes_per_iteration": by["std_iteration_unif"],
         "moved_GBps_iteration": round(exact_ips * by["std_iteration_unif"] / 1e9, 1),
         "plain_fp64": {"iters_per_s": round(plain_ips, 2), "iterations": plain_info["iters"]},

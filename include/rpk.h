@@ -92,11 +92,14 @@ typedef enum { RPK_DOT_EXACT = 0, RPK_DOT_PLAIN = 1, RPK_DOT_FPE = 2 } rpk_dotmo
  * Small solves (block and grid both 0): a standard or PCG rpk_solve of at most
  * 512 rows with exact or plain dots runs every iteration in one workgroup of
  * 1024 threads and one kernel launch (graph is then unused; info->used reports
- * grid 1, block 1024); other solves of fewer than 65536 rows use workgroups of
- * 256 threads.  Exact results are the same bits either way. */
+ * grid 1, block 1024); other solves of fewer than 262,144 rows use workgroups of
+ * 512 threads (256 below 1,024 rows), at most 248 of them.  Matrices of scattered
+ * columns inside a band use 256 workgroups.  Exact results are the same bits
+ * either way. */
 typedef struct {
-  int32_t block;  /* workgroup size, a multiple of 64 in [64, 1024]; 0 = 512, or
-                     1024 from 262,144 rows on when the grid is automatic too */
+  int32_t block;  /* workgroup size, a multiple of 64 in [64, 1024]; 0 = 512, or,
+                     when the grid is automatic too, 1024 from 262,144 elements
+                     on (scattered matrices: 131,073 rows) and as said above */
   int32_t grid;   /* workgroups of the streaming kernels, 1 .. 65535; 0 = automatic */
   int32_t fpe;    /* FPE length 1, 2, 3, 4 or 8 (1 sends almost every term to
                      the long accumulator); 0 = 3 */

@@ -5,10 +5,10 @@
 // the next kernel rounds them and takes the scalar step (Deferred), with
 // lightweight dots (and in the batched loop) the last workgroup of the
 // publishing kernel does (kernels.h, block_publish_last), so no separate
-// finishing kernel and no grid-wide fence is needed.  Recomputing p^ / q^ inside the SpMV
-// gathers instead of storing them was measured slower: it multiplies the
-// gathered vectors by 3-4 (gathering p and dinv alone, 2, still cost more than
-// the stores it saves).  Where the Jacobi vector is uniform (Csr::unif) they are
+// finishing kernel and no grid-wide fence is needed.  For a varying Jacobi vector,
+// recomputing p^ / q^ inside the SpMV gathers instead of storing them was measured
+// slower: it multiplies the gathered vectors by 3-4 (gathering p and dinv alone, 2,
+// still cost more than the stores it saves).  Where the Jacobi vector is uniform (Csr::unif) they are
 // formed where they are read, RN(du v_i) at the gathers and in E, and never
 // stored: 19 vector streams per iteration instead of 25.  The host picks that
 // path (the Unif instantiations) per launch: for a single solve from the
