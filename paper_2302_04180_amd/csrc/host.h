@@ -86,8 +86,16 @@ constexpr int64_t kSmallSolveGroups = 248;
 // Dots of at most this many elements with the automatic launch shape run in one
 // workgroup: 1,000 elements 4.3 us against 5.4 in two workgroups of 512
 constexpr int64_t kOneGroupDot = 4096;
+// Dots of kMidDot to kLongDot - 1 elements with the automatic launch shape take
+// workgroups of 512 threads for 1,024 elements each, at most kSmallSolveGroups: a
+// call with up to 512 workgroups of 512 (256 of 1,024 from 262,144 elements on) and
+// in this shape, exact / plain / lightweight, us: 128,000 elements 8.2 / 7.5 / 19.2
+// and 7.7 / 7.3 / 17.9, 262,143 12.3 / 10.5 / 26.0 and 9.0 / 7.5 / 20.2, 500,000 10.1 /
+// 8.0 / 24.2 and 9.7 / 7.7 / 21.4; exact at 1M 10.6 and 10.5, at 2M 12.4 and 12.8;
+// below 65,536 the same within 2 %
+constexpr int64_t kMidDot = 65536, kLongDot = 1 << 20;
 // From this many rows on the automatic shape is 256 workgroups of 1,024 threads
-// instead of 512 of 512 (solves: see kSmallSolveGroups): as many wavefronts, but half the partial sums that
+// instead of 512 of 512 (solves: see kSmallSolveGroups; dots: kLongDot): as many wavefronts, but half the partial sums that
 // queue on the accumulators (128^3 solve: B 25.0 and 23.5, D 30.6 and 28.0 us,
 // 101^3 PCG: S1 15.8 and 14.6, S3 17.5 and 16.6 us)
 constexpr int64_t kBigBlockRows = 262144;

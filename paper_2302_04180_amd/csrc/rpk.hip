@@ -74,13 +74,18 @@ rpk_status resolve(const rpk_launch* L, int64_t n, Cfg* c, bool scattered = fals
 }
 
 // Launch shape of a dot: that of the streaming kernels, but with the automatic
-// shape one workgroup for short vectors, which reduces in LDS with no
-// accumulator, ticket or second workgroup to wait for.
-rpk_status dot_shape(const rpk_launch* L, int64_t n, Cfg* c) {
+// shape one workgroup for short vectors, which reduces in LDS with no accumulator,
+// ticket or second workgroup to wait for (not the lightweight ones), and for middle
+// ones (kMidDot) fewer workgroups of two elements a thread.
+rpk_status dot_shape(const rpk_launch* L, int64_t n, Cfg* c, bool light = false) {
   RET_IF(resolve(L, n, c));
-  if (n <= kOneGroupDot && (!L || (L->block == 0 && L->grid == 0))) {
+  if (L && (L->block != 0 || L->grid != 0)) return RPK_OK;
+  if (n <= kOneGroupDot && !light) {
     c->block = 1024;
     c->grid = 1;
+  } else if (n >= kMidDot && n < kLongDot) {
+    c->block = 512;
+    c->grid = (int)std::min<int64_t>(kSmallSolveGroups, n / 1024 & ~7ll);
   }
   return RPK_OK;
 }
@@ -569,7 +574,7 @@ rpk_status rpk_fpedot(int64_t n, const double* x, const double* y, double* out_d
                       const rpk_launch* launch_cfg, void* ws, size_t ws_bytes, void* stream) {
   if (n < 0 || n >= (1ll << 32) || !out_dev || !lost_dev || !ws || (n > 0 && (!x || !y))) return RPK_ERR_ARG;
   Cfg c;
-  RET_IF(resolve(launch_cfg, n, &c));
+  RET_IF(dot_shape(launch_cfg, n, &c, true));
   const Layout l = layout(c.grid, 0, 0);
   if (ws_bytes < l.total) return RPK_ERR_ARG;
   Red red = make_red((char*)ws, l, c.grid);
