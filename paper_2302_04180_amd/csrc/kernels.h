@@ -15,6 +15,7 @@
 #include <climits>
 
 #include "device.h"
+#include "span.h"
 
 namespace rpk {
 
@@ -745,9 +746,9 @@ template <int N, bool Win = false, class Gth, class Pre, class Use>
 __device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, const Shm<N>& s, Pre pre, Use use) {
   if constexpr (Win) win_load(A, gx, R, s);
   // the wavefront's 64 rows (one slice)
-  for (int first = __builtin_amdgcn_readfirstlane(R.lo + (int)(threadIdx.x & ~63u)); first < R.hi;
-       first += blockDim.x) {
-    const int i = first + (int)(threadIdx.x & 63), sl = first >> 6;
+  for (unsigned at = __builtin_amdgcn_readfirstlane(R.lo + (int)(threadIdx.x & ~63u)); row_below(at, R.hi);
+       at += blockDim.x) {
+    const int first = (int)at, i = first + (int)(threadIdx.x & 63), sl = first >> 6;
     const bool ok = i < R.hi;
     double y = 0.0;
     if constexpr (Win) {

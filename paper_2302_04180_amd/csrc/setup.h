@@ -47,7 +47,7 @@ struct SliceRows {
     const int lane = threadIdx.x & 63;
     const int r = 64 * s + lane;
     rp[lane] = g[r < n ? r : n];
-    if (lane == 0) rp[64] = g[64 * s + 64 < n ? 64 * s + 64 : n];
+    if (lane == 0) rp[64] = g[slice_end(n, s)];
   }
   __device__ __forceinline__ int row_of(int e) const {
     int lo = 0;  // the last row that starts at or before e
@@ -78,9 +78,8 @@ __global__ void __launch_bounds__(256) k_setup_rows(const int* rp, const int* ci
     cnt[w][lane] = 0;
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     __builtin_amdgcn_wave_barrier();
-    const int e1 = R[w].rp[64];
-    for (int e = R[w].rp[0] + lane; e < e1; e += 64) {
-      const int l = R[w].row_of(e), r = 64 * s + l;
+    for (LaneEntries it(R[w].rp[0], R[w].rp[64], lane); it.more(); it.next()) {
+      const int e = it.at(), l = R[w].row_of(e), r = 64 * s + l;
       const int c = ci[e];
       const double val = v[e];
       if (c < 0 || c >= n) fl |= CHK_ARG;
@@ -376,9 +375,8 @@ __global__ void __launch_bounds__(256) k_pat_rows(const int* rp, const int* ci, 
     if (lane == 0) swid[s] = (unsigned char)width[s];
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     __builtin_amdgcn_wave_barrier();
-    const int e1 = R[w].rp[64];
-    for (int e = R[w].rp[0] + lane; e < e1; e += 64) {
-      const int l = R[w].row_of(e);
+    for (LaneEntries it(R[w].rp[0], R[w].rp[64], lane); it.more(); it.next()) {
+      const int e = it.at(), l = R[w].row_of(e);
       const int j = e - R[w].rp[l];
       const PatEnt p = pat[id[w][l] * stride + (j < pw ? j : 0)];
       bad |= j >= pw || 8 * (ci[e] - (64 * s + l)) != p.off8 ||
