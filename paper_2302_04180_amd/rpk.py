@@ -7,6 +7,7 @@ fails: there is no CPU fallback.
 import ctypes
 import functools
 import os
+import threading
 import warnings
 
 import numpy as np
@@ -117,13 +118,15 @@ def _check(code, where):
         raise RpkError(code, where)
 
 
-def _raw_stream():
-    """The current stream as an integer (torch.cuda.current_stream() builds an object, 3 us)."""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+def _here():
+    """The current device and its current stream as integers (torch.cuda.current_stream()
+    builds an object, 3 us)."""
+    dev = torch.cuda.current_device()
+    return dev, torch._C._cuda_getCurrentRawStream(dev)
 
 
 def _stream():
-    return ctypes.c_void_p(_raw_stream())
+    return ctypes.c_void_p(_here()[1])
 
 
 def _ptr(t):
@@ -163,6 +166,29 @@ def _workspace(nbytes, key):
     if t is None or t.numel() < nbytes:
         t = torch.zeros(max(nbytes, 256), dtype=torch.uint8, device="cuda")
         _ws_cache[key] = t
+    return t
+
+
+_dot_ws = {}
+_dot_ws_lock = threading.Lock()
+_DOT_STREAMS = 64  # workspaces of dots kept at a time, a few hundred KiB to 2 MiB each
+
+
+def _dot_workspace(nbytes, dev, stream):
+    """Zero-filled workspace for a dot on this stream.  Dots are asynchronous: those of
+    one stream run one after another and share a workspace (counters, accumulators),
+    those of two streams overlap and must not.  A dot that is being captured has one
+    of its own: its graph may be replayed on any stream."""
+    if torch._C._cuda_isCurrentStreamCapturing():
+        return torch.zeros(nbytes, dtype=torch.uint8, device="cuda")
+    t = _dot_ws.get((dev, stream))
+    if t is None or t.numel() < nbytes:
+        t = torch.zeros(max(nbytes, 256), dtype=torch.uint8, device="cuda")
+        with _dot_ws_lock:  # one that is dropped returns to the allocator in its stream's order
+            _dot_ws.pop((dev, stream), None)
+            while len(_dot_ws) >= _DOT_STREAMS:
+                del _dot_ws[next(iter(_dot_ws))]
+            _dot_ws[(dev, stream)] = t
     return t
 
 
@@ -253,10 +279,11 @@ def exdot(x, y, dots=EXACT, block=0, grid=0, fpe=0):
     x, y = _dev(x), _dev(y)
     n = x.numel()
     assert n == y.numel()
-    ws = _workspace(_dot_bytes(n, block, grid, fpe), ("dot", x.device.index))
+    dev, stream = _here()
+    ws = _dot_workspace(_dot_bytes(n, block, grid, fpe), dev, stream)
     out = x.new_empty(())
     code = lib.rpk_exdot(n, x.data_ptr(), y.data_ptr(), out.data_ptr(), int(dots), _launch_ref(block, grid, fpe),
-                         ws.data_ptr(), ws.numel(), _raw_stream())
+                         ws.data_ptr(), ws.numel(), stream)
     if code:
         _check(code, "rpk_exdot")
     return out
@@ -291,11 +318,12 @@ def fpedot(x, y, block=0, grid=0):
     L = _launch(block, grid, 0)
     nb = ctypes.c_size_t()
     _check(lib.rpk_exdot_workspace_bytes(x.numel(), ctypes.byref(L), ctypes.byref(nb)), "workspace")
-    ws = _workspace(nb.value, ("dot", x.device.index))
+    dev, stream = _here()
+    ws = _dot_workspace(nb.value, dev, stream)
     out = torch.empty((), dtype=torch.float64, device=x.device)
     lost = torch.empty((), dtype=torch.int32, device=x.device)
     _check(lib.rpk_fpedot(x.numel(), _ptr(x), _ptr(y), _ptr(out), _ptr(lost), ctypes.byref(L), _ptr(ws),
-                          ws.numel(), _stream()), "rpk_fpedot")
+                          ws.numel(), stream), "rpk_fpedot")
     return out, lost
 
 
