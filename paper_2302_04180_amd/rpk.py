@@ -4,6 +4,7 @@ Every operation runs in the library's HIP kernels; torch is used for device
 memory and streams.  If the shared library is missing the import of this module
 fails: there is no CPU fallback.
 """
+import contextlib
 import ctypes
 import functools
 import os
@@ -158,10 +159,14 @@ def _launch_ref(block, grid, fpe):
 
 
 _ws_cache = {}
+# Held from the look-up of a solve's workspace to the end of the solve, which waits
+# for its stream: a thread on another stream must not get a workspace whose zero fill
+# is still queued.  The library runs one solve at a time in any case.
+_solve_lock = threading.Lock()
 
 
 def _workspace(nbytes, key):
-    """Zero-filled device workspace, reused (the library leaves it reusable)."""
+    """Zero-filled device workspace of a solve, reused (the library leaves it reusable)."""
     t = _ws_cache.get(key)
     if t is None or t.numel() < nbytes:
         t = torch.zeros(max(nbytes, 256), dtype=torch.uint8, device="cuda")
@@ -363,13 +368,13 @@ def solve(A, b, x0=None, tol=1e-8, maxit=500, variant=STD, dots=EXACT, block=0, 
     _check(lib.rpk_solve_workspace_bytes(A.handle, ctypes.byref(o), ctypes.byref(nb)), "workspace")
     if workspace is not None:
         assert workspace.is_cuda and workspace.dtype == torch.uint8 and workspace.numel() >= nb.value
-        ws = workspace
     else:
         assert not resume, "resuming needs the workspace of the interrupted solve"
-        ws = _workspace(nb.value, ("solve", b.device.index))
     info = Info()
-    code = lib.rpk_solve(A.handle, _ptr(b), _ptr(x), ctypes.byref(o), _ptr(ws), ws.numel(), _stream(),
-                         ctypes.byref(info))
+    with contextlib.nullcontext() if workspace is not None else _solve_lock:
+        ws = _workspace(nb.value, ("solve", b.device.index)) if workspace is None else workspace
+        code = lib.rpk_solve(A.handle, _ptr(b), _ptr(x), ctypes.byref(o), _ptr(ws), ws.numel(), _stream(),
+                             ctypes.byref(info))
     if code in (1, 2, 3):
         _check(code, "rpk_solve")
     res = _info_dict(info)
@@ -416,9 +421,10 @@ def solve_batched(As, bs, x0s=None, tol=1e-8, maxit=500, variant=STD, dots=EXACT
     xa = (ctypes.c_void_p * ns)(*[x.data_ptr() for x in xs])
     nb = ctypes.c_size_t()
     _check(lib.rpk_solve_batched_workspace_bytes(ns, Aa, ctypes.byref(o), ctypes.byref(nb)), "workspace")
-    ws = _workspace(nb.value, ("batch", bs[0].device.index))
     infos = (Info * ns)()
-    code = lib.rpk_solve_batched(ns, Aa, ba, xa, ctypes.byref(o), _ptr(ws), ws.numel(), _stream(), infos)
+    with _solve_lock:
+        ws = _workspace(nb.value, ("batch", bs[0].device.index))
+        code = lib.rpk_solve_batched(ns, Aa, ba, xa, ctypes.byref(o), _ptr(ws), ws.numel(), _stream(), infos)
     if code in (1, 2, 3):
         _check(code, "rpk_solve_batched")
     out = [_info_dict(infos[k]) for k in range(ns)]
