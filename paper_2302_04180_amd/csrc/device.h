@@ -208,6 +208,41 @@ __device__ __forceinline__ void decode(double x, bool& neg, unsigned long long& 
   }
 }
 
+// The exact value of a finite double c as three digit values on the long-
+// accumulator grid: c = D[0] G(d) + D[1] G(d+1) + D[2] G(d+2) with G(k) =
+// 2^(32 k + SA_LSB) and d the returned digit, taken from the two's complement of
+// the signed significand shifted into place, so D[0], D[1] lie in [0, 2^32) and
+// D[2] = floor(value / G(d+2)) is small and signed; c = +-0 gives three zeros.
+// d depends only on the exponent field, so it never decreases with |c|.
+__device__ __forceinline__ int digits3(double c, long long (&D)[3]) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(c);
+  const int ex = (int)((b >> 52) & 0x7ffull);
+  const unsigned long long m = (b & ((1ull << 52) - 1ull)) | ((unsigned long long)(ex != 0) << 52);
+  const long long sm = (b >> 63) ? -(long long)m : (long long)m;
+  const int pos = (ex > 1 ? ex : 1) - 1075 - SA_LSB;  // grid bit of the significand's last place
+  const int sh = pos & 31;
+  const unsigned long long lo = (unsigned long long)sm << sh;
+  D[0] = (long long)(lo & 0xffffffffull);
+  D[1] = (long long)(lo >> 32);
+  D[2] = (sm >> 32) >> (32 - sh);  // floor(sm 2^sh / 2^64): shifts of 32 + (32 - sh) bits
+  return pos >> 5;
+}
+
+__device__ __forceinline__ void lds_add(long long* p, long long v) {
+  __hip_atomic_fetch_add((unsigned long long*)p, (unsigned long long)v, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// acc (in LDS) += the finite double x, as at most three digits
+__device__ __forceinline__ void sa_add_double(long long* acc, double x) {
+  if (x == 0.0) return;
+  long long D[3];
+  const int d = digits3(x, D);
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+    if (D[j] != 0) lds_add(acc + d + j, D[j]);
+}
+
 // exact a*b of finite doubles through the 106-bit integer product
 __device__ __forceinline__ void sa_add_prod(long long* acc, double a, double b) {
   if (a == 0.0 || b == 0.0) return;
@@ -385,6 +420,16 @@ __device__ inline double sa_round_wave(long long* acc) {
   return __shfl(r, 0, 64);
 }
 
+// Whole wavefront: round the long accumulator `acc`, every lane returns the result.
+__device__ __forceinline__ double sa_round(long long* acc) {
+  int lo, hi;
+  wave_digit_range(acc, SA_D, lo, hi);
+  if (hi < 0) return 0.0;
+  const int lane = threadIdx.x & 63;
+  if (hi - lo <= 61) return round_lanes(lane <= hi - lo ? acc[lo + lane] : 0ll, lo);
+  return sa_round_wave(acc);  // digits further apart than a wavefront holds
+}
+
 // Whole wavefront: rewrite acc so that its non-zero digits below the top one lie
 // in [0, 2^32) (same value); returns the digit range [lo, hi] that may be non-zero.
 __device__ inline void sa_normalize_wave(long long* acc, int& lo, int& hi) {
@@ -413,46 +458,62 @@ __device__ inline void sa_normalize_wave(long long* acc, int& lo, int& hi) {
 // product was outside the exact twoprod range) and was added in plain FP64.
 enum : int { F_SA = 1, F_NONFINITE = 2, F_LOST = 4 };
 
-// acc += a*b exactly.  Leftovers and extreme products go to the LDS long
-// accumulator `sa`; `flag` collects F_SA / F_NONFINITE.
+// What an insertion of a product left over: acc_left adds it to the long accumulator.
+struct Left {
+  double l1, l2;
+  bool extreme;  // the product is out of the range of twoprod and was not inserted
+  __device__ __forceinline__ bool any() const { return l1 != 0.0 || l2 != 0.0 || extreme; }
+};
+
 template <int N>
-__device__ __forceinline__ void acc_prod(Fpe<N>& f, double a, double b, long long* sa, int* flag) {
+__device__ __forceinline__ Left acc_insert(Fpe<N>& f, double a, double b) {
   double p = a * b;
   double e = fma(a, b, -p);
   const double ap = fabs(p);
   const bool ok = ap >= kProdLo && ap < kProdHi;
-  bool extreme = false;
-  if (__ballot(!ok)) {  // out-of-range products insert 0 and are handled below; zeros need nothing
-    extreme = !ok && !(p == 0.0 && (a == 0.0 || b == 0.0));
+  Left r;
+  r.extreme = false;
+  if (__ballot(!ok)) {  // out-of-range products insert 0; zeros need nothing
+    r.extreme = !ok && !(p == 0.0 && (a == 0.0 || b == 0.0));
     p = ok ? p : 0.0;
     e = ok ? e : 0.0;
   }
-  const double l1 = fpe_add_all<N, 0>(f, p);
-  const double l2 = fpe_add_all<N, (N > 1 ? 1 : 0)>(f, e);
-  if (l1 != 0.0 || l2 != 0.0 || extreme) {
-    const bool finite = isfinite(a) && isfinite(b);
-    atomicOr(flag, extreme && !finite ? F_NONFINITE : F_SA);
-#pragma unroll 1  // one body for l1, l2 and the product (rare, inlined often)
-    for (int k = 0; k < 3; ++k) {
-      const double x = k == 0 ? l1 : k == 1 ? l2 : (extreme && finite) ? a : 0.0;
-      if (x == 0.0) continue;
-      bool neg;
-      unsigned long long m, hi = 0ull;
-      int e;
-      decode(x, neg, m, e);
-      if (k == 2) {  // the exact product
-        bool nb;
-        unsigned long long mb;
-        int eb;
-        decode(b, nb, mb, eb);
-        hi = __umul64hi(m, mb);
-        m *= mb;
-        neg = neg != nb;
-        e += eb;
-      }
-      sa_add_int(sa, neg, hi, m, e);
+  r.l1 = fpe_add_all<N, 0>(f, p);
+  r.l2 = fpe_add_all<N, (N > 1 ? 1 : 0)>(f, e);
+  return r;
+}
+
+// Called by the lanes with r.any().  Every insertion comes here where the factors'
+// exponents are spread over more bits than the FPE holds, so it is kept straight:
+// six LDS additions at most, and one value of the flag for all lanes (with one that
+// differed from lane to lane the compiler walked the lanes one by one).  10M
+// elements, exponents of +-20 / 60 / 480: 76 / 149 / 184 us with that walk and a loop
+// over the digits, 51 / 62 / 67 so.  Rolled: one body for the two leftovers, in kernels
+// that have few registers left beside a row of the matrix (batched D: 92 bytes of
+// spills a lane without it, 40 with it; the batch of 256 systems 40.4 and 39.1 ms).
+template <bool Rolled>
+__device__ __forceinline__ void acc_left(const Left& r, double a, double b, long long* sa, int* flag) {
+  const bool nan = r.extreme && !(isfinite(a) && isfinite(b));
+  atomicOr(flag, (__ballot(nan) ? F_NONFINITE : 0) | (__ballot(!nan) ? F_SA : 0));
+  if (!r.extreme) {
+    if constexpr (Rolled) {
+#pragma unroll 1
+      for (int k = 0; k < 2; ++k) sa_add_double(sa, k ? r.l2 : r.l1);
+    } else {
+      sa_add_double(sa, r.l1);
+      sa_add_double(sa, r.l2);
     }
+  } else if (!nan) {
+    sa_add_prod(sa, a, b);
   }
+}
+
+// acc += a*b exactly.  Leftovers and extreme products go to the LDS long
+// accumulator `sa`; `flag` collects F_SA / F_NONFINITE.
+template <int N>
+__device__ __forceinline__ void acc_prod(Fpe<N>& f, double a, double b, long long* sa, int* flag) {
+  const Left r = acc_insert(f, a, b);
+  if (r.any()) acc_left<true>(r, a, b, sa, flag);
 }
 
 // ---------------------------------------------------------------------------

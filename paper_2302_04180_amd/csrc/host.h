@@ -84,8 +84,10 @@ constexpr int64_t kTinySolveRows = 1024;
 constexpr int64_t kShortSolveRows = 4096;
 constexpr int64_t kSmallSolveGroups = 248;
 // Dots of at most this many elements with the automatic launch shape run in one
-// workgroup: 1,000 elements 4.3 us against 5.4 in two workgroups of 512
-constexpr int64_t kOneGroupDot = 4096;
+// workgroup: 1,000 elements 4.3 us against 5.4 in two workgroups of 512.  With FPEs of
+// one component nearly every term goes to the long accumulator, which one workgroup
+// adds to at 3 us for 1,024 elements (a call of 4,096: 16.0 us, in eight workgroups 8.4).
+constexpr int64_t kOneGroupDot = 4096, kOneGroupDotFpe1 = 1024;
 // Dots of kMidDot to kLongDot - 1 elements with the automatic launch shape take
 // workgroups of 512 threads for 1,024 elements each, at most kSmallSolveGroups: a
 // call with up to 512 workgroups of 512 (256 of 1,024 from 262,144 elements on) and

@@ -677,8 +677,7 @@ __device__ inline double row_slow(const Src& src, int l, const Gth& gx, int w, l
   const bool any_nf = __ballot(nf) != 0ull;
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
   __builtin_amdgcn_wave_barrier();
-  double r = 0.0;
-  r = sa_round_wave(wsa);
+  double r = sa_round(wsa);  // with the digits one a lane: in lane 0 alone, rows of wide exponents took 1,225 us (100^3), 514 so
   if (any_nf) r = __longlong_as_double(0x7ff8000000000000ll);
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
   __builtin_amdgcn_wave_barrier();
@@ -839,36 +838,11 @@ __device__ __forceinline__ long long wave_sum_i64(long long v) {
   return v;
 }
 
-// The exact value of a finite double c as three digit values on the long-
-// accumulator grid: c = D[0] G(d) + D[1] G(d+1) + D[2] G(d+2) with G(k) =
-// 2^(32 k + SA_LSB) and d the returned digit, taken from the two's complement of
-// the signed significand shifted into place, so D[0], D[1] lie in [0, 2^32) and
-// D[2] = floor(value / G(d+2)) is small and signed; c = +-0 gives three zeros.
-// d depends only on the exponent field, so it never decreases with |c|.
-__device__ __forceinline__ int digits3(double c, long long (&D)[3]) {
-  const unsigned long long b = (unsigned long long)__double_as_longlong(c);
-  const int ex = (int)((b >> 52) & 0x7ffull);
-  const unsigned long long m = (b & ((1ull << 52) - 1ull)) | ((unsigned long long)(ex != 0) << 52);
-  const long long sm = (b >> 63) ? -(long long)m : (long long)m;
-  const int pos = (ex > 1 ? ex : 1) - 1075 - SA_LSB;  // grid bit of the significand's last place
-  const int sh = pos & 31;
-  const unsigned long long lo = (unsigned long long)sm << sh;
-  D[0] = (long long)(lo & 0xffffffffull);
-  D[1] = (long long)(lo >> 32);
-  D[2] = (sm >> 32) >> (32 - sh);  // floor(sm 2^sh / 2^64): shifts of 32 + (32 - sh) bits
-  return pos >> 5;
-}
-
 // The highest grid digit that digits3 gives a non-zero value for any double of
 // magnitude at most |c| (c != 0).
 __device__ __forceinline__ int digits3_top(double c) {
   const int ex = (int)(((unsigned long long)__double_as_longlong(c) >> 52) & 0x7ffull);
   return (((ex > 1 ? ex : 1) - 1075 - SA_LSB) >> 5) + 2;
-}
-
-__device__ __forceinline__ void lds_add(long long* p, long long v) {
-  __hip_atomic_fetch_add((unsigned long long*)p, (unsigned long long)v, __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // This lane's FPE into its window row (digit 0 = grid digit d0; d0 + WIN - 1 is
@@ -1135,14 +1109,7 @@ template <int N, int K>
 __device__ __forceinline__ void block_round_sa(const Shm<N>& s) {
   const int nw = blockDim.x >> 6, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   for (int j = w; j < K; j += nw) {  // one wave per dot
-    long long* tot = s.sa + (size_t)j * SA_D;
-    int lo, hi;
-    wave_digit_range(tot, SA_D, lo, hi);
-    double r = 0.0;
-    if (hi >= 0) {
-      if (hi - lo <= 61) r = round_lanes(lane <= hi - lo ? tot[lo + lane] : 0ll, lo);
-      else r = sa_round_wave(tot);  // digits further apart than a wavefront holds
-    }
+    const double r = sa_round(s.sa + (size_t)j * SA_D);
     if (lane == 0) s.res[j] = (s.misc[1 + j] & F_NONFINITE) ? __longlong_as_double(0x7ff8000000000000ll) : r;
   }
   __syncthreads();
@@ -1404,8 +1371,24 @@ __global__ void __launch_bounds__(1024) k_dot(long long n, const double* __restr
       a[u] = x[i + u * (long long)blockDim.x];
       b[u] = y[i + u * (long long)blockDim.x];
     }
+    if constexpr (N > 0 && N != LW8) {
+      // what two insertions left over is added behind them, in one body: with one
+      // behind every insertion 40M elements took 120 us, so 115
 #pragma unroll
-    for (int u = 0; u < U; ++u) d[0].add(a[u], b[u], s.sa, &s.flag[0]);
+      for (int v = 0; v < U; v += 2) {
+        const Left l = acc_insert(d[0].f, a[v], b[v]), r = acc_insert(d[0].f, a[v + 1], b[v + 1]);
+        if (l.any() || r.any()) {
+#pragma unroll 1
+          for (int k = 0; k < 2; ++k) {
+            const Left& w = k ? r : l;
+            if (w.any()) acc_left<false>(w, a[v + k], b[v + k], s.sa, &s.flag[0]);
+          }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) d[0].add(a[u], b[u], s.sa, &s.flag[0]);
+    }
   }
   for (; i < hi; i += blockDim.x) d[0].add(x[i], y[i], s.sa, &s.flag[0]);
   if (gridDim.x == 1) {

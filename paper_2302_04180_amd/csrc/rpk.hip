@@ -80,7 +80,7 @@ rpk_status resolve(const rpk_launch* L, int64_t n, Cfg* c, bool scattered = fals
 rpk_status dot_shape(const rpk_launch* L, int64_t n, Cfg* c, bool light = false) {
   RET_IF(resolve(L, n, c));
   if (L && (L->block != 0 || L->grid != 0)) return RPK_OK;
-  if (n <= kOneGroupDot && !light) {
+  if (n <= (c->fpe > 1 ? kOneGroupDot : kOneGroupDotFpe1) && !light) {
     c->block = 1024;
     c->grid = 1;
   } else if (n >= kMidDot && n < kLongDot) {
