@@ -325,6 +325,14 @@ rpk_status rpk_server_get_stats(const rpk_server* s, rpk_server_stats* out);
 /* Finish every submitted request, stop the worker, free the budget. */
 rpk_status rpk_server_destroy(rpk_server* s);
 
+/* Test hook (host only, no device work): how the library holds A and multiplies by
+ * it.  form[0]: rows of its row dictionary (0: a SELL-64 copy); form[1]: elements of
+ * the operand window that an exact rpk_exspmv with this launch (NULL = defaults) keeps
+ * in LDS (0: none); form[2]: 1 if its rows try the certified sum first; form[3]:
+ * kernels of one iteration of the standard loop with exact dots, in launch shapes of
+ * several workgroups. */
+rpk_status rpk_matrix_form(const rpk_matrix* A, const rpk_launch* launch, int32_t form[4]);
+
 /* Test hook (host only, no device work): the tile table rpk_solve_batched
  * builds for systems of n[0..nsys-1] rows and `tile` rows per tile, every system
  * on one XCD (the solver cuts systems over several where this leaves XCDs idle).  tiles

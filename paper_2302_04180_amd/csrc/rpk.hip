@@ -851,6 +851,18 @@ rpk_status rpk_solve(const rpk_matrix* A, const double* b, double* x, const rpk_
   return (rpk_status)h.status;
 }
 
+rpk_status rpk_matrix_form(const rpk_matrix* A, const rpk_launch* launch_cfg, int32_t form[4]) {
+  if (!A || !form) return RPK_ERR_ARG;
+  Cfg c;
+  RET_IF(resolve(launch_cfg, A->n, &c, A->sdif != nullptr));
+  const int loop = std_loop(A, RPK_STD, RPK_DOT_EXACT);
+  form[0] = A->np ? A->np - 1 : 0;  // the last one is the empty row
+  form[1] = window_for(A, c.fpe, 0, c.grid, c.block);
+  form[2] = A->cert;
+  form[3] = loop == LOOP3 ? 3 : loop == LOOP4 ? 4 : 5;
+  return RPK_OK;
+}
+
 rpk_status rpk_device_divsqrt(int64_t n, const double* a, const double* b, double* q, double* r, void* stream) {
   if (n < 0 || (n > 0 && (!a || !b || !q || !r))) return RPK_ERR_ARG;
   if (n == 0) return RPK_OK;

@@ -61,7 +61,7 @@ EXPORTS = ["rpk_version", "rpk_status_str", "rpk_matrix_create", "rpk_matrix_des
            "rpk_exspmv", "rpk_solve_workspace_bytes", "rpk_solve", "rpk_batched_check",
            "rpk_solve_batched_workspace_bytes", "rpk_solve_batched", "rpk_server_create", "rpk_server_footprint", "rpk_server_submit",
            "rpk_server_poll", "rpk_server_wait", "rpk_server_get_stats", "rpk_server_destroy",
-           "rpk_plan_tiles", "rpk_device_divsqrt"]
+           "rpk_plan_tiles", "rpk_matrix_form", "rpk_device_divsqrt"]
 
 _lib = None
 
@@ -101,6 +101,7 @@ def load(path=LIB_PATH):
     lib.rpk_server_get_stats.argtypes = [P, ctypes.POINTER(ServerStats)]
     lib.rpk_server_destroy.argtypes = [P]
     lib.rpk_plan_tiles.argtypes = [I32, P, I32, P, I64, ctypes.POINTER(I64)]
+    lib.rpk_matrix_form.argtypes = [P, ctypes.POINTER(Launch), ctypes.POINTER(I32)]
     lib.rpk_device_divsqrt.argtypes = [I64, P, P, P, P, P]
     for name in EXPORTS[2:]:
         getattr(lib, name).restype = I32
@@ -246,6 +247,14 @@ class Matrix:
         torch.cuda.synchronize()
         _copy_device(p.value, out)
         return out
+
+    def form(self, block=0, grid=0, fpe=0):
+        """How the library holds this matrix (host only): rows of its dictionary, LDS window
+        of an exspmv with this launch, certified rows, kernels of a standard iteration."""
+        out = (ctypes.c_int32 * 4)()
+        L = _launch(block, grid, fpe)
+        _check(load().rpk_matrix_form(self.handle, ctypes.byref(L), out), "rpk_matrix_form")
+        return dict(zip(("dictionary", "window", "certified", "std_kernels"), out))
 
     def close(self):
         if self.handle:
