@@ -30,7 +30,8 @@ struct rpk_matrix {
   rpk::PatEnt* pat = nullptr;
   int np = 0, pw = 0;
   int cert = 0;                    // rows try the certified sum (see Csr)
-  int xlo = 0, xhi = 0, xlsb = 0;
+  int* slim = nullptr;             // limits of slices and rows, behind sptr in its allocation
+  signed char* rlsb = nullptr;
   int unif = 0;                    // every dinv_i has the bits of du (see Csr)
   double du = 0.0;
 };
@@ -119,7 +120,7 @@ inline bool records_fit(int64_t records, int64_t lanes, int fpe) {
 }
 
 inline Csr csr_of(const rpk_matrix* A) {
-  return Csr{A->sptr, A->scol, A->sval, A->dinv, (int)A->n, A->cert, A->xlo, A->xhi, A->xlsb, 0, A->unif, A->du,
+  return Csr{A->sptr, A->scol, A->sval, A->dinv, (int)A->n, A->cert, A->slim, A->rlsb, 0, A->unif, A->du,
              A->pid, A->swid, A->pat, A->np, A->pw, A->sdif, A->wlo, A->whi, 0};
 }
 

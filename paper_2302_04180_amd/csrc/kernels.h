@@ -42,9 +42,10 @@ enum : int { ST_OK = 0, ST_NONFINITE = 5, ST_NOT_CONVERGED = 6, ST_BREAKDOWN = 7
 
 // An entry of the row dictionary (Csr::pid): value and 8 (column - row), the
 // distance in bytes between the operand's element and the row's own.
+// A dictionary row's first entry holds its limits for the certified sum (cert_pack).
 struct __align__(16) PatEnt {
   double a;
-  int off8, pad;
+  int off8, lim;
 };
 // Dictionary rows are padded with (0, own element) to a multiple of four
 // entries, so that a batch reads no entry behind them, and by one more, so that
@@ -68,9 +69,12 @@ struct Csr {
   const double* dinv;
   int n;
   // rows first try the certified row sum (decided once per matrix at creation
-  // by a probe; every path gives the same bits); xlo, xhi, xlsb: see row_cert
+  // by a probe; every path gives the same bits); with the SELL copy, the limits of
+  // slice s are slim[s] (range) and of row i rlsb[i]: a word a row cost 1.0 us of the
+  // 32 of an SpMV of 128^3 rows and 14.6M entries
   int cert;
-  int xlo, xhi, xlsb;
+  const int* slim;          // [nslices]
+  const signed char* rlsb;  // [64 nslices]
   // slices [0, keep) read their entries with ordinary loads, which leave them
   // in the Infinity Cache for the next SpMV; the rest with non-temporal loads,
   // which leave the cache to the vectors (the same values either way)
@@ -560,15 +564,19 @@ __device__ __forceinline__ double tsum(double x, double y, double& err) {
 // and sums of a few short products often are (a quarter of the 7-point rows);
 // there the additions into q are usually exact, because all their operands are
 // multiples of one power of two: a_j is an odd multiple of at least 2^lsb (the
-// matrix's smallest, Csr::xlsb = lsb - 1), x_j a multiple of 2^(ex_j - 53) with
+// row's smallest), x_j a multiple of 2^(ex_j - 53) with
 // ex_j its binary exponent, so every p, e and t, and every partial sum of them,
 // is a multiple of U = 2^(lsb + min ex - 53).  A partial sum is at most
 // m = sum(|t| + |e|) in magnitude; where m < 2^52 U (the computed m is within
 // 2^-40 of it), it is below 2^53 U and hence a double: q is the exact sum, T =
 // s + q, and y = RN(s + q) = RN(T) whatever it is.  The products are in range
-// by the same exponents (Csr::xlo, xhi), which costs three integer operations
+// by the same exponents (CertLim), which costs three integer operations
 // an entry instead of four comparisons; an x_j = 0 counts as exponent 0, which
-// can only make the tests stricter.  Returns false -- the caller then takes the
+// can only make the tests stricter (it takes the exactness test from rows that hold
+// zeros beside values above some 2^48; leaving zeros out costs two operations an entry,
+// 76 -> 81 us of the 27-point 159^3 SpMV).  lsb and the exponents are the row's own: one entry of many bits in a matrix of short ones
+// (0.1 on a boundary row) then leaves the other rows certified, where with those of
+// the whole matrix it left none.  Returns false -- the caller then takes the
 // FPE path -- when neither shows it, or for a product out of range or a sum that
 // is non-finite or, for the bound, zero, tiny or huge.  When it returns true, y
 // is the correctly rounded row sum: the same bits as the FPE path.  Checking
@@ -581,15 +589,33 @@ struct CertSum {
   int elo = INT_MAX, ehi = INT_MIN;  // binary exponents of the x_j
 };
 
+// A row's limits as they are held.
+struct PatLim {
+  const PatEnt* row;  // its first entry, read again when the sums are there
+  __device__ __forceinline__ CertLim get() const { return cert_unpack(row->lim); }
+};
+// Both words are read at the start of a row: read behind the entries' addresses, the
+// gathers of an SpMV of 400,000 rows with 15 random columns took 39.0 us, so 36.0.
+struct SellLim {
+  int range;
+  signed char lsb;
+  __device__ __forceinline__ SellLim(const Csr& A, int sl, int i) : range(A.slim[sl]), lsb(A.rlsb[i]) {}
+  __device__ __forceinline__ CertLim get() const {
+    CertLim l = cert_unpack(range);
+    l.lsb1 = cert_unpack_lsb(lsb);
+    return l;
+  }
+};
+
 // Whether the sums prove y = RN(T) (terms: entries summed, padding included).
-__device__ __forceinline__ bool cert_finish(const Csr& A, const CertSum& c, int terms, double& y) {
+__device__ __forceinline__ bool cert_finish(const CertLim& lim, const CertSum& c, int terms, double& y) {
   const double s = c.s, q = c.q, m = c.m;
   y = s + (q + 0.0);  // +0 where both are zero
   const double ay = fabs(y);
-  const bool in = c.elo >= A.xlo && c.ehi <= A.xhi && ay < 0x1p1020;  // false for a NaN y
+  const bool in = c.elo >= lim.xlo && c.ehi <= lim.xhi && ay < 0x1p1020;  // false for a NaN y
   // every error term is 0 (the sum is s exactly, +0 for a zero row), or every
   // addition into q was exact
-  const bool exactq = m == 0.0 || __builtin_amdgcn_frexp_exp(m) <= c.elo + A.xlsb;
+  const bool exactq = m == 0.0 || __builtin_amdgcn_frexp_exp(m) <= c.elo + lim.lsb1;
   const double k = 2.0 * terms + 2.0;  // two error terms per entry
   const double E = (m * (k * 0x1p-53)) * (1.0 + 0x1p-28) + k * 0x1p-1074;
   const double z = y - s;
@@ -647,8 +673,8 @@ __device__ __forceinline__ void cert_batch(const Src& src, const Gth& gx, int j0
   }
 }
 
-template <class Src, class Gth>
-__device__ __forceinline__ bool row_cert(const Csr& A, const Src& src, const Gth& gx, int w, double& y) {
+template <class Lim, class Src, class Gth>
+__device__ __forceinline__ bool row_cert(const Lim& lim, const Src& src, const Gth& gx, int w, double& y) {
   CertSum c;
   int j0 = 0;
   for (; w - j0 > 4; j0 += 8) cert_batch<8>(src, gx, j0, w, c);
@@ -656,7 +682,7 @@ __device__ __forceinline__ bool row_cert(const Csr& A, const Src& src, const Gth
     cert_batch<4>(src, gx, j0, w, c);
     j0 += 4;
   }
-  return cert_finish(A, c, j0, y);
+  return cert_finish(lim.get(), c, j0, y);
 }
 
 // Exact slow path: the whole wavefront sums lane l's row in its private long
@@ -756,11 +782,12 @@ __device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, c
       const double* w0 = (const double*)s.pat + (first - R.lo);
       const WinSrc<false> kept{A.sval + off, A.sdif + off, w0};
       const WinSrc<true> passing{A.sval + off, A.sdif + off, w0};
+      const SellLim lim(A, sl, i);
       const auto p = pre(ok ? i : R.hi - 1);
       if constexpr (N == 0) {
         y = sl < A.keep ? row_plain(kept, gx, w) : row_plain(passing, gx, w);
       } else {
-        const bool cert = A.cert && (sl < A.keep ? row_cert(A, kept, gx, w, y) : row_cert(A, passing, gx, w, y));
+        const bool cert = A.cert && (sl < A.keep ? row_cert(lim, kept, gx, w, y) : row_cert(lim, passing, gx, w, y));
         if (__ballot(ok && !cert) != 0ull) y = rows_fpe<N>(kept, gx, w, ok, s.wsa);
       }
       use(i, ok, y, p);
@@ -771,7 +798,7 @@ __device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, c
       if constexpr (N == 0) {
         y = row_plain(src, gx, w);
       } else {
-        const bool cert = A.cert && row_cert(A, src, gx, w, y);
+        const bool cert = A.cert && row_cert(PatLim{s.pat + src.at0}, src, gx, w, y);
         if (__ballot(ok && !cert) != 0ull) y = rows_fpe<N>(src, gx, w, ok, s.wsa);
       }
       use(i, ok, y, p);
@@ -780,11 +807,12 @@ __device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, c
       const int w = (int)((A.sptr[sl + 1] - off) >> 6);
       const SellSrc<false> kept{A.sval + off, A.scol + off};
       const SellSrc<true> passing{A.sval + off, A.scol + off};
+      const SellLim lim(A, sl, i);
       const auto p = pre(ok ? i : R.hi - 1);
       if constexpr (N == 0) {
         y = sl < A.keep ? row_plain(kept, gx, w) : row_plain(passing, gx, w);
       } else {
-        const bool cert = A.cert && (sl < A.keep ? row_cert(A, kept, gx, w, y) : row_cert(A, passing, gx, w, y));
+        const bool cert = A.cert && (sl < A.keep ? row_cert(lim, kept, gx, w, y) : row_cert(lim, passing, gx, w, y));
         if (__ballot(ok && !cert) != 0ull) y = rows_fpe<N>(kept, gx, w, ok, s.wsa);
       }
       use(i, ok, y, p);

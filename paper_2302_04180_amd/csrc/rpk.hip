@@ -324,7 +324,10 @@ constexpr int64_t kMaxBand = 16384;
 // SELL-64 copy of the validated CSR (prefix sum of the slice widths, padded fill)
 static rpk_status build_sell(rpk_matrix* A, const int* width, Band* band, hipStream_t s) {
   const int n = (int)A->n, ns = A->nslices;
-  if (hipMalloc((void**)&A->sptr, (size_t)(ns + 1) * sizeof(long long)) != hipSuccess) return RPK_ERR_NOMEM;
+  const size_t o_slim = (size_t)(ns + 1) * sizeof(long long), o_rlsb = o_slim + (size_t)ns * sizeof(int);
+  if (hipMalloc((void**)&A->sptr, o_rlsb + (size_t)ns * 64) != hipSuccess) return RPK_ERR_NOMEM;
+  A->slim = (int*)((char*)A->sptr + o_slim);
+  A->rlsb = (signed char*)((char*)A->sptr + o_rlsb);
   long long total = 0;
   hipLaunchKernelGGL(k_slice_scan, dim3(1), dim3(1024), 0, s, width, ns, A->sptr);
   HIPCHK(hipGetLastError());
@@ -337,7 +340,7 @@ static rpk_status build_sell(rpk_matrix* A, const int* width, Band* band, hipStr
     return RPK_ERR_NOMEM;
   const long long rows = (long long)ns * 64;
   hipLaunchKernelGGL(k_fill_sell, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, A->rp, A->ci, A->v, n, ns,
-                     (const long long*)A->sptr, A->scol, A->sval);
+                     (const long long*)A->sptr, A->scol, A->sval, A->slim, A->rlsb);
   hipLaunchKernelGGL(k_band, dim3((unsigned)std::min(512, (ns + 3) / 4)), dim3(256), 0, s, n, ns,
                      (const long long*)A->sptr, (const int*)A->scol, band);
   HIPCHK(hipGetLastError());
@@ -417,7 +420,7 @@ static rpk_status check_and_lay_out(rpk_matrix* A, const Setup& u, hipStream_t s
   if (hflags[0]) return RPK_ERR_ARG;  // row_ptr unusable: do not read the rows
   const unsigned G = (unsigned)std::min(4096, (ns + 3) / 4);
   hipLaunchKernelGGL(k_setup_rows, dim3(G), dim3(256), 0, s, A->rp, A->ci, A->v, n, ns, A->dinv, u.width, u.words,
-                     u.flags + 1, u.t);
+                     u.flags + 1);
   hipLaunchKernelGGL(k_slice_max, dim3(1), dim3(1024), 0, s, u.width, ns, &u.t->wide);
   hipLaunchKernelGGL(k_pat_find, dim3((unsigned)std::min<int64_t>(512, (A->n + 255) / 256)), dim3(256), 0, s, u.words,
                      n, u.t);
@@ -428,7 +431,7 @@ static rpk_status check_and_lay_out(rpk_matrix* A, const Setup& u, hipStream_t s
   PatHash found;
   unsigned differ = 0;
   double d0 = 0.0;
-  constexpr size_t kTail = offsetof(PatHash, elo);
+  constexpr size_t kTail = offsetof(PatHash, count);
   HIPCHK(hipMemcpyAsync(hflags + 1, u.flags + 1, sizeof(int), hipMemcpyDeviceToHost, s));
   HIPCHK(hipMemcpyAsync((char*)&found + kTail, (char*)u.t + kTail, sizeof(PatHash) - kTail, hipMemcpyDeviceToHost, s));
   HIPCHK(hipMemcpyAsync(&differ, u.counts + 2, sizeof(unsigned), hipMemcpyDeviceToHost, s));
@@ -441,11 +444,6 @@ static rpk_status check_and_lay_out(rpk_matrix* A, const Setup& u, hipStream_t s
   A->du = d0;
   RET_IF(build_dictionary(A, found, u.width, u.words, u.t, s));
   if (!A->np) RET_IF(build_sell(A, u.width, (Band*)(u.counts + 4), s));
-  // x_j for which every product is in the exact range of twoprod (kProdLo,
-  // kProdHi): 2^(ea + ex - 2) <= |a x| < 2^(ea + ex)
-  A->xlo = -966 - found.elo;
-  A->xhi = 989 - found.ehi;
-  A->xlsb = found.lsb - 1;
   // Whether rows should try the certified row sum first: probe it on a
   // pseudo-random vector; not when more than one slice in eight has a row that it
   // cannot certify (results are the same either way).

@@ -19,14 +19,30 @@ __global__ void k_check_rowptr(const int* rp, int n, int nnz, int* flags) {
   if (bad) atomicOr(flags, CHK_ARG);
 }
 
-// What a creation learns of the matrix: its distinct rows and the range of its values.
+// What a creation learns of the matrix: its distinct rows.
 constexpr int kPatMax = 255;    // distinct rows (an id is a byte; the last id is the empty row)
 constexpr int kPatSlots = 1024; // hash slots
+
+// Limits of a row for the certified sum (CertLim), from its entries one after another.
+struct RowLimits {
+  int elo = INT_MAX, ehi = INT_MIN, lsb = INT_MAX;
+  __device__ __forceinline__ void add(double v) {
+    if (v == 0.0) return;
+    bool neg;
+    unsigned long long mant;
+    int e;
+    decode(v, neg, mant, e);
+    const int top = e + 64 - __clzll((long long)mant);
+    lsb = min(lsb, e + __ffsll((long long)mant) - 1);
+    elo = min(elo, top);
+    ehi = max(ehi, top);
+  }
+  __device__ __forceinline__ int pack() const { return elo == INT_MAX ? cert_pack(0, 0, 0) : cert_pack(elo, ehi, lsb); }
+};
 
 struct PatHash {
   unsigned long long key[kPatSlots];  // 0 = free
   int rep[kPatSlots];                 // lowest row with that hash; k_pat_table: -1 - id
-  int elo, ehi, lsb;                  // of the non-zero values: smallest / largest binary exponent, lowest set bit
   int count;                          // distinct hashes so far (counts on past kPatMax)
   int wide;                           // widest slice
   int fail;                           // a row differs from its representative
@@ -64,14 +80,13 @@ struct SliceRows {
 // and, for the row dictionary, each row's hash over its (position, column - row,
 // value).  n + 64 entries of hash.
 __global__ void __launch_bounds__(256) k_setup_rows(const int* rp, const int* ci, const double* v, int n, int nslices,
-                                                    double* dinv, int* width, unsigned long long* hash, int* flags,
-                                                    PatHash* t) {
+                                                    double* dinv, int* width, unsigned long long* hash, int* flags) {
   __shared__ SliceRows R[4];
   __shared__ unsigned long long h[4][64];
   __shared__ double diag[4][64];
   __shared__ int cnt[4][64];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  int fl = 0, elo = INT_MAX, ehi = INT_MIN, lsb = INT_MAX;
+  int fl = 0;
   for (int s = blockIdx.x * 4 + w; s < nslices; s += gridDim.x * 4) {
     R[w].load(rp, n, s);
     h[w][lane] = 0ull;
@@ -83,17 +98,7 @@ __global__ void __launch_bounds__(256) k_setup_rows(const int* rp, const int* ci
       const int c = ci[e];
       const double val = v[e];
       if (c < 0 || c >= n) fl |= CHK_ARG;
-      if (!isfinite(val)) {
-        fl |= CHK_NONFINITE;
-      } else if (val != 0.0) {
-        bool neg;
-        unsigned long long mant;
-        int e2;
-        decode(val, neg, mant, e2);
-        lsb = min(lsb, e2 + __ffsll((long long)mant) - 1);
-        elo = min(elo, e2 + 64 - __clzll((long long)mant));
-        ehi = max(ehi, e2 + 64 - __clzll((long long)mant));
-      }
+      if (!isfinite(val)) fl |= CHK_NONFINITE;
       if (c == r) {
         atomicAdd(&cnt[w][l], 1);
         diag[w][l] = val;
@@ -116,15 +121,6 @@ __global__ void __launch_bounds__(256) k_setup_rows(const int* rp, const int* ci
     __builtin_amdgcn_wave_barrier();
   }
   if (fl) atomicOr(flags, fl);
-  elo = -wave_max_int(-elo);
-  ehi = wave_max_int(ehi);
-  lsb = -wave_max_int(-lsb);
-  // most wavefronts have nothing new for the three words
-  if (lane == 0) {
-    if (elo < __hip_atomic_load(&t->elo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&t->elo, elo);
-    if (ehi > __hip_atomic_load(&t->ehi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&t->ehi, ehi);
-    if (lsb < __hip_atomic_load(&t->lsb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&t->lsb, lsb);
-  }
 }
 
 // *differ = 1 when some dinv_i does not have the bits of dinv_0 (Csr::unif)
@@ -171,25 +167,32 @@ __global__ void __launch_bounds__(1024) k_slice_scan(const int* width, int nslic
   if (threadIdx.x == 0) sptr[0] = 0;
 }
 
-// ... and the entries, padded with (0, own row); rows past n point at column 0.
+// ... and the entries, padded with (0, own row); rows past n point at column 0.  The
+// limits of each slice and row (CertLim).
 __global__ void k_fill_sell(const int* rp, const int* ci, const double* v, int n, int nslices, const long long* sptr,
-                            int* scol, double* sval) {
+                            int* scol, double* sval, int* slim, signed char* rlsb) {
   const long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= (long long)nslices * 64) return;
   const int s = (int)(r >> 6), lane = (int)(r & 63);
   const long long off = sptr[s];
   const int w = (int)((sptr[s + 1] - off) >> 6);
   const int k0 = (r < n) ? rp[r] : 0, len = (r < n) ? rp[r + 1] - rp[r] : 0;
+  RowLimits lim;
   for (int j = 0; j < w; ++j) {
     const long long at = off + 64ll * j + lane;
     if (j < len) {
+      const double a = v[k0 + j];
       scol[at] = ci[k0 + j];
-      sval[at] = v[k0 + j];
+      sval[at] = a;
+      lim.add(a);
     } else {
       scol[at] = (r < n) ? (int)r : 0;
       sval[at] = 0.0;
     }
   }
+  rlsb[r] = cert_pack_lsb(lim.lsb == INT_MAX ? 0 : lim.lsb);
+  const int elo = -wave_max_int(-lim.elo), ehi = wave_max_int(lim.ehi);  // the wavefront holds the slice
+  if (lane == 0) slim[s] = cert_pack(elo, ehi, 0);
 }
 
 // For the operand window (Csr::win): how far columns lie before and behind their
@@ -256,8 +259,6 @@ __global__ void __launch_bounds__(1024) k_pat_clear(PatHash* t) {
   }
   if (threadIdx.x == 0) {
     t->count = t->wide = t->fail = 0;
-    t->elo = t->lsb = INT_MAX;
-    t->ehi = INT_MIN;
   }
 }
 
@@ -328,7 +329,13 @@ __global__ void __launch_bounds__(1024) k_pat_table(const int* rp, const int* ci
     const int id = k / stride, j = k - id * stride;
     const int r = id < np - 1 ? byid[id] : 0;
     const int k0 = rp[r], len = id < np - 1 ? rp[r + 1] - k0 : 0;
-    pat[k] = j < len ? PatEnt{v[k0 + j], 8 * (ci[k0 + j] - r), 0} : PatEnt{0.0, 0, 0};
+    int lim = 0;
+    if (j == 0) {
+      RowLimits l;
+      for (int e = 0; e < len; ++e) l.add(v[k0 + e]);
+      lim = l.pack();
+    }
+    pat[k] = j < len ? PatEnt{v[k0 + j], 8 * (ci[k0 + j] - r), lim} : PatEnt{0.0, 0, lim};
   }
 }
 
@@ -405,11 +412,11 @@ __global__ void __launch_bounds__(256) k_cert_probe(Csr A, const double* __restr
     bool c;
     if (A.np) {  // the dictionary read from device memory
       const PatSrc src{A.pat, (unsigned)(row < A.n ? row : A.n - 1) * 8u, (int)A.pid[row] * pat_stride(A.pw)};
-      c = row_cert(A, src, GatherX{x}, A.swid[s], y);
+      c = row_cert(PatLim{A.pat + src.at0}, src, GatherX{x}, A.swid[s], y);
     } else {
       const long long off = A.sptr[s];
       const SellSrc<true> src{A.sval + off, A.scol + off};
-      c = row_cert(A, src, GatherX{x}, (int)((A.sptr[s + 1] - off) >> 6), y);
+      c = row_cert(SellLim(A, s, row), src, GatherX{x}, (int)((A.sptr[s + 1] - off) >> 6), y);
     }
     const bool fail = __ballot(row < A.n && !c) != 0ull;
     if (lane == 0) {

@@ -128,7 +128,7 @@ def _here():
 
 
 def _stream():
-    return ctypes.c_void_p(_here()[1])
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _ptr(t):
