@@ -341,6 +341,9 @@ static rpk_status build_sell(rpk_matrix* A, const int* width, Band* band, hipStr
   const long long rows = (long long)ns * 64;
   hipLaunchKernelGGL(k_fill_sell, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, A->rp, A->ci, A->v, n, ns,
                      (const long long*)A->sptr, A->scol, A->sval, A->slim, A->rlsb);
+  HIPCHK(hipGetLastError());
+  // a tiny matrix is in the L1 caches: no window, and 25 of 215 us saved here
+  if (A->n < kTinySolveRows) return RPK_OK;
   hipLaunchKernelGGL(k_band, dim3((unsigned)std::min(512, (ns + 3) / 4)), dim3(256), 0, s, n, ns,
                      (const long long*)A->sptr, (const int*)A->scol, band);
   HIPCHK(hipGetLastError());
@@ -364,11 +367,11 @@ static rpk_status build_sell(rpk_matrix* A, const int* width, Band* band, hipStr
 // LDS set aside for it (kPatEntries) and a workgroup must read far fewer bytes
 // for it than for its rows: at least 32 rows for each distinct one.  Byte
 // offsets of a column and a slice's width must fit 32 bits and a byte.
-// `found`: the counters k_pat_find and k_slice_max left.
-static rpk_status build_dictionary(rpk_matrix* A, const PatHash& found, const int* width,
+// `found`, `pw`: the counters k_pat_find and k_slice_max left.
+static rpk_status build_dictionary(rpk_matrix* A, int64_t found, int64_t pw, const int* width,
                                    const unsigned long long* hash, PatHash* t, hipStream_t s) {
-  const int64_t np = (int64_t)found.count + 1, pw = found.wide;
-  if (found.count > kPatMax || pw > 252 || np * pat_stride((int)pw) > kPatEntries || A->n < 32ll * found.count || A->n > (1ll << 28))
+  const int64_t np = found + 1;
+  if (found > kPatMax || pw > 252 || np * pat_stride((int)pw) > kPatEntries || A->n < 32 * found || A->n > (1ll << 28))
     return RPK_OK;
   const size_t o_swid = up((size_t)A->nslices * 64), o_val = o_swid + up((size_t)A->nslices);
   if (hipMalloc((void**)&A->dict, o_val + (size_t)np * pat_stride((int)pw) * sizeof(PatEnt)) != hipSuccess)
@@ -396,12 +399,23 @@ static rpk_status build_dictionary(rpk_matrix* A, const PatHash& found, const in
   return RPK_OK;
 }
 
-// Scratch of a creation (one allocation): flags and probe counts, hash table,
-// slice widths, and n + 64 words that hold the rows' hashes, then the probe's x.
+// Scratch of a creation: what the host reads (Learned), the hash table's head behind it,
+// slice widths; and n words that hold the rows' hashes, then the probe's x, in an
+// allocation of their own.
+// One copy tells the host what four did (262,144 different rows from device arrays 549 us
+// before the row dictionary, 1,100 with four copies and one allocation just above 2 MiB, 425 so).
+struct Learned {
+  int flags[2];       // [0] row pointers, [1] entries
+  unsigned probe[2];  // slices not certified, slices
+  unsigned differ;    // the Jacobi vector is not uniform
+  int pad;
+  double d0;          // its first element
+  Band band;
+  int count, wide;    // head of the hash table
+};
 struct Setup {
-  int* flags;          // [0] row pointers, [1] entries
-  unsigned* counts;    // [0], [1] probe; [2] the Jacobi vector is not uniform
-  PatHash* t;
+  Learned* l;
+  PatHash* t;  // at &l->count
   int* width;
   unsigned long long* words;
 };
@@ -409,52 +423,44 @@ struct Setup {
 static rpk_status check_and_lay_out(rpk_matrix* A, const Setup& u, hipStream_t s) {
   const int n = (int)A->n, ns = A->nslices;
   const int B = 256;
-  hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, (unsigned*)u.flags, 64ll);
+  hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, (unsigned*)u.l, (long long)(offsetof(Learned, count) / sizeof(unsigned)));
   hipLaunchKernelGGL(k_pat_clear, dim3(1), dim3(1024), 0, s, u.t);
   hipLaunchKernelGGL(k_check_rowptr, dim3((unsigned)(((int64_t)n + 1 + B - 1) / B)), dim3(B), 0, s, A->rp, n,
-                     (int)A->nnz, u.flags);
+                     (int)A->nnz, u.l->flags);
   HIPCHK(hipGetLastError());
-  int hflags[2] = {0, 0};
-  HIPCHK(hipMemcpyAsync(hflags, u.flags, sizeof(int), hipMemcpyDeviceToHost, s));
+  Learned h;
+  HIPCHK(hipMemcpyAsync(&h, u.l, sizeof(int), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
-  if (hflags[0]) return RPK_ERR_ARG;  // row_ptr unusable: do not read the rows
+  if (h.flags[0]) return RPK_ERR_ARG;  // row_ptr unusable: do not read the rows
   const unsigned G = (unsigned)std::min(4096, (ns + 3) / 4);
   hipLaunchKernelGGL(k_setup_rows, dim3(G), dim3(256), 0, s, A->rp, A->ci, A->v, n, ns, A->dinv, u.width, u.words,
-                     u.flags + 1);
+                     u.l->flags + 1);
   hipLaunchKernelGGL(k_slice_max, dim3(1), dim3(1024), 0, s, u.width, ns, &u.t->wide);
   hipLaunchKernelGGL(k_pat_find, dim3((unsigned)std::min<int64_t>(512, (A->n + 255) / 256)), dim3(256), 0, s, u.words,
                      n, u.t);
   // a uniform Jacobi vector (every dinv_i with the bits of dinv_0)
   hipLaunchKernelGGL(k_dinv_uniform, dim3((unsigned)(((int64_t)n + B - 1) / B)), dim3(B), 0, s, A->dinv, n,
-                     u.counts + 2);
+                     &u.l->differ, &u.l->d0);
   HIPCHK(hipGetLastError());
-  PatHash found;
-  unsigned differ = 0;
-  double d0 = 0.0;
-  constexpr size_t kTail = offsetof(PatHash, count);
-  HIPCHK(hipMemcpyAsync(hflags + 1, u.flags + 1, sizeof(int), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync((char*)&found + kTail, (char*)u.t + kTail, sizeof(PatHash) - kTail, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(&differ, u.counts + 2, sizeof(unsigned), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(&d0, A->dinv, sizeof(double), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(&h, u.l, sizeof(h), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
-  if (hflags[1] & CHK_ARG) return RPK_ERR_ARG;
-  if (hflags[1] & CHK_NONFINITE) return RPK_ERR_NONFINITE;
-  if (hflags[1] & CHK_DIAG) return RPK_ERR_ZERO_DIAG;
-  A->unif = differ == 0u ? 1 : 0;
-  A->du = d0;
-  RET_IF(build_dictionary(A, found, u.width, u.words, u.t, s));
-  if (!A->np) RET_IF(build_sell(A, u.width, (Band*)(u.counts + 4), s));
+  if (h.flags[1] & CHK_ARG) return RPK_ERR_ARG;
+  if (h.flags[1] & CHK_NONFINITE) return RPK_ERR_NONFINITE;
+  if (h.flags[1] & CHK_DIAG) return RPK_ERR_ZERO_DIAG;
+  A->unif = h.differ == 0u ? 1 : 0;
+  A->du = h.d0;
+  RET_IF(build_dictionary(A, h.count, h.wide, u.width, u.words, u.t, s));
+  if (!A->np) RET_IF(build_sell(A, u.width, &u.l->band, s));
   // Whether rows should try the certified row sum first: probe it on a
   // pseudo-random vector; not when more than one slice in eight has a row that it
   // cannot certify (results are the same either way).
   double* x = (double*)u.words;
   hipLaunchKernelGGL(k_fill_hash, dim3(1024), dim3(256), 0, s, x, (long long)n);
-  hipLaunchKernelGGL(k_cert_probe, dim3(G), dim3(256), 0, s, csr_of(A), (const double*)x, u.counts);
+  hipLaunchKernelGGL(k_cert_probe, dim3(G), dim3(256), 0, s, csr_of(A), (const double*)x, u.l->probe);
   HIPCHK(hipGetLastError());
-  unsigned h[2] = {0u, 0u};
-  HIPCHK(hipMemcpyAsync(h, u.counts, sizeof(h), hipMemcpyDeviceToHost, s));
+  HIPCHK(hipMemcpyAsync(h.probe, u.l->probe, sizeof(h.probe), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
-  A->cert = 8ull * h[0] <= h[1] ? 1 : 0;
+  A->cert = 8ull * h.probe[0] <= h.probe[1] ? 1 : 0;
   return RPK_OK;
 }
 
@@ -474,12 +480,16 @@ static rpk_status create_impl(int64_t n, int64_t nnz, const int32_t* rp, const i
     HIPCHK(hipMemcpyAsync(A->v, v, (size_t)nnz * 8, kind, s));
   }
   char* buf = nullptr;
-  const size_t o_t = kAlign, o_width = o_t + up(sizeof(PatHash));
-  const size_t o_words = o_width + up((size_t)A->nslices * sizeof(int));
-  if (hipMalloc((void**)&buf, o_words + ((size_t)n + 64) * 8) != hipSuccess) return RPK_ERR_NOMEM;
-  const Setup u{(int*)buf, (unsigned*)buf + 4, (PatHash*)(buf + o_t), (int*)(buf + o_width),
-                (unsigned long long*)(buf + o_words)};
-  const rpk_status st = check_and_lay_out(A, u, s);
+  unsigned long long* words = nullptr;
+  const size_t o_t = offsetof(Learned, count), o_width = up(o_t + sizeof(PatHash));
+  static_assert(offsetof(Learned, wide) - offsetof(Learned, count) == offsetof(PatHash, wide) && offsetof(PatHash, count) == 0 &&
+                offsetof(Learned, count) % alignof(PatHash) == 0, "Learned ends with the head of the hash table");
+  if (hipMalloc((void**)&buf, o_width + (size_t)A->nslices * sizeof(int)) != hipSuccess) return RPK_ERR_NOMEM;
+  rpk_status st = RPK_ERR_NOMEM;
+  if (hipMalloc((void**)&words, (size_t)n * 8) == hipSuccess) {
+    st = check_and_lay_out(A, Setup{(Learned*)buf, (PatHash*)(buf + o_t), (int*)(buf + o_width), words}, s);
+    (void)hipFree(words);
+  }
   (void)hipFree(buf);
   return st;
 }

@@ -41,11 +41,12 @@ struct RowLimits {
 };
 
 struct PatHash {
-  unsigned long long key[kPatSlots];  // 0 = free
-  int rep[kPatSlots];                 // lowest row with that hash; k_pat_table: -1 - id
   int count;                          // distinct hashes so far (counts on past kPatMax)
   int wide;                           // widest slice
   int fail;                           // a row differs from its representative
+  int pad;
+  unsigned long long key[kPatSlots];  // 0 = free
+  int rep[kPatSlots];                 // some row with that hash; k_pat_table: -1 - id
 };
 
 __device__ __forceinline__ unsigned long long pat_mix(unsigned long long v) {
@@ -78,7 +79,7 @@ struct SliceRows {
 // coalesce whatever the rows' lengths; one row a thread took 3.1 ms on the
 // 27-point 159^3 matrix): the checks of every entry, dinv, the slice's width
 // and, for the row dictionary, each row's hash over its (position, column - row,
-// value).  n + 64 entries of hash.
+// value).  n entries of hash.
 __global__ void __launch_bounds__(256) k_setup_rows(const int* rp, const int* ci, const double* v, int n, int nslices,
                                                     double* dinv, int* width, unsigned long long* hash, int* flags) {
   __shared__ SliceRows R[4];
@@ -123,8 +124,9 @@ __global__ void __launch_bounds__(256) k_setup_rows(const int* rp, const int* ci
   if (fl) atomicOr(flags, fl);
 }
 
-// *differ = 1 when some dinv_i does not have the bits of dinv_0 (Csr::unif)
-__global__ void k_dinv_uniform(const double* dinv, int n, unsigned* differ) {
+// *differ = 1 when some dinv_i does not have the bits of dinv_0 (Csr::unif), *first = dinv_0
+__global__ void k_dinv_uniform(const double* dinv, int n, unsigned* differ, double* first) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *first = dinv[0];
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const bool d = i < n && __double_as_longlong(dinv[i]) != __double_as_longlong(dinv[0]);
   // one store for the first workgroups that find a difference, not one of every lane
