@@ -938,10 +938,25 @@ __device__ __forceinline__ void block_window(Dot<N> (&d)[K], const Shm<N>& s) {
       lane_deposit(d[j].f, top - (WIN - 1), s.scat + (j * 64 + lane) * ROW_STRIDE, s.sa + (size_t)j * SA_D, &s.flag[j]);
   }
   __syncthreads();
-  for (int c = w; c < K * WIN; c += nw) {
-    const int j = c / WIN, k = c - j * WIN;
-    const long long v = wave_sum_i64(s.scat[(j * 64 + lane) * ROW_STRIDE + k]);
-    if (lane == 63) s.wsum[c] = v;
+  if (nw < 4) {
+    // few wavefronts for K WIN columns: a dot's columns at once, four lanes each (a
+    // batch of 64 systems in tiles of 64 rows and workgroups of 64: 2.82 ms with one
+    // column at a time, 2.50 so)
+    const int col = lane % WIN, part = lane / WIN;
+    for (int j = w; j < K; j += nw) {
+      long long v = 0;
+      if (lane < 4 * WIN)
+        for (int r = part; r < 64; r += 4) v += s.scat[(j * 64 + r) * ROW_STRIDE + col];
+      const long long a = __shfl(v, (lane + WIN) & 63, 64), b = __shfl(v, (lane + 2 * WIN) & 63, 64);
+      v += a + b + __shfl(v, (lane + 3 * WIN) & 63, 64);
+      if (lane < WIN) s.wsum[j * WIN + lane] = v;
+    }
+  } else {
+    for (int c = w; c < K * WIN; c += nw) {
+      const int j = c / WIN, k = c - j * WIN;
+      const long long v = wave_sum_i64(s.scat[(j * 64 + lane) * ROW_STRIDE + k]);
+      if (lane == 63) s.wsum[c] = v;
+    }
   }
   __syncthreads();
 }
