@@ -100,7 +100,9 @@ typedef struct {
   int32_t block;  /* workgroup size, a multiple of 64 in [64, 1024]; 0 = 512, or,
                      when the grid is automatic too, 1024 from 262,144 elements
                      on (scattered matrices: 131,073 rows) and as said above */
-  int32_t grid;   /* workgroups of the streaming kernels, 1 .. 65535; 0 = automatic */
+  int32_t grid;   /* workgroups of the streaming kernels, 1 .. 65535; 0 = automatic.
+                     Batched: workgroups of a launch, but no fewer than a quarter of
+                     the tiles */
   int32_t fpe;    /* FPE length 1, 2, 3, 4 or 8 (1 sends almost every term to
                      the long accumulator); 0 = 3 */
   int32_t graph;  /* solve: iterations per captured HIP graph launch; 0 = automatic,

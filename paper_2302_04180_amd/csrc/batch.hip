@@ -287,7 +287,12 @@ struct Shape {
 Shape shape_of(const Ctx& c, const BCfg& cfg, const Plan& plan) {
   Shape sh;
   const int nt = (int)plan.tiles.size();  // a multiple of 8
-  const int cap = cfg.grid_cap ? (cfg.grid_cap + 7) & ~7 : kMaxTileGrid;
+  // launch.grid limits a launch, but four launches a phase cover the tiles: more gaps
+  // and half-filled ends cost more than the tiles.  64 systems of 8^3 to 32^3 rows, eight
+  // iterations, ms, in workgroups that walked the tiles / in as many launches as the
+  // limit asks for / in four at most: tiles of 512 and grid 64 6.6 / 7.2 / 2.3, of 64 and
+  // grid 256 8.5 / 11.9 / 3.4
+  const int cap = cfg.grid_cap ? (std::max(cfg.grid_cap, (nt + 3) / 4) + 7) & ~7 : kMaxTileGrid;
   sh.G = std::max(8, std::min(nt, cap));
   sh.Gf = std::min((c.ns + 7) & ~7, 1024);
   sh.B = cfg.block;
