@@ -98,9 +98,11 @@ constexpr int64_t kOneGroupDot = 4096, kOneGroupDotFpe1 = 1024;
 // below 65,536 the same within 2 %
 constexpr int64_t kMidDot = 65536, kLongDot = 1 << 20;
 // From this many rows on the automatic shape is 256 workgroups of 1,024 threads
-// instead of 512 of 512 (solves: see kSmallSolveGroups; dots: kLongDot): as many wavefronts, but half the partial sums that
-// queue on the accumulators (128^3 solve: B 25.0 and 23.5, D 30.6 and 28.0 us,
-// 101^3 PCG: S1 15.8 and 14.6, S3 17.5 and 16.6 us)
+// instead of 512 of 512 (solves: see kSmallSolveGroups; dots: kLongDot): as many
+// wavefronts, but half the partial sums that queue on the accumulators (128^3 solve: B
+// 25.0 and 23.5, D 30.6 and 28.0 us, 101^3 PCG: S1 15.8 and 14.6, S3 17.5 and 16.6 us).
+// Solves with plain dots have no accumulators and keep 512 of 512: 24 iterations of
+// 128^3 rows without a dictionary 3,573 us in 256 of 1,024, 3,481 so.
 constexpr int64_t kBigBlockRows = 262144;
 // Matrices of scattered columns (rpk_matrix::sdif) of at least kTinySolveRows rows
 // take 256 workgroups, of 512 threads and from this many rows on of 1,024: their gathers keep a

@@ -618,6 +618,10 @@ static rpk_status solve_shape(const rpk_matrix* A, const rpk_opts* o, Cfg* c) {
     L.block = A->n < kTinySolveRows ? 256 : 512;
     L.grid = (int32_t)std::min<int64_t>(kSmallSolveGroups, need < 8 ? need : (need + 7) & ~7ll);
   }
+  if (automatic && A->n >= kBigBlockRows && !scattered && o->dots == RPK_DOT_PLAIN) {
+    L.block = 512;  // see kBigBlockRows
+    L.grid = 512;
+  }
   RET_IF(resolve(&L, A->n, c, scattered));
   if (automatic && A->n <= kOneGroupRows && (o->variant == RPK_STD || o->variant == RPK_PCG) &&
       o->dots != RPK_DOT_FPE) {
