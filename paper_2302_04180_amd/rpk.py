@@ -121,9 +121,10 @@ def _check(code, where):
 
 
 def _here():
-    """The current device and its current stream as integers (torch.cuda.current_stream()
-    builds an object, 3 us)."""
-    dev = torch.cuda.current_device()
+    """The current device and its current stream as integers, once CUDA is initialised
+    (torch.cuda.current_stream() builds an object, 3 us, torch.cuda.current_device()
+    checks the initialisation first, 0.4 us)."""
+    dev = torch._C._cuda_getDevice()
     return dev, torch._C._cuda_getCurrentRawStream(dev)
 
 

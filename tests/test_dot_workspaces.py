@@ -40,6 +40,7 @@ def fake(monkeypatch):
     monkeypatch.setattr(rpk, "_lib", now.lib)
     monkeypatch.setattr(rpk, "_dev", lambda t: t)
     monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
     monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda dev: now.stream, raising=False)
     monkeypatch.setattr(torch._C, "_cuda_isCurrentStreamCapturing", lambda: now.capturing, raising=False)
     monkeypatch.setattr(torch, "zeros", cpu_zeros)
