@@ -335,14 +335,17 @@ rpk_status rpk_server_destroy(rpk_server* s);
  * several workgroups. */
 rpk_status rpk_matrix_form(const rpk_matrix* A, const rpk_launch* launch, int32_t form[4]);
 
-/* Test hook (host only, no device work): the tile table rpk_solve_batched
- * builds for systems of n[0..nsys-1] rows and `tile` rows per tile, every system
- * on one XCD (the solver cuts systems over several where this leaves XCDs idle).  tiles
+/* Test hooks (host only, no device work): tile tables for systems of n[0..nsys-1] rows
+ * and `tile` rows per tile.  rpk_plan_tiles_spread gives the table rpk_solve_batched and
+ * the server build, which cuts systems over several XCDs where whole ones leave XCDs
+ * idle; rpk_plan_tiles the table before that, every system on one XCD.  tiles
  * receives 4 int32 per tile (system, first row, end row, index of the tile in
  * its system; system -1 for padding); tile t runs on XCD t % 8.  *ntiles is the
  * table length; RPK_ERR_ARG if it exceeds cap. */
 rpk_status rpk_plan_tiles(int32_t nsys, const int64_t* n, int32_t tile, int32_t* tiles, int64_t cap,
                           int64_t* ntiles);
+rpk_status rpk_plan_tiles_spread(int32_t nsys, const int64_t* n, int32_t tile, int32_t* tiles, int64_t cap,
+                                 int64_t* ntiles);
 
 /* Test hook: q[i] = a[i]/b[i] and s[i] = sqrt(a[i]) with the device operations the
  * solver's scalar steps use (to check them against IEEE-754 on the host). */

@@ -564,13 +564,13 @@ rpk_status prepare(int32_t nsys, const rpk_matrix* const* A, const rpk_opts* o, 
 
 extern "C" {
 
-rpk_status rpk_plan_tiles(int32_t nsys, const int64_t* n, int32_t tile, int32_t* tiles, int64_t cap,
-                          int64_t* ntiles) {
+static rpk_status plan_hook(int32_t nsys, const int64_t* n, int32_t tile, int32_t* tiles, int64_t cap, int64_t* ntiles,
+                            bool spread) {
   if (nsys < 1 || nsys > kMaxSys || !n || !tiles || !ntiles || tile < 64 || tile % 64) return RPK_ERR_ARG;
   std::vector<int64_t> nv(n, n + nsys);
   for (int64_t v : nv)
     if (v < 1 || v >= (1ll << 31)) return RPK_ERR_ARG;
-  const Plan p = make_plan(nv, tile, nullptr, false);
+  const Plan p = make_plan(nv, tile, nullptr, spread);
   *ntiles = (int64_t)p.tiles.size();
   if ((int64_t)p.tiles.size() > cap) return RPK_ERR_ARG;
   for (size_t t = 0; t < p.tiles.size(); ++t) {
@@ -580,6 +580,16 @@ rpk_status rpk_plan_tiles(int32_t nsys, const int64_t* n, int32_t tile, int32_t*
     tiles[4 * t + 3] = p.tiles[t].rec;
   }
   return RPK_OK;
+}
+
+rpk_status rpk_plan_tiles(int32_t nsys, const int64_t* n, int32_t tile, int32_t* tiles, int64_t cap,
+                          int64_t* ntiles) {
+  return plan_hook(nsys, n, tile, tiles, cap, ntiles, false);
+}
+
+rpk_status rpk_plan_tiles_spread(int32_t nsys, const int64_t* n, int32_t tile, int32_t* tiles, int64_t cap,
+                                 int64_t* ntiles) {
+  return plan_hook(nsys, n, tile, tiles, cap, ntiles, true);
 }
 
 rpk_status rpk_batched_check(int32_t nsys, const int64_t* n, const rpk_opts* opts) {

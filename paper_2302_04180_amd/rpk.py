@@ -61,7 +61,7 @@ EXPORTS = ["rpk_version", "rpk_status_str", "rpk_matrix_create", "rpk_matrix_des
            "rpk_exspmv", "rpk_solve_workspace_bytes", "rpk_solve", "rpk_batched_check",
            "rpk_solve_batched_workspace_bytes", "rpk_solve_batched", "rpk_server_create", "rpk_server_footprint", "rpk_server_submit",
            "rpk_server_poll", "rpk_server_wait", "rpk_server_get_stats", "rpk_server_destroy",
-           "rpk_plan_tiles", "rpk_matrix_form", "rpk_device_divsqrt"]
+           "rpk_plan_tiles", "rpk_plan_tiles_spread", "rpk_matrix_form", "rpk_device_divsqrt"]
 
 _lib = None
 
@@ -101,6 +101,7 @@ def load(path=LIB_PATH):
     lib.rpk_server_get_stats.argtypes = [P, ctypes.POINTER(ServerStats)]
     lib.rpk_server_destroy.argtypes = [P]
     lib.rpk_plan_tiles.argtypes = [I32, P, I32, P, I64, ctypes.POINTER(I64)]
+    lib.rpk_plan_tiles_spread.argtypes = [I32, P, I32, P, I64, ctypes.POINTER(I64)]
     lib.rpk_matrix_form.argtypes = [P, ctypes.POINTER(Launch), ctypes.POINTER(I32)]
     lib.rpk_device_divsqrt.argtypes = [I64, P, P, P, P, P]
     for name in EXPORTS[2:]:
@@ -513,16 +514,16 @@ class Server:
             pass
 
 
-def plan_tiles(sizes, tile):
-    """Host-only: the batched solver's tile table for systems of these sizes, every
-    system on one XCD (large ones are cut over several when a batch runs), as an
-    int32 array of rows (system, first row, end row, tile index in its system)."""
+def plan_tiles(sizes, tile, spread=False):
+    """Host-only: a tile table for systems of these sizes, as an int32 array of rows
+    (system, first row, end row, tile index in its system): with spread the one that
+    batches and the server run, else the one before systems are cut over several XCDs."""
     n = np.ascontiguousarray(sizes, dtype=np.int64)
     cap = 8 * (int(np.sum(-(-n // tile))) // 8 + int(np.max(-(-n // tile))) + 2)
     out = np.zeros((cap, 4), dtype=np.int32)
     nt = ctypes.c_int64()
-    _check(load().rpk_plan_tiles(n.size, n.ctypes.data, int(tile), out.ctypes.data, cap, ctypes.byref(nt)),
-           "rpk_plan_tiles")
+    plan = load().rpk_plan_tiles_spread if spread else load().rpk_plan_tiles
+    _check(plan(n.size, n.ctypes.data, int(tile), out.ctypes.data, cap, ctypes.byref(nt)), "rpk_plan_tiles")
     return out[:nt.value].copy()
 
 
