@@ -353,7 +353,11 @@ static rpk_status build_sell(rpk_matrix* A, const int* width, Band* band, hipStr
   HIPCHK(hipMemcpyAsync(&h, band, sizeof(h), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   if (h.gathers == 0 || h.lines < 16 * (uint64_t)h.gathers || (int64_t)h.lo + h.hi > kMaxBand) return RPK_OK;
-  if (hipMalloc((void**)&A->sdif, cnt * sizeof(unsigned short)) != hipSuccess) return RPK_ERR_NOMEM;
+  if (hipMalloc((void**)&A->sdif, cnt * sizeof(unsigned short)) != hipSuccess) {
+    (void)hipGetLastError();  // the matrix does without
+    A->sdif = nullptr;
+    return RPK_OK;
+  }
   A->wlo = h.lo;
   A->whi = h.hi;
   hipLaunchKernelGGL(k_fill_dif, dim3((unsigned)std::min(4096, (ns + 3) / 4)), dim3(256), 0, s, n, ns,
