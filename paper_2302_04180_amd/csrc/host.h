@@ -247,7 +247,11 @@ int64_t tile_capacity(const std::vector<int64_t>& n, int Tcap);
 
 // Device block of one system: tickets + flags | long accumulators | plain-mode
 // sums of gcap tiles | nvec solver vectors of n doubles.
+// Counters, flags and one counter for each copy of the accumulators (Red), of a
+// single call and of a system of a batch (which has one copy and draws no such ticket)
+constexpr size_t kTicketBytes = (kSubTickets + kMaxCopies) * sizeof(unsigned);
 constexpr size_t kFlagsBytes = 8 * sizeof(unsigned) + MAX_DOTS * sizeof(int);
+static_assert(kSubTickets * sizeof(unsigned) == kFlagsBytes, "the copies' counters lie behind the flags");
 size_t sys_bytes(int64_t n, int gcap, int nvec);
 // Descriptor of a system whose block starts at `base` (device address).
 SysDesc make_desc(const rpk_matrix* A, const double* b, double* x, char* base, int gcap, int G, int variant,

@@ -102,7 +102,7 @@ Layout layout(int grid, int64_t n, int nvec) {
   off += up(sizeof(State));
   l.tickets = off;
   l.gflags = off + 8 * sizeof(unsigned);
-  off += up(8 * sizeof(unsigned) + MAX_DOTS * sizeof(int));
+  off += up(kTicketBytes);
   l.gsa = off;
   // room for every launch shape's copies: a workspace serves calls of different
   // shapes, and the partials of one must not lie on the accumulators of another

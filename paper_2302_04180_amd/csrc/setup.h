@@ -251,7 +251,7 @@ __global__ void k_fill_dif(int n, int nslices, const long long* sptr, const int*
 
 // Row dictionary (Csr::pid).  A row is its list of (column - row, value) in CSR
 // order; every distinct one is found by the 64-bit hash k_setup_rows took, in an
-// open-addressing table, the lowest row with a hash represents it, and every
+// open-addressing table, some row with a hash represents it, and every
 // row is then compared with its representative entry by entry, so a hash
 // collision only costs the dictionary, never a value.
 __global__ void __launch_bounds__(1024) k_pat_clear(PatHash* t) {
@@ -264,7 +264,7 @@ __global__ void __launch_bounds__(1024) k_pat_clear(PatHash* t) {
   }
 }
 
-// Enter every row's hash and note the lowest row seen with it.  Each workgroup
+// Enter every row's hash and note a row that has it.  Each workgroup
 // takes a contiguous chunk of rows; a hash goes to the device's table once per
 // wavefront that meets it first (its lowest lane) and then never again from
 // that workgroup, which keeps the hashes it has entered in LDS: with every
@@ -305,7 +305,8 @@ __global__ void __launch_bounds__(256) k_pat_find(const unsigned long long* hash
   }
 }
 
-// One workgroup: number the distinct rows by their lowest row, and write the
+// One workgroup: number the distinct rows by the rows that represent them (which may
+// differ from one creation to the next, and the numbers with them), and write the
 // dictionary, its rows padded with (0, own element); id np - 1 is the empty row.
 __global__ void __launch_bounds__(1024) k_pat_table(const int* rp, const int* ci, const double* v, PatHash* t, int np,
                                                     int pw, PatEnt* pat) {

@@ -119,7 +119,7 @@ __device__ __forceinline__ void step_entry(State* st, double rho) {
     stop(st, ST_NONFINITE);
     return;
   }
-  st->rho = st->stg = rho;
+  st->rho = rho;
   st->tau0 = sqrt(rho);
   st->tau = st->tau0;
   if (st->tau0 == 0.0) stop(st, ST_OK);
