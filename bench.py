@@ -69,7 +69,8 @@ def algorithmic_bytes(n, nnz):
     with a uniform Jacobi vector (every diagonal entry equal, as in the Poisson
     and convection-diffusion systems) and few different rows (read through a
     dictionary, one byte a row) the standard loop forms p^, q and q^ where it
-    reads them and moves 18 vectors per iteration instead of 25, and no matrix."""
+    reads them and moves 18 vectors per iteration instead of 25, and no matrix:
+    the counts with the CSR matrix measure work, moved_bytes what is moved."""
     V = 8 * n
     csr = 12 * nnz + 4 * (n + 1)
     return {
@@ -88,6 +89,28 @@ def algorithmic_bytes(n, nnz):
         "std_kernel_unif": {0: 4 * V, 1: n + 3 * V, 2: 0, 3: n + 4 * V, 4: 7 * V},
         "std_iteration_unif": 2 * n + 18 * V,
     }
+
+
+def moved_bytes(M, variant, uniform, batched=False):
+    """Bytes one iteration moves with the matrix as the library holds it: each vector
+    a kernel reads or writes once, a matrix with a row dictionary one byte a row,
+    with an operand window ten an entry, else twelve.  uniform: its Jacobi vector is.
+    batched: systems of a batch or the server, which take the loops in five phases
+    (standard) and no operand window."""
+    f = M.form()
+    matrix = M.n if f["dictionary"] else (10 if f["window"] and not batched else 12) * M.nnz
+    products, vectors = {0: (2, 19 if uniform else 25), 1: (2, 35 if uniform else 42),
+                         2: (1, 11 if uniform else 13)}[variant]
+    if variant == 0 and uniform and not batched:  # q (and p) formed at the gathers
+        vectors = {5: 19, 4: 18, 3: 17}[f["std_kernels"]]
+    return products * matrix + vectors * 8 * M.n
+
+
+def rates(ips, work, moved):
+    """Work rate in bytes of the CSR form, bytes moved per second, and these as a
+    share of the HBM peak (bytes served by the caches count as moved)."""
+    return {"algorithmic_GBps": round(ips * work / 1e9, 1), "moved_GBps": round(ips * moved / 1e9, 1),
+            "roofline_frac": round(ips * moved / 1e9 / HBM_PEAK_GBS, 4)}
 
 
 def _lscpu_model():
@@ -266,9 +289,11 @@ def config_legs(torch, rpk, inputs):
         n, nnz = M.n, M.nnz
         b = rpk.exspmv(M, torch.tensor(rhs(n), dtype=torch.float64, device="cuda"))
         per_it = 2 * (12 * nnz + 4 * (n + 1)) + nvec * 8 * n
+        moved = moved_bytes(M, variant, "banded" not in name)
         leg = {"n": n, "nnz": nnz, "tol": tol, "variant": "standard (Fig. 2)" if variant == rpk.STD
-               else "pipelined (Fig. 3)", "bytes_per_iteration": per_it,
-               "bound": "hbm" if hbm else "latency (an iteration's operands stay in the caches; no roofline claim)"}
+               else "pipelined (Fig. 3)", "bytes_per_iteration": per_it, "moved_bytes_per_iteration": moved,
+               "bound": "vector streams (Infinity Cache or HBM), then row products" if hbm
+               else "latency (an iteration's operands stay in the caches; no roofline claim)"}
         for dots, dname in ((rpk.EXACT, "exact"), (rpk.PLAIN, "plain")):
             x, info = rpk.solve(M, b, tol=tol, maxit=maxit, variant=variant, dots=dots)  # graphs captured
             torch.cuda.synchronize()
@@ -281,9 +306,9 @@ def config_legs(torch, rpk, inputs):
             dt = time.perf_counter() - t0
             ips = it / dt
             r = {"iters_per_s": round(ips, 1), "iterations": info["iters"], "status": info["status"],
-                 "ms_per_solve": round(1e3 * dt / reps, 3), "algorithmic_GBps": round(ips * per_it / 1e9, 1)}
-            if hbm:
-                r["roofline_frac"] = round(ips * per_it / 1e9 / HBM_PEAK_GBS, 4)
+                 "ms_per_solve": round(1e3 * dt / reps, 3), **rates(ips, per_it, moved)}
+            if not hbm:
+                del r["roofline_frac"]
             leg[dname] = r
             if dots == rpk.EXACT:
                 host[name] = (A, b.cpu().numpy(), variant, tol, maxit, info["iters"], x.cpu().numpy())
@@ -336,6 +361,7 @@ def batched_leg(torch, rpk, inputs, reps=3):
     t_alone = time.perf_counter() - t1
     ok = all(i["status"] == "OK" for i in infos)
     alg_bytes = sum(i["iters"] * std_bytes(M) for i, M in zip(infos, Ms))
+    moved = sum(i["iters"] * moved_bytes(M, rpk.STD, True, batched=True) for i, M in zip(infos, Ms))
     # where the batch loses bandwidth: the share of its rows still iterating at
     # each tenth of the longest solve (systems that converged leave the launches)
     imax = max(iters)
@@ -347,8 +373,7 @@ def batched_leg(torch, rpk, inputs, reps=3):
             "solves_per_s": round(len(infos) / dt, 1), "ms_per_batch": round(1e3 * dt, 2),
             "iters_min_max": [min(iters), max(iters)], "iters_total": int(sum(iters)),
             "alone_solves_per_s": round(len(infos) / t_alone, 1),
-            "algorithmic_GBps": round(alg_bytes / dt / 1e9, 1),
-            "roofline_frac": round(alg_bytes / dt / 1e9 / HBM_PEAK_GBS, 4),
+            **rates(1.0 / dt, alg_bytes, moved),
             "sampled_results_equal_alone": same, "launch": infos[0]["used"],
             "active_rows_share_by_tenth_of_longest_solve": active,
             "row_iterations_over_longest_times_rows": round(busy, 3)}
@@ -377,10 +402,9 @@ def etype_leg(torch, rpk, inputs, reps=2):
                 it += info["iters"]
             torch.cuda.synchronize()
             ips = it / (time.perf_counter() - t0)
-            gbs = ips * (2 * csr + vbytes * 8 * n) / 1e9
             out["%s_%s" % (vname, dname)] = {"iters_per_s": round(ips, 1), "iterations": info["iters"],
-                                             "status": info["status"], "algorithmic_GBps": round(gbs, 1),
-                                             "roofline_frac": round(gbs / HBM_PEAK_GBS, 4)}
+                                             "status": info["status"],
+                                             **rates(ips, 2 * csr + vbytes * 8 * n, moved_bytes(M, variant, True))}
     M.close()
     # PCG (Fig. 1) on the symmetric 27-point Poisson of the same size (the e-type
     # stencil without its perturbation), b = A*1, tol 1e-6: one SpMV and 13 vector
@@ -400,10 +424,9 @@ def etype_leg(torch, rpk, inputs, reps=2):
             it += info["iters"]
         torch.cuda.synchronize()
         ips = it / (time.perf_counter() - t0)
-        gbs = ips * (csr + 13 * 8 * n) / 1e9
         out["sym27_pcg_%s" % dname] = {"iters_per_s": round(ips, 1), "iterations": info["iters"],
-                                       "status": info["status"], "algorithmic_GBps": round(gbs, 1),
-                                       "roofline_frac": round(gbs / HBM_PEAK_GBS, 4)}
+                                       "status": info["status"],
+                                       **rates(ips, csr + 13 * 8 * n, moved_bytes(M, rpk.PCG, True))}
     M.close()
     return out
 
@@ -619,22 +642,24 @@ def main():
     by = algorithmic_bytes(n, nnz)
     dom = max(range(5), key=lambda k: tinfo["phase_ms"][k])
     avg_s = tinfo["phase_ms"][dom] / tinfo["phase_launches"][dom] / 1e3
-    dom_bytes = by["std_kernel"][dom]
-    achieved = dom_bytes / avg_s / 1e9
+    moved_dom = by["std_kernel_unif"][dom]
     traffic, trace_us = None, None
     if (TRAFFIC and TRAFFIC["src_sha256"] == kernel_digest() and TRAFFIC["phase"] == dom
             and TRAFFIC["fpe"] == tinfo["used"]["fpe"]):
         traffic, trace_us = TRAFFIC["bytes"], TRAFFIC["trace_busy_avg_us"]
-    roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+    # the share of the HBM peak that the kernel's own bytes take: what bounds it is vector
+    # issue and the L1's line lookups of its gathers, each busy most of the time
+    achieved = moved_dom / avg_s / 1e9
+    roofline = {"bound": "vector issue and L1 lookups of the gathers (59 % and 65 % busy in D)" if dom == 3 else "hbm",
+                "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": names[dom], "bytes_per_launch": dom_bytes,
-                # what the kernel moves (bytes_per_launch counts the CSR matrix, which the row
-                # dictionary replaces)
-                "moved_bytes_per_launch": by["std_kernel_unif"][dom], "avg_launch_us": round(avg_s * 1e6, 2),
+                "kernel": names[dom], "moved_bytes_per_launch": moved_dom,
+                # the same kernel's bytes with a CSR matrix: a measure of work, not of traffic
+                "csr_bytes_per_launch": by["std_kernel"][dom], "avg_launch_us": round(avg_s * 1e6, 2),
                 # HIP events around direct launches include the dispatch of each kernel (a few us);
                 # the kernel trace of the same sources times the kernels alone
                 "trace_avg_us": trace_us,
-                "trace_frac": round(dom_bytes / (trace_us * 1e-6) / 1e9 / HBM_PEAK_GBS, 4) if trace_us else None}
+                "trace_frac": round(moved_dom / (trace_us * 1e-6) / 1e9 / HBM_PEAK_GBS, 4) if trace_us else None}
 
     result = {
         "metric": METRIC, "value": round(exact_ips, 2), "unit": "iters/s", "n_gpus": 1,
@@ -646,19 +671,18 @@ def main():
                    "parallelism": "single GPU"},
         "iterations_per_solve": it_exact,
         "algorithmic_GBps_iteration": round(exact_ips * by["std_iteration"] / 1e9, 1),
-        "iteration_roofline_frac": round(exact_ips * by["std_iteration"] / 1e9 / HBM_PEAK_GBS, 4),
         # what the kernels move (18 vector streams and a byte a row twice)
         "moved_bytes_per_iteration": by["std_iteration_unif"],
         "moved_GBps_iteration": round(exact_ips * by["std_iteration_unif"] / 1e9, 1),
+        "iteration_roofline_frac": round(exact_ips * by["std_iteration_unif"] / 1e9 / HBM_PEAK_GBS, 4),
         "plain_fp64": {"iters_per_s": round(plain_ips, 2), "iterations": plain_info["iters"]},
         "exact_over_plain_time_per_iteration": round(plain_ips / exact_ips, 3),
         "pipelined_exact": {"iters_per_s": round(pipe_ips, 2), "iterations": pipe_info["iters"],
-                            "GBps": round(pipe_ips * by["pipelined_iteration"] / 1e9, 1)},
+                            **rates(pipe_ips, by["pipelined_iteration"], moved_bytes(M, rpk.PIPELINED, True))},
         "pipelined_plain": {"iters_per_s": round(pplain_ips, 2), "iterations": pplain_info["iters"]},
         # preconditioned CG (Fig. 1) on the same system: one SpMV and CSR + 13V per iteration
         "pcg_exact": {"iters_per_s": round(pcg_ips, 2), "iterations": pcg_info["iters"],
-                      "GBps": round(pcg_ips * by["pcg_iteration"] / 1e9, 1),
-                      "roofline_frac": round(pcg_ips * by["pcg_iteration"] / 1e9 / HBM_PEAK_GBS, 4)},
+                      **rates(pcg_ips, by["pcg_iteration"], moved_bytes(M, rpk.PCG, True))},
         "pcg_plain": {"iters_per_s": round(pcg_plain_ips, 2), "iterations": pcg_plain_info["iters"]},
         "lightweight_fpe8": light,
         "phase_us": phase,

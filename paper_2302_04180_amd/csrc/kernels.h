@@ -762,7 +762,10 @@ __device__ __forceinline__ double rows_fpe(const Src& src, const Gth& gx, int w,
 // twosums with a data-dependent exit after each; a wavefront with a row that is
 // not certified takes all its rows the other way (its entries are in the caches
 // by then).  Every path gives the same values.  With the dictionary the loop is
-// bound by its arithmetic (about 290 vector operations a row in D); loading the
+// bound by vector issue and by the L1's line lookups together, of which a gather of
+// 64 lanes takes about 17: busy in the 27-point 159^3 SpMV 73 % and 84 % of the time
+// (plain rows 27 % and all of it), in D3 at 128^3 59 % and 65 % (19 % and 77 %).
+// Loading the
 // next row's id, operands and own values ahead of this row's sums was slower (D
 // 32.9 instead of 27.4 us at 128^3), and so was a second pass for the rows that
 // are not certified.
