@@ -99,7 +99,7 @@ def moved_bytes(M, variant, uniform, batched=False):
     (standard) and no operand window."""
     f = M.form()
     matrix = M.n if f["dictionary"] else (10 if f["window"] and not batched else 12) * M.nnz
-    products, vectors = {0: (2, 19 if uniform else 25), 1: (2, 35 if uniform else 42),
+    products, vectors = {0: (2, 19 if uniform else 25), 1: (2, 35 if uniform else 41),
                          2: (1, 11 if uniform else 13)}[variant]
     if variant == 0 and uniform and not batched:  # q (and p) formed at the gathers
         vectors = {5: 19, 4: 18, 3: 17}[f["std_kernels"]]
