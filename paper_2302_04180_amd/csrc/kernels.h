@@ -52,7 +52,9 @@ struct __align__(16) PatEnt {
 // different rows lie on different LDS banks.
 __host__ __device__ constexpr int pat_stride(int pw) { return ((pw + 3) & ~3) + 1; }
 // entries of the LDS set aside for the dictionary in every kernel that multiplies
-// by the matrix
+// by the matrix: 16 KB.  The limit is that reserve, not where the two forms cross: a
+// 7-point grid of 128^3 rows takes 19.1 us an SpMV with five values on its diagonal
+// (103 different rows), 32.2 from the SELL copy with eight, whose rows do not fit.
 constexpr int kPatEntries = 1024;
 
 // Matrix as the kernels see it.  The CSR input is re-laid out at creation as
@@ -574,9 +576,10 @@ __device__ __forceinline__ double tsum(double x, double y, double& err) {
 // an entry instead of four comparisons; an x_j = 0 counts as exponent 0, which
 // can only make the tests stricter (it takes the exactness test from rows that hold
 // zeros beside values above some 2^48; leaving zeros out costs two operations an entry,
-// 76 -> 81 us of the 27-point 159^3 SpMV).  lsb and the exponents are the row's own: one entry of many bits in a matrix of short ones
-// (0.1 on a boundary row) then leaves the other rows certified, where with those of
-// the whole matrix it left none.  Returns false -- the caller then takes the
+// 76 -> 81 us of the 27-point 159^3 SpMV).  lsb and the exponents are those of the row
+// (the exponents, in the SELL copy, of its slice): one entry of many bits in a matrix of
+// short ones (0.1 on a boundary row) then leaves the other rows certified, where with
+// limits of the whole matrix it left none.  Returns false -- the caller then takes the
 // FPE path -- when neither shows it, or for a product out of range or a sum that
 // is non-finite or, for the bound, zero, tiny or huge.  When it returns true, y
 // is the correctly rounded row sum: the same bits as the FPE path.  Checking
@@ -703,7 +706,9 @@ __device__ inline double row_slow(const Src& src, int l, const Gth& gx, int w, l
   const bool any_nf = __ballot(nf) != 0ull;
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
   __builtin_amdgcn_wave_barrier();
-  double r = sa_round(wsa);  // with the digits one a lane: in lane 0 alone, rows of wide exponents took 1,225 us (100^3), 514 so
+  // with the digits one a lane: in lane 0 alone, the SpMV of 100^3 rows of wide
+  // exponents took 1,225 us, 514 so
+  double r = sa_round(wsa);
   if (any_nf) r = __longlong_as_double(0x7ff8000000000000ll);
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
   __builtin_amdgcn_wave_barrier();
@@ -763,12 +768,11 @@ __device__ __forceinline__ double rows_fpe(const Src& src, const Gth& gx, int w,
 // not certified takes all its rows the other way (its entries are in the caches
 // by then).  Every path gives the same values.  With the dictionary the loop is
 // bound by vector issue and by the L1's line lookups together, of which a gather of
-// 64 lanes takes about 17: busy in the 27-point 159^3 SpMV 73 % and 84 % of the time
-// (plain rows 27 % and all of it), in D3 at 128^3 59 % and 65 % (19 % and 77 %).
-// Loading the
-// next row's id, operands and own values ahead of this row's sums was slower (D
-// 32.9 instead of 27.4 us at 128^3), and so was a second pass for the rows that
-// are not certified.
+// 64 lanes takes about 17: busy in the 27-point 159^3 SpMV 70 % and 81 % of the time
+// (plain rows 26 % and all of it), in D3 at 128^3 54 % and 58 % (19 % and 77 %).
+// Loading the next row's id, operands and own values ahead of this row's sums was
+// slower (D 32.9 instead of 27.4 us at 128^3), and so was a second pass for the rows
+// that are not certified.
 // Win: the operand comes from LDS (Csr::win).
 template <int N, bool Win = false, class Gth, class Pre, class Use>
 __device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, const Shm<N>& s, Pre pre, Use use) {
