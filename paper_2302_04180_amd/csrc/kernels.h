@@ -795,7 +795,7 @@ __device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, c
         y = sl < A.keep ? row_plain(kept, gx, w) : row_plain(passing, gx, w);
       } else {
         const bool cert = A.cert && (sl < A.keep ? row_cert(lim, kept, gx, w, y) : row_cert(lim, passing, gx, w, y));
-        if (__ballot(ok && !cert) != 0ull) y = rows_fpe<N>(kept, gx, w, ok, s.wsa);
+        if (__builtin_expect(__ballot(ok && !cert) != 0ull, 0)) y = rows_fpe<N>(kept, gx, w, ok, s.wsa);
       }
       use(i, ok, y, p);
     } else if (Gth::kDict || A.np) {
@@ -806,7 +806,7 @@ __device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, c
         y = row_plain(src, gx, w);
       } else {
         const bool cert = A.cert && row_cert(PatLim{s.pat + src.at0}, src, gx, w, y);
-        if (__ballot(ok && !cert) != 0ull) y = rows_fpe<N>(src, gx, w, ok, s.wsa);
+        if (__builtin_expect(__ballot(ok && !cert) != 0ull, 0)) y = rows_fpe<N>(src, gx, w, ok, s.wsa);
       }
       use(i, ok, y, p);
     } else if constexpr (!Gth::kDict) {
@@ -820,7 +820,7 @@ __device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, c
         y = sl < A.keep ? row_plain(kept, gx, w) : row_plain(passing, gx, w);
       } else {
         const bool cert = A.cert && (sl < A.keep ? row_cert(lim, kept, gx, w, y) : row_cert(lim, passing, gx, w, y));
-        if (__ballot(ok && !cert) != 0ull) y = rows_fpe<N>(kept, gx, w, ok, s.wsa);
+        if (__builtin_expect(__ballot(ok && !cert) != 0ull, 0)) y = rows_fpe<N>(kept, gx, w, ok, s.wsa);
       }
       use(i, ok, y, p);
     }
@@ -899,7 +899,7 @@ __device__ __forceinline__ void lane_deposit(const Fpe<N>& f, int d0, long long*
       below = true;
     }
   }
-  if (below) {  // rare: components whose low digits lie below the window
+  if (__builtin_expect(below, 0)) {  // rare: components whose low digits lie below the window
 #pragma unroll
     for (int k = 0; k < N; ++k) {
       long long D[3];
@@ -945,7 +945,7 @@ __device__ __forceinline__ void block_window(Dot<N> (&d)[K], const Shm<N>& s) {
       lane_deposit(d[j].f, top - (WIN - 1), s.scat + (j * 64 + lane) * ROW_STRIDE, s.sa + (size_t)j * SA_D, &s.flag[j]);
   }
   __syncthreads();
-  if (nw < 4) {
+  if (__builtin_expect(nw < 4, 0)) {
     // few wavefronts for K WIN columns: a dot's columns at once, four lanes each (a
     // batch of 64 systems in tiles of 64 rows and workgroups of 64: 2.82 ms with one
     // column at a time, 2.50 so)
@@ -1427,7 +1427,7 @@ __global__ void __launch_bounds__(1024) k_dot(long long n, const double* __restr
 #pragma unroll
       for (int v = 0; v < U; v += 2) {
         const Left l = acc_insert(d[0].f, a[v], b[v]), r = acc_insert(d[0].f, a[v + 1], b[v + 1]);
-        if (l.any() || r.any()) {
+        if (__builtin_expect(l.any() || r.any(), 0)) {
 #pragma unroll 1
           for (int k = 0; k < 2; ++k) {
             const Left& w = k ? r : l;
