@@ -468,8 +468,10 @@ struct Left {
 // Branches that hardly any wavefront takes carry __builtin_expect here and in kernels.h:
 // their blocks then lie behind the kernel's others instead of among them, and the kernels
 // of a loop push less of one another out of the instruction cache.  27-point 128^3 rows,
-// us under events, with the blocks in place and so: A 16.9 and 16.4, B 49.0 and 48.4, C
-// 14.8 and 14.1, D 54.1 and 52.3, E 27.0 and 25.5.
+// us under events, with the blocks in place and so: A 16.9 and 16.5, B 49.0 and 48.7, C
+// 14.8 and 14.3, D 54.1 and 53.0, E 27.0 and 25.6.  The rows' FPE path stays where it is:
+// behind the others it took 0.3 us from B and D of single solves and added 8 to the 109
+// of the batched B.
 template <int N>
 __device__ __forceinline__ Left acc_insert(Fpe<N>& f, double a, double b) {
   double p = a * b;

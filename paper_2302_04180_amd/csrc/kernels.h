@@ -795,7 +795,7 @@ __device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, c
         y = sl < A.keep ? row_plain(kept, gx, w) : row_plain(passing, gx, w);
       } else {
         const bool cert = A.cert && (sl < A.keep ? row_cert(lim, kept, gx, w, y) : row_cert(lim, passing, gx, w, y));
-        if (__builtin_expect(__ballot(ok && !cert) != 0ull, 0)) y = rows_fpe<N>(kept, gx, w, ok, s.wsa);
+        if (__ballot(ok && !cert) != 0ull) y = rows_fpe<N>(kept, gx, w, ok, s.wsa);
       }
       use(i, ok, y, p);
     } else if (Gth::kDict || A.np) {
@@ -806,7 +806,7 @@ __device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, c
         y = row_plain(src, gx, w);
       } else {
         const bool cert = A.cert && row_cert(PatLim{s.pat + src.at0}, src, gx, w, y);
-        if (__builtin_expect(__ballot(ok && !cert) != 0ull, 0)) y = rows_fpe<N>(src, gx, w, ok, s.wsa);
+        if (__ballot(ok && !cert) != 0ull) y = rows_fpe<N>(src, gx, w, ok, s.wsa);
       }
       use(i, ok, y, p);
     } else if constexpr (!Gth::kDict) {
@@ -820,7 +820,7 @@ __device__ __forceinline__ void for_rows(const Csr& A, const Gth& gx, Range R, c
         y = sl < A.keep ? row_plain(kept, gx, w) : row_plain(passing, gx, w);
       } else {
         const bool cert = A.cert && (sl < A.keep ? row_cert(lim, kept, gx, w, y) : row_cert(lim, passing, gx, w, y));
-        if (__builtin_expect(__ballot(ok && !cert) != 0ull, 0)) y = rows_fpe<N>(kept, gx, w, ok, s.wsa);
+        if (__ballot(ok && !cert) != 0ull) y = rows_fpe<N>(kept, gx, w, ok, s.wsa);
       }
       use(i, ok, y, p);
     }
