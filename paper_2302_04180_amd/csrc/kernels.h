@@ -769,7 +769,7 @@ __device__ __forceinline__ double rows_fpe(const Src& src, const Gth& gx, int w,
 // by then).  Every path gives the same values.  With the dictionary the loop is
 // bound by vector issue and by the L1's line lookups together, of which a gather of
 // 64 lanes takes about 17: busy in the 27-point 159^3 SpMV 70 % and 81 % of the time
-// (plain rows 26 % and all of it), in D3 at 128^3 54 % and 58 % (19 % and 77 %).
+// (plain rows 26 % and all of it), in D3 at 128^3 52 % and 56 % (19 % and 76 %).
 // Loading the next row's id, operands and own values ahead of this row's sums was
 // slower (D 32.9 instead of 27.4 us at 128^3), and so was a second pass for the rows
 // that are not certified.
